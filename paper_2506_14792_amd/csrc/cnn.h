@@ -26,7 +26,7 @@ class Cnn {
   void grad_flush(double* th_bar);
 
  private:
-  void backward(const double* x, const double* yb, double* xb, double xscale, bool accumulate, bool add);
+  void backward(const double* x, const double* yb, double* xb, double xscale, bool accumulate, bool params, bool add);
   struct Impl;
   std::unique_ptr<Impl> p_;
 };

@@ -387,31 +387,49 @@ __global__ void __launch_bounds__(NTK) kol_cols_fwd(KolDev d, KolCol a, int tc, 
 }
 
 // rollout loss per instance: (1/nsteps) sum_k sum_modes w |canon(X_k - T_k)|^2 (= mean over the
-// N x N grid of the squared difference); one block per instance
-__global__ void __launch_bounds__(NTK) kol_loss(KolDev d, const cplx* H, const cplx* T, int nsteps, double* J) {
+// N x N grid of the squared difference).  One block per step and instance writes that step's sum
+// (the states and targets are read once, at the memory's rate); kol_loss_sum adds the steps in a
+// fixed order.  One block per instance for the whole run: 884 us, now 33 + 5 us (16 runs of
+// 64 x 64, 200 steps; 420 MB read).
+__global__ void __launch_bounds__(NTK) kol_loss(KolDev d, const cplx* H, const cplx* T, double* part) {
   __shared__ double red[NTK];
-  const int b = blockIdx.x, N = d.N, Nh = d.Nh, tid = threadIdx.x;
+  const int b = blockIdx.y, k = blockIdx.x + 1, N = d.N, Nh = d.Nh, tid = threadIdx.x;
   const long long st = (long long)d.B * Nh * N, io = (long long)b * Nh * N;
+  const cplx* Hk = H + (long long)k * st + io;
+  const cplx* Tk = T + (long long)(k - 1) * st + io;
   double s = 0.0;
-  for (int k = 1; k <= nsteps; ++k)
-    for (int e = tid; e < Nh * N; e += NTK) {
-      const int m = e / N, iy = e - m * N;
-      if (iy == N / 2) continue;
-      cplx c = csub(H[(long long)k * st + io + e], T[(long long)(k - 1) * st + io + e]);
-      if (m == 0) {
-        const long long sm = io + (N - iy) % N;
-        const cplx c2 = csub(H[(long long)k * st + sm], T[(long long)(k - 1) * st + sm]);
-        c = cmk(0.5 * (c.x + c2.x), 0.5 * (c.y - c2.y));
-      }
-      s += ((m == 0) ? 1.0 : 2.0) * (c.x * c.x + c.y * c.y);
+  for (int e = tid; e < Nh * N; e += NTK) {
+    const int m = e / N, iy = e - m * N;
+    if (iy == N / 2) continue;
+    cplx c = csub(Hk[e], Tk[e]);
+    if (m == 0) {
+      const int sm = (N - iy) % N;
+      const cplx c2 = csub(Hk[sm], Tk[sm]);
+      c = cmk(0.5 * (c.x + c2.x), 0.5 * (c.y - c2.y));
     }
+    s += ((m == 0) ? 1.0 : 2.0) * (c.x * c.x + c.y * c.y);
+  }
   red[tid] = s;
   __syncthreads();
   for (int w = NTK / 2; w > 0; w >>= 1) {
     if (tid < w) red[tid] += red[tid + w];
     __syncthreads();
   }
-  if (tid == 0) J[b] = red[0] / nsteps;
+  if (tid == 0) part[(long long)b * gridDim.x + blockIdx.x] = red[0];
+}
+// J[b] = (1/nsteps) sum of the steps' sums, one block per instance
+__global__ void __launch_bounds__(NTK) kol_loss_sum(const double* part, int nsteps, double* J) {
+  __shared__ double red[NTK];
+  const int tid = threadIdx.x;
+  double s = 0.0;
+  for (int k = tid; k < nsteps; k += NTK) s += part[(long long)blockIdx.x * nsteps + k];
+  red[tid] = s;
+  __syncthreads();
+  for (int w = NTK / 2; w > 0; w >>= 1) {
+    if (tid < w) red[tid] += red[tid + w];
+    __syncthreads();
+  }
+  if (tid == 0) J[blockIdx.x] = red[0] / nsteps;
 }
 
 // Adam update of the closure parameters (theta, first and second moments in FP64)
@@ -465,6 +483,7 @@ class KolProblem : public ProblemImpl {
     SPS_HIP(hipMemsetAsync(err_, 0, sizeof(int), stream));
     const int nh = keep_history ? max_steps + 1 : 3;
     H_ = arena_.alloc<cplx>((size_t)nh * st_);
+    if (keep_history) lpart_ = arena_.alloc<double>((size_t)max_steps * B_);
     Fr_ = arena_.alloc<cplx>(2 * st_);
     Yn_ = arena_.alloc<cplx>(st_);
     Ln_ = arena_.alloc<cplx>(st_);
@@ -580,7 +599,9 @@ class KolProblem : public ProblemImpl {
 
   void loss(const cplx* targets, int nsteps, double* J) {
     SPS_REQUIRE(hring_ == 0 && tape_ == nsteps, "loss: needs the full history of the last forward run");
-    hipLaunchKernelGGL(kol_loss, dim3(B_), dim3(NTK), 0, stream, d_, H_, targets, nsteps, J);
+    hipLaunchKernelGGL(kol_loss, dim3(nsteps, B_), dim3(NTK), 0, stream, d_, H_, targets, lpart_);
+    SPS_CHECK_LAUNCH();
+    hipLaunchKernelGGL(kol_loss_sum, dim3(B_), dim3(NTK), 0, stream, lpart_, nsteps, J);
     SPS_CHECK_LAUNCH();
   }
 
@@ -752,6 +773,7 @@ class KolProblem : public ProblemImpl {
   int* err_ = nullptr;
   cplx *H_, *Fr_, *Yn_, *Ln_, *Gk_, *Xw_, *Z4_, *Zg_, *W_, *Zc_ = nullptr, *Zgc_ = nullptr, *Wc_ = nullptr;
   double *og_ = nullptr, *yg_ = nullptr, *xg_ = nullptr, *theta_ = nullptr;
+  double* lpart_ = nullptr;   // [B][steps] sums of the rollout loss
 };
 
 }  // namespace
