@@ -16,7 +16,11 @@ __device__ __forceinline__ double writelane_d(double v, int lane, double old) {
 // with no per-row lane broadcasts:
 //   T_t  (TW x TW): the row exchanges and eliminations of L-sweep steps t*BLK .. t*BLK+BLK-1
 //        acting on the window [t*BLK, t*BLK + TW) (identity beyond BLK + kl); the L sweep is
-//        T_last ... T_1 T_0.
+//        T_last ... T_1 T_0.  With all of the block's exchanges done first (the permutation P_t, row
+//        r of P_t v is v[pi(r)]), the eliminations touch only its first BLK entries:
+//        T_t = [A_t | (0; I)] P_t with A_t of TW x BLK, so A_t and the sixteen bytes pi are kept
+//        (148 doubles; the whole T_t took 272, and reading the operators is what bounds launches of
+//        thousands of systems and what the staged solves wait for).
 //   G_t  (BLK x GW): back substitution of U rows t*BLK .. t*BLK+BLK-1,
 //        x_block = G_t [y_block; x(t*BLK + BLK .. t*BLK + GW)], G_t = [U_tt^{-1} | -U_tt^{-1} U_t,off]
 //        (zero beyond BLK + uw - 1); the U sweep applies G_t for t descending.
@@ -24,23 +28,25 @@ __device__ __forceinline__ double writelane_d(double v, int lane, double old) {
 // Block shapes are compile-time so every read is unconditional: the right-hand side must
 // be followed by at least SPS_PAD zero entries (positions n .. n + SPS_PAD - 1), which the
 // operators keep at zero.
-// Layout per system: T[nblk][TW][TS] (row-major, padded rows) followed by G[nblk][BLK][GS].
+// Layout per system: T[nblk][TB] (A_t row-major at stride TS, then pi) followed by G[nblk][BLK][GS].
 // One complex right-hand side per wave (lanes 0-31 the real parts, 32-63 the imaginary parts):
 // b[2*i], b[2*i + 1] in LDS; operators in LDS.
 #define SPS_BLK 8
 #define SPS_TW 16     // T window: needs SPS_BLK + kl <= SPS_TW
 #define SPS_GW 36     // G width: needs SPS_BLK + uw - 1 <= SPS_GW
-#define SPS_TS 17     // row stride of T (odd: rows and columns are both read without LDS bank conflicts)
+#define SPS_TS 9      // row stride of A_t (odd: rows and columns are both read with few LDS bank conflicts)
+#define SPS_TP (SPS_TW * SPS_TS)   // pi within a T block
+#define SPS_TB (SPS_TP + 4)        // doubles per T block
 #define SPS_GS 37     // row stride of G
 #define SPS_PAD 40    // zero tail after the right-hand side (>= SPS_GW)
 
 __host__ __device__ inline int blk_count(int n) { return (n + SPS_BLK - 1) / SPS_BLK; }
 // doubles of the T blocks and of the G blocks of an n-row system (multiples of 4, so every
 // set of operators starts 32-byte aligned), and of both
-__host__ __device__ inline int blk_t_size(int n) { return blk_count(n) * SPS_TW * SPS_TS; }
+__host__ __device__ inline int blk_t_size(int n) { return blk_count(n) * SPS_TB; }
 __host__ __device__ inline int blk_g_size(int n) { return blk_count(n) * SPS_BLK * SPS_GS; }
 __host__ __device__ inline int blk_ops_size(int n) { return blk_t_size(n) + blk_g_size(n); }
-static_assert((SPS_TW * SPS_TS) % 4 == 0 && (SPS_BLK * SPS_GS) % 4 == 0, "block sizes keep 32-byte alignment");
+static_assert(SPS_TB % 4 == 0 && (SPS_BLK * SPS_GS) % 4 == 0, "block sizes keep 32-byte alignment");
 
 // The four sweeps over a range of blocks [t0, t1), with the operators of that range at T (T
 // blocks t0 .. t1-1) or G (G blocks t0 .. t1-1): forward L sweep (t ascending) and U sweep
@@ -50,21 +56,30 @@ static_assert((SPS_TW * SPS_TS) % 4 == 0 && (SPS_BLK * SPS_GS) % 4 == 0, "block 
 // nrow and beyond are read (the operators multiply them by zero, or copy them) but never
 // written, so a system whose rows are followed by another system's live rows can be solved
 // in place while that one is solved by another wave.
-// L sweep: output r = l/2, half h = l&1 sums columns 8h .. 8h+7 (l = lane within the half)
+// L sweep: output r = l/2, half h = l&1 sums the permuted window's entries 4h .. 4h+3 (l = lane
+// within the half); the next block's permutation bytes are read a block ahead, so that the chain of
+// a block is one LDS round trip, four products and a DPP sum
 __device__ inline void blk_L_range(const double* T, int t0, int t1, double* b, int nrow) {
   const int lane = lane_id(), l = lane & 31;
   const int r = l >> 1, h = l & 1;
   double* bc = b + (lane >> 5);
+  auto pis = [&](int t, unsigned& four, int& own) {   // pi(4h .. 4h+3), pi(r)
+    const double* P = T + min(t - t0, t1 - 1 - t0) * SPS_TB + SPS_TP;
+    four = reinterpret_cast<const unsigned*>(P)[h];
+    own = reinterpret_cast<const unsigned char*>(P)[r];
+  };
+  const double own = (h == 0 && r >= SPS_BLK) ? 1.0 : 0.0;   // rows past the eliminations keep their entry
+  unsigned w4;
+  int wr;
+  pis(t0, w4, wr);
   for (int t = t0; t < t1; ++t) {
-    const double* v = bc + 2 * (t * SPS_BLK + 8 * h);
-    const double* Tr = T + ((t - t0) * SPS_TW + r) * SPS_TS + 8 * h;
-    double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-    for (int c = 0; c < 8; c += 2) {
-      a0 = fma(Tr[c], v[2 * (c)], a0);
-      a1 = fma(Tr[c + 1], v[2 * (c + 1)], a1);
-    }
-    double s = a0 + a1;
+    const double* v = bc + 2 * (t * SPS_BLK);
+    const double* Ar = T + (t - t0) * SPS_TB + r * SPS_TS + 4 * h;
+    const double x0 = v[2 * (w4 & 255)], x1 = v[2 * ((w4 >> 8) & 255)], x2 = v[2 * ((w4 >> 16) & 255)],
+                 x3 = v[2 * (w4 >> 24)], xr = v[2 * wr];
+    const double c0 = Ar[0], c1 = Ar[1], c2 = Ar[2], c3 = Ar[3];
+    pis(t + 1, w4, wr);
+    double s = fma(c0, x0, c1 * x1) + fma(c2, x2, fma(c3, x3, own * xr));
     s += dpp_xor1(s);
     if (h == 0 && t * SPS_BLK + r < nrow) bc[2 * (t * SPS_BLK + r)] = s;
   }
@@ -113,23 +128,28 @@ __device__ inline void blk_Ut_range(const double* G, int t0, int t1, double* b, 
     if (c + 32 < SPS_GW && t * SPS_BLK + c2 < nrow) bc[2 * (t * SPS_BLK + c2)] = keep2 + (e0 + e1);
   }
 }
-// L^T sweep: output column c = l/2, half h = l&1 sums rows 8h .. 8h+7 of column c
+// L^T sweep: column c = l/4 of A_t, quarter q = l&3 sums rows 4q .. 4q+3; lane q = 0 stores the sum
+// at pi(c), lane q = 1 the window's entry BLK + c at pi(BLK + c)
 __device__ inline void blk_Lt_range(const double* T, int t0, int t1, double* b, int nrow) {
   const int lane = lane_id(), l = lane & 31;
-  const int c = l >> 1, h = l & 1;
+  const int c = l >> 2, q = l & 3;
   double* bc = b + (lane >> 5);
+  auto pi = [&](int t) {
+    return (int)reinterpret_cast<const unsigned char*>(T + max(t - t0, 0) * SPS_TB + SPS_TP)[(q & 1) * SPS_BLK + c];
+  };
+  int wd = pi(t1 - 1);
   for (int t = t1 - 1; t >= t0; --t) {
-    const double* v = bc + 2 * (t * SPS_BLK + 8 * h);
-    const double* Tc = T + ((t - t0) * SPS_TW + 8 * h) * SPS_TS + c;
-    double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-    for (int r = 0; r < 8; r += 2) {
-      a0 = fma(Tc[r * SPS_TS], v[2 * (r)], a0);
-      a1 = fma(Tc[(r + 1) * SPS_TS], v[2 * (r + 1)], a1);
-    }
-    double s = a0 + a1;
+    const double* v = bc + 2 * (t * SPS_BLK);
+    const double* Ac = T + (t - t0) * SPS_TB + 4 * q * SPS_TS + c;
+    const double x0 = v[2 * (4 * q)], x1 = v[2 * (4 * q + 1)], x2 = v[2 * (4 * q + 2)], x3 = v[2 * (4 * q + 3)],
+                 xb = v[2 * (SPS_BLK + c)];
+    const double c0 = Ac[0], c1 = Ac[SPS_TS], c2 = Ac[2 * SPS_TS], c3 = Ac[3 * SPS_TS];
+    const int dst = t * SPS_BLK + wd;
+    wd = pi(t - 1);
+    double s = fma(c0, x0, c1 * x1) + fma(c2, x2, c3 * x3);
     s += dpp_xor1(s);
-    if (h == 0 && t * SPS_BLK + c < nrow) bc[2 * (t * SPS_BLK + c)] = s;
+    s += dpp_xor2(s);
+    if (q < 2 && dst < nrow) bc[2 * dst] = (q == 0) ? s : xb;
   }
 }
 // One system's block operators are brought into LDS in two steps so that their memory
@@ -138,7 +158,7 @@ __device__ inline void blk_Lt_range(const double* T, int t0, int t1, double* b, 
 // The T blocks and the G blocks of a system are loaded and stored separately, so that the set
 // the first sweep needs can go to LDS before the other has arrived.  Counts (doubles) must be
 // multiples of 2; at most SPS_OPS_REG_T / SPS_OPS_REG_G 16-byte loads per thread.
-#define SPS_OPS_REG_T 9
+#define SPS_OPS_REG_T 5
 #define SPS_OPS_REG_G 10
 struct OpsRegs {
   double2 t[SPS_OPS_REG_T];
@@ -274,8 +294,9 @@ __device__ inline void band_lu_factor(const double* __restrict__ BM, const doubl
   __syncthreads();
 }
 
-// Block operators (see above) of the factors in ab; T_t column c is the image of the window's
-// unit vector e_c.
+// Block operators (see above) of the factors in ab; the image of the window's unit vector e_c under
+// T_t is column pos of A_t, pos the row to which the block's exchanges bring entry c (pi(pos) = c), or
+// e_pos for pos >= BLK.
 __device__ inline void band_condense(const double* ab, const int* spiv, int n, int kl, int ku, double* T, double* G) {
   const int tid = threadIdx.x, nt = blockDim.x;
   const int ldab = 2 * kl + ku + 1, kv = kl + ku;
@@ -286,10 +307,13 @@ __device__ inline void band_condense(const double* ab, const int* spiv, int n, i
     double v[SPS_TW];
 #pragma unroll
     for (int r = 0; r < SPS_TW; ++r) v[r] = (r == c) ? 1.0 : 0.0;
+    int pos = c;
     for (int q = 0; q < SPS_BLK; ++q) {
       const int j = tb + q;
       if (j >= n) break;
       const int p = spiv[j] - j;
+      if (pos == q) pos = q + p;
+      else if (pos == q + p) pos = q;
       double vq = 0.0, vp = 0.0;
 #pragma unroll
       for (int r = 0; r < SPS_TW; ++r) {
@@ -308,7 +332,10 @@ __device__ inline void band_condense(const double* ab, const int* spiv, int n, i
         if (i >= 1 && i <= km) v[r] -= ab[j * ldab + kv + i] * vp;
       }
     }
-    for (int r = 0; r < SPS_TW; ++r) T[(t * SPS_TW + r) * SPS_TS + c] = v[r];
+    double* Tt = T + t * SPS_TB;
+    reinterpret_cast<unsigned char*>(Tt + SPS_TP)[pos] = (unsigned char)c;
+    if (pos < SPS_BLK)
+      for (int r = 0; r < SPS_TW; ++r) Tt[r * SPS_TS + pos] = v[r];
   }
   // G_t row i: Ui[i][c] for c < BLK (row i of the inverse of the diagonal block of U),
   // then -sum_i' Ui[i][i'] U[tb+i'][tb+c] for BLK <= c < GW

@@ -88,6 +88,7 @@ constexpr int SPS_MAXPART = 4;
 constexpr int SPS_SPIKE_W = 24;
 constexpr int SPS_RED_MAX = 72;
 constexpr int SPS_CP_REG = 16;   // 16-byte loads per thread of the spike copy
+constexpr int SPS_SPIKE_AREA = 272;   // doubles per block row that the forward solve's spikes may take in LDS
 constexpr int NTX = 512;  // threads per block of the grid-row step kernels
 
 struct RbcDev {
@@ -627,11 +628,11 @@ __device__ void rbc_solve_staged(const RbcDev& d, const OpsRegs& regs, double* o
 // chunk q + 1 (for launches with many more systems than CUs: no register prefetch and a small
 // LDS footprint, so several blocks share a CU).  Block-wide; buf holds 2 * SOLVE_CHUNK_D doubles.
 constexpr int SPS_CHUNK = 6;
-constexpr int SOLVE_CHUNK_D = SPS_CHUNK * SPS_BLK * SPS_GS;   // >= SPS_CHUNK * SPS_TW * SPS_TS
+constexpr int SOLVE_CHUNK_D = SPS_CHUNK * SPS_BLK * SPS_GS;   // >= SPS_CHUNK * SPS_TB
 __device__ void rbc_solve_streamed(const RbcDev& d, const double* gops, double* buf, cplx* vA, bool transposed) {
   const int nblk = blk_count(d.n), nch = (nblk + SPS_CHUNK - 1) / SPS_CHUNK, Q = 2 * nch;
   const double* Tg = gops;
-  const double* Gg = gops + nblk * SPS_TW * SPS_TS;
+  const double* Gg = gops + nblk * SPS_TB;
   const int tid = threadIdx.x, wave = tid >> 6;
   // chunk q: the first sweep (L, or U^T) runs over ascending chunks, the second (U, or L^T)
   // over descending ones; the forward solve reads T then G, the transposed G then T
@@ -646,7 +647,7 @@ __device__ void rbc_solve_streamed(const RbcDev& d, const double* gops, double* 
     int t0, t1;
     bool useT;
     range(q, &t0, &t1, &useT);
-    const int per = useT ? SPS_TW * SPS_TS : SPS_BLK * SPS_GS;
+    const int per = useT ? SPS_TB : SPS_BLK * SPS_GS;
     const double2* src = reinterpret_cast<const double2*>((useT ? Tg : Gg) + (size_t)t0 * per);
     double2* d2 = reinterpret_cast<double2*>(dst);
     const int h = (t1 - t0) * per / 2;
@@ -702,7 +703,7 @@ __device__ __forceinline__ void rbc_solve_part(const RbcDev& d, int k, const Ops
   auto pstart = [&](int q) { return (q >= 1 ? ps1 : 0) + (q >= 2 ? ps2 - ps1 : 0) + (q >= 3 ? ps3 - ps2 : 0); };
   const int p0 = pstart(wave), p1 = (wave + 1 >= P) ? n : pstart(wave + 1);
   const StagedOps s = staged_ops(d, o, transposed);
-  const double* T = s.T + (p0 / SPS_BLK) * (SPS_TW * SPS_TS);
+  const double* T = s.T + (p0 / SPS_BLK) * SPS_TB;
   const double* G = s.G + (p0 / SPS_BLK) * (SPS_BLK * SPS_GS);
   double* b = reinterpret_cast<double*>(vA + p0);
   if (wave < P) sweep_first(T, G, p1 - p0, b, transposed);
@@ -1781,7 +1782,7 @@ __global__ void __launch_bounds__(NT) rbc_factor(RbcDev d, const double* BM, con
     const int s0 = pm[8 * p], np = pm[8 * p + 1], s1 = s0 + np;
     band_lu_factor(BM + ko + (size_t)s0 * bw, BL + ko + (size_t)s0 * bw, am, bl, np, d.kl, d.ku, ab, sh, spiv, d.err,
                    bnu ? bnu + (size_t)s0 * bw : nullptr, bka ? bka + (size_t)s0 * bw : nullptr, nu, ka);
-    band_condense(ab, spiv, np, d.kl, d.ku, O + (s0 / SPS_BLK) * (SPS_TW * SPS_TS),
+    band_condense(ab, spiv, np, d.kl, d.ku, O + (s0 / SPS_BLK) * SPS_TB,
                   O + d.tsz + (s0 / SPS_BLK) * (SPS_BLK * SPS_GS));
     for (int dir = 0; dir < 2; ++dir) {
       const int wV = pm[8 * p + 2 + 3 * dir], wW = pm[8 * p + 3 + 3 * dir], w = wV + wW;
@@ -3365,6 +3366,11 @@ class RbcProblem : public ProblemImpl {
     if (stream_solve_) return sizeof(double) * 2 * (size_t)SOLVE_CHUNK_D;
     return sizeof(double) * (size_t)dv_.blksz;
   }
+  // the forward solve's operators with the spikes that replace its T blocks, the last of them
+  size_t spike_bytes() const {
+    if (!dv_.part) return 0;
+    return sizeof(double) * ((size_t)(dv_.blksz - dv_.tsz) + dv_.rof[0] + dv_.nrr[0] * dv_.nrr[0] + 1);
+  }
   // launches with many more systems than CUs stream the operators (several blocks per CU);
   // smaller ones stage them whole (one block per CU, shortest dependent chain)
   typedef void (*KfFn)(RbcDev, KfArgs);
@@ -3380,7 +3386,7 @@ class RbcProblem : public ProblemImpl {
   }
   size_t kf_lds() const {
     const size_t post = sizeof(double) * 4 * Ngz_ + sizeof(cplx) * 3 * N_;
-    return sizeof(cplx) * (2 * S_ + SPS_PAD) + std::max({kf_pre(), post, ops_bytes()});
+    return sizeof(cplx) * (2 * S_ + SPS_PAD) + std::max({kf_pre(), post, ops_bytes(), spike_bytes()});
   }
   size_t ka_lds() const {
     const size_t post = sizeof(double) * (4 * Ngz_ + 2 * NTK / 64) + sizeof(cplx) * (5 * S_ + 3 * N_);
@@ -4188,9 +4194,10 @@ class RbcProblem : public ProblemImpl {
       }
       const int nr = std::max(nr0, nr1);
       if (!ok || nr > SPS_RED_MAX || nr > S_) continue;
-      // each direction's spikes (rounded to 4 doubles) and inverse must fit the space of the
-      // early set of its solve (the T blocks for the forward solve, the G blocks for the
-      // transposed one) and the copy's loads; offsets below 2^16
+      // each direction's spikes (rounded to 4 doubles) and inverse must fit the space from the
+      // early set of its solve on (the T blocks for the forward solve, which end the operators
+      // and are followed by free LDS, see spike_bytes; the G blocks for the transposed one) and the
+      // copy's loads; offsets below 2^16
       int sz[2] = {0, 0};
       for (int p = 0; p < P; ++p) {
         const int np = st[p + 1] - st[p];
@@ -4200,7 +4207,7 @@ class RbcProblem : public ProblemImpl {
       const int area0 = (sz[0] + 3) / 4 * 4 + nr0 * nr0, area1 = (sz[1] + 3) / 4 * 4 + nr1 * nr1;
       if (std::max(sz[0], sz[1]) >= 0xffff) continue;
       const int cap = SPS_CP_REG * 2 * (NTK - SPS_WAVE * P);
-      if (area0 > blk_t_size(S_) || area1 > blk_g_size(S_) || area0 + 1 > cap || area1 + 1 > cap) continue;
+      if (area0 > SPS_SPIKE_AREA * blk_count(S_) || area1 > blk_g_size(S_) || area0 + 1 > cap || area1 + 1 > cap) continue;
       // accepted: descriptor fields and the tables of both directions
       dv_.part = P;
       dv_.ps1 = st[1];
