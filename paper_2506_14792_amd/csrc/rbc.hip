@@ -119,6 +119,12 @@ struct RbcDev {
   const int* sflag;     // colph[i] (slot i)
   const double* gram;   // [N][N] int_0^1 T_m T_n dz
   const double* ops;    // [B][K][opsize] block operators of the LU factors (T blocks, then G blocks)
+  // Modes with the same |k| have the same operator and share one factor set (plane Couette: (kx, kz)
+  // and (kx, -kz)): kmap[block position] = (mode, factor set), sharing modes next to each other;
+  // null when every mode has its own.  krep[set]: a mode of the set, nops sets.
+  const int2* kmap;
+  const int* krep;
+  int nops;
   int opsize;           // doubles per system (stride)
   int blksz;            // of which block operators (staged into LDS)
   int tsz;              // of which T blocks (the G blocks follow at tsz)
@@ -154,6 +160,17 @@ __device__ __forceinline__ int xcd_wavenumber(int b, int K) {
   constexpr int X = 8;
   const int per = K / X, rem = K - per * X, x = b % X;
   return x * per + min(x, rem) + b / X;
+}
+
+// The mode of a per-mode block and its factor set.
+struct ModeSet {
+  int k, op;
+};
+__device__ __forceinline__ ModeSet mode_set(const RbcDev& d) {
+  const int q = xcd_wavenumber(blockIdx.x, d.K);
+  if (!d.kmap) return ModeSet{q, q};
+  const int2 m = d.kmap[q];
+  return ModeSet{__builtin_amdgcn_readfirstlane(m.x), __builtin_amdgcn_readfirstlane(m.y)};
 }
 
 // Instance b's view of the problem: its diffusivities and its factors.
@@ -691,7 +708,7 @@ __device__ void rbc_solve_streamed(const RbcDev& d, const double* gops, double* 
 // the spikes and the inverse into the early set's space (free once every first sweep is
 // done).  vB is scratch (the coupled entries).  Block-wide; vA holds the gathered right-hand
 // side and gets the solution.
-__device__ __forceinline__ void rbc_solve_part(const RbcDev& d, int k, const OpsRegs& regs, double* o, cplx* vA, cplx* vB,
+__device__ __forceinline__ void rbc_solve_part(const RbcDev& d, int op, const OpsRegs& regs, double* o, cplx* vA, cplx* vB,
                                bool transposed) {
   const int tid = threadIdx.x, wave = tid >> 6, n = d.n, P = d.part, dir = transposed ? 1 : 0;
   const int2 sm2 = d.smap[dir * n + min(tid, n - 1)];   // this row's spike layout (used last)
@@ -716,7 +733,7 @@ __device__ __forceinline__ void rbc_solve_part(const RbcDev& d, int k, const Ops
   if (wave < P) {
     sweep_second(T, G, p1 - p0, b, transposed);
   } else {
-    const double2* src = reinterpret_cast<const double2*>(d.ops + (size_t)k * d.opsize + d.spk[dir]);
+    const double2* src = reinterpret_cast<const double2*>(d.ops + (size_t)op * d.opsize + d.spk[dir]);
     double2* dst = reinterpret_cast<double2*>(lsp);
     const int h = (d.rof[dir] + nr * nr + 1) / 2, t0 = tid - P * SPS_WAVE, nth = blockDim.x - P * SPS_WAVE;
     double2 v[SPS_CP_REG];
@@ -779,10 +796,10 @@ __device__ __forceinline__ void rbc_solve_part(const RbcDev& d, int k, const Ops
 // The staged solves need stage_early(d, regs, lds, transposed) by every thread before the last
 // barrier.
 template <bool STREAM>
-__device__ __forceinline__ void rbc_solve(const RbcDev& d, int k, const OpsRegs& regs, double* lds, cplx* vA,
+__device__ __forceinline__ void rbc_solve(const RbcDev& d, int op, const OpsRegs& regs, double* lds, cplx* vA,
                                           cplx* vB, bool transposed) {
-  if (STREAM) rbc_solve_streamed(d, d.ops + (size_t)k * d.opsize, lds, vA, transposed);
-  else if (d.part) rbc_solve_part(d, k, regs, lds, vA, vB, transposed);
+  if (STREAM) rbc_solve_streamed(d, d.ops + (size_t)op * d.opsize, lds, vA, transposed);
+  else if (d.part) rbc_solve_part(d, op, regs, lds, vA, vB, transposed);
   else rbc_solve_staged(d, regs, lds, vA, transposed);
 }
 
@@ -880,7 +897,8 @@ __global__ void __launch_bounds__(NTK) rbc_kfwd(RbcDev d, KfArgs a) {
   }
   extern __shared__ double smem_d[];
   cplx* sm = reinterpret_cast<cplx*>(smem_d);
-  const int k = xcd_wavenumber(blockIdx.x, d.K), tid = threadIdx.x;
+  const ModeSet ms = mode_set(d);
+  const int k = ms.k, tid = threadIdx.x;
   const int N = d.N, S = d.S, K = d.K, Ngz = d.Ngz, Hc = half_nodes(Ngz);
   const int mode = a.mode;
   cplx* vA = sm;                // S + SPS_PAD : right-hand side, then solution / state
@@ -925,7 +943,7 @@ __global__ void __launch_bounds__(NTK) rbc_kfwd(RbcDev d, KfArgs a) {
   // (issued in every mode, so that no load is under a branch; T blocks first: the first sweep
   // needs them, the G blocks arrive during it)
   load_maps(d, mr);
-  if (!STREAM) ops_issue(d.ops + (size_t)k * d.opsize, d.tsz, d.blksz - d.tsz, opsr);
+  if (!STREAM) ops_issue(d.ops + (size_t)ms.op * d.opsize, d.tsz, d.blksz - d.tsz, opsr);
   cplx xc = czero(), fc = czero();
   if (stage) {
 #pragma unroll
@@ -1016,7 +1034,7 @@ __global__ void __launch_bounds__(NTK) rbc_kfwd(RbcDev d, KfArgs a) {
   } else {
     if (!STREAM) stage_early(d, opsr, reinterpret_cast<double*>(un), false);
     rbc_gather(d, mr, rr, vA);
-    rbc_solve<STREAM>(d, k, opsr, reinterpret_cast<double*>(un), vA, vB, false);
+    rbc_solve<STREAM>(d, ms.op, opsr, reinterpret_cast<double*>(un), vA, vB, false);
     rbc_scatter(d, mr, vA, vB, vA);   // vA <- new state (ABI slots)
     if (tid < S) {
       const cplx v = vA[tid];
@@ -1614,7 +1632,8 @@ __global__ void __launch_bounds__(NTK, STREAM ? 6 : 1) rbc_kadj(RbcDev d, KaArgs
   }
   extern __shared__ double smem_d[];
   cplx* sm = reinterpret_cast<cplx*>(smem_d);
-  const int k = xcd_wavenumber(blockIdx.x, d.K), tid = threadIdx.x;
+  const ModeSet ms = mode_set(d);
+  const int k = ms.k, tid = threadIdx.x;
   const int N = d.N, S = d.S, Ngz = d.Ngz, Hc = half_nodes(Ngz);
   const int fl = a.flags;
   const double dt = a.dt;
@@ -1661,7 +1680,7 @@ __global__ void __launch_bounds__(NTK, STREAM ? 6 : 1) rbc_kadj(RbcDev d, KaArgs
   // (issued for every flag set, so that no load is under a branch; the transposed solve's first
   // sweep reads the G blocks: those first)
   load_maps(d, mr);
-  if (!STREAM) ops_issue_gt(d.ops + (size_t)k * d.opsize, d.tsz, d.blksz - d.tsz, opsr);
+  if (!STREAM) ops_issue_gt(d.ops + (size_t)ms.op * d.opsize, d.tsz, d.blksz - d.tsz, opsr);
   cplx yc = czero(), fs = czero(), ys = czero();
   if ((fl & KA_B) && sl) {
 #pragma unroll
@@ -1713,7 +1732,7 @@ __global__ void __launch_bounds__(NTK, STREAM ? 6 : 1) rbc_kadj(RbcDev d, KaArgs
   // Y_m = (M + dt H_mm L)^{-H} xbar
   if (!STREAM) stage_early(d, opsr, ops, true);
   rbc_gather_h(d, mr, xbar, vA);
-  rbc_solve<STREAM>(d, k, opsr, ops, vA, vB, true);
+  rbc_solve<STREAM>(d, ms.op, opsr, ops, vA, vB, true);
   rbc_scatter_h(d, mr, vA, vB);       // vB = Y_m
   if (fl & KA_SOLVE_T) {
     if (sl) a.Xb_out[ks] = vB[tid];
@@ -1742,11 +1761,11 @@ __global__ void __launch_bounds__(NT) rbc_factor(RbcDev d, const double* BM, con
                                                  const double* BLka = nullptr) {
   extern __shared__ double smem_d[];
   __shared__ int sh[4];
-  const int k = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int k = d.krep ? d.krep[blockIdx.x] : blockIdx.x, b = blockIdx.y;
   const int bw = d.kl + d.ku + 1, ldab = 2 * d.kl + d.ku + 1;
   const size_t ko = (size_t)k * d.n * bw;
   const double nu = d.nub ? d.nub[b] : 0.0, ka = d.kab ? d.kab[b] : 0.0;
-  double* O = ops + ((size_t)b * d.K + k) * d.opsize;
+  double* O = ops + ((size_t)b * d.K + blockIdx.x) * d.opsize;
   const double* bnu = BLnu ? BLnu + ko : nullptr;
   const double* bka = BLka ? BLka + ko : nullptr;
   if (!d.part) {
@@ -2758,6 +2777,7 @@ class RbcProblem : public ProblemImpl {
     const double lx = 0.5 * c.lx, lz = 0.5 * c.lz;
     kxs_.resize(K_);
     ckeep_.resize(K_);
+    share_ = true;
     for (int m = 0; m < Kx; ++m)
       for (int n = 0; n < c.nz; ++n) {
         const int ns = (n < c.nz / 2) ? n : n - c.nz;
@@ -2785,8 +2805,42 @@ class RbcProblem : public ProblemImpl {
     init();
   }
 
+  // Factor sets shared by the modes of equal wavenumber modulus (mode 0, whose rows hold the gauge, keeps
+  // its own).  The block order puts the modes of one set and x wavenumber next to each other, so that
+  // they run at the same time on one XCD and the second reads the operators from its L2: the streamed
+  // stage kernels are bound by reading them.
+  void share_factors() {
+    std::map<double, int> set;
+    std::vector<int> op(K_), rep;
+    for (int k = 0; k < K_; ++k) {
+      const auto it = k > 0 ? set.find(kxs_[k]) : set.end();
+      if (it != set.end()) {
+        op[k] = it->second;
+        continue;
+      }
+      op[k] = (int)rep.size();
+      if (k > 0) set.emplace(kxs_[k], op[k]);
+      rep.push_back(k);
+    }
+    std::vector<int2> map;
+    for (int m = 0; m < K_ / Kz_; ++m) {
+      std::vector<char> done(Kz_, 0);
+      for (int n = 0; n < Kz_; ++n)
+        for (int n2 = n; n2 < Kz_ && !done[n]; ++n2)
+          if (!done[n2] && op[m * Kz_ + n2] == op[m * Kz_ + n]) {
+            map.push_back(make_int2(m * Kz_ + n2, op[m * Kz_ + n2]));
+            if (n2 > n) done[n2] = 1;
+          }
+    }
+    dv_.kmap = arena_.upload(map, stream);
+    dv_.krep = arena_.upload(rep, stream);
+    dv_.nops = (int)rep.size();
+  }
+
   void init() {
     dv_.B = B_;
+    dv_.nops = K_;
+    if (share_) share_factors();
     cur_dt_ = dt_;
     stream_solve_ = (long long)K_ * B_ > 1024;
     build_tables();
@@ -2836,7 +2890,7 @@ class RbcProblem : public ProblemImpl {
   void factor_into(double dt, double* ops) {
     RbcDev d = dv_;
     d.ops = ops;
-    hipLaunchKernelGGL(rbc_factor, dim3(K_, B_), dim3(NT), factor_lds(), stream, d, BM_, BL_, 1.0, dt * tab_.H[1][1],
+    hipLaunchKernelGGL(rbc_factor, dim3(dv_.nops, B_), dim3(NT), factor_lds(), stream, d, BM_, BL_, 1.0, dt * tab_.H[1][1],
                        ops, BLnu_, BLka_);
     SPS_CHECK_LAUNCH();
   }
@@ -2873,7 +2927,7 @@ class RbcProblem : public ProblemImpl {
       auto c = opcache_.find(distinct[q]);
       if (c == opcache_.end()) {
         SPS_REQUIRE(opcache_.size() < 4 * kMaxStepSets, "too many distinct steps over the problem's lifetime");
-        double* o = arena_.alloc<double>((size_t)B_ * K_ * dv_.opsize);
+        double* o = arena_.alloc<double>((size_t)B_ * dv_.nops * dv_.opsize);
         factor_into(distinct[q], o);
         c = opcache_.emplace(distinct[q], o).first;
       }
@@ -4278,7 +4332,7 @@ class RbcProblem : public ProblemImpl {
       SPS_REQUIRE(kf_pre() <= sizeof(double) * gsz && ka_pre() <= sizeof(double) * dv_.tsz,
                   "stage buffers overlap the staged operators");
     }
-    ops_ = arena_.alloc<double>((size_t)B_ * K_ * dv_.opsize);
+    ops_ = arena_.alloc<double>((size_t)B_ * dv_.nops * dv_.opsize);
     dv_.ops = ops_;
     err_ = arena_.alloc<int>(1);
     SPS_HIP(hipMemsetAsync(err_, 0, sizeof(int), stream));
@@ -4328,7 +4382,7 @@ class RbcProblem : public ProblemImpl {
   int K_, N_, S_, Ngx_, Ngz_, kl_ = 0, ku_ = 0;
   double nu_, ka_, dt_ = 0.0, cp_ = 1.0, bc0_ = 1.0, cost_scale_ = 1.0;
   int Kz_ = 1, ncost_ = 2;
-  bool cou_ = false, stream_solve_ = false;
+  bool cou_ = false, stream_solve_ = false, share_ = false;
   int wave_r1_ = 0;                  // grid rows of 64*wave_r1_ points use the one-wave-per-FFT kernels (0: off)
   int B_ = 1;                        // instances of a batch
   std::vector<double> rab_;          // a batch's Rayleigh numbers (empty: a single problem)
