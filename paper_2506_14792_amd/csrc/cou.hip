@@ -15,9 +15,10 @@
 // (m < Kx half-spectrum x modes, n < Nz z modes in FFT order, the z Nyquist n = Nz/2 unforced);
 // plane intermediates [f][Ngy][Ngz][Kx] (x modes contiguous).  Steps:
 //   A  per (y, tile of x modes, velocity component): the component, its y-derivative and its
-//      x- and z-derivatives (i kx, i kz), inverse z-FFT onto the padded z grid;
-//   B  per (y, pair of z rows): packed real inverse x-FFTs of the 12 fields, the products, forward
-//      real x-FFTs of the 3 densities;
+//      z-derivative (i kz), inverse z-FFT onto the padded z grid (9 fields);
+//   B  per (y, pair of z rows): the x-derivatives (i kx times the components' x spectra, which are at
+//      hand here), packed real inverse x-FFTs of the 12 fields, the products, forward real x-FFTs of
+//      the 3 densities;
 //   C  per (y, tile of x modes): forward z-FFTs, truncation, 1/(Ngx Ngz), rotation to
 //      (par, v, perp).
 // The VJP runs the transposes in reverse order (C', B' with the primal fields of A, A').
@@ -167,8 +168,10 @@ __device__ __forceinline__ cplx cou_unpack(const cplx* r, int base, int m, int G
 }
 
 // ---------------------------------------------------------------------------- A: z inverse
-// Grid (x-mode tiles, 3 components, Ngy).  Component g (u, v, w) writes fields g, 3 + g,
-// 6 + 2g, 7 + 2g of Z: the component, its y-derivative, i kx times it, i kz times it.
+// Grid (x-mode tiles, 3 components, Ngy).  Component g (u, v, w) writes fields g, 3 + g, 6 + g
+// of Z: the component, its y-derivative, i kz times it.  (The x-derivative is a factor per x mode that
+// the row kernels apply: a quarter fewer transforms here and fields through memory, 58 -> 47 us per
+// launch at 128x64x64.)
 template <int NT>
 __global__ void __launch_bounds__(NT) cou_zinv(CouDev d, const cplx* zg, int tc, cplx* Z) {
   extern __shared__ double smem_d[];
@@ -179,7 +182,7 @@ __global__ void __launch_bounds__(NT) cou_zinv(CouDev d, const cplx* zg, int tc,
   cplx* tw = reinterpret_cast<cplx*>(smem_d);
   cplx* b0 = tw + G;
   for (int e = tid; e < G; e += NT) tw[e] = d.twz[e];
-  for (int e = tid; e < 4 * tcn * G; e += NT) b0[fpad(e)] = czero();
+  for (int e = tid; e < 3 * tcn * G; e += NT) b0[fpad(e)] = czero();
   __syncthreads();
   for (int e = tid; e < tcn * Nz; e += NT) {
     const int j = e / Nz, n = e - j * Nz, m = m0 + j;
@@ -204,16 +207,14 @@ __global__ void __launch_bounds__(NT) cou_zinv(CouDev d, const cplx* zg, int tc,
     }
     b0[fpad((0 * tcn + j) * G + row)] = val;
     b0[fpad((1 * tcn + j) * G + row)] = dy;
-    b0[fpad((2 * tcn + j) * G + row)] = cscale(cmul_i(val), w.kx);
-    b0[fpad((3 * tcn + j) * G + row)] = cscale(cmul_i(val), w.kz);
+    b0[fpad((2 * tcn + j) * G + row)] = cscale(cmul_i(val), w.kz);
   }
   __syncthreads();
-  ip_fft(b0, d.pz, tw, +1, 4 * tcn, G, tid, NT);
+  ip_fft(b0, d.pz, tw, +1, 3 * tcn, G, tid, NT);
   const cplx* o = b0;
-  const int fid[4] = {g, 3 + g, 6 + 2 * g, 7 + 2 * g};
-  for (int e = tid; e < 4 * G * tcn; e += NT) {
+  for (int e = tid; e < 3 * G * tcn; e += NT) {
     const int q = e / (G * tcn), r = e - q * G * tcn, z = r / tcn, j = r - z * tcn;
-    Z[(((long long)fid[q] * Ngy + y) * G + z) * Kx + m0 + j] = o[fpad((q * tcn + j) * G + z)];
+    Z[(((long long)(3 * q + g) * Ngy + y) * G + z) * Kx + m0 + j] = o[fpad((q * tcn + j) * G + z)];
   }
 }
 
@@ -231,6 +232,18 @@ __device__ __forceinline__ Dens cou_dens(const double* f, double U, double dU) {
   return r;
 }
 
+// Field f of Z (u, v, w, uy, vy, wy, uz, vz, wz) at point x of the packed rows' spectrum p into its
+// slot of h (u v w uy vy wy ux uz vx vz wx wz), and a component's x-derivative: i k p with the signed
+// wavenumber k of x.
+__device__ __forceinline__ void cou_put(const CouDev& d, cplx* h, int f, int x, cplx p) {
+  const int G = d.Ngx, Kx = d.Kx;
+  h[fpad((f < 6 ? f : 2 * f - 5) * G + x)] = p;
+  if (f < 3) {
+    const int k = x < Kx ? x : (x > G - Kx ? x - G : 0);
+    h[fpad((6 + 2 * f) * G + x)] = cscale(cmul_i(p), 2.0 * M_PI * k / d.lx);
+  }
+}
+
 // Grid (Ngz / 2, Ngy), 12 Ngx <= 6 NT.  LDS twiddles(Ngx) + fpad_size(12 Ngx).  The densities
 // of a grid point overwrite its u, v, w slots (one thread reads and writes each x).
 template <int NT>
@@ -240,10 +253,10 @@ __global__ void __launch_bounds__(NT) cou_xrow(CouDev d, const cplx* __restrict_
   cplx* tw = reinterpret_cast<cplx*>(smem_d);
   cplx* h = tw + G;
   for (int e = tid; e < G; e += NT) tw[e] = d.twx[e];
-  for (int e = tid; e < 12 * G; e += NT) {
+  for (int e = tid; e < 9 * G; e += NT) {
     const int f = e / G, x = e - f * G;
     const cplx* U = Z + (((long long)f * Ngy + y) * Gz + z0) * Kx;
-    h[fpad(e)] = cou_pack(U, U + Kx, x, G, Kx, 1.0);
+    cou_put(d, h, f, x, cou_pack(U, U + Kx, x, G, Kx, 1.0));
   }
   __syncthreads();
   ip_fft(h, d.px, tw, +1, 12, G, tid, NT);
@@ -347,9 +360,10 @@ __global__ void __launch_bounds__(NT) cou_zfwd_adj(CouDev d, const cplx* nlbar, 
 
 // ---------------------------------------------------------------------------- B': transpose of B
 // Grid (Ngz / 2, Ngy), 15 Ngx <= 6 NT.  LDS twiddles(Ngx / 2) + fpad_size(15 Ngx): three
-// 512-thread blocks share a CU at Ngx = 192.  The primal fields Zp (12) and
-// the density cotangents Wb (3, weight-1 modes) in; the 12 field cotangents out, as x half
-// spectra times w_m (the transpose of the inverse transform).  The cotangents of a grid point
+// 512-thread blocks share a CU at Ngx = 192.  The primal fields Zp (9) and
+// the density cotangents Wb (3, weight-1 modes) in; the cotangents of the 9 fields out, as x half
+// spectra times w_m (the transpose of the inverse transform), the x-derivatives' (times conj(i kx))
+// within their components'.  The cotangents of a grid point
 // overwrite its first 12 slots (one thread reads and writes each x).
 template <int NT>
 __global__ void __launch_bounds__(NT)
@@ -360,11 +374,13 @@ cou_xrow_adj(CouDev d, const cplx* __restrict__ Zp, const cplx* __restrict__ Wb,
   cplx* h = tw + G / 2;
   cplx* o = h;
   for (int e = tid; e < G / 2; e += NT) tw[e] = d.twx[e];
-  for (int e = tid; e < 15 * G; e += NT) {
+  for (int e = tid; e < 12 * G; e += NT) {
     const int f = e / G, x = e - f * G;
-    const cplx* U = (f < 12) ? Zp + (((long long)f * Ngy + y) * Gz + z0) * Kx
-                             : Wb + (((long long)(f - 12) * Ngy + y) * Gz + z0) * Kx;
-    h[fpad(e)] = cou_pack(U, U + Kx, x, G, Kx, f < 12 ? 1.0 : 0.5);
+    const cplx* U = (f < 9) ? Zp + (((long long)f * Ngy + y) * Gz + z0) * Kx
+                            : Wb + (((long long)(f - 9) * Ngy + y) * Gz + z0) * Kx;
+    const cplx p = cou_pack(U, U + Kx, x, G, Kx, f < 9 ? 1.0 : 0.5);
+    if (f < 9) cou_put(d, h, f, x, p);
+    else h[fpad((f + 3) * G + x)] = p;
   }
   __syncthreads();
   ip_fft<true>(h, d.px, tw, +1, 15, G, tid, NT);
@@ -399,16 +415,17 @@ cou_xrow_adj(CouDev d, const cplx* __restrict__ Zp, const cplx* __restrict__ Wb,
   __syncthreads();
   ip_fft<true>(o, d.px, tw, -1, 12, G, tid, NT);
   const cplx* r = o;
-  for (int e = tid; e < 12 * 2 * Kx; e += NT) {
+  for (int e = tid; e < 9 * 2 * Kx; e += NT) {
     const int f = e / (2 * Kx), rr = e - f * 2 * Kx, yy = rr / Kx, m = rr - yy * Kx;
-    const cplx v = cou_unpack(r, f * G, m, G, yy);
+    cplx v = cou_unpack(r, (f < 6 ? f : 2 * f - 5) * G, m, G, yy);
+    if (f < 3) v = cadd(v, cscale(cmul_mi(cou_unpack(r, (6 + 2 * f) * G, m, G, yy)), 2.0 * M_PI * m / d.lx));
     Gb[(((long long)f * Ngy + y) * Gz + z0 + yy) * Kx + m] = (m == 0) ? v : cscale(v, 2.0);
   }
 }
 
 // ---------------------------------------------------------------------------- A': transpose of A
-// Grid (x-mode tiles, 2 groups, Ngy): group 0 the u and w fields (8: they mix in the rotation),
-// group 1 the v fields (4).  Forward z-FFTs of the field cotangents, the transposes of the
+// Grid (x-mode tiles, 2 groups, Ngy): group 0 the u and w fields (6: they mix in the rotation),
+// group 1 the v fields (3).  Forward z-FFTs of the field cotangents, the transposes of the
 // derivative factors and of the rotation, into zbar[6][Ngy][K].
 template <int NT>
 __global__ void __launch_bounds__(NT) cou_zinv_adj(CouDev d, const cplx* Gb, int tc, cplx* zbar) {
@@ -417,16 +434,14 @@ __global__ void __launch_bounds__(NT) cou_zinv_adj(CouDev d, const cplx* Gb, int
   const int Nz = d.Nz, G = d.Ngz, K = d.K, Kx = d.Kx, Ngy = d.Ngy;
   if (m0 >= Kx) return;
   const int tcn = min(tc, Kx - m0);
-  const int nf = grp == 0 ? 8 : 4;
-  // local slot -> field of Gb: group 0: u, uy, ux, uz, w, wy, wx, wz; group 1: v, vy, vx, vz
-  const int fid0[8] = {0, 3, 6, 7, 2, 5, 10, 11};
-  const int fid1[4] = {1, 4, 8, 9};
+  const int nf = grp == 0 ? 6 : 3;
+  // local slot -> field of Gb: group 0: u, uy, uz, w, wy, wz; group 1: v, vy, vz
   cplx* tw = reinterpret_cast<cplx*>(smem_d);
   cplx* b0 = tw + G;
   for (int e = tid; e < G; e += NT) tw[e] = d.twz[e];
   for (int e = tid; e < nf * G * tcn; e += NT) {
     const int q = e / (G * tcn), r = e - q * G * tcn, z = r / tcn, j = r - z * tcn;
-    const int f = grp == 0 ? fid0[q] : fid1[q];
+    const int f = 3 * (q % 3) + (grp == 1 ? 1 : (q < 3 ? 0 : 2));
     b0[fpad((q * tcn + j) * G + z)] = Gb[(((long long)f * Ngy + y) * G + z) * Kx + m0 + j];
   }
   __syncthreads();
@@ -438,19 +453,17 @@ __global__ void __launch_bounds__(NT) cou_zinv_adj(CouDev d, const cplx* Gb, int
     const int row = cou_zrow(n, Nz, G);
     const Wave w = cou_wave(d, m, n);
     auto at = [&](int q) { return row < 0 ? czero() : res[fpad((q * tcn + j) * G + row)]; };
-    // total cotangent of a component: value + conj(i kx) d/dx part + conj(i kz) d/dz part
-    auto total = [&](int qv, int qx, int qz) {
-      return cadd(at(qv), cadd(cscale(cmul_mi(at(qx)), w.kx), cscale(cmul_mi(at(qz)), w.kz)));
-    };
+    // total cotangent of a component: value (with the d/dx part) + conj(i kz) d/dz part
+    auto total = [&](int qv, int qz) { return cadd(at(qv), cscale(cmul_mi(at(qz)), w.kz)); };
     if (grp == 0) {
-      const cplx ut = total(0, 2, 3), wt = total(4, 6, 7);
-      const cplx uy = at(1), wy = at(5);
+      const cplx ut = total(0, 2), wt = total(3, 5);
+      const cplx uy = at(1), wy = at(4);
       zbar[(0LL * Ngy + y) * K + k] = lin2(w.ex, ut, w.ez, wt);
       zbar[(2LL * Ngy + y) * K + k] = lin2(-w.ez, ut, w.ex, wt);
       zbar[(3LL * Ngy + y) * K + k] = lin2(w.ex, uy, w.ez, wy);
       zbar[(5LL * Ngy + y) * K + k] = lin2(-w.ez, uy, w.ex, wy);
     } else {
-      zbar[(1LL * Ngy + y) * K + k] = total(0, 2, 3);
+      zbar[(1LL * Ngy + y) * K + k] = total(0, 2);
       zbar[(4LL * Ngy + y) * K + k] = at(1);
     }
   }
@@ -517,9 +530,10 @@ CouettePlanes::CouettePlanes(const CouetteGeom& g, hipStream_t s) : p_(new Impl)
   d.unode = m.arena.upload(std::vector<double>(g.unode, g.unode + g.Ngy), s);
   d.twx = m.arena.upload(twiddles(g.Ngx), s);
   d.twz = m.arena.upload(twiddles(g.Ngz), s);
-  m.A = col_shape(g.Ngz, 4, g.Kx);
+  SPS_REQUIRE(8 * g.Ngz <= 6 * kColLarge, "padded z grid too large for the plane kernels");
+  m.A = col_shape(g.Ngz, 3, g.Kx);
   m.C = col_shape(g.Ngz, 3, g.Kx);
-  m.A2 = col_shape(g.Ngz, 8, g.Kx);
+  m.A2 = col_shape(g.Ngz, 6, g.Kx);
   m.ntB = pick_nt(12 * g.Ngx);
   m.ntB2 = pick_nt(15 * g.Ngx);
   m.ldsB = lds_bytes(g.Ngx, 12 * g.Ngx);
@@ -533,11 +547,11 @@ CouettePlanes::CouettePlanes(const CouetteGeom& g, hipStream_t s) : p_(new Impl)
         (const void*)cou_xrow_adj<512>, (const void*)cou_xrow_adj<1024>})
     SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCouLdsMax));
   const size_t plane = (size_t)g.Ngy * g.Ngz * g.Kx;
-  m.Zf = m.arena.alloc<cplx>(12 * plane);
+  m.Zf = m.arena.alloc<cplx>(9 * plane);
   m.Wf = m.arena.alloc<cplx>(3 * plane);
-  m.Zv = m.arena.alloc<cplx>(12 * plane);
+  m.Zv = m.arena.alloc<cplx>(9 * plane);
   m.Wbv = m.arena.alloc<cplx>(3 * plane);
-  m.Gv = m.arena.alloc<cplx>(12 * plane);
+  m.Gv = m.arena.alloc<cplx>(9 * plane);
 }
 CouettePlanes::~CouettePlanes() = default;
 
