@@ -485,8 +485,10 @@ ColShape col_shape(int G, int nf, int Kx) {
   ColShape c;
   c.nt = (nf * G <= 6 * kColSmall) ? kColSmall : kColLarge;
   SPS_REQUIRE(nf * G <= 6 * c.nt, "padded z grid too large for the plane kernels");
+  // (tiles of 8, 4 or 2 columns: whole 64-byte pieces of the plane fields' lines per row; five columns
+  // of three fields would also fit, and were 5 to 15 % slower)
   int tc = std::min(8, Kx);
-  while (tc > 1 && (nf * tc * G > 6 * c.nt || lds_bytes(G, nf * tc * G) > kCouLdsBudget)) --tc;
+  while (tc > 1 && (nf * tc * G > 6 * c.nt || lds_bytes(G, nf * tc * G) > kCouLdsBudget)) tc = (tc & (tc - 1)) ? tc - 1 : tc / 2;
   c.tc = tc;
   c.lds = lds_bytes(G, nf * tc * G);
   SPS_REQUIRE(c.lds <= kCouLdsMax, "padded z grid too large for LDS");
