@@ -1922,26 +1922,67 @@ __device__ __forceinline__ void block_sums(double (&v)[C], double (*red)[NT]) {
   for (int c = 0; c < C; ++c) v[c] = red[c][0];
 }
 
-// One inverse-iteration update per wavenumber: mu = <x, y> (x has unit norm), x <- y / |y|,
-// lam = sigma - 1/mu (lam may be null).
-__global__ void __launch_bounds__(NT) rbc_evp_update(RbcDev d, cplx* x, const cplx* y, double sigma, cplx* lam) {
-  __shared__ double red[3][NT];
-  const int k = blockIdx.x, S = d.S;
-  cplx* xk = x + (size_t)k * S;
-  const cplx* yk = y + (size_t)k * S;
-  double v[3] = {0.0, 0.0, 0.0};
-  for (int s = threadIdx.x; s < S; s += NT) {
-    const cplx a = xk[s], b = yk[s];
-    v[0] += a.x * b.x + a.y * b.y;   // Re conj(a) b
-    v[1] += a.x * b.y - a.y * b.x;   // Im conj(a) b
-    v[2] += b.x * b.x + b.y * b.y;
+// All inverse iterations of one wavenumber in one block, the right (blockIdx.y = 0) and the left
+// (1) eigenvector side by side: mu = <x, y> (x has unit norm), x <- y / |y|, lam = sigma - 1/mu.  The
+// block operators are read once and stay in LDS, so an iteration is bound by the two sweeps' dependent
+// chain (256x64, 30 iterations: 1.63 ms as three launches per iteration and side, 0.53 ms here).
+// LDS: vA (S + SPS_PAD), vB, x (S complex each), the T and G blocks.
+__global__ void __launch_bounds__(NTK) rbc_evp_iterate(RbcDev d, const cplx* start, cplx* X, cplx* Y, double sigma,
+                                                       int iters, cplx* lam) {
+  extern __shared__ double smem_d[];
+  __shared__ double red[NTK / SPS_WAVE][3];
+  const int k = xcd_wavenumber(blockIdx.x, d.K), tid = threadIdx.x, N = d.N, S = d.S;
+  const bool left = blockIdx.y != 0, sl = tid < S;
+  cplx* vA = reinterpret_cast<cplx*>(smem_d);
+  cplx* vB = vA + S + SPS_PAD;
+  cplx* x = vB + S;
+  double* ops = reinterpret_cast<double*>(x + S);
+  MapRegs mr;
+  load_maps(d, mr);
+  {
+    const double2* src = reinterpret_cast<const double2*>(d.ops + (size_t)k * d.opsize);
+    double2* dst = reinterpret_cast<double2*>(ops);
+    for (int e = tid; e < d.blksz / 2; e += NTK) dst[e] = src[e];
   }
-  block_sums<3>(v, red);
-  const double inv = v[2] > 0.0 ? 1.0 / sqrt(v[2]) : 0.0;
-  for (int s = threadIdx.x; s < S; s += NT) xk[s] = cscale(yk[s], inv);
-  if (lam && threadIdx.x == 0) {
-    const double m2 = v[0] * v[0] + v[1] * v[1];
-    lam[k] = cmk(sigma - v[0] / m2, v[1] / m2);   // sigma - 1/mu
+  if (sl) x[tid] = start[(size_t)k * S + tid];
+  __syncthreads();
+  double* b = reinterpret_cast<double*>(vA);
+  const int f = tid / N, n = tid - f * N;
+  double mr0 = 0.0, mi0 = 0.0;
+  for (int it = 0; it < iters; ++it) {
+    if (sl) vB[tid] = (tid >= 3 * N) ? czero() : (left ? s10t_at(x + f * N, n, N) : s10_at(x + f * N, n, N));
+    __syncthreads();
+    if (left) rbc_gather_h(d, mr, vB, vA);
+    else rbc_gather(d, mr, vB, vA);
+    if (tid < SPS_WAVE) {
+      sweep_first(ops, ops + d.tsz, d.n, b, left);
+      sweep_second(ops, ops + d.tsz, d.n, b, left);
+    }
+    __syncthreads();
+    if (left) rbc_scatter_h(d, mr, vA, vB);
+    else rbc_scatter(d, mr, vA, vB, vA);
+    const cplx y = sl ? (left ? vB[tid] : vA[tid]) : czero(), xo = sl ? x[tid] : czero();
+    double v[3] = {xo.x * y.x + xo.y * y.y, xo.x * y.y - xo.y * y.x, y.x * y.x + y.y * y.y};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      for (int o = 32; o >= 1; o >>= 1) v[c] += __shfl_xor(v[c], o);
+      if (lane_id() == 0) red[tid >> 6][c] = v[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      v[c] = 0.0;
+      for (int w = 0; w < NTK / SPS_WAVE; ++w) v[c] += red[w][c];
+    }
+    mr0 = v[0];
+    mi0 = v[1];
+    if (sl) x[tid] = cscale(y, v[2] > 0.0 ? 1.0 / sqrt(v[2]) : 0.0);
+    __syncthreads();
+  }
+  if (sl) (left ? Y : X)[(size_t)k * S + tid] = x[tid];
+  if (!left && tid == 0) {
+    const double m2 = mr0 * mr0 + mi0 * mi0;
+    lam[k] = cmk(sigma - mr0 / m2, mi0 / m2);   // sigma - 1/mu
   }
 }
 
@@ -3237,6 +3278,9 @@ class RbcProblem : public ProblemImpl {
       estart_ = arena_.upload(x0, stream);
       const size_t lds = (size_t)(2 * ekl_ + eku_ + 1) * S_ * sizeof(double) + sizeof(int) * S_;
       SPS_REQUIRE(lds <= 160 * 1024, "problem too large for LDS");
+      SPS_REQUIRE(evp_lds() <= 160 * 1024, "problem too large for LDS");
+      SPS_HIP(hipFuncSetAttribute((const void*)rbc_evp_iterate, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)evp_lds()));
       if (lds > factor_lds())
         SPS_HIP(hipFuncSetAttribute((const void*)rbc_factor, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     }
@@ -3250,6 +3294,7 @@ class RbcProblem : public ProblemImpl {
     SPS_CHECK_LAUNCH();
     return de;
   }
+  size_t evp_lds() const { return sizeof(cplx) * (3 * S_ + SPS_PAD) + sizeof(double) * blk_ops_size(S_); }
   // y = (sigma M + L_s)^-1 M x for every wavenumber through the factors of evp_setup
   void evp_apply(const RbcDev& de, const cplx* x, cplx* y) {
     hipLaunchKernelGGL(rbc_apply_m, dim3(K_), dim3(NT), 0, stream, de, x, ework_);
@@ -3274,26 +3319,8 @@ class RbcProblem : public ProblemImpl {
     cplx* x = reinterpret_cast<cplx*>(X);
     cplx* y = reinterpret_cast<cplx*>(Y);
     cplx* l = reinterpret_cast<cplx*>(lam);
-    // right eigenvector
-    copy_state(x, estart_);
-    for (int it = 0; it < iters; ++it) {
-      evp_apply(de, x, y);   // y is scratch until the left iteration
-      hipLaunchKernelGGL(rbc_evp_update, dim3(K_), dim3(NT), 0, stream, de, x, y, sigma, l);
-      SPS_CHECK_LAUNCH();
-    }
-    // left (adjoint) eigenvector through the same factors
-    copy_state(y, estart_);
-    for (int it = 0; it < iters; ++it) {
-      hipLaunchKernelGGL(rbc_lbvp_rhs_adj, dim3(K_), dim3(NT), 0, stream, de, y, ework_);   // M^H y
-      SPS_CHECK_LAUNCH();
-      KaArgs a = ka_args(KA_SOLVE_T);
-      a.Xb_in = ework_;
-      a.Xb_out = Xw_;
-      hipLaunchKernelGGL(kadj_fn(), dim3(K_), dim3(NTK), ka_lds(), stream, de, a);
-      SPS_CHECK_LAUNCH();
-      hipLaunchKernelGGL(rbc_evp_update, dim3(K_), dim3(NT), 0, stream, de, y, Xw_, sigma, nullptr);
-      SPS_CHECK_LAUNCH();
-    }
+    hipLaunchKernelGGL(rbc_evp_iterate, dim3(K_, 2), dim3(NTK), evp_lds(), stream, de, estart_, x, y, sigma, iters, l);
+    SPS_CHECK_LAUNCH();
     const double Ra = desc_.param0;
     hipLaunchKernelGGL(rbc_evp_sens, dim3(K_), dim3(NT), 0, stream, de, x, y, -0.5 * nu_ / Ra, -0.5 * ka_ / Ra,
                        reinterpret_cast<cplx*>(dlam));

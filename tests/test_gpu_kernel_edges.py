@@ -42,3 +42,30 @@ def test_rollout_loss_steps(nsteps):
     for i in range(2):
         Jo = rollout_loss_and_gradients(P, v[i].reshape(-1, 1), [t.reshape(-1, 1) for t in tg], dt, nsteps)[0]
         assert abs(J[i].item() - Jo) < 1e-11 * Jo
+
+
+# inverse iteration from the library's fixed start vector, iteration by iteration, on the smallest
+# Chebyshev size, a size whose last block of eight rows is partial, and the largest; the solves' relative
+# error is about eps times the condition number of sigma M + L_s (1e5 to 1e6 here)
+@pytest.mark.parametrize("nx,nz,iters", [(8, 8, 1), (8, 10, 3), (24, 64, 2)])
+def test_inverse_iteration_steps(nx, nz, iters):
+    from oracle.rbc import RBC
+    print(f"inverse iteration {nx}x{nz}, {iters}", flush=True)
+    sigma, P = 0.3, RBC(Nx=nx, Nz=nz, Lx=4.0, Ra=1e5, Pr=1.0)
+    G = sps.Problem(sps.RBC2D, nx, nz, 4.0, 1e5, 1.0, 1.5, 1e-3, 1, 1)
+    lam, X, Y, _ = G.stability(sigma, iters)
+    G.sync()
+    s = np.arange(P.S)
+    start = np.where(s < 3 * nz, 1.0 / (1 + s % nz) + 0.5j / (1 + s // nz), 0.0)
+    Ls = P.stability_operator()
+    for k in range(P.K):
+        A, M = sigma * P.M[k] + Ls[k], P.M[k]
+        x, y = start, start
+        for _ in range(iters):
+            z = np.linalg.solve(A, M @ x)
+            mu, x = np.vdot(x, z), z / np.linalg.norm(z)
+            z = np.linalg.solve(A.conj().T, M.conj().T @ y)
+            y = z / np.linalg.norm(z)
+        assert abs(lam[k].item() - (sigma - 1.0 / mu)) <= 1e-9 * abs(1.0 / mu)
+        assert np.linalg.norm(X[k].cpu().numpy() - x) <= 1e-9
+        assert np.linalg.norm(Y[k].cpu().numpy() - y) <= 1e-9
