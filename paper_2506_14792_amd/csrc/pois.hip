@@ -25,8 +25,8 @@
 // banded (kl = 11, ku = 19 at every N).
 //
 // One block per system runs, for every Newton iteration: assembly, the LU factorization, the
-// right eigenvector by inverse iteration y <- A^{-1} M y (wave 0) and at the same time the left
-// eigenvector by w <- A^{-H} M^H w (wave 1) through the same factors, then the sensitivities
+// right eigenvector by inverse iteration y <- A^{-1} M y and at the same time the left
+// eigenvector by w <- A^{-H} M^H w through the same factors, then the sensitivities
 // d lambda/dRe = -<w, dL/dRe y> / <w, M y>, d lambda/dalpha likewise, and the Newton update of Re
 // (or alpha) on the growth rate Re(lambda) with the next shift at the new eigenvalue.  A
 // continuation step (the paper's tracing of the neutral curve) first moves along the curve's
@@ -50,24 +50,36 @@
 namespace sps {
 namespace {
 
-constexpr int PT = 256;   // threads per system block (wave 0: right iteration, wave 1: left)
+constexpr int PT = 256;    // threads of the start and finish blocks
+constexpr int PTF = 512;   // threads of a factor block
+// Block operators of the factors, eight rows each (window and width for kl = 11, ku <= 19):
+//   L  in block t, with all of its row exchanges done first (permutation pi_t of the PTW-row window),
+//      is [A_t | (0; I)] with A_t of PTW x 8;
+//   U  back substitution of block t: x_block = G_t [y_block; the next entries], G_t of 8 x PGW.
+// The forward solve applies the T_t for t ascending, then the G_t for t descending, the solve with
+// the conjugate transpose G_t^H ascending, then T_t^H descending.
+constexpr int PB = 8, PTW = 20, PGW = 40;
+// A block's operators as the lanes of the right (r) and left (l) iterations read them, entry u of
+// lane L at u * lanes + L:
+constexpr int PTR = 4 * 2 * PTW;   // A_t: lane 2 row + half, entries 4 half + u
+constexpr int PTL = 3 * 64;        // A_t: lane 8 column + q, rows q + 8 u (zero from PTW on)
+constexpr int PGR = 5 * 64;        // G_t: lane 8 row + q, columns 5 q + u
+constexpr int PGL = 8 * PGW;       // G_t: lane = column, rows u
+constexpr int PWIN = 16, PWC = 64; // LDS window of the factorization: rows and columns mod these
 
 __device__ __forceinline__ double cabs1(cplx a) { return fabs(a.x) + fabs(a.y); }
 __device__ __forceinline__ cplx cmulc(cplx a, cplx b) {   // conj(a) b
   return cmk(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
+__device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx c) {   // a b + c
+  return cmk(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
+}
+__device__ __forceinline__ cplx cfmac(cplx a, cplx b, cplx c) {   // conj(a) b + c
+  return cmk(fma(a.x, b.x, fma(a.y, b.y, c.x)), fma(a.x, b.y, fma(-a.y, b.x, c.y)));
+}
 __device__ __forceinline__ cplx crecip(cplx a) {
   const double s = 1.0 / (a.x * a.x + a.y * a.y);
   return cmk(a.x * s, -a.y * s);
-}
-// LDS vectors are read and written through volatile pointers: within one wave LDS accesses
-// execute in program order, so a value one lane writes is seen by the next access of every
-// lane, and the compiler keeps them in that order without a fence (a fence would also wait for
-// the global loads issued ahead).
-__device__ __forceinline__ cplx vld(const volatile double* v, int i) { return cmk(v[2 * i], v[2 * i + 1]); }
-__device__ __forceinline__ void vst(volatile double* v, int i, cplx a) {
-  v[2 * i] = a.x;
-  v[2 * i + 1] = a.y;
 }
 __device__ __forceinline__ cplx wave_csum(cplx a) {
   for (int o = 32; o >= 1; o >>= 1) {
@@ -76,20 +88,41 @@ __device__ __forceinline__ cplx wave_csum(cplx a) {
   }
   return a;
 }
+// Compiler-only barrier between LDS accesses of one wave (a wave's LDS instructions execute in order).
+__device__ __forceinline__ void wsync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// A system between the launches of one call.
+struct PoisState {
+  double alpha, Re;
+  cplx sig, lam;
+  int stop, solves;
+};
 
 struct PoisDev {
-  int N, S, kl, ku, bw, ldw;     // bw = kl + ku + 1 (the operators), ldw = 2 kl + ku + 1 (LU with fill)
+  int N, S, kl, ku, bw, ldw;     // bw = kl + ku + 1 (the operators), ldw = 2 kl + ku + 1 (a factor row)
+  int nb, mw;                    // blocks of eight rows; most entries of a row of M or of M^H
   const cplx* bM;                // [S][bw] row bands of the permuted, recombined M
   const cplx* bL0;               // parts of L: L0 + alpha La + nu Ln + nu alpha^2 Lq
   const cplx* bLa;
   const cplx* bLn;
   const cplx* bLq;
+  const int* mcol[2];            // M and M^H by rows: column of entry e of row i at e S + i (padded rows
+  const double* mval[2];         // repeat an entry with value 0); M is real
   const int* rowmap;             // band row i <- state row rowmap[i]
   const int* colinv;             // state column c -> band column colinv[c]
   const double* rho;             // recombination: x[c] = y'[c] + rho[c] y'[c + 2]
-  cplx* W;                       // [sys][S][ldw] LU factors, column-major (element (i, j) at j ldw + kl + ku + i - j)
+  cplx* W;                       // [sys][S][ldw]: U row j (U[j][j + r] at r <= kl + ku), then L's multipliers of step j
   cplx* dinv;                    // [sys][S] reciprocals of U's diagonal
-  int* piv;                      // [sys][S] row interchanges
+  int* piv;                      // [sys][S] row interchanges (p - j)
+  cplx *Tr, *Tl, *Gr, *Gl;       // [sys][nb][PTR] ...: the block operators
+  unsigned char* perm;           // [sys][nb][PTW]
+  cplx* vec;                     // [2][sys][S] right and left vectors
+  PoisState* st;                 // [sys]
+  int* active;                   // [solve] systems that go on after it
+  int maxsys;
   int* err;
 };
 
@@ -105,167 +138,363 @@ struct PoisArgs {
   cplx* Y;                       // [sys][S] left eigenvector (nullable)
 };
 
-// y = B x (op band [S][bw]) for rows i = lane, lane + 64, ...; one wave; x, y in LDS
-__device__ void wave_band_mv(const PoisDev& d, const cplx* B, const volatile double* x, volatile double* y) {
-  const int lane = threadIdx.x & 63, n = d.S;
-  for (int i = lane; i < n; i += 64) {
-    cplx s = czero();
-    const int d0 = max(0, d.kl - i), d1 = min(d.bw - 1, n - 1 - i + d.kl);
-    for (int q = d0; q <= d1; ++q) s = cadd(s, cmul(B[(size_t)i * d.bw + q], vld(x, i + q - d.kl)));
-    vst(y, i, s);
-  }
-}
-// y = B^H x
-__device__ void wave_band_mvh(const PoisDev& d, const cplx* B, const volatile double* x, volatile double* y) {
-  const int lane = threadIdx.x & 63, n = d.S;
-  for (int j = lane; j < n; j += 64) {
-    cplx s = czero();
-    const int i0 = max(0, j - d.ku), i1 = min(n - 1, j + d.kl);
-    for (int i = i0; i <= i1; ++i) s = cadd(s, cmulc(B[(size_t)i * d.bw + (j - i + d.kl)], vld(x, i)));
-    vst(y, j, s);
-  }
-}
-
-// b <- A^{-1} b through the factors (row interchanges and L, then U); one wave.  The factor
-// entries of the next D columns are loaded ahead into a register ring.
-constexpr int PD = 8;
-__device__ void wave_lu_solve(const PoisDev& d, const cplx* W, const cplx* dinv, const int* piv,
-                              volatile double* b) {
-  const int lane = threadIdx.x & 63, n = d.S, kl = d.kl, kv = d.kl + d.ku, ldw = d.ldw;
-  auto lload = [&](int j) {
-    return (j < n - 1 && lane >= 1 && lane <= min(kl, n - 1 - j)) ? W[(size_t)j * ldw + kv + lane] : czero();
-  };
-  cplx ring[PD];
-  int pr[PD];
-#pragma unroll
-  for (int k = 0; k < PD; ++k) {
-    ring[k] = lload(k);
-    pr[k] = (k < n) ? piv[k] : k;
-  }
-  for (int j0 = 0; j0 < n - 1; j0 += PD) {
-#pragma unroll
-    for (int k = 0; k < PD; ++k) {
-      const int j = j0 + k;
-      if (j < n - 1) {
-        const cplx l = ring[k];
-        const int p = pr[k];
-        ring[k] = lload(j + PD);
-        pr[k] = (j + PD < n) ? piv[j + PD] : j + PD;
-        if (p != j && lane == 0) {
-          const cplx t = vld(b, j);
-          vst(b, j, vld(b, p));
-          vst(b, p, t);
-        }
-        const cplx bj = vld(b, j);
-        if (lane >= 1 && lane <= min(kl, n - 1 - j)) vst(b, j + lane, csub(vld(b, j + lane), cmul(l, bj)));
-      }
-    }
-  }
-  auto uload = [&](int j) {
-    return (j >= 0 && lane >= 1 && lane <= min(kv, j)) ? W[(size_t)j * ldw + kv - lane] : czero();
-  };
-#pragma unroll
-  for (int k = 0; k < PD; ++k) {
-    ring[k] = uload(n - 1 - k);
-  }
-  cplx dr[PD];
-#pragma unroll
-  for (int k = 0; k < PD; ++k) dr[k] = (n - 1 - k >= 0) ? dinv[n - 1 - k] : czero();
-  for (int j0 = n - 1; j0 >= 0; j0 -= PD) {
-#pragma unroll
-    for (int k = 0; k < PD; ++k) {
-      const int j = j0 - k;
-      if (j >= 0) {
-        const cplx u = ring[k], di = dr[k];
-        ring[k] = uload(j - PD);
-        dr[k] = (j - PD >= 0) ? dinv[j - PD] : czero();
-        const cplx bj = cmul(vld(b, j), di);
-        if (lane == 0) vst(b, j, bj);
-        if (lane >= 1 && lane <= min(kv, j)) vst(b, j - lane, csub(vld(b, j - lane), cmul(u, bj)));
-      }
-    }
-  }
-}
-
-// b <- A^{-H} b: U^H forward (row sums), then L^H backward with the row interchanges in reverse;
-// one wave.
-__device__ void wave_lu_solve_h(const PoisDev& d, const cplx* W, const cplx* dinv, const int* piv,
-                                volatile double* b) {
-  const int lane = threadIdx.x & 63, n = d.S, kl = d.kl, kv = d.kl + d.ku, ldw = d.ldw;
-  auto uload = [&](int j) {
-    return (j < n && lane >= 1 && lane <= min(kv, j)) ? W[(size_t)j * ldw + kv - lane] : czero();
-  };
-  cplx ring[PD], dr[PD];
-#pragma unroll
-  for (int k = 0; k < PD; ++k) {
-    ring[k] = uload(k);
-    dr[k] = (k < n) ? dinv[k] : czero();
-  }
-  for (int j0 = 0; j0 < n; j0 += PD) {
-#pragma unroll
-    for (int k = 0; k < PD; ++k) {
-      const int j = j0 + k;
-      if (j < n) {
-        const cplx u = ring[k], di = dr[k];
-        ring[k] = uload(j + PD);
-        dr[k] = (j + PD < n) ? dinv[j + PD] : czero();
-        cplx t = (lane >= 1 && lane <= min(kv, j)) ? cmulc(u, vld(b, j - lane)) : czero();
-        t = wave_csum(t);
-        if (lane == 0) vst(b, j, cmulc(di, csub(vld(b, j), t)));   // (b_j - sum) / conj(u_jj)
-      }
-    }
-  }
-  auto lload = [&](int j) {
-    return (j >= 0 && j < n - 1 && lane >= 1 && lane <= min(kl, n - 1 - j)) ? W[(size_t)j * ldw + kv + lane]
-                                                                             : czero();
-  };
-  int pr[PD];
-#pragma unroll
-  for (int k = 0; k < PD; ++k) {
-    ring[k] = lload(n - 2 - k);
-    pr[k] = (n - 2 - k >= 0) ? piv[n - 2 - k] : 0;
-  }
-  for (int j0 = n - 2; j0 >= 0; j0 -= PD) {
-#pragma unroll
-    for (int k = 0; k < PD; ++k) {
-      const int j = j0 - k;
-      if (j >= 0) {
-        const cplx l = ring[k];
-        const int p = pr[k];
-        ring[k] = lload(j - PD);
-        pr[k] = (j - PD >= 0) ? piv[j - PD] : 0;
-        cplx t = (lane >= 1 && lane <= min(kl, n - 1 - j)) ? cmulc(l, vld(b, j + lane)) : czero();
-        t = wave_csum(t);
-        if (lane == 0) {
-          const cplx bj = csub(vld(b, j), t);
-          if (p != j) {
-            vst(b, j, vld(b, p));
-            vst(b, p, bj);
-          } else {
-            vst(b, j, bj);
-          }
-        }
-      }
-    }
-  }
-}
-
-// Normalizes x (one wave) and returns <prev, x> / |x| before normalization's scale applied, i.e.
-// mu = conj(prev) . x with prev of unit norm (the inverse-iteration Rayleigh estimate).
-__device__ cplx wave_normalize(const PoisDev& d, const volatile double* prev, volatile double* x) {
-  const int lane = threadIdx.x & 63;
-  cplx mu = czero();
+// State of each system and its start vectors (the same for every system), unit norm.  One wave per system.
+__global__ void __launch_bounds__(64) pois_start(PoisDev d, PoisArgs a) {
+  const int sys = blockIdx.x, lane = threadIdx.x, n = d.S;
   double nn = 0.0;
-  for (int i = lane; i < d.S; i += 64) {
-    const cplx a = vld(prev, i), b = vld(x, i);
-    mu = cadd(mu, cmulc(a, b));
-    nn += b.x * b.x + b.y * b.y;
+  auto s0 = [](int i) { return cmk(1.0 / (1 + i % 7), 0.5 / (1 + i % 5)); };
+  for (int i = lane; i < n; i += 64) {
+    const cplx v = s0(i);
+    nn += v.x * v.x + v.y * v.y;
   }
-  mu = wave_csum(mu);
   for (int o = 32; o >= 1; o >>= 1) nn += __shfl_xor(nn, o);
-  const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
-  for (int i = lane; i < d.S; i += 64) vst(x, i, cscale(vld(x, i), inv));
-  return mu;
+  const double inv = 1.0 / sqrt(nn);
+  for (int i = lane; i < n; i += 64)
+    for (int side = 0; side < 2; ++side) d.vec[((size_t)side * d.maxsys + sys) * n + i] = cscale(s0(i), inv);
+  if (lane == 0) {
+    PoisState s;
+    s.alpha = a.params[5 * sys];
+    s.Re = a.params[5 * sys + 1];
+    s.sig = cmk(a.params[5 * sys + 2], a.params[5 * sys + 3]);
+    s.lam = czero();
+    s.stop = 0;
+    s.solves = 0;
+    d.st[sys] = s;
+  }
+}
+
+// Banded LU with partial pivoting of A = sigma M + L0 + alpha La + nu Ln + nu alpha^2 Lq, then the block
+// operators of its factors.  One block per system.  The rows and columns a step touches (kl + 1 by
+// kl + ku + 1) are in an LDS window, entry (i, c) at [i mod 16][c mod 64], one entry per thread: every
+// wave finds the pivot by itself, then reads its entry, its row's multiplier and the pivot row, and
+// writes the updated entry, with two block barriers a column.  The rows that enter are read eight
+// columns ahead.  Bound by that chain: 0.3 us a column (3 us with the band in global memory and four
+// barriers).
+__global__ void __launch_bounds__(PTF) pois_factor(PoisDev d) {
+  __shared__ cplx win[PWIN][PWC];
+  const int sys = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int n = d.S, kl = d.kl, kv = d.kl + d.ku, ldw = d.ldw, bw = d.bw;
+  const PoisState st = d.st[sys];
+  if (st.stop) return;
+  const double alpha = st.alpha, nu = 1.0 / st.Re, q2 = nu * alpha * alpha;
+  cplx* W = d.W + (size_t)sys * n * ldw;
+  cplx* dinv = d.dinv + (size_t)sys * n;
+  int* piv = d.piv + (size_t)sys * n;
+  // assembly: row i of A at W[i ldw + q], column i + q - kl
+  for (int e = tid; e < n * bw; e += PTF) {
+    const int i = e / bw, q = e - i * bw, j = i + q - kl;
+    cplx v = czero();
+    if (j >= 0 && j < n) {
+      v = cadd(cmul(st.sig, d.bM[e]), d.bL0[e]);
+      v = cadd(v, cscale(d.bLa[e], alpha));
+      v = cadd(v, cscale(d.bLn[e], nu));
+      v = cadd(v, cscale(d.bLq[e], q2));
+    }
+    W[(size_t)i * ldw + q] = v;
+  }
+  for (int e = tid; e < PWIN * PWC; e += PTF) win[e / PWC][e % PWC] = czero();
+  __syncthreads();
+  for (int e = tid; e < (kl + 1) * bw; e += PTF) {
+    const int i = e / bw, c = e - i * bw + i - kl;
+    if (c >= 0 && i < n) win[i % PWIN][c % PWC] = W[(size_t)i * ldw + (c - i + kl)];
+  }
+  const bool feeder = tid >= PTF - 64;   // the wave that brings in the rows
+  auto enter = [&](int i) { return (feeder && lane < bw && i < n) ? W[(size_t)i * ldw + lane] : czero(); };
+  cplx ring[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) ring[u] = enter(kl + 1 + u);
+  __syncthreads();
+  const int r = tid >> 5, cl = tid & 31;
+  for (int j0 = 0; j0 < n; j0 += 8) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int j = j0 + u;
+      if (j >= n) break;
+      const int km = min(kl, n - 1 - j), jc = j % PWC;
+      const cplx cv = win[(j + (lane & 15)) % PWIN][jc];
+      double best = ((lane & 15) <= km) ? cabs1(cv) : -1.0;
+      int p = lane & 15;
+      auto merge = [&](double ob, int op) {
+        if (ob > best || (ob == best && op < p)) {
+          best = ob;
+          p = op;
+        }
+      };
+      merge(dpp_xor1(best), __builtin_amdgcn_mov_dpp(p, 0xB1, 0xF, 0xF, false));
+      merge(dpp_xor2(best), __builtin_amdgcn_mov_dpp(p, 0x4E, 0xF, 0xF, false));
+      merge(dpp_mirror8(best), __builtin_amdgcn_mov_dpp(p, 0x141, 0xF, 0xF, false));
+      merge(dpp_d<0x140>(best), __builtin_amdgcn_mov_dpp(p, 0x140, 0xF, 0xF, false));
+      p = __builtin_amdgcn_readfirstlane(p);
+      const cplx pv = cmk(readlane_d(cv.x, p), readlane_d(cv.y, p));
+      const cplx pinv = (pv.x != 0.0 || pv.y != 0.0) ? crecip(pv) : czero();
+      // this thread's entry: row j + r (after the interchange), column j + cl
+      const int src = ((r == p) ? j : j + r) % PWIN, cc = (j + cl) % PWC;
+      const cplx up = win[(j + p) % PWIN][cc], a0 = win[src][cc], aj = win[src][jc];
+      const cplx l = cmul(aj, pinv), nv = csub(a0, cmul(l, up));
+      __syncthreads();
+      if (r == 0) {
+        if (cl <= kv) W[(size_t)j * ldw + cl] = (j + cl < n) ? up : czero();
+        if (cl == 0) {
+          dinv[j] = pinv;
+          piv[j] = p;
+          if (!(best > 0.0)) atomicOr(d.err, 1);
+        }
+      } else if (r <= kl) {
+        if (cl == 0) W[(size_t)j * ldw + kv + r] = (r <= km) ? l : czero();
+        else if (cl <= kv) win[(j + r) % PWIN][cc] = (r <= km) ? nv : czero();
+        else if (cl == kv + 1) win[(j + r) % PWIN][cc] = czero();   // the column that enters
+      }
+      if (feeder) {
+        const int i = j + kl + 1;
+        if (lane < bw) win[i % PWIN][(i + lane - kl) % PWC] = ring[u];
+        ring[u] = enter(i + 8);
+      }
+      __syncthreads();
+    }
+  }
+  // T_t: the image of the window's unit vector c under the block's exchanges and eliminations is column
+  // pos of A_t, pos the row that the exchanges bring entry c to (or e_pos for pos >= 8)
+  const int nb = d.nb;
+  const size_t ob = (size_t)sys * nb;
+  for (int e = tid; e < nb * PTW; e += PTF) {
+    const int t = e / PTW, c = e - t * PTW, tb = t * PB;
+    cplx v[PTW];
+#pragma unroll
+    for (int i = 0; i < PTW; ++i) v[i] = cmk(i == c ? 1.0 : 0.0, 0.0);
+    int pos = c;
+    for (int q = 0; q < PB; ++q) {
+      const int j = tb + q;
+      if (j >= n) break;
+      const int p = piv[j], km = min(kl, n - 1 - j);
+      if (pos == q) pos = q + p;
+      else if (pos == q + p) pos = q;
+      cplx vq = czero(), vp = czero();
+#pragma unroll
+      for (int i = 0; i < PTW; ++i) {
+        if (i == q) vq = v[i];
+        if (i == q + p) vp = v[i];
+      }
+#pragma unroll
+      for (int i = 0; i < PTW; ++i) {
+        if (i == q) v[i] = vp;
+        else if (i == q + p) v[i] = vq;
+        if (i > q && i - q <= km) v[i] = csub(v[i], cmul(W[(size_t)j * ldw + kv + i - q], vp));
+      }
+    }
+    d.perm[(ob + t) * PTW + pos] = (unsigned char)c;
+    if (pos < PB) {
+      cplx* Tr = d.Tr + (ob + t) * PTR;
+      cplx* Tl = d.Tl + (ob + t) * PTL;
+#pragma unroll
+      for (int i = 0; i < PTW; ++i) {
+        Tr[(pos & 3) * (2 * PTW) + 2 * i + (pos >> 2)] = v[i];
+        Tl[(i >> 3) * 64 + pos * 8 + (i & 7)] = v[i];
+      }
+#pragma unroll
+      for (int i = PTW; i < 24; ++i) Tl[(i >> 3) * 64 + pos * 8 + (i & 7)] = czero();
+    }
+  }
+  // G_t by columns: U_tt x = e_c (c < 8), or -U's column tb + c
+  for (int e = tid; e < nb * PGW; e += PTF) {
+    const int t = e / PGW, c = e - t * PGW, tb = t * PB;
+    cplx x[PB];
+#pragma unroll
+    for (int i = PB - 1; i >= 0; --i) {
+      const cplx* Ur = W + (size_t)min(tb + i, n - 1) * ldw;
+      cplx s = czero();
+      if (c < PB) s.x = (i == c) ? 1.0 : 0.0;
+      else if (tb + c < n && c - i <= kv) s = cscale(Ur[c - i], -1.0);
+#pragma unroll
+      for (int k = i + 1; k < PB; ++k) s = csub(s, cmul(Ur[k - i], x[k]));
+      x[i] = (tb + i < n) ? cmul(s, dinv[min(tb + i, n - 1)]) : czero();
+    }
+    cplx* Gr = d.Gr + (ob + t) * PGR;
+    cplx* Gl = d.Gl + (ob + t) * PGL;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      Gr[(c % 5) * 64 + i * 8 + c / 5] = x[i];
+      Gl[i * PGW + c] = x[i];
+    }
+  }
+}
+
+// All inverse iterations of one system's right (blockIdx.y = 0: y <- A^{-1} M y) or left (w <- A^{-H} M^H w)
+// vector, in one wave: no barriers; the vector is in LDS, and every block operator goes straight from
+// memory to the registers of the lanes that use it, PD blocks ahead (a block step is one LDS round
+// trip, a short sum per lane and a DPP sum).  Bound by that chain and by a wave's reads, 8 kB a
+// block: 128 systems put 256 waves on 256 CUs.
+// LDS: x, t (S + PGW each), M's values and columns, the permutations.
+constexpr int PD = 4;
+template <int side>
+__device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double* sm) {
+  const int sys = blockIdx.x, lane = threadIdx.x, n = d.S, nb = d.nb, mw = d.mw;
+  const PoisState* st = d.st + sys;
+  if (st->stop) return;
+  cplx* x = reinterpret_cast<cplx*>(sm);
+  cplx* t = x + n;
+  double* mv = reinterpret_cast<double*>(t + n + PGW);
+  int* mc = reinterpret_cast<int*>(mv + mw * n);
+  unsigned char* pm = reinterpret_cast<unsigned char*>(mc + mw * n);
+  cplx* gx = d.vec + ((size_t)side * d.maxsys + sys) * n;
+  for (int i = lane; i < n; i += 64) x[i] = gx[i];
+  for (int i = lane; i < PGW; i += 64) t[n + i] = czero();
+  for (int i = lane; i < mw * n; i += 64) {
+    mv[i] = d.mval[side][i];
+    mc[i] = d.mcol[side][i];
+  }
+  const size_t ob = (size_t)sys * nb;
+  for (int i = lane; i < nb * PTW; i += 64) pm[i] = d.perm[ob * PTW + i];
+  wsync();
+  const cplx* T = side ? d.Tl + ob * PTL : d.Tr + ob * PTR;
+  const cplx* G = side ? d.Gl + ob * PGL : d.Gr + ob * PGR;
+  cplx tr[PD][4], gr[PD][8];
+  const int lt = side ? lane : min(lane, 2 * PTW - 1), lg = side ? min(lane, PGW - 1) : lane;
+  // entries of block b for this lane (indices clamped, so that every load is issued)
+  auto load_t = [&](int b, cplx (&v)[4]) {
+    const cplx* p = T + (size_t)min(max(b, 0), nb - 1) * (side ? PTL : PTR) + lt;
+    const int s = side ? 64 : 2 * PTW;
+    v[0] = p[0];
+    v[1] = p[s];
+    v[2] = p[2 * s];
+    if (!side) v[3] = p[3 * s];
+  };
+  auto load_g = [&](int b, cplx (&v)[8]) {
+    const cplx* p = G + (size_t)min(max(b, 0), nb - 1) * (side ? PGL : PGR) + lg;
+    const int s = side ? PGW : 64;
+#pragma unroll
+    for (int u = 0; u < 5; ++u) v[u] = p[u * s];
+    if (side) {
+#pragma unroll
+      for (int u = 5; u < 8; ++u) v[u] = p[u * s];
+    }
+  };
+  auto first_t = [&](int u) { return side ? nb - 1 - u : u; };   // T ascends on the right, descends on the left
+  auto first_g = [&](int u) { return side ? u : nb - 1 - u; };
+#pragma unroll
+  for (int u = 0; u < PD; ++u) load_t(first_t(u), tr[u]);
+#pragma unroll
+  for (int u = 0; u < PD; ++u) load_g(first_g(u), gr[u]);
+  // right: rows 2 row + half of A_t; left: column lane / 8, rows lane % 8 + 8 u
+  const int rr = lane >> 1, hh = lane & 1, c8 = lane >> 3, q8 = lane & 7;
+  auto step_t = [&](int b, const cplx (&v)[4]) {
+    cplx* w = t + b * PB;
+    const unsigned char* pb = pm + b * PTW;
+    if (!side) {
+      const int rc = min(rr, PTW - 1);
+      cplx s = (hh == 0 && rc >= PB) ? w[pb[rc]] : czero();
+      cplx s2 = czero();
+      s = cfma(v[0], w[pb[4 * hh]], s);
+      s2 = cfma(v[1], w[pb[4 * hh + 1]], s2);
+      s = cfma(v[2], w[pb[4 * hh + 2]], s);
+      s2 = cfma(v[3], w[pb[4 * hh + 3]], s2);
+      s = cadd(s, s2);
+      s = cadd(s, cmk(dpp_xor1(s.x), dpp_xor1(s.y)));
+      wsync();
+      if (hh == 0 && rr < PTW && b * PB + rr < n) w[rr] = s;
+    } else {
+      // lane q = 0 stores the sum at pi(c), lanes q = 1, 2 the entries that only move
+      const int row = (q8 == 1) ? PB + c8 : 2 * PB + (c8 & 3);
+      const cplx keep = w[row];
+      cplx s = cfmac(v[0], w[q8], czero());
+      s = cfmac(v[1], w[q8 + 8], s);
+      s = cfmac(v[2], w[q8 + 16], s);
+      s = group_sum<8>(s);
+      const int dst = b * PB + pb[(q8 == 0) ? c8 : row];
+      wsync();
+      if ((q8 < 2 || (q8 == 2 && c8 < 4)) && dst < n) t[dst] = (q8 == 0) ? s : keep;
+    }
+    wsync();
+  };
+  auto step_g = [&](int b, const cplx (&v)[8]) {
+    cplx* w = t + b * PB;
+    if (!side) {   // row c8, columns 5 q8 + u
+      cplx s = czero(), s2 = czero();
+      s = cfma(v[0], w[5 * q8], s);
+      s2 = cfma(v[1], w[5 * q8 + 1], s2);
+      s = cfma(v[2], w[5 * q8 + 2], s);
+      s2 = cfma(v[3], w[5 * q8 + 3], s2);
+      s = cfma(v[4], w[5 * q8 + 4], s);
+      s = group_sum<8>(cadd(s, s2));
+      wsync();
+      if (q8 == 0 && b * PB + c8 < n) w[c8] = s;
+    } else {       // column lane
+      cplx s = (lane >= PB && lane < PGW) ? w[lg] : czero(), s2 = czero();
+#pragma unroll
+      for (int u = 0; u < 8; u += 2) {
+        s = cfmac(v[u], w[u], s);
+        s2 = cfmac(v[u + 1], w[u + 1], s2);
+      }
+      s = cadd(s, s2);
+      wsync();
+      if (lane < PGW && b * PB + lane < n) w[lane] = s;
+    }
+    wsync();
+  };
+  auto sweep_t = [&]() {
+    for (int b0 = 0; b0 < nb; b0 += PD)
+#pragma unroll
+      for (int u = 0; u < PD; ++u)
+        if (b0 + u < nb) {
+          step_t(first_t(b0 + u), tr[u]);
+          load_t(first_t(b0 + u + PD), tr[u]);
+        }
+#pragma unroll
+    for (int u = 0; u < PD; ++u) load_t(first_t(u), tr[u]);   // the next iteration's
+  };
+  auto sweep_g = [&]() {
+    for (int b0 = 0; b0 < nb; b0 += PD)
+#pragma unroll
+      for (int u = 0; u < PD; ++u)
+        if (b0 + u < nb) {
+          step_g(first_g(b0 + u), gr[u]);
+          load_g(first_g(b0 + u + PD), gr[u]);
+        }
+#pragma unroll
+    for (int u = 0; u < PD; ++u) load_g(first_g(u), gr[u]);
+  };
+  cplx mu = czero();
+  for (int k = 0; k < iters; ++k) {
+    for (int i = lane; i < n; i += 64) {
+      cplx s = czero();
+      for (int e = 0; e < mw; ++e) {
+        const cplx xv = x[mc[e * n + i]];
+        const double m = mv[e * n + i];
+        s = cmk(fma(m, xv.x, s.x), fma(m, xv.y, s.y));
+      }
+      t[i] = s;
+    }
+    wsync();
+    if (!side) {
+      sweep_t();
+      sweep_g();
+    } else {
+      sweep_g();
+      sweep_t();
+    }
+    // x <- t / |t|, mu = <x, t>
+    mu = czero();
+    double nn = 0.0;
+    for (int i = lane; i < n; i += 64) {
+      const cplx b = t[i];
+      mu = cfmac(x[i], b, mu);
+      nn += b.x * b.x + b.y * b.y;
+    }
+    mu = wave_csum(mu);
+    for (int o = 32; o >= 1; o >>= 1) nn += __shfl_xor(nn, o);
+    const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
+    for (int i = lane; i < n; i += 64) x[i] = cscale(t[i], inv);
+    wsync();
+  }
+  for (int i = lane; i < n; i += 64) gx[i] = x[i];
+  if (side == 0 && lane == 0) {
+    const double m2 = mu.x * mu.x + mu.y * mu.y;
+    d.st[sys].lam = cmk(st->sig.x - mu.x / m2, st->sig.y + mu.y / m2);   // sigma - 1/mu
+  }
+}
+__global__ void __launch_bounds__(64) pois_iterate(PoisDev d, int iters) {
+  extern __shared__ double sm[];
+  if (blockIdx.y == 0) iterate_side<0>(d, iters, sm);
+  else iterate_side<1>(d, iters, sm);
 }
 
 template <int NV>
@@ -287,225 +516,116 @@ __device__ void block_csums(cplx* v, double* red) {
   __syncthreads();
 }
 
-// LDS: y, w (right and left vectors), t0, t1 (their matrix products), S complex each; then
-// reduction and pivot scratch.
-__global__ void __launch_bounds__(PT) pois_evp(PoisDev d, PoisArgs a) {
+// After eigenvalue solve `it`: the sensitivities, the Newton or continuation update of a system that
+// goes on, the outputs of one that is done.  One block per system.  LDS: y, w, t (S complex each).
+__global__ void __launch_bounds__(PT) pois_finish(PoisDev d, PoisArgs a, int it) {
   extern __shared__ double sm[];
-  volatile double* y = sm;
-  volatile double* w = y + 2 * d.S;
-  volatile double* t0 = w + 2 * d.S;
-  volatile double* t1 = t0 + 2 * d.S;
-  cplx* lm = reinterpret_cast<cplx*>(sm + 8 * d.S);   // kl + 1 multipliers of the current column
-  double* red = reinterpret_cast<double*>(lm + 32);   // 2 * 3 * PT / 64 doubles
-  __shared__ int s_p, s_ju, s_stop;
-  __shared__ double s_par[2];     // alpha, Re
-  __shared__ cplx s_sig, s_lam;
-  const int sys = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int n = d.S, kl = d.kl, ku = d.ku, kv = kl + ku, ldw = d.ldw, bw = d.bw;
-  cplx* W = d.W + (size_t)sys * n * ldw;
-  cplx* dinv = d.dinv + (size_t)sys * n;
-  int* piv = d.piv + (size_t)sys * n;
-  if (tid == 0) {
-    s_par[0] = a.params[5 * sys];
-    s_par[1] = a.params[5 * sys + 1];
-    s_sig = cmk(a.params[5 * sys + 2], a.params[5 * sys + 3]);
-    s_stop = 0;
-  }
-  // start vectors (the same for every system), unit norm
+  __shared__ double red[2 * 3 * PT / 64];
+  __shared__ int s_stop;
+  cplx* y = reinterpret_cast<cplx*>(sm);
+  cplx* w = y + d.S;
+  cplx* t0 = w + d.S;
+  const int sys = blockIdx.x, tid = threadIdx.x, n = d.S, kl = d.kl, bw = d.bw;
+  const PoisState st = d.st[sys];
+  if (st.stop) return;
   for (int i = tid; i < n; i += PT) {
-    const cplx s0 = cmk(1.0 / (1 + i % 7), 0.5 / (1 + i % 5));
-    vst(t0, i, s0);
-    vst(y, i, s0);
-    vst(w, i, s0);
+    y[i] = d.vec[(size_t)sys * n + i];
+    w[i] = d.vec[((size_t)d.maxsys + sys) * n + i];
   }
   __syncthreads();
-  if (wave == 0) (void)wave_normalize(d, t0, y);
-  else if (wave == 1) (void)wave_normalize(d, t0, w);
-  __syncthreads();
-  int solves = 0;
-  cplx dl0 = czero(), dl1 = czero();
-  for (int it = 0; it < max(1, a.maxit); ++it) {
-    const double alpha = s_par[0], Re = s_par[1], nu = 1.0 / Re, q2 = nu * alpha * alpha;
-    const cplx sig = s_sig;
-    // ---- assembly of A = sigma M + L0 + alpha La + nu Ln + nu alpha^2 Lq (fill rows zero)
-    for (size_t e = tid; e < (size_t)n * ldw; e += PT) W[e] = czero();
-    __syncthreads();
-    for (size_t e = tid; e < (size_t)n * bw; e += PT) {
-      const int i = (int)(e / bw), q = (int)(e - (size_t)i * bw), j = i + q - kl;
-      if (j < 0 || j >= n) continue;
-      cplx v = cadd(cmul(sig, d.bM[e]), d.bL0[e]);
-      v = cadd(v, cscale(d.bLa[e], alpha));
-      v = cadd(v, cscale(d.bLn[e], nu));
-      v = cadd(v, cscale(d.bLq[e], q2));
-      W[(size_t)j * ldw + kv + i - j] = v;
+  const double alpha = st.alpha, Re = st.Re, nu = 1.0 / Re;
+  const int solves = st.solves + 1;
+  // ---- sensitivities: <w, M y>, <w, dL/dRe y>, <w, dL/dalpha y>
+  cplx acc[3] = {czero(), czero(), czero()};
+  for (int i = tid; i < n; i += PT) {
+    cplx my = czero(), dr = czero(), da = czero();
+    const int q0 = max(0, kl - i), q1 = min(bw - 1, n - 1 - i + kl);
+    for (int q = q0; q <= q1; ++q) {
+      const size_t e = (size_t)i * bw + q;
+      const cplx yv = y[i + q - kl];
+      my = cadd(my, cmul(d.bM[e], yv));
+      // dL/dRe = -nu^2 (Ln + alpha^2 Lq), dL/dalpha = La + 2 nu alpha Lq
+      dr = cadd(dr, cmul(cadd(d.bLn[e], cscale(d.bLq[e], alpha * alpha)), yv));
+      da = cadd(da, cmul(cadd(d.bLa[e], cscale(d.bLq[e], 2.0 * nu * alpha)), yv));
     }
-    if (tid == 0) s_ju = 0;
-    __syncthreads();
-    // ---- banded LU with partial pivoting (row interchanges applied up to the fill column)
-    for (int j = 0; j < n; ++j) {
-      const int km = min(kl, n - 1 - j);
-      if (wave == 0) {
-        const cplx v = (lane <= km) ? W[(size_t)j * ldw + kv + lane] : czero();
-        double m = (lane <= km) ? cabs1(v) : -1.0;
-        int idx = lane;
-        for (int o = 32; o >= 1; o >>= 1) {
-          const double mo = __shfl_xor(m, o);
-          const int io = __shfl_xor(idx, o);
-          if (mo > m || (mo == m && io < idx)) {
-            m = mo;
-            idx = io;
-          }
-        }
-        if (lane == 0) {
-          s_p = idx;
-          s_ju = max(s_ju, min(j + ku + idx, n - 1));
-          piv[j] = j + idx;
-          if (!(m > 0.0)) atomicOr(d.err, 1);
-        }
-      }
-      __syncthreads();
-      const int p = s_p, ju = s_ju;
-      if (p != 0)
-        for (int c = j + tid; c <= ju; c += PT) {
-          cplx* r0 = W + (size_t)c * ldw + kv + j - c;
-          cplx* r1 = r0 + p;
-          const cplx t = *r0;
-          *r0 = *r1;
-          *r1 = t;
-        }
-      __syncthreads();
-      const cplx pv = W[(size_t)j * ldw + kv];
-      const cplx pinv = (pv.x != 0.0 || pv.y != 0.0) ? crecip(pv) : czero();
-      if (tid == 0) dinv[j] = pinv;
-      if (tid >= 1 && tid <= km) {
-        const cplx l = cmul(W[(size_t)j * ldw + kv + tid], pinv);
-        W[(size_t)j * ldw + kv + tid] = l;
-        lm[tid] = l;
-      }
-      __syncthreads();
-      const int nc = ju - j;
-      for (int e = tid; e < km * nc; e += PT) {
-        const int r = 1 + e / nc, c = j + 1 + e % nc;
-        cplx* t = W + (size_t)c * ldw + kv + j + r - c;
-        *t = csub(*t, cmul(lm[r], W[(size_t)c * ldw + kv + j - c]));
-      }
-      __syncthreads();
-    }
-    // ---- right (wave 0) and left (wave 1) inverse iterations through the factors
-    if (wave == 0) {
-      cplx mu = czero();
-      for (int k = 0; k < a.iters; ++k) {
-        wave_band_mv(d, d.bM, y, t0);
-        wave_lu_solve(d, W, dinv, piv, t0);
-        mu = wave_normalize(d, y, t0);
-        for (int i = lane; i < n; i += 64) vst(y, i, vld(t0, i));
-      }
-      if (lane == 0) {
-        const double m2 = mu.x * mu.x + mu.y * mu.y;
-        s_lam = cmk(sig.x - mu.x / m2, sig.y + mu.y / m2);   // sigma - 1/mu
-      }
-    } else if (wave == 1) {
-      for (int k = 0; k < a.iters; ++k) {
-        wave_band_mvh(d, d.bM, w, t1);
-        wave_lu_solve_h(d, W, dinv, piv, t1);
-        (void)wave_normalize(d, w, t1);
-        for (int i = lane; i < n; i += 64) vst(w, i, vld(t1, i));
-      }
-    }
-    __syncthreads();
-    ++solves;
-    // ---- sensitivities: <w, M y>, <w, dL/dRe y>, <w, dL/dalpha y>
-    cplx acc[3] = {czero(), czero(), czero()};
-    for (int i = tid; i < n; i += PT) {
-      cplx my = czero(), dr = czero(), da = czero();
-      const int q0 = max(0, kl - i), q1 = min(bw - 1, n - 1 - i + kl);
-      for (int q = q0; q <= q1; ++q) {
-        const size_t e = (size_t)i * bw + q;
-        const cplx yv = vld(y, i + q - kl);
-        my = cadd(my, cmul(d.bM[e], yv));
-        // dL/dRe = -nu^2 (Ln + alpha^2 Lq), dL/dalpha = La + 2 nu alpha Lq
-        dr = cadd(dr, cmul(cadd(d.bLn[e], cscale(d.bLq[e], alpha * alpha)), yv));
-        da = cadd(da, cmul(cadd(d.bLa[e], cscale(d.bLq[e], 2.0 * nu * alpha)), yv));
-      }
-      const cplx wv = vld(w, i);
-      acc[0] = cadd(acc[0], cmulc(wv, my));
-      acc[1] = cadd(acc[1], cmulc(wv, dr));
-      acc[2] = cadd(acc[2], cmulc(wv, da));
-    }
-    block_csums<3>(acc, red);
-    {
-      const cplx den = acc[0];
-      const double dd = den.x * den.x + den.y * den.y;
-      auto qdiv = [&](cplx num) { return cscale(cmulc(den, num), -1.0 / dd); };   // -num / den
-      dl0 = cscale(qdiv(acc[1]), -nu * nu);
-      dl1 = qdiv(acc[2]);
-    }
-    if (tid == 0) {
-      const cplx lam = s_lam;
-      const double g = lam.x;
-      // gradient of the growth rate in (alpha, ln Re)
-      const double ga = dl1.x, gr = Re * dl0.x, g2 = ga * ga + gr * gr;
-      if (a.mode == 3 && it == 0) {
-        // predictor: a step ds along the tangent of the level curve, the gradient turned by a
-        // right angle (the unstable side stays on the same hand)
-        const double gn = sqrt(g2), ds = a.params[5 * sys + 4];
-        s_par[0] = alpha - ds * gr / gn;
-        s_par[1] = Re * exp(ds * ga / gn);
-        s_sig = lam;
-      } else if (a.mode == 0 || fabs(g) <= a.tol || it + 1 >= max(1, a.maxit)) {
-        s_stop = 1;
-        if (a.mode != 0 && fabs(g) > a.tol) atomicOr(d.err, 4);
-      } else if (a.mode == 3) {
-        // corrector: the minimum-norm Newton step in (alpha, ln Re)
-        s_par[0] = alpha - g * ga / g2;
-        s_par[1] = Re * exp(-g * gr / g2);
-        s_sig = lam;
-      } else if (a.mode == 1) {
-        s_par[1] = Re - g / dl0.x;
-        s_sig = lam;
-      } else {
-        s_par[0] = alpha - g / dl1.x;
-        s_sig = lam;
-      }
-    }
-    __syncthreads();
-    if (s_stop) break;
+    acc[0] = cadd(acc[0], cmulc(w[i], my));
+    acc[1] = cadd(acc[1], cmulc(w[i], dr));
+    acc[2] = cadd(acc[2], cmulc(w[i], da));
   }
-  // ---- outputs
+  block_csums<3>(acc, red);
+  const cplx den = acc[0];
+  const double dd = den.x * den.x + den.y * den.y;
+  auto qdiv = [&](cplx num) { return cscale(cmulc(den, num), -1.0 / dd); };   // -num / den
+  const cplx dl0 = cscale(qdiv(acc[1]), -nu * nu), dl1 = qdiv(acc[2]);
   if (tid == 0) {
-    a.lam[sys] = s_lam;
-    a.dlam[2 * sys] = dl0;
-    a.dlam[2 * sys + 1] = dl1;
-    a.info[3 * sys] = s_par[0];
-    a.info[3 * sys + 1] = s_par[1];
-    a.info[3 * sys + 2] = solves;
+    const cplx lam = st.lam;
+    const double g = lam.x;
+    // gradient of the growth rate in (alpha, ln Re)
+    const double ga = dl1.x, gr = Re * dl0.x, g2 = ga * ga + gr * gr;
+    PoisState ns = st;
+    ns.solves = solves;
+    int stop = 0;
+    if (a.mode == 3 && it == 0) {
+      // predictor: a step ds along the tangent of the level curve, the gradient turned by a
+      // right angle (the unstable side stays on the same hand)
+      const double gn = sqrt(g2), ds = a.params[5 * sys + 4];
+      ns.alpha = alpha - ds * gr / gn;
+      ns.Re = Re * exp(ds * ga / gn);
+      ns.sig = lam;
+      if (it + 1 >= max(1, a.maxit)) stop = 1;   // no solve left to correct it
+    } else if (a.mode == 0 || fabs(g) <= a.tol || it + 1 >= max(1, a.maxit)) {
+      stop = 1;
+      if (a.mode != 0 && fabs(g) > a.tol) atomicOr(d.err, 4);
+    } else if (a.mode == 3) {
+      // corrector: the minimum-norm Newton step in (alpha, ln Re)
+      ns.alpha = alpha - g * ga / g2;
+      ns.Re = Re * exp(-g * gr / g2);
+      ns.sig = lam;
+    } else if (a.mode == 1) {
+      ns.Re = Re - g / dl0.x;
+      ns.sig = lam;
+    } else {
+      ns.alpha = alpha - g / dl1.x;
+      ns.sig = lam;
+    }
+    ns.stop = stop;
+    d.st[sys] = ns;
+    if (!stop) atomicAdd(d.active + it, 1);
+    s_stop = stop;
+    if (stop) {
+      a.lam[sys] = lam;
+      a.dlam[2 * sys] = dl0;
+      a.dlam[2 * sys + 1] = dl1;
+      a.info[3 * sys] = ns.alpha;
+      a.info[3 * sys + 1] = ns.Re;
+      a.info[3 * sys + 2] = solves;
+    }
   }
+  __syncthreads();
+  if (!s_stop) return;
   if (a.X) {
     // X = R P_c y in the state layout, then unit norm
     cplx* X = a.X + (size_t)sys * n;
     double nn = 0.0;
     for (int c = tid; c < n; c += PT) {
-      cplx v = vld(y, d.colinv[c]);
-      if (d.rho[c] != 0.0) v = cadd(v, cscale(vld(y, d.colinv[c + 2]), d.rho[c]));
-      vst(t0, c, v);
+      cplx v = y[d.colinv[c]];
+      if (d.rho[c] != 0.0) v = cadd(v, cscale(y[d.colinv[c + 2]], d.rho[c]));
+      t0[c] = v;
       nn += v.x * v.x + v.y * v.y;
     }
     cplx s[1] = {cmk(nn, 0.0)};
     block_csums<1>(s, red);
     const double inv = 1.0 / sqrt(s[0].x);
-    for (int c = tid; c < n; c += PT) X[c] = cscale(vld(t0, c), inv);
+    for (int c = tid; c < n; c += PT) X[c] = cscale(t0[c], inv);
   }
   if (a.Y) {
     cplx* Y = a.Y + (size_t)sys * n;
     double nn = 0.0;
-    for (int i = tid; i < n; i += PT) {
-      const cplx v = vld(w, i);
-      nn += v.x * v.x + v.y * v.y;
-    }
+    for (int i = tid; i < n; i += PT) nn += w[i].x * w[i].x + w[i].y * w[i].y;
     cplx s[1] = {cmk(nn, 0.0)};
     block_csums<1>(s, red);
     const double inv = 1.0 / sqrt(s[0].x);
-    for (int i = tid; i < n; i += PT) Y[d.rowmap[i]] = cscale(vld(w, i), inv);
+    for (int i = tid; i < n; i += PT) Y[d.rowmap[i]] = cscale(w[i], inv);
   }
 }
 
@@ -687,19 +807,67 @@ class PoisProblem : public ProblemImpl {
     dv_.rowmap = arena_.upload(hb.rowmap, stream);
     dv_.colinv = arena_.upload(colinv, stream);
     dv_.rho = arena_.upload(hb.rho, stream);
-    dv_.W = arena_.alloc<cplx>((size_t)maxsys_ * hb.S * dv_.ldw);
-    dv_.dinv = arena_.alloc<cplx>((size_t)maxsys_ * hb.S);
-    dv_.piv = arena_.alloc<int>((size_t)maxsys_ * hb.S);
+    dv_.nb = (hb.S + PB - 1) / PB;
+    SPS_REQUIRE(hb.kl + PB <= PTW && PB + hb.kl + hb.ku <= PGW && hb.kl < PWIN - 1 && dv_.bw < 32,
+                "band too wide for the block operators");
+    upload_m(hb);
+    const size_t sn = (size_t)maxsys_ * hb.S, sb = (size_t)maxsys_ * dv_.nb;
+    dv_.W = arena_.alloc<cplx>(sn * dv_.ldw);
+    dv_.dinv = arena_.alloc<cplx>(sn);
+    dv_.piv = arena_.alloc<int>(sn);
+    dv_.Tr = arena_.alloc<cplx>(sb * PTR);
+    dv_.Tl = arena_.alloc<cplx>(sb * PTL);
+    dv_.Gr = arena_.alloc<cplx>(sb * PGR);
+    dv_.Gl = arena_.alloc<cplx>(sb * PGL);
+    dv_.perm = arena_.alloc<unsigned char>(sb * PTW);
+    dv_.vec = arena_.alloc<cplx>(2 * sn);
+    dv_.st = arena_.alloc<PoisState>(maxsys_);
+    dv_.active = arena_.alloc<int>(kMaxSolves);
+    dv_.maxsys = maxsys_;
     dv_.err = arena_.alloc<int>(1);
     params_ = arena_.alloc<double>((size_t)5 * maxsys_);
     SPS_HIP(hipMemsetAsync(dv_.err, 0, sizeof(int), stream));
-    const size_t lds = lds_bytes();
-    SPS_REQUIRE(lds <= 160 * 1024, "problem too large for LDS");
-    SPS_HIP(hipFuncSetAttribute((const void*)pois_evp, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    SPS_REQUIRE(std::max(iterate_lds(), finish_lds()) <= 160 * 1024, "problem too large for LDS");
+    SPS_HIP(hipFuncSetAttribute((const void*)pois_iterate, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)iterate_lds()));
+    SPS_HIP(hipFuncSetAttribute((const void*)pois_finish, hipFuncAttributeMaxDynamicSharedMemorySize, (int)finish_lds()));
     SPS_HIP(hipStreamSynchronize(stream));
   }
-  size_t lds_bytes() const {
-    return sizeof(double) * 8 * (size_t)dv_.S + sizeof(cplx) * 32 + sizeof(double) * 2 * 3 * (PT / 64);
+  static constexpr int kMaxSolves = 1000;   // largest maxit
+  size_t iterate_lds() const {
+    return sizeof(cplx) * (2 * (size_t)dv_.S + PGW) + (sizeof(double) + sizeof(int)) * (size_t)dv_.mw * dv_.S +
+           (size_t)dv_.nb * PTW;
+  }
+  size_t finish_lds() const { return sizeof(cplx) * 3 * (size_t)dv_.S; }
+  // M (real) and its transpose by rows, padded to the longest row
+  void upload_m(const PoisBands& hb) {
+    const int S = hb.S, bw = hb.kl + hb.ku + 1;
+    std::vector<std::vector<std::pair<int, double>>> row[2];
+    for (auto& r : row) r.resize(S);
+    for (int i = 0; i < S; ++i)
+      for (int q = 0; q < bw; ++q) {
+        const double2 v = hb.parts[0][(size_t)i * bw + q];
+        const int c = i + q - hb.kl;
+        if (c < 0 || c >= S || (v.x == 0.0 && v.y == 0.0)) continue;
+        SPS_REQUIRE(v.y == 0.0, "the mass matrix is not real");
+        row[0][i].push_back({c, v.x});
+        row[1][c].push_back({i, v.x});
+      }
+    int mw = 1;
+    for (const auto& r : row)
+      for (const auto& e : r) mw = std::max(mw, (int)e.size());
+    dv_.mw = mw;
+    for (int side = 0; side < 2; ++side) {
+      std::vector<int> col((size_t)mw * S, 0);
+      std::vector<double> val((size_t)mw * S, 0.0);
+      for (int i = 0; i < S; ++i)
+        for (size_t e = 0; e < row[side][i].size(); ++e) {
+          col[e * S + i] = row[side][i][e].first;
+          val[e * S + i] = row[side][i][e].second;
+        }
+      dv_.mcol[side] = arena_.upload(col, stream);
+      dv_.mval[side] = arena_.upload(val, stream);
+    }
   }
 
   void run(int nsys, const double* params, int iters, int mode, double tol, int maxit, double* lam, double* dlam,
@@ -708,7 +876,7 @@ class PoisProblem : public ProblemImpl {
     SPS_REQUIRE(params && lam && dlam && info, "null argument");
     SPS_REQUIRE(iters >= 1 && iters <= 10000, "iters must be in [1, 10000]");
     SPS_REQUIRE(mode >= 0 && mode <= 3, "mode must be 0, 1, 2 or 3");
-    SPS_REQUIRE(maxit >= 1 && maxit <= 1000, "maxit must be in [1, 1000]");
+    SPS_REQUIRE(maxit >= 1 && maxit <= kMaxSolves, "maxit must be in [1, 1000]");
     SPS_REQUIRE(std::isfinite(tol) && tol >= 0.0, "tol must be finite and >= 0");
     for (int s = 0; s < nsys; ++s) {
       const double* p = params + 5 * s;
@@ -718,10 +886,27 @@ class PoisProblem : public ProblemImpl {
       SPS_REQUIRE(std::isfinite(p[4]), "the continuation step must be finite");
     }
     SPS_HIP(hipMemcpyAsync(params_, params, sizeof(double) * 5 * nsys, hipMemcpyHostToDevice, stream));
+    SPS_HIP(hipMemsetAsync(dv_.active, 0, sizeof(int) * maxit, stream));
     PoisArgs a{params_, iters, mode, maxit, tol, reinterpret_cast<cplx*>(lam), reinterpret_cast<cplx*>(dlam), info,
                reinterpret_cast<cplx*>(X), reinterpret_cast<cplx*>(Y)};
-    hipLaunchKernelGGL(pois_evp, dim3(nsys), dim3(PT), lds_bytes(), stream, dv_, a);
+    hipLaunchKernelGGL(pois_start, dim3(nsys), dim3(64), 0, stream, dv_, a);
     SPS_CHECK_LAUNCH();
+    // one eigenvalue solve per pass; systems that are done skip the later ones, and the passes end when
+    // every system is
+    for (int it = 0; it < (mode == 0 ? 1 : maxit); ++it) {
+      hipLaunchKernelGGL(pois_factor, dim3(nsys), dim3(PTF), 0, stream, dv_);
+      SPS_CHECK_LAUNCH();
+      hipLaunchKernelGGL(pois_iterate, dim3(nsys, 2), dim3(64), iterate_lds(), stream, dv_, iters);
+      SPS_CHECK_LAUNCH();
+      hipLaunchKernelGGL(pois_finish, dim3(nsys), dim3(PT), finish_lds(), stream, dv_, a, it);
+      SPS_CHECK_LAUNCH();
+      if (mode != 0 && it + 1 < maxit) {
+        int go = 0;
+        SPS_HIP(hipMemcpyAsync(&go, dv_.active + it, sizeof(int), hipMemcpyDeviceToHost, stream));
+        SPS_HIP(hipStreamSynchronize(stream));
+        if (go == 0) break;
+      }
+    }
     // the host parameters are copied before the call returns
     SPS_HIP(hipStreamSynchronize(stream));
   }
