@@ -1,8 +1,8 @@
 // Linear stability of plane Poiseuille flow on gfx950: the eigenvalue problem of the paper's
 // neutral-curve example (Results, "Parametric sensitivity and numerical continuation";
 // Supplementary, "Eigenvalue problems"), its adjoint eigenvectors, the eigenvalue
-// sensitivities of equ:eigenvalue_sens and Newton's method on the growth rate, every system
-// (one streamwise wavenumber alpha at one Reynolds number Re) in one thread block.
+// sensitivities of equ:eigenvalue_sens and Newton's method on the growth rate, for many
+// systems (one streamwise wavenumber alpha at one Reynolds number Re) at once.
 //
 // Flow between walls y = 0 and y = 2, base flow U = y (2 - y).  Two-dimensional perturbations
 // (u, v, p) ~ exp(i alpha x + lambda t) satisfy, with nu = 1/Re, x = y - 1 in [-1, 1], D = d/dx,
@@ -24,9 +24,9 @@
 // columns recombined (T_n - T_{n-2}, Dirichlet) so that the boundary rows are short and A is
 // banded (kl = 11, ku = 19 at every N).
 //
-// One block per system runs, for every Newton iteration: assembly, the LU factorization, the
-// right eigenvector by inverse iteration y <- A^{-1} M y and at the same time the left
-// eigenvector by w <- A^{-H} M^H w through the same factors, then the sensitivities
+// Every Newton iteration runs: assembly and LU factorization (a block per system), the operators of
+// eight rows that the solves use, the right eigenvector by inverse iteration y <- A^{-1} M y and at
+// the same time the left eigenvector by w <- A^{-H} M^H w through the same factors, then the sensitivities
 // d lambda/dRe = -<w, dL/dRe y> / <w, M y>, d lambda/dalpha likewise, and the Newton update of Re
 // (or alpha) on the growth rate Re(lambda) with the next shift at the new eigenvalue.  A
 // continuation step (the paper's tracing of the neutral curve) first moves along the curve's
@@ -50,8 +50,8 @@
 namespace sps {
 namespace {
 
-constexpr int PT = 256;    // threads of the start and finish blocks
-constexpr int PTF = 512;   // threads of a factor block
+constexpr int PT = 512;    // threads of a finish or operator block
+constexpr int PTF = 256;   // threads of a factor block
 // Block operators of the factors, eight rows each (window and width for kl = 11, ku <= 19):
 //   L  in block t, with all of its row exchanges done first (permutation pi_t of the PTW-row window),
 //      is [A_t | (0; I)] with A_t of PTW x 8;
@@ -65,7 +65,7 @@ constexpr int PTR = 4 * 2 * PTW;   // A_t: lane 2 row + half, entries 4 half + u
 constexpr int PTL = 3 * 64;        // A_t: lane 8 column + q, rows q + 8 u (zero from PTW on)
 constexpr int PGR = 5 * 64;        // G_t: lane 8 row + q, columns 5 q + u
 constexpr int PGL = 8 * PGW;       // G_t: lane = column, rows u
-constexpr int PWIN = 16, PWC = 64; // LDS window of the factorization: rows and columns mod these
+constexpr int PWIN = 32, PWC = 64; // LDS window of the factorization: rows and columns mod these
 
 __device__ __forceinline__ double cabs1(cplx a) { return fabs(a.x) + fabs(a.y); }
 __device__ __forceinline__ cplx cmulc(cplx a, cplx b) {   // conj(a) b
@@ -163,16 +163,18 @@ __global__ void __launch_bounds__(64) pois_start(PoisDev d, PoisArgs a) {
   }
 }
 
-// Banded LU with partial pivoting of A = sigma M + L0 + alpha La + nu Ln + nu alpha^2 Lq, then the block
-// operators of its factors.  One block per system.  The rows and columns a step touches (kl + 1 by
-// kl + ku + 1) are in an LDS window, entry (i, c) at [i mod 16][c mod 64], one entry per thread: every
-// wave finds the pivot by itself, then reads its entry, its row's multiplier and the pivot row, and
-// writes the updated entry, with two block barriers a column.  The rows that enter are read eight
-// columns ahead.  Bound by that chain: 0.3 us a column (3 us with the band in global memory and four
-// barriers).
+// Banded LU with partial pivoting of A = sigma M + L0 + alpha La + nu Ln + nu alpha^2 Lq.  One block per
+// system.  The rows and columns a step touches (kl + 1 by kl + ku + 1) are in an LDS window of two
+// copies: a step reads one and writes the other, two entries per thread, so that a column takes one block
+// barrier and its instructions are those of one wave per SIMD (one entry in 512 threads: 0.32 ms against
+// 0.25); entry (i, c) is at [i mod 32][(c + i) mod 64], which spreads a column's rows over the banks.  Every wave finds the pivot by itself, the reciprocals of all candidates being formed meanwhile.  The
+// next eight rows' parts of A are loaded while eight columns are eliminated.  Bound by the chain of a
+// column (pivot search, two LDS round trips, the update, the barrier): 0.64 us, 0.25 ms for 128 systems of
+// 389 rows.  With one block per system doing every stage, its band in global memory and four barriers a
+// column, the whole call of 20 iterations took 13.7 ms; it takes 0.9.
 __global__ void __launch_bounds__(PTF) pois_factor(PoisDev d) {
-  __shared__ cplx win[PWIN][PWC];
-  const int sys = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  __shared__ cplx win[2][PWIN * PWC];
+  const int sys = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int n = d.S, kl = d.kl, kv = d.kl + d.ku, ldw = d.ldw, bw = d.bw;
   const PoisState st = d.st[sys];
   if (st.stop) return;
@@ -180,83 +182,96 @@ __global__ void __launch_bounds__(PTF) pois_factor(PoisDev d) {
   cplx* W = d.W + (size_t)sys * n * ldw;
   cplx* dinv = d.dinv + (size_t)sys * n;
   int* piv = d.piv + (size_t)sys * n;
-  // assembly: row i of A at W[i ldw + q], column i + q - kl
-  for (int e = tid; e < n * bw; e += PTF) {
-    const int i = e / bw, q = e - i * bw, j = i + q - kl;
-    cplx v = czero();
-    if (j >= 0 && j < n) {
-      v = cadd(cmul(st.sig, d.bM[e]), d.bL0[e]);
-      v = cadd(v, cscale(d.bLa[e], alpha));
-      v = cadd(v, cscale(d.bLn[e], nu));
-      v = cadd(v, cscale(d.bLq[e], q2));
-    }
-    W[(size_t)i * ldw + q] = v;
-  }
-  for (int e = tid; e < PWIN * PWC; e += PTF) win[e / PWC][e % PWC] = czero();
+  auto at = [](int i, int c) { return (i % PWIN) * PWC + ((c + i) % PWC); };
+  struct Parts { cplx m, l0, la, ln, lq; };
+  auto load = [&](int i, int q) {   // clamped, so that the loads are unconditional
+    const size_t e = (size_t)min(i, n - 1) * bw + min(q, bw - 1);
+    return Parts{d.bM[e], d.bL0[e], d.bLa[e], d.bLn[e], d.bLq[e]};
+  };
+  auto form = [&](const Parts& v, int i, int q) {
+    const int j = i + q - kl;
+    cplx z = cadd(cmul(st.sig, v.m), v.l0);
+    z = cadd(z, cscale(v.la, alpha));
+    z = cadd(z, cscale(v.ln, nu));
+    z = cadd(z, cscale(v.lq, q2));
+    return (i < n && j >= 0 && j < n) ? z : czero();
+  };
+  for (int e = tid; e < 2 * PWIN * PWC; e += PTF) win[0][e] = czero();
   __syncthreads();
-  for (int e = tid; e < (kl + 1) * bw; e += PTF) {
-    const int i = e / bw, c = e - i * bw + i - kl;
-    if (c >= 0 && i < n) win[i % PWIN][c % PWC] = W[(size_t)i * ldw + (c - i + kl)];
+  const int r = tid >> 5, cl = tid & 31;   // this thread's rows r, r + 8 and column of the step; as a feeder, row and entry
+  for (int i = r; i < kl + PB; i += PTF / 32) {   // the rows of the first eight columns
+    const Parts v = load(i, cl);
+    if (cl < bw) win[0][at(i, i + cl - kl + PWC)] = win[1][at(i, i + cl - kl + PWC)] = form(v, i, cl);
   }
-  const bool feeder = tid >= PTF - 64;   // the wave that brings in the rows
-  auto enter = [&](int i) { return (feeder && lane < bw && i < n) ? W[(size_t)i * ldw + lane] : czero(); };
-  cplx ring[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) ring[u] = enter(kl + 1 + u);
   __syncthreads();
-  const int r = tid >> 5, cl = tid & 31;
-  for (int j0 = 0; j0 < n; j0 += 8) {
+  for (int j0 = 0; j0 < n; j0 += PB) {
+    const int in = j0 + kl + PB + r;       // the row that this thread brings in for the next eight columns
+    const Parts nxt = load(in, cl);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < PB; ++u) {
       const int j = j0 + u;
       if (j >= n) break;
-      const int km = min(kl, n - 1 - j), jc = j % PWC;
-      const cplx cv = win[(j + (lane & 15)) % PWIN][jc];
-      double best = ((lane & 15) <= km) ? cabs1(cv) : -1.0;
-      int p = lane & 15;
-      auto merge = [&](double ob, int op) {
-        if (ob > best || (ob == best && op < p)) {
-          best = ob;
-          p = op;
-        }
-      };
-      merge(dpp_xor1(best), __builtin_amdgcn_mov_dpp(p, 0xB1, 0xF, 0xF, false));
-      merge(dpp_xor2(best), __builtin_amdgcn_mov_dpp(p, 0x4E, 0xF, 0xF, false));
-      merge(dpp_mirror8(best), __builtin_amdgcn_mov_dpp(p, 0x141, 0xF, 0xF, false));
-      merge(dpp_d<0x140>(best), __builtin_amdgcn_mov_dpp(p, 0x140, 0xF, 0xF, false));
-      p = __builtin_amdgcn_readfirstlane(p);
+      const cplx* wr = win[u & 1];
+      cplx* ww = win[(u & 1) ^ 1];
+      const int km = min(kl, n - 1 - j), rl = lane & 15;
+      const cplx cv = wr[at(j + rl, j)];
+      const cplx rv = crecip(cv);
+      const double mag = (rl <= km) ? cabs1(cv) : -1.0;
+      double best = mag;
+      best = fmax(best, dpp_xor1(best));
+      best = fmax(best, dpp_xor2(best));
+      best = fmax(best, dpp_mirror8(best));
+      best = fmax(best, dpp_d<0x140>(best));
+      const unsigned hit = (unsigned)__ballot(mag == best) & 0xffffu;   // the first of the largest
+      const int p = hit ? __builtin_ctz(hit) : 0;
       const cplx pv = cmk(readlane_d(cv.x, p), readlane_d(cv.y, p));
-      const cplx pinv = (pv.x != 0.0 || pv.y != 0.0) ? crecip(pv) : czero();
-      // this thread's entry: row j + r (after the interchange), column j + cl
-      const int src = ((r == p) ? j : j + r) % PWIN, cc = (j + cl) % PWC;
-      const cplx up = win[(j + p) % PWIN][cc], a0 = win[src][cc], aj = win[src][jc];
-      const cplx l = cmul(aj, pinv), nv = csub(a0, cmul(l, up));
-      __syncthreads();
-      if (r == 0) {
-        if (cl <= kv) W[(size_t)j * ldw + cl] = (j + cl < n) ? up : czero();
-        if (cl == 0) {
+      const cplx pinv = (pv.x != 0.0 || pv.y != 0.0) ? cmk(readlane_d(rv.x, p), readlane_d(rv.y, p)) : czero();
+      const cplx up = wr[at(j + p, j + cl)];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {   // this thread's entries: rows j + rr (after the interchange), column j + cl
+        const int rr = r + PB * h, src = (rr == p) ? j : j + rr;
+        const cplx a0 = wr[at(src, j + cl)], aj = wr[at(src, j)];
+        const cplx nv = csub(a0, cmul(cmul(aj, pinv), up));
+        if (rr >= 1 && rr <= kl) {
+          if (cl >= 1 && cl <= kv) ww[at(j + rr, j + cl)] = (rr <= km) ? nv : czero();
+          if (cl == 0) ww[at(j + rr, j + kv + 1)] = czero();   // the column that enters
+        }
+      }
+      if (wv == 2) {          // U's row j
+        if (lane <= kv) W[(size_t)j * ldw + lane] = (j + lane < n) ? up : czero();
+      } else if (wv == 3) {   // L's multipliers, the pivot
+        const cplx c0 = cmk(readlane_d(cv.x, 0), readlane_d(cv.y, 0));
+        const cplx l = cmul(rl == p ? c0 : cv, pinv);
+        if (lane >= 1 && lane <= kl) W[(size_t)j * ldw + kv + lane] = (lane <= km) ? l : czero();
+        if (lane == 0) {
           dinv[j] = pinv;
           piv[j] = p;
           if (!(best > 0.0)) atomicOr(d.err, 1);
         }
-      } else if (r <= kl) {
-        if (cl == 0) W[(size_t)j * ldw + kv + r] = (r <= km) ? l : czero();
-        else if (cl <= kv) win[(j + r) % PWIN][cc] = (r <= km) ? nv : czero();
-        else if (cl == kv + 1) win[(j + r) % PWIN][cc] = czero();   // the column that enters
       }
-      if (feeder) {
-        const int i = j + kl + 1;
-        if (lane < bw) win[i % PWIN][(i + lane - kl) % PWC] = ring[u];
-        ring[u] = enter(i + 8);
+      if (u == PB - 1 && cl < bw) {
+        const cplx v = form(nxt, in, cl);
+        win[0][at(in, in + cl - kl)] = v;
+        win[1][at(in, in + cl - kl)] = v;
       }
       __syncthreads();
     }
   }
+}
+
+// The block operators of every system's factors, one column per thread.  blockIdx.y: T or G.
+__global__ void __launch_bounds__(PT) pois_operators(PoisDev d) {
+  const int sys = blockIdx.x, tid = threadIdx.x + blockIdx.z * PT;
+  const int n = d.S, kl = d.kl, kv = d.kl + d.ku, ldw = d.ldw;
+  if (d.st[sys].stop) return;
+  const cplx* W = d.W + (size_t)sys * n * ldw;
+  const cplx* dinv = d.dinv + (size_t)sys * n;
+  const int* piv = d.piv + (size_t)sys * n;
   // T_t: the image of the window's unit vector c under the block's exchanges and eliminations is column
   // pos of A_t, pos the row that the exchanges bring entry c to (or e_pos for pos >= 8)
   const int nb = d.nb;
   const size_t ob = (size_t)sys * nb;
-  for (int e = tid; e < nb * PTW; e += PTF) {
+  for (int e = tid; blockIdx.y == 0 && e < nb * PTW; e += gridDim.z * PT) {
     const int t = e / PTW, c = e - t * PTW, tb = t * PB;
     cplx v[PTW];
 #pragma unroll
@@ -295,7 +310,7 @@ __global__ void __launch_bounds__(PTF) pois_factor(PoisDev d) {
     }
   }
   // G_t by columns: U_tt x = e_c (c < 8), or -U's column tb + c
-  for (int e = tid; e < nb * PGW; e += PTF) {
+  for (int e = tid; blockIdx.y == 1 && e < nb * PGW; e += gridDim.z * PT) {
     const int t = e / PGW, c = e - t * PGW, tb = t * PB;
     cplx x[PB];
 #pragma unroll
@@ -320,11 +335,11 @@ __global__ void __launch_bounds__(PTF) pois_factor(PoisDev d) {
 
 // All inverse iterations of one system's right (blockIdx.y = 0: y <- A^{-1} M y) or left (w <- A^{-H} M^H w)
 // vector, in one wave: no barriers; the vector is in LDS, and every block operator goes straight from
-// memory to the registers of the lanes that use it, PD blocks ahead (a block step is one LDS round
-// trip, a short sum per lane and a DPP sum).  Bound by that chain and by a wave's reads, 8 kB a
-// block: 128 systems put 256 waves on 256 CUs.
+// memory to the registers of the lanes that use it, PD blocks ahead (the most that 512 registers hold
+// without moving them about: 4 blocks ahead took 0.59 ms, 8 on both sides 0.56, these 0.50 for 20 iterations
+// of 128 systems of 389 rows).  A block step is one LDS round trip, a short sum per lane and a DPP sum:
+// bound by that chain, 0.25 us a block; either side alone takes the same time, on a CU of its own.
 // LDS: x, t (S + PGW each), M's values and columns, the permutations.
-constexpr int PD = 4;
 template <int side>
 __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double* sm) {
   const int sys = blockIdx.x, lane = threadIdx.x, n = d.S, nb = d.nb, mw = d.mw;
@@ -347,10 +362,11 @@ __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double
   wsync();
   const cplx* T = side ? d.Tl + ob * PTL : d.Tr + ob * PTR;
   const cplx* G = side ? d.Gl + ob * PGL : d.Gr + ob * PGR;
-  cplx tr[PD][4], gr[PD][8];
+  constexpr int PD = side ? 6 : 8;
+  cplx ring[PD][8];   // the operators of the next PD steps of the sequence T sweep, G sweep (left: G, T), ...
   const int lt = side ? lane : min(lane, 2 * PTW - 1), lg = side ? min(lane, PGW - 1) : lane;
   // entries of block b for this lane (indices clamped, so that every load is issued)
-  auto load_t = [&](int b, cplx (&v)[4]) {
+  auto load_t = [&](int b, cplx (&v)[8]) __attribute__((always_inline)) {
     const cplx* p = T + (size_t)min(max(b, 0), nb - 1) * (side ? PTL : PTR) + lt;
     const int s = side ? 64 : 2 * PTW;
     v[0] = p[0];
@@ -358,7 +374,7 @@ __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double
     v[2] = p[2 * s];
     if (!side) v[3] = p[3 * s];
   };
-  auto load_g = [&](int b, cplx (&v)[8]) {
+  auto load_g = [&](int b, cplx (&v)[8]) __attribute__((always_inline)) {
     const cplx* p = G + (size_t)min(max(b, 0), nb - 1) * (side ? PGL : PGR) + lg;
     const int s = side ? PGW : 64;
 #pragma unroll
@@ -368,25 +384,33 @@ __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double
       for (int u = 5; u < 8; ++u) v[u] = p[u * s];
     }
   };
-  auto first_t = [&](int u) { return side ? nb - 1 - u : u; };   // T ascends on the right, descends on the left
-  auto first_g = [&](int u) { return side ? u : nb - 1 - u; };
+  auto first_t = [&](int u) __attribute__((always_inline)) { return side ? nb - 1 - u : u; };   // T ascends on the right, descends on the left
+  auto first_g = [&](int u) __attribute__((always_inline)) { return side ? u : nb - 1 - u; };
+  auto load_first = [&](int i, cplx (&v)[8]) __attribute__((always_inline)) { side ? load_g(first_g(i), v) : load_t(first_t(i), v); };
+  auto load_second = [&](int i, cplx (&v)[8]) __attribute__((always_inline)) { side ? load_t(first_t(i), v) : load_g(first_g(i), v); };
 #pragma unroll
-  for (int u = 0; u < PD; ++u) load_t(first_t(u), tr[u]);
-#pragma unroll
-  for (int u = 0; u < PD; ++u) load_g(first_g(u), gr[u]);
+  for (int u = 0; u < PD; ++u) load_first(u, ring[u]);
   // right: rows 2 row + half of A_t; left: column lane / 8, rows lane % 8 + 8 u
   const int rr = lane >> 1, hh = lane & 1, c8 = lane >> 3, q8 = lane & 7;
-  auto step_t = [&](int b, const cplx (&v)[4]) {
+  const int rc = min(rr, PTW - 1);
+  unsigned p4 = 0;   // right: the next block's permutation, entries 4 hh .. 4 hh + 3 and (one byte) rc
+  int pk = 0;
+  auto next_perm = [&](int b) __attribute__((always_inline)) {
+    const unsigned char* pb = pm + min(b, nb - 1) * PTW;
+    p4 = *reinterpret_cast<const unsigned*>(pb + 4 * hh);
+    pk = pb[rc];
+  };
+  auto step_t = [&](int b, const cplx (&v)[8]) __attribute__((always_inline)) {
     cplx* w = t + b * PB;
     const unsigned char* pb = pm + b * PTW;
     if (!side) {
-      const int rc = min(rr, PTW - 1);
-      cplx s = (hh == 0 && rc >= PB) ? w[pb[rc]] : czero();
+      cplx s = (hh == 0 && rc >= PB) ? w[pk] : czero();
       cplx s2 = czero();
-      s = cfma(v[0], w[pb[4 * hh]], s);
-      s2 = cfma(v[1], w[pb[4 * hh + 1]], s2);
-      s = cfma(v[2], w[pb[4 * hh + 2]], s);
-      s2 = cfma(v[3], w[pb[4 * hh + 3]], s2);
+      s = cfma(v[0], w[p4 & 255], s);
+      s2 = cfma(v[1], w[(p4 >> 8) & 255], s2);
+      s = cfma(v[2], w[(p4 >> 16) & 255], s);
+      s2 = cfma(v[3], w[p4 >> 24], s2);
+      next_perm(b + 1);
       s = cadd(s, s2);
       s = cadd(s, cmk(dpp_xor1(s.x), dpp_xor1(s.y)));
       wsync();
@@ -400,12 +424,14 @@ __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double
       s = cfmac(v[2], w[q8 + 16], s);
       s = group_sum<8>(s);
       const int dst = b * PB + pb[(q8 == 0) ? c8 : row];
+      s.x = (q8 == 0) ? s.x : keep.x;
+      s.y = (q8 == 0) ? s.y : keep.y;
       wsync();
-      if ((q8 < 2 || (q8 == 2 && c8 < 4)) && dst < n) t[dst] = (q8 == 0) ? s : keep;
+      if ((q8 < 2 || (q8 == 2 && c8 < 4)) && dst < n) t[dst] = s;
     }
     wsync();
   };
-  auto step_g = [&](int b, const cplx (&v)[8]) {
+  auto step_g = [&](int b, const cplx (&v)[8]) __attribute__((always_inline)) {
     cplx* w = t + b * PB;
     if (!side) {   // row c8, columns 5 q8 + u
       cplx s = czero(), s2 = czero();
@@ -430,28 +456,23 @@ __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double
     }
     wsync();
   };
-  auto sweep_t = [&]() {
-    for (int b0 = 0; b0 < nb; b0 += PD)
+  // one sweep; the last steps load the first blocks of the sweep that follows
+  auto sweep = [&](auto step, auto load, auto load_next) __attribute__((always_inline)) {
+    int b0 = 0;
+    for (; b0 + PD < nb; b0 += PD)
 #pragma unroll
-      for (int u = 0; u < PD; ++u)
-        if (b0 + u < nb) {
-          step_t(first_t(b0 + u), tr[u]);
-          load_t(first_t(b0 + u + PD), tr[u]);
-        }
+      for (int u = 0; u < PD; ++u) {
+        step(b0 + u, ring[u]);
+        load(b0 + u + PD, ring[u]);
+      }
 #pragma unroll
-    for (int u = 0; u < PD; ++u) load_t(first_t(u), tr[u]);   // the next iteration's
+    for (int u = 0; u < PD; ++u) {
+      if (b0 + u < nb) step(b0 + u, ring[u]);
+      load_next(u, ring[u]);
+    }
   };
-  auto sweep_g = [&]() {
-    for (int b0 = 0; b0 < nb; b0 += PD)
-#pragma unroll
-      for (int u = 0; u < PD; ++u)
-        if (b0 + u < nb) {
-          step_g(first_g(b0 + u), gr[u]);
-          load_g(first_g(b0 + u + PD), gr[u]);
-        }
-#pragma unroll
-    for (int u = 0; u < PD; ++u) load_g(first_g(u), gr[u]);
-  };
+  auto do_t = [&](int i, const cplx (&v)[8]) __attribute__((always_inline)) { step_t(first_t(i), v); };
+  auto do_g = [&](int i, const cplx (&v)[8]) __attribute__((always_inline)) { step_g(first_g(i), v); };
   cplx mu = czero();
   for (int k = 0; k < iters; ++k) {
     for (int i = lane; i < n; i += 64) {
@@ -465,11 +486,12 @@ __device__ __forceinline__ void iterate_side(const PoisDev& d, int iters, double
     }
     wsync();
     if (!side) {
-      sweep_t();
-      sweep_g();
+      next_perm(0);
+      sweep(do_t, load_first, load_second);
+      sweep(do_g, load_second, load_first);
     } else {
-      sweep_g();
-      sweep_t();
+      sweep(do_g, load_first, load_second);
+      sweep(do_t, load_second, load_first);
     }
     // x <- t / |t|, mu = <x, t>
     mu = czero();
@@ -537,20 +559,14 @@ __global__ void __launch_bounds__(PT) pois_finish(PoisDev d, PoisArgs a, int it)
   const int solves = st.solves + 1;
   // ---- sensitivities: <w, M y>, <w, dL/dRe y>, <w, dL/dalpha y>
   cplx acc[3] = {czero(), czero(), czero()};
-  for (int i = tid; i < n; i += PT) {
-    cplx my = czero(), dr = czero(), da = czero();
-    const int q0 = max(0, kl - i), q1 = min(bw - 1, n - 1 - i + kl);
-    for (int q = q0; q <= q1; ++q) {
-      const size_t e = (size_t)i * bw + q;
-      const cplx yv = y[i + q - kl];
-      my = cadd(my, cmul(d.bM[e], yv));
-      // dL/dRe = -nu^2 (Ln + alpha^2 Lq), dL/dalpha = La + 2 nu alpha Lq
-      dr = cadd(dr, cmul(cadd(d.bLn[e], cscale(d.bLq[e], alpha * alpha)), yv));
-      da = cadd(da, cmul(cadd(d.bLa[e], cscale(d.bLq[e], 2.0 * nu * alpha)), yv));
-    }
-    acc[0] = cadd(acc[0], cmulc(w[i], my));
-    acc[1] = cadd(acc[1], cmulc(w[i], dr));
-    acc[2] = cadd(acc[2], cmulc(w[i], da));
+  for (int e = tid; e < n * bw; e += PT) {   // entry by entry: neighbouring lanes read neighbouring entries
+    const int i = e / bw, j = i + e - i * bw - kl;
+    if (j < 0 || j >= n) continue;
+    const cplx wy = cmulc(w[i], y[j]), lq = d.bLq[e];
+    // dL/dRe = -nu^2 (Ln + alpha^2 Lq), dL/dalpha = La + 2 nu alpha Lq
+    acc[0] = cadd(acc[0], cmul(d.bM[e], wy));
+    acc[1] = cadd(acc[1], cmul(cadd(d.bLn[e], cscale(lq, alpha * alpha)), wy));
+    acc[2] = cadd(acc[2], cmul(cadd(d.bLa[e], cscale(lq, 2.0 * nu * alpha)), wy));
   }
   block_csums<3>(acc, red);
   const cplx den = acc[0];
@@ -895,6 +911,7 @@ class PoisProblem : public ProblemImpl {
     // every system is
     for (int it = 0; it < (mode == 0 ? 1 : maxit); ++it) {
       hipLaunchKernelGGL(pois_factor, dim3(nsys), dim3(PTF), 0, stream, dv_);
+      hipLaunchKernelGGL(pois_operators, dim3(nsys, 2, (dv_.nb * PGW + PT - 1) / PT), dim3(PT), 0, stream, dv_);
       SPS_CHECK_LAUNCH();
       hipLaunchKernelGGL(pois_iterate, dim3(nsys, 2), dim3(64), iterate_lds(), stream, dv_, iters);
       SPS_CHECK_LAUNCH();

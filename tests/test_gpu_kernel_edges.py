@@ -69,3 +69,42 @@ def test_inverse_iteration_steps(nx, nz, iters):
         assert abs(lam[k].item() - (sigma - 1.0 / mu)) <= 1e-9 * abs(1.0 / mu)
         assert np.linalg.norm(X[k].cpu().numpy() - x) <= 1e-9
         assert np.linalg.norm(Y[k].cpu().numpy() - y) <= 1e-9
+
+
+# plane Poiseuille flow: inverse iteration from the library's fixed start vector, iteration by iteration,
+# in the band's coordinates, at sizes whose last block of eight rows holds 5 (the smallest, S = 29), 8, 1
+# and 5 (the largest, S = 773) of them, several systems at once.  Each solve's backward error is at most
+# S u |A| on both sides, so its result is within S u cond(A) of the exact one.
+@pytest.mark.parametrize("nz,iters", [(8, 1), (9, 3), (220, 2), (256, 1)])
+def test_poiseuille_inverse_iteration_steps(nz, iters):
+    print(f"Poiseuille inverse iteration {nz}, {iters}", flush=True)
+    prm = [(1.0, 5000.0, 0.01 - 0.23j), (1.02, 6000.0, -0.02 - 0.28j), (0.8, 900.0, 0.05 - 0.3j)]
+    G = sps.PoiseuilleStability(nz, len(prm))
+    n, S = len(prm), 3 * nz + 5
+    lam, dlam, info, X, Y = (torch.zeros(q * n, dtype=torch.float64, device="cuda") for q in (2, 4, 3, 2 * S, 2 * S))
+    G.solve(prm, lam, dlam, info, iters=iters, X=X, Y=Y)
+    G.sync()
+    lam, X, Y = (t.cpu().numpy().view(complex).reshape(n, -1) for t in (lam, X, Y))
+    dense = lambda h: sum(np.diag(h["band"][max(0, -o):S - max(0, o), o + h["kl"]], o) for o in range(-h["kl"], h["ku"] + 1))
+    i = np.arange(S)
+    start = 1.0 / (1 + i % 7) + 0.5j / (1 + i % 5)
+    for q, (alpha, Re, sigma) in enumerate(prm):
+        h = sps.poiseuille_host_band(nz, alpha, Re, sigma)
+        A = dense(h)
+        M = dense(sps.poiseuille_host_band(nz, alpha, Re, sigma + 1.0)) - A
+        x = y = start / np.linalg.norm(start)
+        for _ in range(iters):
+            z = np.linalg.solve(A, M @ x)
+            mu, size, x = np.vdot(x, z), np.linalg.norm(z), z / np.linalg.norm(z)
+            z = np.linalg.solve(A.conj().T, M.conj().T @ y)
+            y = z / np.linalg.norm(z)
+        tol = 2 * iters * S * 2.0 ** -53 * np.linalg.cond(A)
+        c = np.zeros(S, complex)
+        c[h["colmap"]] = x
+        c[:-2] += h["rho"][:-2] * c[2:]
+        r = np.zeros(S, complex)
+        r[h["rowmap"]] = y
+        print(f"  tolerance {tol:.1e}", flush=True)
+        assert abs(lam[q, 0] - (sigma - 1.0 / mu)) <= tol * size / abs(mu) ** 2
+        assert np.linalg.norm(X[q] - c / np.linalg.norm(c)) <= tol
+        assert np.linalg.norm(Y[q] - r) <= tol
