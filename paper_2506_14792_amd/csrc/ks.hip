@@ -19,7 +19,7 @@
 namespace sps {
 namespace {
 
-constexpr int NTS = 256;  // threads of every KS block
+constexpr int NTS = 256;  // threads of a KS block (direct sums, cost, solve)
 
 struct KsDev {
   int K, Ng;
@@ -186,117 +186,319 @@ struct RkTab {
   double H[5][5];
 };
 
-// LDS of every KS kernel: ex (Ng), c, g, sb, fo (K each), u (Ng doubles)
-struct KsLds {
-  cplx *ex, *c, *g, *sb, *fo;
-  double* u;
+// The sweeps run on one of two evaluators of F and its VJP.  An evaluator gives every thread its share
+// of a state (a value of type V; the recurrences in time are diagonal and real, so they act on shares),
+// loads and stores shares, and maps shares to the shares of F or of the VJP, block-wide; `work` is the
+// caller's arithmetic that needs no result of the evaluation, done while its first loads are under way.
+__device__ __forceinline__ double cadd(double a, double b) { return a + b; }
+__device__ __forceinline__ double csub(double a, double b) { return a - b; }
+__device__ __forceinline__ double cscale(double a, double s) { return a * s; }
+__device__ __forceinline__ bool ks_finite(double a) { return isfinite(a); }
+__device__ __forceinline__ bool ks_finite(cplx a) { return isfinite(a.x) && isfinite(a.y); }
+
+// Direct sums over every mode and grid point, the twiddles in LDS: any size.  A share is one mode.
+struct KsDirect {
+  static constexpr int NT = NTS;
+  using V = cplx;
+  static size_t lds(const KsDev& d) { return sizeof(cplx) * (d.Ng + 4 * d.K) + sizeof(double) * d.Ng; }
+  template <bool ADJ>
+  struct Eval {
+    const KsDev& d;
+    cplx *ex, *c, *g, *sb, *fo;   // LDS: ex (Ng), c, g, sb, fo (K each), u (Ng doubles)
+    double* u;
+    int m;
+    bool own;
+    double lin;
+    __device__ __forceinline__ Eval(const KsDev& dd, double* smem) : d(dd) {
+      ex = reinterpret_cast<cplx*>(smem);
+      c = ex + d.Ng;
+      g = c + d.K;
+      sb = g + d.K;
+      fo = sb + d.K;
+      u = reinterpret_cast<double*>(fo + d.K);
+      for (int t = threadIdx.x; t < d.Ng; t += NT) ex[t] = d.ex[t];
+      m = threadIdx.x;
+      own = m < d.K;
+      lin = own ? d.lin[m] : 0.0;
+    }
+    __device__ __forceinline__ V load(const cplx* p) const { return own ? p[m] : czero(); }
+    __device__ __forceinline__ void store(cplx* p, V v) const {
+      if (own) p[m] = v;
+    }
+    template <class W>
+    __device__ __forceinline__ V F(V x, W work) {
+      if (own) c[m] = x;
+      __syncthreads();
+      work();
+      ks_eval_F(d, ex, c, u, fo);
+      return own ? fo[m] : czero();
+    }
+    template <class W>
+    __device__ __forceinline__ V vjp(V h, V gv, W work) {
+      if (own) {
+        c[m] = h;
+        g[m] = gv;
+      }
+      __syncthreads();
+      work();
+      ks_F_vjp(d, ex, c, g, sb, u, fo);
+      return own ? fo[m] : czero();
+    }
+  };
 };
-__device__ __forceinline__ KsLds ks_lds(const KsDev& d, double* smem) {
-  KsLds L;
-  L.ex = reinterpret_cast<cplx*>(smem);
-  L.c = L.ex + d.Ng;
-  L.g = L.c + d.K;
-  L.sb = L.g + d.K;
-  L.fo = L.sb + d.K;
-  L.u = reinterpret_cast<double*>(L.fo + d.K);
-  for (int t = threadIdx.x; t < d.Ng; t += NTS) L.ex[t] = d.ex[t];
-  return L;
-}
+
+// Sums folded by the symmetries of the grid.  With theta = 2 pi j / Ng, the points theta, -theta,
+// pi + theta and pi - theta need the same four sums, over the even or odd modes of the real parts by
+// cosines or the imaginary parts by sines: a base point's four sums and four grid values are related by
+// a 4 x 4 Hadamard matrix, as are the values' contributions to the sums back.  So a transform has a
+// quarter of the direct products, each a single multiply, and every lane's twiddles (T1 to the grid, T2
+// back) stay in registers for the whole sweep; a share is the real or the imaginary part of one mode,
+// held by every lane of its group.  To the grid: lane ((base point) 4 + sum) LP + part; back: lane (2
+// mode + type) LPM + part.  An odd Ng has no points pi + theta on its grid: they get weight 0 and there
+// are twice as many base points.  Two barriers an evaluation.  Bound by the chain of a step (two LDS
+// round trips and barriers, T1 and T2 products, seven DPP steps): 200 steps at K = 32 and their reverse
+// sweep take 0.12 and 0.14 ms, with the direct sums 0.6 each.
+template <int NT_, int LP, int T1, int T2>
+struct KsFold {
+  static constexpr int NT = NT_, LPM = 4;
+  static constexpr int CS = LP * T1 + 2, VS = LPM * T2 + 2;   // strides in LDS (16 B off the banks' period)
+  using V = double;
+  static int base_points(int Ng) { return (Ng % 2) ? (Ng + 1) / 2 : Ng / 4 + 1; }
+  // every lane's sums fit
+  static bool fits(int K, int Ng) {
+    const int nb = base_points(Ng);
+    return nb * 4 * LP <= NT && 2 * K * LPM <= NT && (K + 1) / 2 <= LP * T1 && nb <= LPM * T2;
+  }
+  static size_t lds(const KsDev&) { return sizeof(double) * 4 * (2 * CS + VS); }
+  template <bool ADJ>
+  struct Eval {
+    double *cs, *ss, *vs;   // LDS: [4][CS] state, [4][CS] cotangent, [4][VS] folded grid values
+    double tw1[T1], tw2[T2];
+    const double *rc, *rs, *rv;   // this lane's terms
+    double *wv, *wc, *wsb;        // where it writes
+    double so, sb_, wt, lin, k2, w, scale;
+    int comp;
+    bool own, put, putv;
+    __device__ __forceinline__ Eval(const KsDev& d, double* smem) {
+      cs = smem;
+      ss = cs + 4 * CS;
+      vs = ss + 4 * CS;
+      for (int t = threadIdx.x; t < 4 * (2 * CS + VS); t += NT) smem[t] = 0.0;
+      const int tid = threadIdx.x, Ng = d.Ng, K = d.K;
+      const int nb = (Ng % 2) ? (Ng + 1) / 2 : Ng / 4 + 1;
+      auto trig = [&](int m, int j, int type) {
+        const cplx e = d.ex[(m * j) % Ng];
+        return type ? -e.y : e.x;
+      };
+      {
+        const int l = tid % LP, s = (tid / LP) & 3, o = s & 1, b = s >> 1, jb = tid / (4 * LP);
+        const bool in = jb < nb;
+#pragma unroll
+        for (int i = 0; i < T1; ++i) {
+          const int m = 2 * (l * T1 + i) + o;
+          tw1[i] = (in && m < K) ? trig(m, jb, b) : 0.0;
+        }
+        rc = cs + s * CS + l * T1;
+        rs = ss + s * CS + l * T1;
+        so = o ? -1.0 : 1.0;
+        sb_ = b ? -1.0 : 1.0;
+        // weight of grid value (p, q) = (o, b): points that coincide in pairs count a half
+        if (Ng % 2) wt = o ? 0.0 : (jb == 0 ? 0.5 : 1.0);
+        else wt = (jb == 0 || 4 * jb == Ng) ? 0.5 : 1.0;
+        putv = in && l == 0;
+        wv = vs + s * VS + min(jb, VS - 1);
+      }
+      {
+        const int h = tid % LPM, cq = tid / LPM, b = cq & 1, m = cq >> 1, o = m & 1;
+        own = m < K;
+        const int mc = min(m, K - 1);
+#pragma unroll
+        for (int i = 0; i < T2; ++i) {
+          const int jb = h * T2 + i;
+          tw2[i] = (own && jb < nb) ? trig(mc, jb, b) : 0.0;
+        }
+        rv = vs + (2 * b + o) * VS + h * T2;
+        put = own && h == 0;
+        // F: the cosine sums give imaginary parts; VJP: real parts
+        comp = 2 * mc + (ADJ ? b : 1 - b);
+        const int im = comp & 1;
+        lin = own ? d.lin[mc] : 0.0;
+        w = (mc == 0) ? 1.0 : 2.0;
+        const double k = d.kx[mc];
+        k2 = 0.5 * k;
+        wc = cs + (2 * im + o) * CS + (mc >> 1);
+        wsb = ss + (2 * (1 - im) + o) * CS + (mc >> 1);   // sqbar = (1/2) i k G
+        if (im) k2 = -k2;
+        scale = ADJ ? w : (im ? -0.5 : 0.5) * k * (1.0 / Ng);
+        if (ADJ) wt *= 2.0 * (1.0 / Ng);
+        // the imaginary part of mode 0 is in no sum
+        if (mc == 0) {
+          if (im) w = 0.0;
+        }
+      }
+      __syncthreads();
+    }
+    __device__ __forceinline__ V load(const cplx* p) const {
+      return own ? reinterpret_cast<const double*>(p)[comp] : 0.0;
+    }
+    __device__ __forceinline__ void store(cplx* p, V v) const {
+      if (put) reinterpret_cast<double*>(p)[comp] = v;
+    }
+    // 4 x 4 Hadamard transform over the lanes of a base point
+    __device__ __forceinline__ double hadamard(double v) const {
+      if (LP == 1) {
+        v = fma(so, v, dpp_xor1(v));
+        return fma(sb_, v, dpp_xor2(v));
+      }
+      v = fma(so, v, dpp_xor2(v));
+      return fma(sb_, v, dpp_d<0x1B>(dpp_mirror8(v)));   // reversed in eight, then in four: lane ^ 4
+    }
+    template <int T>
+    __device__ __forceinline__ static double dot(const double (&t)[T], const double* v) {
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < T; ++i) s[i & 3] = fma(t[i], v[i], s[i & 3]);
+      return (s[0] + s[1]) + (s[2] + s[3]);
+    }
+    __device__ __forceinline__ double grid(const double* v) const { return hadamard(group_sum<LP>(dot(tw1, v))); }
+    __device__ __forceinline__ V back(double v) {
+      v = hadamard(v);
+      if (putv) *wv = v;
+      __syncthreads();
+      return scale * group_sum<LPM>(dot(tw2, rv));
+    }
+    template <class W>
+    __device__ __forceinline__ V F(V x, W work) {
+      if (put) *wc = (w == 0.0) ? 0.0 : w * x;
+      __syncthreads();
+      work();
+      const double u = grid(rc);
+      return back(wt * u * u);
+    }
+    template <class W>
+    __device__ __forceinline__ V vjp(V h, V g, W work) {
+      if (put) {
+        *wc = (w == 0.0) ? 0.0 : w * h;
+        *wsb = k2 * g;
+      }
+      __syncthreads();
+      work();
+      const double u = grid(rc), r = grid(rs);
+      return back(wt * u * r);
+    }
+  };
+};
 
 // Forward sweep: X (in: X_0, out: X_N), history H[n][K] of X_0 .. X_N.  One block.
 // rows[n]: the coefficients of step n (device array, rows beyond the run zero)
-__global__ void __launch_bounds__(NTS) ks_forward(KsDev d, cplx* X, cplx* H, int nsteps, const SbdfCoef* rows,
-                                                 int* err) {
+template <class E>
+__global__ void __launch_bounds__(E::NT) ks_forward(KsDev d, cplx* X, cplx* H, int nsteps, const SbdfCoef* rows,
+                                                    int* err) {
   extern __shared__ double smem_d[];
-  const KsLds L = ks_lds(d, smem_d);
-  const int m = threadIdx.x, K = d.K;
-  const bool own = m < K;
-  const double lin = own ? d.lin[m] : 0.0;
-  // x[i] = X_{n-1-i}, f[i] = F(X_{n-1-i}) of this mode (zero before X_0)
-  cplx x[KS_MAX_ORDER], f[KS_MAX_ORDER];
+  using V = typename E::V;
+  typename E::template Eval<false> ev(d, smem_d);
+  const int K = d.K;
+  // x[i] = X_{n-1-i}, f[i] = F(X_{n-1-i}) of this share (zero before X_0)
+  V x[KS_MAX_ORDER], f[KS_MAX_ORDER];
 #pragma unroll
-  for (int i = 0; i < KS_MAX_ORDER; ++i) x[i] = f[i] = czero();
-  x[0] = own ? X[m] : czero();
-  if (own) {
-    H[m] = x[0];
-    L.c[m] = x[0];
-  }
-  __syncthreads();
-  ks_eval_F(d, L.ex, L.c, L.u, L.fo);
-  if (own) f[0] = L.fo[m];
-  for (int n = 1; n <= nsteps; ++n) {
-    const SbdfCoef q = rows[n];
-    cplx fs = czero(), xs = czero();
+  for (int i = 0; i < KS_MAX_ORDER; ++i) x[i] = f[i] = V{};
+  x[0] = ev.load(X);
+  ev.store(H, x[0]);
+  // the rows are loaded two steps ahead (one ahead is as fast at K = 32; a smaller step is near a load)
+  SbdfCoef q = rows[1], q1 = rows[2];
+  double a0 = q.a[0], inv = 1.0 / (a0 + ev.lin);
+  V rest{};   // the part of a step's right-hand side that its newest F is not in
+  auto rest_of = [&](const SbdfCoef& r) {
+    V fs{}, xs{};
 #pragma unroll
     for (int i = 1; i <= KS_MAX_ORDER; ++i) {
-      fs = cadd(fs, cscale(f[i - 1], q.c[i]));
-      xs = cadd(xs, cscale(x[i - 1], q.a[i]));
+      if (i >= 2) fs = cadd(fs, cscale(f[i - 1], r.c[i]));
+      xs = cadd(xs, cscale(x[i - 1], r.a[i]));
     }
-    const cplx xn = cscale(csub(fs, xs), 1.0 / (q.a[0] + lin));
-    if (own) {
-      H[(size_t)n * K + m] = xn;
-      L.c[m] = xn;
-    }
+    rest = csub(fs, xs);
+  };
+  f[0] = ev.F(x[0], [&] { rest_of(q); });
+  for (int n = 1; n <= nsteps; ++n) {
+    const V xn = cscale(cadd(cscale(f[0], q.c[1]), rest), inv);
+    ev.store(H + (size_t)n * K, xn);
+    q = q1;
+    q1 = rows[n + 2];
 #pragma unroll
     for (int i = KS_MAX_ORDER - 1; i > 0; --i) {
       x[i] = x[i - 1];
       f[i] = f[i - 1];
     }
     x[0] = xn;
-    if (n < nsteps) {
-      __syncthreads();
-      ks_eval_F(d, L.ex, L.c, L.u, L.fo);
-      if (own) f[0] = L.fo[m];
-    }
+    if (n < nsteps)
+      f[0] = ev.F(xn, [&] {
+        if (q.a[0] != a0) {   // the row changes in the first steps, or at every variable step
+          a0 = q.a[0];
+          inv = 1.0 / (a0 + ev.lin);
+        }
+        rest_of(q);
+      });
   }
-  if (own) {
-    const cplx x1 = x[0];
-    X[m] = x1;
-    if (__any(!(isfinite(x1.x) && isfinite(x1.y))) && lane_id() == 0) atomicOr(err, 2);
-  }
+  ev.store(X, x[0]);
+  if (__any(ev.own && !ks_finite(x[0])) && lane_id() == 0) atomicOr(err, 2);
 }
 
 // Reverse sweep: Xbar (in: dJ/dX_N, out: dJ/dX_0) through the history H of the forward run.
 // The cotangent of X_{n-1} collects Y_{n-1+i} from steps n-1+i, i = 1..order (equ:IMEX_adjoint),
 // so it is complete once Y_n is known; F's VJP, linear in its cotangent, is applied once per
 // state.  Y of steps beyond nsteps are zero.
-__global__ void __launch_bounds__(NTS) ks_adjoint(KsDev d, cplx* Xbar, const cplx* H, int nsteps,
-                                                 const SbdfCoef* rows) {
+template <class E>
+__global__ void __launch_bounds__(E::NT) ks_adjoint(KsDev d, cplx* Xbar, const cplx* H, int nsteps,
+                                                    const SbdfCoef* rows) {
   extern __shared__ double smem_d[];
-  const KsLds L = ks_lds(d, smem_d);
-  const int m = threadIdx.x, K = d.K;
-  const bool own = m < K;
-  const double lin = own ? d.lin[m] : 0.0;
-  cplx xb = own ? Xbar[m] : czero();   // cotangent of X_n (complete)
-  cplx ys[KS_MAX_ORDER - 1];           // Y_{n+1}, Y_{n+2}, Y_{n+3}
+  using V = typename E::V;
+  typename E::template Eval<true> ev(d, smem_d);
+  const int K = d.K;
+  V xb = ev.load(Xbar);        // cotangent of X_n (complete)
+  V ys[KS_MAX_ORDER - 1];      // Y_{n+1}, Y_{n+2}, Y_{n+3}
 #pragma unroll
-  for (int i = 0; i < KS_MAX_ORDER - 1; ++i) ys[i] = czero();
-  cplx hnext = (own && nsteps >= 1) ? H[(size_t)(nsteps - 1) * K + m] : czero();
+  for (int i = 0; i < KS_MAX_ORDER - 1; ++i) ys[i] = V{};
+  // term i of step n - 1 + i, i = 1..order, and a_0 of step n
+  struct Row { double a[KS_MAX_ORDER + 1], c[KS_MAX_ORDER + 1]; };
+  auto row = [&](int n) {
+    Row r;
+    r.a[0] = rows[n].a[0];
+#pragma unroll
+    for (int i = 1; i <= KS_MAX_ORDER; ++i) {
+      r.a[i] = rows[n - 1 + i].a[i];
+      r.c[i] = rows[n - 1 + i].c[i];
+    }
+    return r;
+  };
+  Row q = row(nsteps), q1 = row(max(nsteps - 1, 1));   // two steps ahead, as the states
+  double a0 = q.a[0], inv = 1.0 / (a0 + ev.lin);
+  V h0 = ev.load(H + (size_t)(nsteps - 1) * K), h1 = ev.load(H + (size_t)max(nsteps - 2, 0) * K);
+  V rest{};   // the part of the cotangent of F that the newest Y is not in
   for (int n = nsteps; n >= 1; --n) {
-    const SbdfCoef q = rows[n];
-    const cplx y = cscale(xb, 1.0 / (q.a[0] + lin));
-    cplx g = cscale(y, q.c[1]);
-    cplx lin_part = cscale(y, q.a[1]);
+    const V y = cscale(xb, inv);
+    const V g = cadd(cscale(y, q.c[1]), rest);
+    const V hcur = h0;
+    V lin_part = cscale(y, q.a[1]);
+    const V v = ev.vjp(hcur, g, [&] {
 #pragma unroll
-    for (int i = 2; i <= KS_MAX_ORDER; ++i) {
-      const SbdfCoef qi = rows[n - 1 + i];   // step n-1+i, its term i
-      g = cadd(g, cscale(ys[i - 2], qi.c[i]));
-      lin_part = cadd(lin_part, cscale(ys[i - 2], qi.a[i]));
-    }
-    const cplx hcur = hnext;
-    if (own && n >= 2) hnext = H[(size_t)(n - 2) * K + m];   // next iteration's state, early
-    if (own) {
-      L.c[m] = hcur;
-      L.g[m] = g;
-    }
-    __syncthreads();
-    ks_F_vjp(d, L.ex, L.c, L.g, L.sb, L.u, L.fo);
-    xb = own ? csub(L.fo[m], lin_part) : czero();
+      for (int i = 2; i <= KS_MAX_ORDER; ++i) lin_part = cadd(lin_part, cscale(ys[i - 2], q.a[i]));
 #pragma unroll
-    for (int i = KS_MAX_ORDER - 2; i > 0; --i) ys[i] = ys[i - 1];
-    ys[0] = y;
+      for (int i = KS_MAX_ORDER - 2; i > 0; --i) ys[i] = ys[i - 1];
+      ys[0] = y;
+      h0 = h1;
+      h1 = ev.load(H + (size_t)max(n - 3, 0) * K);
+      q = q1;
+      q1 = row(max(n - 2, 1));
+      if (q.a[0] != a0) {
+        a0 = q.a[0];
+        inv = 1.0 / (a0 + ev.lin);
+      }
+      rest = V{};
+#pragma unroll
+      for (int i = 2; i <= KS_MAX_ORDER; ++i) rest = cadd(rest, cscale(ys[i - 2], q.c[i]));
+    });
+    xb = csub(v, lin_part);
   }
-  if (own) Xbar[m] = xb;
+  ev.store(Xbar, xb);
 }
 
 // RK forward sweep, S stages, step dt0 or dts[n] for step n + 1 (dts: device array, nullable):
@@ -305,28 +507,28 @@ __global__ void __launch_bounds__(NTS) ks_adjoint(KsDev d, cplx* Xbar, const cpl
 // (1 + dt H_ii L_m) X_{n,i} = X_{n,0} + dt sum_{j<i} (A_ij F_{n,j} - H_ij L_m X_{n,j}) per mode
 // (M = 1); F of stage S is not needed (column S of A is zero).  One block; the stage values of
 // this thread's mode stay in registers.
-template <int S>
-__global__ void __launch_bounds__(NTS) ks_forward_rk(KsDev d, cplx* X, cplx* H, int nsteps, RkTab tab, double dt0,
-                                                    const double* dts, int* err) {
+template <class E, int S>
+__global__ void __launch_bounds__(E::NT) ks_forward_rk(KsDev d, cplx* X, cplx* H, int nsteps, RkTab tab, double dt0,
+                                                       const double* dts, int* err) {
   extern __shared__ double smem_d[];
-  const KsLds L = ks_lds(d, smem_d);
-  const int m = threadIdx.x, K = d.K;
-  const bool own = m < K;
-  const double lin = own ? d.lin[m] : 0.0;
+  using V = typename E::V;
+  typename E::template Eval<false> ev(d, smem_d);
+  const int K = d.K;
+  const double lin = ev.lin;
   double inv[S + 1];
-  cplx x0 = own ? X[m] : czero();
+  V x0 = ev.load(X);
   for (int n = 0; n < nsteps; ++n) {
     const double dt = dts ? dts[n] : dt0;   // step n + 1 advances by dts[n]
     if (n == 0 || dts) {
 #pragma unroll
       for (int i = 1; i <= S; ++i) inv[i] = 1.0 / (1.0 + dt * tab.H[i][i] * lin);
     }
-    cplx xs[S + 1], fs[S];
+    V xs[S + 1], fs[S];
     xs[0] = x0;
 #pragma unroll
     for (int i = 0; i <= S; ++i) {
       if (i > 0) {
-        cplx r = xs[0];
+        V r = xs[0];
 #pragma unroll
         for (int j = 0; j < i; ++j) {
           r = cadd(r, cscale(fs[j], dt * tab.A[i][j]));
@@ -335,21 +537,14 @@ __global__ void __launch_bounds__(NTS) ks_forward_rk(KsDev d, cplx* X, cplx* H, 
         xs[i] = cscale(r, inv[i]);
       }
       if (i < S) {
-        if (own) {
-          H[((size_t)n * S + i) * K + m] = xs[i];
-          L.c[m] = xs[i];
-        }
-        __syncthreads();
-        ks_eval_F(d, L.ex, L.c, L.u, L.fo);
-        fs[i] = own ? L.fo[m] : czero();
+        ev.store(H + ((size_t)n * S + i) * K, xs[i]);
+        fs[i] = ev.F(xs[i], [] {});
       }
     }
     x0 = xs[S];
   }
-  if (own) {
-    X[m] = x0;
-    if (__any(!(isfinite(x0.x) && isfinite(x0.y))) && lane_id() == 0) atomicOr(err, 2);
-  }
+  ev.store(X, x0);
+  if (__any(ev.own && !ks_finite(x0)) && lane_id() == 0) atomicOr(err, 2);
 }
 
 // RK reverse sweep: Xbar (in: dJ/dX_N, out: dJ/dX_0) through the stage states of the forward
@@ -358,65 +553,62 @@ __global__ void __launch_bounds__(NTS) ks_forward_rk(KsDev d, cplx* X, cplx* H, 
 //   Y_S = Yn / (1 + dt H_SS L),
 //   Y_i = [dF(X_{n,i})^H (dt sum_{j>i} A_ji Y_j) - dt L sum_{j>i} H_ji Y_j] / (1 + dt H_ii L),
 //   cotangent of X_n = sum_{j>=1} Y_j + dF(X_{n,0})^H (dt sum_j A_j0 Y_j) - dt L sum_j H_j0 Y_j.
-template <int S>
-__global__ void __launch_bounds__(NTS) ks_adjoint_rk(KsDev d, cplx* Xbar, const cplx* H, int nsteps, RkTab tab,
-                                                    double dt0, const double* dts) {
+template <class E, int S>
+__global__ void __launch_bounds__(E::NT) ks_adjoint_rk(KsDev d, cplx* Xbar, const cplx* H, int nsteps, RkTab tab,
+                                                       double dt0, const double* dts) {
   extern __shared__ double smem_d[];
-  const KsLds L = ks_lds(d, smem_d);
-  const int m = threadIdx.x, K = d.K;
-  const bool own = m < K;
-  const double lin = own ? d.lin[m] : 0.0;
+  using V = typename E::V;
+  typename E::template Eval<true> ev(d, smem_d);
+  const int K = d.K;
+  const double lin = ev.lin;
   double inv[S + 1];
-  cplx yn = own ? Xbar[m] : czero();
+  V yn = ev.load(Xbar);
+  V h0 = ev.load(H + ((size_t)nsteps * S - 1) * K), h1 = ev.load(H + ((size_t)nsteps * S - 2) * K);
   for (int n = nsteps - 1; n >= 0; --n) {
     const double dt = dts ? dts[n] : dt0;
     if (n == nsteps - 1 || dts) {
 #pragma unroll
       for (int i = 1; i <= S; ++i) inv[i] = 1.0 / (1.0 + dt * tab.H[i][i] * lin);
     }
-    cplx ys[S + 1];
+    V ys[S + 1];
     ys[S] = cscale(yn, inv[S]);
 #pragma unroll
     for (int i = S - 1; i >= 0; --i) {
-      cplx g = czero(), lp = czero();
+      V g{}, lp{};
 #pragma unroll
       for (int j = i + 1; j <= S; ++j) {
         g = cadd(g, cscale(ys[j], dt * tab.A[j][i]));
         lp = cadd(lp, cscale(ys[j], dt * tab.H[j][i] * lin));
       }
-      if (own) {
-        L.c[m] = H[((size_t)n * S + i) * K + m];
-        L.g[m] = g;
-      }
-      __syncthreads();
-      ks_F_vjp(d, L.ex, L.c, L.g, L.sb, L.u, L.fo);
-      const cplx v = own ? L.fo[m] : czero();
+      const V hcur = h0;   // the stage states are loaded two evaluations ahead
+      h0 = h1;
+      h1 = ev.load(H + (size_t)max(n * S + i - 2, 0) * K);
+      const V v = ev.vjp(hcur, g, [] {});
       if (i > 0) {
         ys[i] = cscale(csub(v, lp), inv[i]);
       } else {
-        cplx sum = czero();
+        V sum{};
 #pragma unroll
         for (int j = 1; j <= S; ++j) sum = cadd(sum, ys[j]);
         yn = csub(cadd(sum, v), lp);
       }
     }
   }
-  if (own) Xbar[m] = yn;
+  ev.store(Xbar, yn);
 }
 
 // F or its VJP at one state (one block).
-__global__ void __launch_bounds__(NTS) ks_eval(KsDev d, const cplx* X, const cplx* G, cplx* out) {
+template <class E>
+__global__ void __launch_bounds__(E::NT) ks_eval_f(KsDev d, const cplx* X, cplx* out) {
   extern __shared__ double smem_d[];
-  const KsLds L = ks_lds(d, smem_d);
-  const int m = threadIdx.x;
-  if (m < d.K) {
-    L.c[m] = X[m];
-    if (G) L.g[m] = G[m];
-  }
-  __syncthreads();
-  if (G) ks_F_vjp(d, L.ex, L.c, L.g, L.sb, L.u, L.fo);
-  else ks_eval_F(d, L.ex, L.c, L.u, L.fo);
-  if (m < d.K) out[m] = L.fo[m];
+  typename E::template Eval<false> ev(d, smem_d);
+  ev.store(out, ev.F(ev.load(X), [] {}));
+}
+template <class E>
+__global__ void __launch_bounds__(E::NT) ks_eval_vjp(KsDev d, const cplx* X, const cplx* G, cplx* out) {
+  extern __shared__ double smem_d[];
+  typename E::template Eval<true> ev(d, smem_d);
+  ev.store(out, ev.vjp(ev.load(X), ev.load(G), [] {}));
 }
 
 // J = 1/2 sum_m w_m |c_m|^2 (Parseval of (1/L) int u^2 / 2, c_0 by its real part), dJ/dX = w c.
@@ -578,14 +770,17 @@ class KsProblem : public ProblemImpl {
     SPS_REQUIRE(Xbar != nullptr, "Xbar is null");
     if (tape_steps_ != nsteps) throw Error(SPS_E_STATE, "adjoint_step: nsteps does not match the recorded forward run");
     cplx* xb = reinterpret_cast<cplx*>(Xbar);
-    if (!rk_)
-      hipLaunchKernelGGL(ks_adjoint, dim3(1), dim3(NTS), lds(), stream, dv_, xb, H_, nsteps, rows_);
-    else if (stages_ == 2)
-      hipLaunchKernelGGL(ks_adjoint_rk<2>, dim3(1), dim3(NTS), lds(), stream, dv_, xb, H_, nsteps, tab_, desc_.dt,
-                         rk_dts());
-    else
-      hipLaunchKernelGGL(ks_adjoint_rk<4>, dim3(1), dim3(NTS), lds(), stream, dv_, xb, H_, nsteps, tab_, desc_.dt,
-                         rk_dts());
+    with_evaluator([&](auto e) {
+      using E = decltype(e);
+      const dim3 b(E::NT);
+      const size_t l = E::lds(dv_);
+      if (!rk_)
+        hipLaunchKernelGGL(ks_adjoint<E>, dim3(1), b, l, stream, dv_, xb, H_, nsteps, rows_);
+      else if (stages_ == 2)
+        hipLaunchKernelGGL((ks_adjoint_rk<E, 2>), dim3(1), b, l, stream, dv_, xb, H_, nsteps, tab_, desc_.dt, rk_dts());
+      else
+        hipLaunchKernelGGL((ks_adjoint_rk<E, 4>), dim3(1), b, l, stream, dv_, xb, H_, nsteps, tab_, desc_.dt, rk_dts());
+    });
     SPS_CHECK_LAUNCH();
   }
   void cost(const double* X, double* J, double* dJdX) override {
@@ -617,14 +812,21 @@ class KsProblem : public ProblemImpl {
   }
   void eval_F(const double* X, double* F) override {
     SPS_REQUIRE(X && F, "null argument");
-    hipLaunchKernelGGL(ks_eval, dim3(1), dim3(NTS), lds(), stream, dv_, reinterpret_cast<const cplx*>(X), nullptr,
-                       reinterpret_cast<cplx*>(F));
+    with_evaluator([&](auto e) {
+      using E = decltype(e);
+      hipLaunchKernelGGL(ks_eval_f<E>, dim3(1), dim3(E::NT), E::lds(dv_), stream, dv_, reinterpret_cast<const cplx*>(X),
+                         reinterpret_cast<cplx*>(F));
+    });
     SPS_CHECK_LAUNCH();
   }
   void eval_F_vjp(const double* X, const double* Fbar, double* Xbar) override {
     SPS_REQUIRE(X && Fbar && Xbar, "null argument");
-    hipLaunchKernelGGL(ks_eval, dim3(1), dim3(NTS), lds(), stream, dv_, reinterpret_cast<const cplx*>(X),
-                       reinterpret_cast<const cplx*>(Fbar), reinterpret_cast<cplx*>(Xbar));
+    with_evaluator([&](auto e) {
+      using E = decltype(e);
+      hipLaunchKernelGGL(ks_eval_vjp<E>, dim3(1), dim3(E::NT), E::lds(dv_), stream, dv_,
+                         reinterpret_cast<const cplx*>(X), reinterpret_cast<const cplx*>(Fbar),
+                         reinterpret_cast<cplx*>(Xbar));
+    });
     SPS_CHECK_LAUNCH();
   }
   void solve(const double* R, double* X, int) override {
@@ -649,21 +851,37 @@ class KsProblem : public ProblemImpl {
   }
 
  private:
-  size_t lds() const { return sizeof(cplx) * (Ng_ + 4 * K_) + sizeof(double) * Ng_; }
   const double* rk_dts() const { return var_n_ ? dts_ : nullptr; }
+  // The folded sums where every lane's twiddles fit its registers (K <= 64), with the fewest threads that
+  // hold them; the direct sums beyond.
+  template <class Fn>
+  void with_evaluator(Fn fn) {
+    if (KsFold<256, 2, 8, 8>::fits(K_, Ng_)) fn(KsFold<256, 2, 8, 8>());          // K <= 32, Ng even
+    else if (KsFold<256, 1, 16, 16>::fits(K_, Ng_)) fn(KsFold<256, 1, 16, 16>());  // K < 32, Ng odd
+    else if (KsFold<512, 2, 16, 16>::fits(K_, Ng_)) fn(KsFold<512, 2, 16, 16>());  // K <= 64, Ng even
+    else if (KsFold<512, 1, 32, 32>::fits(K_, Ng_)) fn(KsFold<512, 1, 32, 32>());  // K < 64, Ng odd
+    else fn(KsDirect());
+  }
   // one-block sweep launch, bracketed by the timer's events while it records
   template <typename... P, typename... A>
-  void launch_timed(void (*kern)(P...), A... args) {
+  void launch_timed(void (*kern)(P...), int threads, size_t lds, A... args) {
     hipEvent_t e0, e1;
     if (timer_.take(&e0, &e1))
-      hipExtLaunchKernelGGL(kern, dim3(1), dim3(NTS), lds(), stream, e0, e1, 0, args...);
+      hipExtLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, e0, e1, 0, args...);
     else
-      hipLaunchKernelGGL(kern, dim3(1), dim3(NTS), lds(), stream, args...);
+      hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, stream, args...);
   }
   void forward(cplx* X, int nsteps) {
-    if (!rk_) launch_timed(ks_forward, dv_, X, H_, nsteps, static_cast<const SbdfCoef*>(rows_), err_);
-    else if (stages_ == 2) launch_timed(ks_forward_rk<2>, dv_, X, H_, nsteps, tab_, desc_.dt, rk_dts(), err_);
-    else launch_timed(ks_forward_rk<4>, dv_, X, H_, nsteps, tab_, desc_.dt, rk_dts(), err_);
+    with_evaluator([&](auto e) {
+      using E = decltype(e);
+      const size_t l = E::lds(dv_);
+      if (!rk_)
+        launch_timed(ks_forward<E>, E::NT, l, dv_, X, H_, nsteps, static_cast<const SbdfCoef*>(rows_), err_);
+      else if (stages_ == 2)
+        launch_timed(ks_forward_rk<E, 2>, E::NT, l, dv_, X, H_, nsteps, tab_, desc_.dt, rk_dts(), err_);
+      else
+        launch_timed(ks_forward_rk<E, 4>, E::NT, l, dv_, X, H_, nsteps, tab_, desc_.dt, rk_dts(), err_);
+    });
     SPS_CHECK_LAUNCH();
     tape_steps_ = nsteps;
   }

@@ -13,6 +13,9 @@ if not torch.cuda.is_available():
 
 import paper_2506_14792_amd as sps  # noqa: E402
 from test_gpu_closure import test_closure_net_forward_and_vjp as check_closure_net  # noqa: E402
+from test_gpu_ks import test_ks_F_vjp_and_solve as check_ks_F  # noqa: E402
+from test_gpu_ks import test_ks_forward_and_gradient as check_ks_gradient  # noqa: E402
+from test_gpu_ks import test_ks_rk_forward_and_gradient as check_ks_rk_gradient  # noqa: E402
 
 dev = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.float64).ravel().copy()).cuda()
 
@@ -108,3 +111,14 @@ def test_poiseuille_inverse_iteration_steps(nz, iters):
         assert abs(lam[q, 0] - (sigma - 1.0 / mu)) <= tol * size / abs(mu) ** 2
         assert np.linalg.norm(X[q] - c / np.linalg.norm(c)) <= tol
         assert np.linalg.norm(Y[q] - r) <= tol
+
+
+# folded sums: the smallest grids (6 and 9 points), the last size of every form (K = 32, 31, 64, 63: 96, 93,
+# 192 and 189 points), the first past it (K = 33), a grid of 4 n + 2 points (K = 6), and the direct sums (K =
+# 65, 256).  Sums of at most 768 terms of size one: 768 u = 1e-13, within the checks' 1e-11.
+@pytest.mark.parametrize("nx", [4, 6, 12, 62, 64, 66, 126, 128, 130, 512])
+def test_ks_sizes(nx):
+    cfg = (nx, 32.0, 0.01)
+    check_ks_F(cfg)
+    check_ks_gradient(cfg, 5)
+    check_ks_rk_gradient(cfg, 2, "rk222")
