@@ -18,8 +18,10 @@
 
 #include <algorithm>
 #include <memory>
+#include <type_traits>
 #include <vector>
 
+#include "block_fft.h"
 #include "cnn.h"
 #include "sps_device.h"
 #include "sps_internal.h"
@@ -257,6 +259,45 @@ __device__ __forceinline__ long long hidx(const KolCol& a, int k, long long st) 
   return (long long)(a.hring ? (k % a.hring) : k) * st;
 }
 
+// One mode of a forward step: the SBDF solve with F of state n - 1, its records and (on snapshot steps) the
+// truncation to the coarse grid's modes.  keep: not the Nyquist row.
+struct StepIn {
+  cplx f2, x1, x2;
+};
+__device__ __forceinline__ StepIn kol_step_load(const KolCol& a, long long st, long long si) {
+  const int n = a.n;
+  StepIn r;
+  r.f2 = (n >= 2) ? a.Fr[(n & 1) * st + si] : czero();
+  r.x1 = a.H[hidx(a, n - 1, st) + si];
+  r.x2 = (n >= 2) ? a.H[hidx(a, n - 2, st) + si] : czero();
+  return r;
+}
+__device__ __forceinline__ void kol_step_entry(const KolDev& d, const KolCol& a, int b, int m, int iy, bool keep, cplx F,
+                                               const StepIn& in, double lin, long long st, long long si) {
+  const int n = a.n, N = d.N;
+  const SbdfC q = sbdf_c(n, d.dt);
+  cplx xn = czero();
+  if (keep) {
+    cplx rhs = cadd(cscale(F, q.c1), cscale(in.f2, q.c2));
+    rhs = csub(rhs, cadd(cscale(in.x1, q.a1), cscale(in.x2, q.a2)));
+    xn = cscale(rhs, 1.0 / (q.a0 + lin));
+  }
+  a.Fr[((n - 1) & 1) * st + si] = F;
+  a.H[hidx(a, n, st) + si] = xn;
+  if (!(isfinite(xn.x) && isfinite(xn.y))) atomicOr(a.err, 2);
+  if (n == a.nsteps && a.out) a.out[si] = xn;
+  if (a.snap && n % a.snap_every == 0) {
+    // spectral truncation to the Nc x Nc modes of the coarse grid
+    const int Nch = a.Nc / 2;
+    const int sy = (iy < N / 2) ? iy : iy - N;
+    if (m < Nch && sy >= -Nch && sy < Nch) {   // sy = -Nch: the coarse Nyquist row, kept zero
+      const int ic = (sy >= 0) ? sy : sy + a.Nc;
+      a.snap[((long long)(n / a.snap_every - 1) * d.B + b) * Nch * a.Nc + (long long)m * a.Nc + ic] =
+          (sy == -Nch) ? czero() : xn;
+    }
+  }
+}
+
 // Grid (column tiles, instances).  LDS twiddles(Ng) + twiddles(N) + 2 wcap (wcap >=
 // fpad_size(nW tc Ng)) + 2 fpad_size(tc N) when the closure runs.
 __global__ void __launch_bounds__(NTK) kol_cols_fwd(KolDev d, KolCol a, int tc, int wcap) {
@@ -306,31 +347,7 @@ __global__ void __launch_bounds__(NTK) kol_cols_fwd(KolDev d, KolCol a, int tc, 
         a.out[si] = F;
         continue;
       }
-      const int n = a.n;
-      const SbdfC q = sbdf_c(n, d.dt);
-      const cplx f2 = (n >= 2) ? a.Fr[(n & 1) * st + si] : czero();
-      const cplx x1 = a.H[hidx(a, n - 1, st) + si];
-      const cplx x2 = (n >= 2) ? a.H[hidx(a, n - 2, st) + si] : czero();
-      cplx xn = czero();
-      if (row >= 0) {
-        cplx rhs = cadd(cscale(F, q.c1), cscale(f2, q.c2));
-        rhs = csub(rhs, cadd(cscale(x1, q.a1), cscale(x2, q.a2)));
-        xn = cscale(rhs, 1.0 / (q.a0 + lin));
-      }
-      a.Fr[((n - 1) & 1) * st + si] = F;
-      a.H[hidx(a, n, st) + si] = xn;
-      if (!(isfinite(xn.x) && isfinite(xn.y))) atomicOr(a.err, 2);
-      if (n == a.nsteps && a.out) a.out[si] = xn;
-      if (a.snap && n % a.snap_every == 0) {
-        // spectral truncation to the Nc x Nc modes of the coarse grid
-        const int Nch = a.Nc / 2;
-        const int sy = (iy < N / 2) ? iy : iy - N;
-        if (m < Nch && sy >= -Nch && sy < Nch) {   // sy = -Nch: the coarse Nyquist row, kept zero
-          const int ic = (sy >= 0) ? sy : sy + a.Nc;
-          a.snap[((long long)(n / a.snap_every - 1) * d.B + b) * Nch * a.Nc + (long long)m * a.Nc + ic] =
-              (sy == -Nch) ? czero() : xn;
-        }
-      }
+      kol_step_entry(d, a, b, m, iy, row >= 0, F, kol_step_load(a, st, si), lin, st, si);
       continue;
     }
     // reverse sweep: xb of state k (K_ADJ: k = n - 1 from the VJP; K_ADJ_INIT: k = nsteps)
@@ -383,6 +400,181 @@ __global__ void __launch_bounds__(NTK) kol_cols_fwd(KolDev d, KolCol a, int tc, 
     a.Yn[si] = y;
     a.Ln[si] = l;
     a.Gk[si] = g;
+  }
+}
+
+// ---------------------------------------------------------------------------- steps of a known grid length
+// The three kernels of a forward step on block_fft.h, for the grid lengths it has a plan for: columns and
+// row pairs are transformed in place with the first pass read from memory and the last one used in
+// registers.  At N = 512, six instances: columns inverse 61 -> 22 us (113 MB moved), rows 87 -> 42 (94 MB), columns
+// forward 34 -> 20 (113 MB).  Bound by LDS and the vector unit together in the rows (some 17 and 14 us of the 42), by
+// memory in the columns.
+template <int G>
+struct KolFft {
+  static constexpr int N = 2 * G / 3, Nh = G / 3, R0 = BlockPlan<G>::R0, R1 = BlockPlan<G>::R1;
+  // columns of a block, and row pairs of a block: about 200 to 400 threads of one butterfly each, and no more
+  // LDS than lets two blocks share a CU
+  static constexpr int TC = G >= 576 ? 4 : 8, PAIRS = G >= 576 ? 1 : (G == 48 ? 4 : 2);
+  static constexpr int NTC = TC * G / R0, NTR = 4 * PAIRS * G / R0;
+  static constexpr size_t lds_cols = sizeof(cplx) * (G + bf_size(TC * G)), lds_rows = sizeof(cplx) * (G + bf_size(4 * PAIRS * G));
+  static_assert(Nh % TC == 0 && (G / 2) % PAIRS == 0, "tiles");
+};
+// Column tile of a block.  Tiles of four columns write half of a 128-byte line: the two halves' blocks are
+// dealt to the same XCD, one after the other.
+template <int TC>
+__device__ __forceinline__ int kol_tile(int x, int tiles) {
+  return (TC == 4 && tiles % 16 == 0) ? ((x & ~15) | ((x & 7) << 1) | ((x >> 3) & 1)) : x;
+}
+
+// kol_cols_inv on the padded grid.  Grid (column tiles, fields, instances).
+template <int G>
+__global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_inv_b(KolDev d, const cplx* X, int set, cplx* Z) {
+  using P = KolFft<G>;
+  constexpr int N = P::N, Nh = P::Nh, R0 = P::R0, TC = P::TC, NR = G / R0;
+  using F = BlockFft<G, TC, P::NTC, 4, 1>;   // the states have a column's modes next to each other, Z a row's
+  static_assert(F::First::MB == 1 && F::First::full, "one butterfly a thread");
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  const int b = blockIdx.z, f = blockIdx.y, nf = gridDim.y, c0 = TC * kol_tile<TC>(blockIdx.x, gridDim.x), tid = threadIdx.x;
+  const int j = F::First::bfly(tid), m = c0 + F::First::seq(tid);
+  const cplx* g = d.tw + d.twoff[d.pNg];
+  const cplx* Xc = X + ((long long)b * Nh + m) * N;
+  cplx v[1][R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {   // grid position p holds mode p (p < N / 2) or p - G + N (p > G - N / 2)
+    const int p = j + r * NR;
+    v[0][r] = czero();
+    if (r * NR >= N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
+    if (p < N / 2 || p > G - N / 2) v[0][r] = Xc[p < N / 2 ? p : p - G + N];
+  }
+  for (int e = tid; e < G; e += P::NTC) tw[e] = g[e];
+  if (set == FS_PRIMAL4) {
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      if (r * NR >= N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
+      const int p = j + r * NR;
+      v[0][r] = cmul(v[0][r], field_factor(f, m, p < N / 2 ? p : p - G + N, N));
+    }
+  }
+  F::First::work(v, tw, +1);   // (the first pass has no twiddles)
+  F::First::write(v, buf);
+  F::rest(v, buf, tw, +1);
+  cplx* Zc = Z + (((long long)b * nf + f) * G + F::Last::bfly(tid)) * Nh + c0 + F::Last::seq(tid);
+#pragma unroll
+  for (int r = 0; r < R0; ++r) Zc[(long long)r * NR * Nh] = v[0][r];
+}
+
+// kol_rows in mode R_ADV.  The four fields of a row pair are in one row of 16 lanes, so the products are formed
+// by lane exchanges in the last inverse pass, whose outputs are the inputs of the forward transform's
+// first.  Grid (G / 2 / PAIRS, instances).
+template <int G>
+__global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const cplx* Z4, cplx* W) {
+  using P = KolFft<G>;
+  constexpr int Nh = P::Nh, R0 = P::R0, PAIRS = P::PAIRS, TC = 4 * PAIRS, NT = P::NTR, NR = G / R0;
+  using FI = BlockFft<G, TC, NT, 4, 4>;
+  using FF = BlockFft<G, PAIRS, NT, 1, 1>;
+  static_assert(FI::First::MB == 1 && FI::First::full && FF::Last::MB == 1, "one butterfly a thread");
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  const int b = blockIdx.y, tid = threadIdx.x, j = FI::First::bfly(tid), f = FI::First::seq(tid) & 3, pr = FI::First::seq(tid) >> 2;
+  const cplx* U = Z4 + (((long long)b * 4 + f) * G + 2 * (blockIdx.x * PAIRS + pr)) * Nh;
+  const cplx* g = d.tw + d.twoff[d.pNg];
+  // two rows' half spectra as one spectrum (kol_pack): x < Nh direct, x > G - Nh mirrored, zero between
+  cplx v[1][R0], u[R0], w[R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    u[r] = w[r] = czero();
+    if (r * NR >= Nh && (r + 1) * NR - 1 <= G - Nh) continue;
+    const int x = j + r * NR;
+    if (x < Nh || x > G - Nh) {
+      const int i = x < Nh ? x : G - x;
+      u[r] = U[i];
+      w[r] = U[Nh + i];
+    }
+  }
+  for (int e = tid; e < G; e += NT) tw[e] = g[e];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    const int x = j + r * NR;
+    if (x == 0) u[r].y = w[r].y = 0.0;
+    v[0][r] = (x < Nh) ? cmk(u[r].x - w[r].y, u[r].y + w[r].x) : cmk(u[r].x + w[r].y, w[r].x - u[r].y);
+  }
+  FI::First::work(v, tw, +1);
+  FI::First::write(v, buf);
+  FI::rest(v, buf, tw, +1);
+  // the fields are on lanes 4 f + (0 .. 3) of a row of 16: u omega_x (f = 0, 2; a turn by 8) + v omega_y (f =
+  // 1, 3; by 4), the two rows in the two parts
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    const double x = v[0][r].x * dpp_d<0x128>(v[0][r].x), y = v[0][r].y * dpp_d<0x128>(v[0][r].y);
+    v[0][r] = cmk(-(x + dpp_d<0x124>(x)), -(y + dpp_d<0x124>(y)));
+  }
+  FI::First::work(v, tw, -1);   // the forward transform's first pass: in every field's lanes, one writes
+  if (f == 0) {
+    const int base = j * R0 * PAIRS + pr;
+#pragma unroll
+    for (int r = 0; r < R0; ++r) buf[bf_pad(base + r * PAIRS)] = v[0][r];
+  }
+  FF::rest(v, buf, tw, -1);
+  if (FF::Last::full || tid < FF::Last::NB) FF::Last::write(v, buf);
+  __syncthreads();
+  // unpack the two real rows' half spectra: Y_y = (Z_m + conj Z_-m) / 2, Y_y+1 = (Z_m - conj Z_-m) / 2i
+  for (int e = tid; e < PAIRS * 2 * Nh; e += NT) {
+    const int rr = e / Nh, m = e - rr * Nh, yy = rr & 1, p = rr >> 1;
+    const cplx zm = buf[bf_pad(m * PAIRS + p)], zq = buf[bf_pad((m == 0 ? 0 : G - m) * PAIRS + p)];
+    const cplx y = yy ? cmk(0.5 * (zm.y + zq.y), -0.5 * (zm.x - zq.x)) : cmk(0.5 * (zm.x + zq.x), 0.5 * (zm.y - zq.y));
+    W[((long long)b * G + 2 * (blockIdx.x * PAIRS + p) + yy) * Nh + m] = y;
+  }
+}
+
+// kol_cols_fwd in mode K_STEP without the closure.  Grid (column tiles, instances).
+template <int G>
+__global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_step_b(KolDev d, KolCol a) {
+  using P = KolFft<G>;
+  constexpr int N = P::N, Nh = P::Nh, R0 = P::R0, TC = P::TC, NR = G / R0;
+  using F = BlockFft<G, TC, P::NTC, 1, 4>;   // as kol_cols_inv_b, the other way
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  const int b = blockIdx.y, tid = threadIdx.x, c0 = TC * kol_tile<TC>(blockIdx.x, gridDim.x);
+  const int j = F::Last::bfly(tid), m = c0 + F::Last::seq(tid);
+  const cplx* g = d.tw + d.twoff[d.pNg];
+  const cplx* Wc = a.W + ((long long)b * G + F::First::bfly(tid)) * Nh + c0 + F::First::seq(tid);
+  cplx v[1][R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) v[0][r] = Wc[(long long)r * NR * Nh];
+  for (int e = tid; e < G; e += P::NTC) tw[e] = g[e];
+  F::First::work(v, tw, -1);
+  F::First::write(v, buf);
+  // the previous states and F of this thread's modes: grid position p holds mode p (p < N / 2) or p - G + N
+  // (p > G - N / 2); p = N / 2 stands for the Nyquist row, which is kept zero
+  const long long st = (long long)d.B * Nh * N, io = ((long long)b * Nh + m) * N;
+  StepIn in[R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    const int p = j + r * NR;
+    if (r * NR > N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
+    if (p <= N / 2 || p > G - N / 2) in[r] = kol_step_load(a, st, io + (p <= N / 2 ? p : p - G + N));
+  }
+  F::rest(v, buf, tw, -1);
+  const double ng2 = 1.0 / ((double)G * G);
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    const int p = j + r * NR;
+    if (r * NR > N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
+    if (p <= N / 2 || p > G - N / 2) {
+      const int iy = p <= N / 2 ? p : p - G + N;
+      const bool keep = p != N / 2;
+      cplx f = czero();
+      if (keep) {
+        f = cscale(v[0][r], ng2);
+        if (m == 0 && N > 8 && (iy == 4 || iy == N - 4)) f = cadd(f, cmk(-2.0, 0.0));   // -4 cos 4y
+      }
+      const double ky = kol_ky(iy, N), lin = d.nu * ((double)m * m + ky * ky) + d.drag;
+      kol_step_entry(d, a, b, m, iy, keep, f, in[r], lin, st, io + iy);
+    }
   }
 }
 
@@ -517,6 +709,12 @@ class KolProblem : public ProblemImpl {
     for (const void* k : {(const void*)kol_cols_inv, (const void*)kol_rows<256>, (const void*)kol_rows<512>,
                           (const void*)kol_rows_adv2<512>, (const void*)kol_cols_fwd})
       SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
+    block_ = with_block_fft([&](auto g) {
+      constexpr int G = decltype(g)::value;
+      SPS_HIP(hipFuncSetAttribute((const void*)kol_cols_inv_b<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)KolFft<G>::lds_cols));
+      SPS_HIP(hipFuncSetAttribute((const void*)kol_rows_adv_b<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)KolFft<G>::lds_rows));
+      SPS_HIP(hipFuncSetAttribute((const void*)kol_cols_step_b<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)KolFft<G>::lds_cols));
+    });
     SPS_HIP(hipStreamSynchronize(stream));
   }
 
@@ -700,7 +898,30 @@ class KolProblem : public ProblemImpl {
     a.err = err_;
     return a;
   }
+  // fn(the padded length as a type) if block_fft.h has a plan for it
+  template <typename Fn>
+  bool with_block_fft(Fn fn) const {
+    switch (Ng_) {
+      case 48: fn(std::integral_constant<int, 48>()); return true;
+      case 96: fn(std::integral_constant<int, 96>()); return true;
+      case 144: fn(std::integral_constant<int, 144>()); return true;
+      case 192: fn(std::integral_constant<int, 192>()); return true;
+      case 288: fn(std::integral_constant<int, 288>()); return true;
+      case 384: fn(std::integral_constant<int, 384>()); return true;
+      case 576: fn(std::integral_constant<int, 576>()); return true;
+      case 768: fn(std::integral_constant<int, 768>()); return true;
+      default: return false;
+    }
+  }
   void launch_cols(const KolCol& a) {
+    if (block_ && a.mode == K_STEP && !a.closure) {
+      with_block_fft([&](auto g) {
+        using P = KolFft<decltype(g)::value>;
+        hipLaunchKernelGGL(kol_cols_step_b<decltype(g)::value>, dim3(P::Nh / P::TC, B_), dim3(P::NTC), P::lds_cols, stream, d_, a);
+      });
+      SPS_CHECK_LAUNCH();
+      return;
+    }
     hipLaunchKernelGGL(kol_cols_fwd, dim3((Nh_ + tc_f_ - 1) / tc_f_, B_), dim3(NTK), fwd_lds(tc_f_), stream, d_, a,
                        tc_f_, wcap(tc_f_));
     SPS_CHECK_LAUNCH();
@@ -708,12 +929,30 @@ class KolProblem : public ProblemImpl {
   void cols_inv(const cplx* X, int set, int G, int plan, cplx* Z) {
     const int tc = (G == Ng_) ? tc_ig_ : tc_in_;
     const int nf = (set == FS_PRIMAL4) ? 4 : 1;
+    if (block_ && G == Ng_) {
+      with_block_fft([&](auto g) {
+        using P = KolFft<decltype(g)::value>;
+        hipLaunchKernelGGL(kol_cols_inv_b<decltype(g)::value>, dim3(P::Nh / P::TC, nf, B_), dim3(P::NTC), P::lds_cols, stream, d_,
+                           X, set, Z);
+      });
+      SPS_CHECK_LAUNCH();
+      return;
+    }
     hipLaunchKernelGGL(kol_cols_inv, dim3((Nh_ + tc - 1) / tc, nf, B_), dim3(NTK), inv_lds(G, tc), stream, d_, X,
                        set, G, plan, tc, Z);
     SPS_CHECK_LAUNCH();
   }
   void rows(int mode, int G, int plan, const cplx* Z4, const cplx* Zg, double* grid, const double* gin, cplx* W,
             double wscale, double gscale) {
+    if (mode == R_ADV && block_) {
+      with_block_fft([&](auto g) {
+        using P = KolFft<decltype(g)::value>;
+        hipLaunchKernelGGL(kol_rows_adv_b<decltype(g)::value>, dim3(decltype(g)::value / 2 / P::PAIRS, B_), dim3(P::NTR), P::lds_rows,
+                           stream, d_, Z4, W);
+      });
+      SPS_CHECK_LAUNCH();
+      return;
+    }
     if (mode == R_ADV && G >= 384) {
       const size_t l2 = sizeof(cplx) * (G + 2 * (size_t)fpad_size(2 * G) + fpad_size(G));
       hipLaunchKernelGGL(kol_rows_adv2<512>, dim3(G / 2, B_), dim3(512), l2, stream, d_, G, plan, Z4, W);
@@ -766,6 +1005,7 @@ class KolProblem : public ProblemImpl {
 
   int B_, N_, Nh_, Ng_, max_steps_, closure_, hring_, nwmax_ = 4, tc_ig_ = 1, tc_in_ = 1, tc_f_ = 1, rcap_ = 0;
   int tape_ = -1;
+  bool block_ = false;   // the padded length has a block_fft.h plan
   long long st_ = 0;
   KolDev d_{};
   DevArena arena_;

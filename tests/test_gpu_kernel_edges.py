@@ -122,3 +122,37 @@ def test_ks_sizes(nx):
     check_ks_F(cfg)
     check_ks_gradient(cfg, 5)
     check_ks_rk_gradient(cfg, 2, "rk222")
+
+
+# the padded grid lengths with a plan of their own (48 to 768), the first and last of them in tiles of one and
+# two row pairs and of four and eight columns; forcing, Nyquist row and snapshots in the fused step.  Same bound as
+# test_gpu_kolmo.py: 1e-11 of the largest magnitude, FP64 on both sides.
+@pytest.mark.parametrize("N", [32, 64, 96, 128, 192, 256, 384, 512])
+def test_kolmo_grid_lengths(N):
+    from oracle import imex
+    from oracle.kolmo import Kolmogorov
+    from test_gpu_kolmo import from_dev, rel, to_dev
+    print(f"Kolmogorov grid length, N = {N}", flush=True)
+    B, dt, n, Nc = (3 if N <= 128 else 1), 1e-3 * 64 / N, 3, 16
+    c0 = wl.kolmo_vorticity(seed=N, N=N, batch=B)
+    P = Kolmogorov(N, Re=1000.0, drag=0.1)
+    G = sps.Kolmogorov(B, N, Re=1000.0, dt=dt, max_steps=1, keep_history=False, drag=0.1)
+    X0 = to_dev(list(c0))
+    XN, F = torch.zeros_like(X0), torch.zeros_like(X0)
+    snap = torch.full((n * B * Nc * Nc,), 7.0, dtype=torch.float64, device="cuda")
+    G.eval_F(X0, F)
+    G.forward(X0, n, XN=XN, snap=snap, every=1, nc=Nc)
+    G.sync()
+    s = snap.cpu().numpy().view(np.complex128).reshape(n, B, Nc // 2, Nc)
+    iy = np.arange(Nc)
+    rows = np.where(iy < Nc // 2, iy, iy - Nc + N)
+    for b in range(B):
+        X = c0[b].reshape(-1, 1)
+        _, states = imex.sbdf_forward(P, X, dt, n)
+        assert rel(from_dev(F, B, N)[b], P.F(X).reshape(N, N // 2)) <= 1e-11
+        assert rel(from_dev(XN, B, N)[b], states[-1].reshape(N, N // 2)) <= 1e-11
+        assert np.all(from_dev(XN, B, N)[b][N // 2] == 0.0)
+        for k in range(n):
+            ref = states[k + 1].reshape(N, N // 2)[rows, : Nc // 2].copy()
+            ref[Nc // 2, :] = 0.0
+            assert rel(s[k, b].T, ref) <= 1e-11
