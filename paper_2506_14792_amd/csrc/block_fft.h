@@ -18,9 +18,12 @@ template <int N> struct BlockPlan { static constexpr bool ok = false; };
   template <> struct BlockPlan<N_> { static constexpr bool ok = true; static constexpr int R0 = A, R1 = B; \
                                      static_assert(A * B * A == N_, "radices"); };
 SPS_BLOCK_PLAN(48, 4, 3)
+SPS_BLOCK_PLAN(64, 4, 4)
 SPS_BLOCK_PLAN(96, 4, 6)
+SPS_BLOCK_PLAN(128, 8, 2)
 SPS_BLOCK_PLAN(144, 6, 4)
 SPS_BLOCK_PLAN(192, 8, 3)
+SPS_BLOCK_PLAN(256, 8, 4)
 SPS_BLOCK_PLAN(288, 6, 8)
 SPS_BLOCK_PLAN(384, 8, 6)
 SPS_BLOCK_PLAN(576, 12, 4)
@@ -78,10 +81,10 @@ struct BlockPass {
     v[r] = buf[bf_at<r * NR * TC>(base, pb)];
     if constexpr (r + 1 < R) read1<r + 1>(v, buf, base, pb);
   }
-  static __device__ __forceinline__ void read(cplx (&v)[MB][R], const cplx* buf) {
+  static __device__ __forceinline__ void read(cplx (&v)[MB][R], const cplx* buf, int tid) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      const int it = (int)threadIdx.x + i * NT;
+      const int it = tid + i * NT;
       if (full || it < NB) {
         const int base = bfly(it) * TC + seq(it);
         read1(v[i], buf, base, bf_pad(base));
@@ -89,10 +92,10 @@ struct BlockPass {
     }
   }
   // twiddles (tw[t] = exp(-2 pi i t / N)) and the butterflies
-  static __device__ __forceinline__ void work(cplx (&v)[MB][R], const cplx* tw, int sign) {
+  static __device__ __forceinline__ void work(cplx (&v)[MB][R], const cplx* tw, int sign, int tid) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      const int it = (int)threadIdx.x + i * NT;
+      const int it = tid + i * NT;
       if (full || it < NB) {
         if constexpr (NS > 1) {
           const int t = (bfly(it) % NS) * (N / (NS * R));
@@ -118,10 +121,10 @@ struct BlockPass {
     else buf[bf_at<r * NS * TC>(base, pb)] = v[r];
     if constexpr (r + 1 < R) write1<r + 1>(v, buf, base, pb);
   }
-  static __device__ __forceinline__ void write(const cplx (&v)[MB][R], cplx* buf) {
+  static __device__ __forceinline__ void write(const cplx (&v)[MB][R], cplx* buf, int tid) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      const int it = (int)threadIdx.x + i * NT;
+      const int it = tid + i * NT;
       if (full || it < NB) {
         const int base = out_base(it);
         write1(v[i], buf, base, bf_pad(base));
@@ -131,7 +134,7 @@ struct BlockPass {
 };
 
 // The passes after the first (its outputs are in buf; no barrier since they were written).  Leaves the
-// last pass's outputs in v: v[i][r] is position bfly(it) + r N / R0 of sequence seq(it), it = threadIdx.x +
+// last pass's outputs in v: v[i][r] is position bfly(it) + r N / R0 of sequence seq(it), it = tid +
 // i NT; every thread is past its last read of buf.  JF0, JF2: the order of the first and the last pass.
 template <int N, int TC, int NT, int JF0, int JF2>
 struct BlockFft {
@@ -139,19 +142,19 @@ struct BlockFft {
   using First = BlockPass<N, R0, 1, TC, NT, JF0>;
   using Mid = BlockPass<N, R1, R0, TC, NT, 1>;
   using Last = BlockPass<N, R0, R0 * R1, TC, NT, JF2>;
-  static __device__ __forceinline__ void rest(cplx (&v)[Last::MB][R0], cplx* buf, const cplx* tw, int sign) {
+  static __device__ __forceinline__ void rest(cplx (&v)[Last::MB][R0], cplx* buf, const cplx* tw, int sign, int tid) {
     {
       cplx m[Mid::MB][R1];
       __syncthreads();
-      Mid::read(m, buf);
+      Mid::read(m, buf, tid);
       __syncthreads();
-      Mid::work(m, tw, sign);
-      Mid::write(m, buf);
+      Mid::work(m, tw, sign, tid);
+      Mid::write(m, buf, tid);
     }
     __syncthreads();
-    Last::read(v, buf);
+    Last::read(v, buf, tid);
     __syncthreads();
-    Last::work(v, tw, sign);
+    Last::work(v, tw, sign, tid);
   }
 };
 

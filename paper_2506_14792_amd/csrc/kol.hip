@@ -457,9 +457,9 @@ __global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_inv_b(KolDev d, const
       v[0][r] = cmul(v[0][r], field_factor(f, m, p < N / 2 ? p : p - G + N, N));
     }
   }
-  F::First::work(v, tw, +1);   // (the first pass has no twiddles)
-  F::First::write(v, buf);
-  F::rest(v, buf, tw, +1);
+  F::First::work(v, tw, +1, tid);   // (the first pass has no twiddles)
+  F::First::write(v, buf, tid);
+  F::rest(v, buf, tw, +1, tid);
   cplx* Zc = Z + (((long long)b * nf + f) * G + F::Last::bfly(tid)) * Nh + c0 + F::Last::seq(tid);
 #pragma unroll
   for (int r = 0; r < R0; ++r) Zc[(long long)r * NR * Nh] = v[0][r];
@@ -501,9 +501,9 @@ __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const
     if (x == 0) u[r].y = w[r].y = 0.0;
     v[0][r] = (x < Nh) ? cmk(u[r].x - w[r].y, u[r].y + w[r].x) : cmk(u[r].x + w[r].y, w[r].x - u[r].y);
   }
-  FI::First::work(v, tw, +1);
-  FI::First::write(v, buf);
-  FI::rest(v, buf, tw, +1);
+  FI::First::work(v, tw, +1, tid);
+  FI::First::write(v, buf, tid);
+  FI::rest(v, buf, tw, +1, tid);
   // the fields are on lanes 4 f + (0 .. 3) of a row of 16: u omega_x (f = 0, 2; a turn by 8) + v omega_y (f =
   // 1, 3; by 4), the two rows in the two parts
 #pragma unroll
@@ -511,14 +511,14 @@ __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const
     const double x = v[0][r].x * dpp_d<0x128>(v[0][r].x), y = v[0][r].y * dpp_d<0x128>(v[0][r].y);
     v[0][r] = cmk(-(x + dpp_d<0x124>(x)), -(y + dpp_d<0x124>(y)));
   }
-  FI::First::work(v, tw, -1);   // the forward transform's first pass: in every field's lanes, one writes
+  FI::First::work(v, tw, -1, tid);   // the forward transform's first pass: in every field's lanes, one writes
   if (f == 0) {
     const int base = j * R0 * PAIRS + pr;
 #pragma unroll
     for (int r = 0; r < R0; ++r) buf[bf_pad(base + r * PAIRS)] = v[0][r];
   }
-  FF::rest(v, buf, tw, -1);
-  if (FF::Last::full || tid < FF::Last::NB) FF::Last::write(v, buf);
+  FF::rest(v, buf, tw, -1, tid);
+  if (FF::Last::full || tid < FF::Last::NB) FF::Last::write(v, buf, tid);
   __syncthreads();
   // unpack the two real rows' half spectra: Y_y = (Z_m + conj Z_-m) / 2, Y_y+1 = (Z_m - conj Z_-m) / 2i
   for (int e = tid; e < PAIRS * 2 * Nh; e += NT) {
@@ -546,8 +546,8 @@ __global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_step_b(KolDev d, KolC
 #pragma unroll
   for (int r = 0; r < R0; ++r) v[0][r] = Wc[(long long)r * NR * Nh];
   for (int e = tid; e < G; e += P::NTC) tw[e] = g[e];
-  F::First::work(v, tw, -1);
-  F::First::write(v, buf);
+  F::First::work(v, tw, -1, tid);
+  F::First::write(v, buf, tid);
   // the previous states and F of this thread's modes: grid position p holds mode p (p < N / 2) or p - G + N
   // (p > G - N / 2); p = N / 2 stands for the Nyquist row, which is kept zero
   const long long st = (long long)d.B * Nh * N, io = ((long long)b * Nh + m) * N;
@@ -558,7 +558,7 @@ __global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_step_b(KolDev d, KolC
     if (r * NR > N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
     if (p <= N / 2 || p > G - N / 2) in[r] = kol_step_load(a, st, io + (p <= N / 2 ? p : p - G + N));
   }
-  F::rest(v, buf, tw, -1);
+  F::rest(v, buf, tw, -1, tid);
   const double ng2 = 1.0 / ((double)G * G);
 #pragma unroll
   for (int r = 0; r < R0; ++r) {

@@ -24,8 +24,10 @@
 
 #include <algorithm>
 #include <memory>
+#include <type_traits>
 #include <vector>
 
+#include "block_fft.h"
 #include "sps_device.h"
 #include "sps_internal.h"
 
@@ -63,6 +65,9 @@ struct ShDev {
   const int2* ritem;    // (instance, first row pair)
   const int* jptr;
   const int* jitem;     // cost items: instance
+  // Block b works for instances of group b % groups only, and only the group's blocks wait for each other
+  // (every data dependence is within an instance).  bar: a counter per group, BAR_STRIDE apart.
+  int groups;
   unsigned* bar;
   int* err;             // bit 1: non-finite state, bit 2: barrier timed out
 };
@@ -121,28 +126,35 @@ __device__ __forceinline__ void stage_tw(const ShDev& d, int plan, int n, cplx* 
   for (int e = threadIdx.x; e < n; e += blockDim.x) tw[e] = g[e];
 }
 
-// ---------------------------------------------------------------------------- grid barrier
-// All blocks of the (cooperative) launch.  Thread 0 arrives with a release and waits with
-// acquire loads; a wait longer than kSpinLimit polls, or another block's timeout, aborts:
-// the block sets err bit 2 and returns false, and the caller leaves the kernel.
+// ---------------------------------------------------------------------------- group barrier
+// The blocks of the caller's group (of a cooperative launch).  Every wave waits for its own stores, then
+// thread 0 releases them to the device, arrives, and polls without ordering; the acquire follows once.  (With
+// an acquire at every poll and a release of system scope the sweep of 128 instances took 27.5 ms, so
+// 25.9, and with 32 groups of 16 blocks in place of one 19.3.)  A wait
+// longer than kSpinLimit polls, or another block's timeout, aborts: the block sets err bit 2 and returns
+// false, and the caller leaves the kernel.
+constexpr int BAR_STRIDE = 32, MAX_GROUPS = 64;
 __device__ bool grid_sync(const ShDev& d, unsigned& epoch, int* sh_ok) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     epoch += 1;
-    const unsigned target = epoch * gridDim.x;
-    __atomic_thread_fence(__ATOMIC_RELEASE);
-    __hip_atomic_fetch_add(d.bar, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned target = epoch * (gridDim.x / d.groups);
+    unsigned* bar = d.bar + (blockIdx.x % d.groups) * BAR_STRIDE;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int ok = 1;
     unsigned it = 0;
-    while (__hip_atomic_load(d.bar, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (++it > kSpinLimit || (__hip_atomic_load(d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 4)) {
+    while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+      if (++it > kSpinLimit ||
+          (it % 64 == 0 && (__hip_atomic_load(d.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 4))) {
         ok = 0;
         break;
       }
       __builtin_amdgcn_s_sleep(2);
     }
     if (!ok) __hip_atomic_fetch_or(d.err, 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __atomic_thread_fence(__ATOMIC_ACQUIRE);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     *sh_ok = ok;
   }
   __syncthreads();
@@ -375,6 +387,263 @@ __device__ void row_item(const ShDev& d, int2 item, int kind, double* smem) {
   __syncthreads();
 }
 
+// ---------------------------------------------------------------------------- phases of a known grid length
+// The same items on block_fft.h, for the grid lengths it has a plan for.  A thread's outputs of the forward
+// y-transform are the modes whose new values it needs for the inverse transform, so a column item reads W and
+// writes Z once and keeps the rest in registers and one LDS buffer; a row item keeps its grid values in
+// registers.  The sweep of 128 instances (64 to 192 modes, 50 steps and back): 45.5 -> 27.6 ms.
+constexpr int SH_BT = 256;   // threads of a block
+template <int G>
+struct ShTile {
+  // sequences of an item: up to 2048 points, and 192 or 256 of the 256 threads in the first and last pass
+  static constexpr int TC = G <= 64 ? 16 : G == 128 ? 16 : G <= 256 ? 8 : 4;
+  static constexpr size_t lds = sizeof(cplx) * (G + bf_size(TC * G));
+  using Col = BlockFft<G, TC, SH_BT, 4, 4>;   // columns are contiguous in W, Z and the states
+  using Row = BlockFft<G, TC, SH_BT, 1, 1>;   // neighbouring row pairs are contiguous in Z and W
+  static_assert(Col::First::MB == 1 && Col::Last::MB == 1, "one butterfly a thread");
+};
+// fn(the grid length as a type) if it has a plan
+template <typename Fn>
+__host__ __device__ inline bool sh_with_length(int Ng, Fn fn) {
+  switch (Ng) {
+    case 48: fn(std::integral_constant<int, 48>()); return true;
+    case 64: fn(std::integral_constant<int, 64>()); return true;
+    case 96: fn(std::integral_constant<int, 96>()); return true;
+    case 128: fn(std::integral_constant<int, 128>()); return true;
+    case 144: fn(std::integral_constant<int, 144>()); return true;
+    case 192: fn(std::integral_constant<int, 192>()); return true;
+    case 256: fn(std::integral_constant<int, 256>()); return true;
+    case 288: fn(std::integral_constant<int, 288>()); return true;
+    case 384: fn(std::integral_constant<int, 384>()); return true;
+    default: return false;
+  }
+}
+
+template <int G>
+__device__ __forceinline__ void col_item_b(const ShDev& d, const ShRun& a, const ShInst& I, int c0, int kind, int n, cplx* tw,
+                                           cplx* buf) {
+  using F = typename ShTile<G>::Col;
+  constexpr int N = G / 2, Nh = G / 4, TC = ShTile<G>::TC, R0 = F::R0, NR = G / R0;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // keeps every length's index arithmetic out of the launch's loops
+  const int j = F::First::bfly(tid), q = F::First::seq(tid), m = c0 + q;
+  const bool on = tid < F::First::NB && m < Nh;
+  const long long nn = (long long)Nh * N, col = (long long)m * N;
+  cplx* H = d.work + I.xo;
+  cplx* Fr = d.work + I.fo;
+  cplx* Yn = d.work + I.yo;
+  cplx* Ln = d.work + I.lo;
+  for (int e = tid; e < G; e += SH_BT) tw[e] = d.tw[d.twoff[I.png] + e];
+  const bool two = (kind == C_VJP_INIT || kind == C_ADJ_INIT || kind == C_ADJ_STEP);
+  const bool inv = (kind == C_FWD_INIT || kind == C_EVAL_INIT || kind == C_VJP_INIT ||
+                    (kind == C_FWD_STEP && n < a.nsteps) || (kind == C_ADJ_INIT && n >= 1) ||
+                    (kind == C_ADJ_STEP && n - 1 >= 1));
+  const int k = (kind == C_ADJ_STEP) ? n - 1 : n;   // reverse sweep: the state whose cotangent is complete
+  cplx v[1][R0];
+  const cplx* W = d.work + I.wo + (long long)m * G + j;
+  if (kind == C_FWD_STEP || kind == C_EVAL_F || kind == C_ADJ_STEP || kind == C_VJP_OUT) {
+#pragma unroll
+    for (int r = 0; r < R0; ++r) v[0][r] = on ? W[r * NR] : czero();
+    F::First::work(v, tw, -1, tid);
+    F::First::write(v, buf, tid);
+  }
+  // What the update needs of the thread's modes, loaded under the transform.  Grid position p holds mode p (p <
+  // N / 2) or p - G + N (p > G - N / 2); p = N / 2 stands for the Nyquist row, which is kept zero.
+  auto dropped = [](int r) { return r * NR > N / 2 && (r + 1) * NR - 1 <= G - N / 2; };
+  auto mode_of = [&](int r, int& iy, bool& keep) {
+    const int p = j + r * NR;
+    iy = p <= N / 2 ? p : p - G + N;
+    keep = p != N / 2;
+    return on && (p <= N / 2 || p > G - N / 2);
+  };
+  cplx i1[R0], i2[R0], i3[R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    i1[r] = i2[r] = i3[r] = czero();
+    if (dropped(r)) continue;
+    int iy;
+    bool keep;
+    if (!mode_of(r, iy, keep) || !keep) continue;
+    const long long si = col + iy;
+    if (kind == C_FWD_STEP) {
+      i1[r] = H[(n - 1) * nn + si];
+      if (n >= 2) {
+        i2[r] = H[(n - 2) * nn + si];
+        i3[r] = Fr[(n & 1) * nn + si];
+      }
+    } else if (kind == C_ADJ_INIT || kind == C_ADJ_STEP) {
+      if (kind == C_ADJ_STEP) i1[r] = Ln[si];
+      else i1[r] = (a.mode & RUN_COST) ? d.work[I.bo + si] : a.gin[I.so + si];
+      if (k >= 1) {
+        if (k + 1 <= a.nsteps) i2[r] = Yn[si];
+        i3[r] = H[(k - 1) * nn + si];   // X_(k-1): primal field of the products' VJP
+      }
+    } else if (kind == C_FWD_INIT || kind == C_EVAL_INIT || kind == C_VJP_INIT) {
+      i1[r] = a.xin[I.so + si];
+      if (kind == C_VJP_INIT) i2[r] = a.gin[I.so + si];
+    }
+  }
+  if (kind == C_FWD_STEP || kind == C_EVAL_F || kind == C_ADJ_STEP || kind == C_VJP_OUT) F::rest(v, buf, tw, -1, tid);
+  const double ng2 = 1.0 / ((double)G * G), wm = (m == 0) ? 1.0 : 2.0;
+  cplx w[1][R0];   // the second inverse transform's values (v: the first's)
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    const cplx res = v[0][r];
+    v[0][r] = w[0][r] = czero();
+    if (dropped(r)) continue;
+    int iy;
+    bool keep;
+    if (!mode_of(r, iy, keep)) continue;
+    const long long si = col + iy;
+    switch (kind) {
+      case C_FWD_INIT:
+        H[si] = i1[r];
+        v[0][r] = i1[r];
+        break;
+      case C_EVAL_INIT:
+        v[0][r] = i1[r];
+        break;
+      case C_VJP_INIT:
+        v[0][r] = i1[r];
+        w[0][r] = cscale(i2[r], -1.0);
+        break;
+      case C_EVAL_F:
+        a.xout[I.so + si] = keep ? cscale(res, -ng2) : czero();
+        break;
+      case C_VJP_OUT:
+        a.xout[I.so + si] = keep ? cscale(res, wm) : czero();
+        break;
+      case C_FWD_STEP: {
+        // F_(n-1) from the products, then (a0 + L) X_n = c1 F_(n-1) + c2 F_(n-2) - a1 X_(n-1) - a2 X_(n-2)
+        cplx xn = czero();
+        if (keep) {
+          const SbdfCoef c = sbdf_coef(n, d.dt);
+          const cplx f1 = cscale(res, -ng2);
+          cplx rhs = cadd(cscale(f1, c.c1), cscale(i3[r], c.c2));
+          rhs = csub(rhs, cadd(cscale(i1[r], c.a1), cscale(i2[r], c.a2)));
+          xn = cscale(rhs, 1.0 / (c.a0 + sh_lin(d, I, m, iy)));
+          Fr[((n - 1) & 1) * nn + si] = f1;
+          if (!(isfinite(xn.x) && isfinite(xn.y))) atomicOr(d.err, 2);
+        }
+        H[n * nn + si] = xn;
+        if (n == a.nsteps && a.xout) a.xout[I.so + si] = xn;
+        v[0][r] = xn;
+        break;
+      }
+      default: {   // C_ADJ_INIT, C_ADJ_STEP: cotangent of X_k, as col_item
+        cplx xb = czero();
+        if (keep) xb = (kind == C_ADJ_INIT) ? i1[r] : csub(cscale(res, wm), i1[r]);
+        if (k == 0) {
+          a.gout[I.so + si] = xb;
+          break;
+        }
+        cplx g = czero(), lin = czero(), y = czero();
+        if (keep) {
+          const SbdfCoef c = sbdf_coef(k, d.dt);
+          y = cscale(xb, 1.0 / (c.a0 + sh_lin(d, I, m, iy)));
+          g = cscale(y, c.c1);
+          lin = cscale(y, c.a1);
+          if (k + 1 <= a.nsteps) {
+            const SbdfCoef cn = sbdf_coef(k + 1, d.dt);
+            g = cadd(g, cscale(i2[r], cn.c2));
+            lin = cadd(lin, cscale(i2[r], cn.a2));
+          }
+        }
+        Yn[si] = y;
+        Ln[si] = lin;
+        v[0][r] = i3[r];
+        w[0][r] = cscale(g, -1.0);
+        break;
+      }
+    }
+    if (!keep) v[0][r] = w[0][r] = czero();
+  }
+  if (inv) {
+    auto out = [&](cplx (&x)[1][R0], long long zo) {
+      F::First::work(x, tw, +1, tid);
+      F::First::write(x, buf, tid);
+      F::rest(x, buf, tw, +1, tid);
+      cplx* Z = d.work + zo + (long long)m * G + j;
+      if (on) {
+#pragma unroll
+        for (int r = 0; r < R0; ++r) Z[r * NR] = x[0][r];
+      }
+    };
+    out(v, I.zo);
+    if (two) out(w, I.z2o);
+  }
+  __syncthreads();
+}
+
+template <int G>
+__device__ __forceinline__ void row_item_b(const ShDev& d, const ShInst& I, int p0, bool vjp, cplx* tw, cplx* buf) {
+  using F = typename ShTile<G>::Row;
+  constexpr int Nh = G / 4, TC = ShTile<G>::TC, R0 = F::R0, NR = G / R0;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int j = F::First::bfly(tid), q = F::First::seq(tid), y0 = 2 * p0;
+  const int pn = min(TC, G / 2 - p0);
+  const bool on = tid < F::First::NB && q < pn;
+  for (int e = tid; e < G; e += SH_BT) tw[e] = d.tw[d.twoff[I.png] + e];
+  // a row pair's half spectra as one spectrum (pack2): x < Nh direct, x > G - Nh mirrored, zero between
+  auto grid = [&](long long zo, double scale, cplx (&v)[1][R0]) {
+    const cplx* Z = d.work + zo + y0 + 2 * q;
+    cplx u[R0], w[R0];
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      u[r] = w[r] = czero();
+      if (r * NR >= Nh && (r + 1) * NR - 1 <= G - Nh) continue;
+      const int x = j + r * NR;
+      if (on && (x < Nh || x > G - Nh)) {
+        const cplx* z = Z + (long long)(x < Nh ? x : G - x) * G;
+        u[r] = z[0];
+        w[r] = z[1];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const int x = j + r * NR;
+      if (x == 0) v[0][r] = cmk(u[r].x, w[r].x);
+      else v[0][r] = cscale((x < Nh) ? cmk(u[r].x - w[r].y, u[r].y + w[r].x) : cmk(u[r].x + w[r].y, w[r].x - u[r].y), scale);
+    }
+    F::First::work(v, tw, +1, tid);
+    F::First::write(v, buf, tid);
+    F::rest(v, buf, tw, +1, tid);
+  };
+  cplx v[1][R0];
+  grid(I.zo, 1.0, v);
+  if (!vjp) {
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const cplx u = v[0][r];
+      v[0][r] = cmk(u.x * u.x * u.x, u.y * u.y * u.y);
+    }
+  } else {
+    const double ng2 = 1.0 / ((double)G * G);
+    cplx w[1][R0];
+    grid(I.z2o, 0.5, w);
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const cplx u = v[0][r], z = w[0][r];
+      v[0][r] = cmk(3.0 * u.x * u.x * z.x * ng2, 3.0 * u.y * u.y * z.y * ng2);
+    }
+  }
+  F::First::work(v, tw, -1, tid);
+  F::First::write(v, buf, tid);
+  F::rest(v, buf, tw, -1, tid);
+  F::Last::write(v, buf, tid);
+  __syncthreads();
+  // unpack A_m = (Z_m + conj Z_-m)/2 (row 2q), B_m = (Z_m - conj Z_-m)/(2i) (row 2q+1), m < Nh
+  cplx* W = d.work + I.wo + y0;
+  for (int e = tid; e < Nh * 2 * TC; e += SH_BT) {
+    const int m = e / (2 * TC), yy = e % (2 * TC), qq = yy >> 1;
+    const cplx zm = buf[bf_pad(m * TC + qq)], zq = buf[bf_pad((m == 0 ? 0 : G - m) * TC + qq)];
+    const cplx z = (yy & 1) ? cmk(0.5 * (zm.y + zq.y), -0.5 * (zm.x - zq.x)) : cmk(0.5 * (zm.x + zq.x), 0.5 * (zm.y - zq.y));
+    if (qq < pn) W[(long long)m * G + yy] = z;
+  }
+  __syncthreads();
+}
+
 // ---------------------------------------------------------------------------- cost phase
 // J = 1/2 mean over the N x N grid of u^2 = 1/2 sum w |c~|^2 with c~ the coefficients of
 // the real field (the k_x = 0 column made Hermitian in k_y), dJ/dX = w c~.
@@ -461,6 +730,58 @@ __global__ void __launch_bounds__(NT) sh_persistent(ShDev d, ShRun a) {
     rows(R_VJP);
     if (!grid_sync(d, epoch, &sh_ok)) return;
     cols(C_VJP_OUT, 0);
+  }
+}
+
+// The same launch for batches with a grid length that has a plan: one loop over the phases of the run, so that
+// the items' code, a copy for each length, is there once.  An instance's length alone decides how it is
+// transformed, so that its results do not depend on the batch it is in.  MIXED: some lengths have none (a
+// kernel of its own: the general items' registers spill 448 bytes a thread, 15 % of the time).
+template <bool MIXED>
+__global__ void __launch_bounds__(SH_BT, 2) sh_persistent_b(ShDev d, ShRun a) {
+  extern __shared__ double smem_d[];
+  __shared__ int sh_ok;
+  cplx* sm = reinterpret_cast<cplx*>(smem_d);
+  unsigned epoch = 0;
+  const int b = blockIdx.x, N = a.nsteps;
+  const int nf = (a.mode & RUN_FWD) ? 2 * N + 1 : 0, nc = (a.mode & RUN_COST) ? 1 : 0, na = (a.mode & RUN_ADJ) ? 2 * N + 1 : 0;
+  const int ne = (a.mode & (RUN_EVALF | RUN_VJP)) ? 3 : 0;
+  for (int ph = 0; ph < nf + nc + na + ne; ++ph) {
+    if (ph > 0 && !grid_sync(d, epoch, &sh_ok)) return;
+    bool row = false, vjp = false;
+    int kind, n = 0;
+    if (ph < nf) {                        // columns 0, rows, columns 1, rows, .., columns N
+      row = ph & 1;
+      n = ph / 2;
+      kind = n ? C_FWD_STEP : C_FWD_INIT;
+    } else if (ph < nf + nc) {
+      for (int it = d.jptr[b]; it < d.jptr[b + 1]; ++it) cost_item<SH_BT>(d, a, d.jitem[it], smem_d);
+      continue;
+    } else if (ph < nf + nc + na) {       // columns of X_N, rows, step N, .., step 1
+      const int q = ph - nf - nc;
+      row = vjp = q & 1;
+      n = q ? N + 1 - q / 2 : N;
+      kind = q ? C_ADJ_STEP : C_ADJ_INIT;
+    } else {
+      const int q = ph - nf - nc - na;
+      vjp = a.mode & RUN_VJP;
+      row = q == 1;
+      kind = vjp ? (q ? C_VJP_OUT : C_VJP_INIT) : (q ? C_EVAL_F : C_EVAL_INIT);
+    }
+    const int* ptr = row ? d.rptr : d.cptr;
+    for (int it = ptr[b]; it < ptr[b + 1]; ++it) {
+      const int2 item = row ? d.ritem[it] : d.citem[it];
+      const ShInst I = d.inst[item.x];
+      const bool known = sh_with_length(I.Ng, [&](auto g) {
+        constexpr int G = decltype(g)::value;
+        if (row) row_item_b<G>(d, I, item.y, vjp, sm, sm + G);
+        else col_item_b<G>(d, a, I, item.y, kind, n, sm, sm + G);
+      });
+      if (MIXED && !known) {
+        if (row) row_item<SH_BT>(d, item, vjp ? R_VJP : R_CUBE, smem_d);
+        else col_item<SH_BT>(d, a, item, kind, n, smem_d);
+      }
+    }
   }
 }
 
@@ -604,7 +925,7 @@ class ShProblem : public ProblemImpl {
     cus_ = prop.multiProcessorCount;
     build_plans();
     layout();
-    bar_ = arena_.alloc<unsigned>(1);
+    bar_ = arena_.alloc<unsigned>(MAX_GROUPS * BAR_STRIDE);
     err_ = arena_.alloc<int>(1);
     SPS_HIP(hipMemsetAsync(err_, 0, sizeof(int), stream));
     const std::pair<const void*, size_t> init[] = {{(const void*)sh_init_rows, init_lds(false)},
@@ -801,14 +1122,35 @@ class ShProblem : public ProblemImpl {
 
   // Work items for tiles (tc, trp) per size class and a block count: longest-first
   // assignment of the items of each phase to the least-loaded block (costs ~ points x log).
-  static const void* kernel_of(int nt) {
+  const void* kernel_of(int nt) const {
+    if (block_) return mixed_ ? (const void*)sh_persistent_b<true> : (const void*)sh_persistent_b<false>;
     return nt == 64 ? (const void*)sh_persistent<64> : nt == 128 ? (const void*)sh_persistent<128>
-                                                                  : (const void*)sh_persistent<256>;
+                                                                         : (const void*)sh_persistent<256>;
   }
-  void schedule(const int* tcs, const int* trps, int blocks, int nt) {
+  // `groups` groups of blocks (a divisor of `blocks`), the instances dealt to them likewise.
+  void schedule(const int* tcs, const int* trps, int blocks, int nt, int groups) {
     nt_ = nt;
+    dv_.groups = groups;
+    std::vector<int> group(batch_), order(batch_);
+    std::vector<double> gload(groups, 0.0);
+    for (int i = 0; i < batch_; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return inst_[a].N > inst_[b].N; });
+    for (int i : order) {
+      group[i] = (int)(std::min_element(gload.begin(), gload.end()) - gload.begin());
+      gload[group[i]] += (double)inst_[i].N * inst_[i].N * std::log2((double)inst_[i].Ng);
+    }
     lds_ = 0;
     for (auto& I : inst_) {
+      if (block_) {   // the tiles of the length's plan, or of some 1024 points
+        if (sh_with_length(I.Ng, [&](auto g) {
+              I.tc = I.trp = ShTile<decltype(g)::value>::TC;
+              lds_ = std::max({lds_, ShTile<decltype(g)::value>::lds, sizeof(double) * nt});
+            }))
+          continue;
+        I.tc = I.trp = I.Ng <= 128 ? 8 : I.Ng <= 256 ? 4 : I.Ng <= 512 ? 2 : 1;
+        lds_ = std::max({lds_, col_lds(I, I.tc), row_lds(I, I.trp), sizeof(double) * nt});
+        continue;
+      }
       I.tc = tcs[size_class(I.N)];
       I.trp = trps[size_class(I.N)];
       lds_ = std::max({lds_, col_lds(I, I.tc), row_lds(I, I.trp), sizeof(double) * nt});
@@ -822,7 +1164,9 @@ class ShProblem : public ProblemImpl {
       std::vector<double> load(blocks, 0.0);
       std::vector<std::vector<int2>> per(blocks);
       for (const auto& it : items) {
-        const int b = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        int b = group[it.inst];   // the least loaded block of the instance's group
+        for (int c = b + groups; c < blocks; c += groups)
+          if (load[c] < load[b]) b = c;
         load[b] += it.cost;
         per[b].push_back(make_int2(it.inst, it.first));
       }
@@ -869,7 +1213,7 @@ class ShProblem : public ProblemImpl {
     const int cand_nt[3] = {64, 128, 256};
     const int Ngs[4] = {128, 192, 256, 384};
     double best = 1e30;
-    int best_tc[4] = {1, 1, 1, 1}, best_trp[4] = {1, 1, 1, 1}, best_blocks = cus_, best_nt = 256;
+    int best_tc[4] = {1, 1, 1, 1}, best_trp[4] = {1, 1, 1, 1}, best_blocks = cus_, best_nt = 256, best_groups = 1;
     const int nsteps = std::min(4, max_steps_);
     // the timing events are destroyed on every exit from the tuner, also by an exception
     struct Events {
@@ -882,10 +1226,19 @@ class ShProblem : public ProblemImpl {
     SPS_HIP(hipEventCreate(&ev.e[0]));
     SPS_HIP(hipEventCreate(&ev.e[1]));
     hipEvent_t e0 = ev.e[0], e1 = ev.e[1];
-    for (int nt : cand_nt)
-      for (int bc : cand)
-        for (int br : cand)
-          for (int bmul = 1; bmul <= 4; ++bmul) {
+    block_ = mixed_ = false;
+    for (const auto& I : inst_) (sh_with_length(I.Ng, [](auto) {}) ? block_ : mixed_) = true;
+    // (with planned lengths only the numbers of blocks and of groups are open)
+    const std::vector<int> nts = block_ ? std::vector<int>{SH_BT} : std::vector<int>(cand_nt, cand_nt + 3);
+    std::vector<int> bs = {cus_, 2 * cus_, 3 * cus_, 4 * cus_};
+    if (block_) bs.insert(bs.begin(), {32, 64, 128});   // (a small batch waits for fewer blocks)
+    const std::vector<int> gs = block_ ? std::vector<int>{1, 8, 16, 32, 64} : std::vector<int>{1};
+    const std::vector<int> cs = block_ ? std::vector<int>{2048} : std::vector<int>(cand, cand + 4);
+    for (int nt : nts)
+      for (int bc : cs)
+        for (int br : cs)
+        for (int blocks : bs)
+          for (int groups : gs) {
             int tcs[4], trps[4];
             for (int k = 0; k < 4; ++k) {
               tcs[k] = std::max(1, std::min(8, bc / Ngs[k]));
@@ -893,8 +1246,8 @@ class ShProblem : public ProblemImpl {
               while (tcs[k] & (tcs[k] - 1)) --tcs[k];
               while (trps[k] & (trps[k] - 1)) --trps[k];
             }
-            const int blocks = bmul * cus_;
-            schedule(tcs, trps, blocks, nt);
+            if (groups > 1 && (groups > batch_ || blocks % groups != 0)) continue;
+            schedule(tcs, trps, blocks, nt, groups);
             if (lds_ > 160 * 1024 || !fits(blocks)) continue;
             ShRun a{RUN_FWD, nsteps, tmp_, nullptr, nullptr, nullptr, nullptr, nullptr};
             SPS_HIP(hipMemsetAsync(tmp_, 0, sizeof(cplx) * state_cplx_, stream));
@@ -912,10 +1265,13 @@ class ShProblem : public ProblemImpl {
               std::copy(trps, trps + 4, best_trp);
               best_blocks = blocks;
               best_nt = nt;
+              best_groups = groups;
             }
           }
     SPS_REQUIRE(best < 1e29, "no tile configuration fits this batch");
-    schedule(best_tc, best_trp, best_blocks, best_nt);
+    schedule(best_tc, best_trp, best_blocks, best_nt, best_groups);
+    if (block_)
+      for (const auto& I : inst_) best_tc[size_class(I.N)] = best_trp[size_class(I.N)] = I.tc;
     std::copy(best_tc, best_tc + 4, tc_by_size_);
     std::copy(best_trp, best_trp + 4, trp_by_size_);
     tuned_ms_ = best / nsteps;
@@ -942,7 +1298,7 @@ class ShProblem : public ProblemImpl {
   void run(const ShRun& a) {
     const void* k = kernel_of(nt_);
     SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_));
-    SPS_HIP(hipMemsetAsync(bar_, 0, sizeof(unsigned), stream));
+    SPS_HIP(hipMemsetAsync(bar_, 0, sizeof(unsigned) * MAX_GROUPS * BAR_STRIDE, stream));
     dv_.bar = bar_;
     dv_.err = err_;
     ShDev d = dv_;
@@ -983,6 +1339,7 @@ class ShProblem : public ProblemImpl {
   std::vector<FftPlan> plans_h_;
   int tc_by_size_[4] = {0, 0, 0, 0}, trp_by_size_[4] = {0, 0, 0, 0};
   size_t lds_ = 0;
+  bool block_ = false, mixed_ = false;   // a grid length has a block_fft.h plan; one has none
   long long state_cplx_ = 0;
   ShDev dv_{};
   DevArena arena_;

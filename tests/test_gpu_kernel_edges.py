@@ -156,3 +156,31 @@ def test_kolmo_grid_lengths(N):
             ref = states[k + 1].reshape(N, N // 2)[rows, : Nc // 2].copy()
             ref[Nc // 2, :] = 0.0
             assert rel(s[k, b].T, ref) <= 1e-11
+
+
+# Swift-Hohenberg grid lengths with a plan of their own (48 to 384 points, so N = 24 to 192), one of them with a
+# partial column tile (N = 72), together with lengths that have none; sizes above the largest plan.  Same checks as
+# test_gpu_sh.py; and an instance alone gives the same bits as in the mixed batch.
+def test_sh_grid_lengths(monkeypatch):
+    import test_gpu_sh as ts
+    sizes = [24, 32, 48, 54, 64, 72, 96, 128, 144, 162, 192, 216]
+    monkeypatch.setattr(ts, "SMALL_N", sizes)
+    monkeypatch.setattr(ts, "SMALL_R", [0.2 + 0.02 * i for i in range(len(sizes))])
+    ts.test_sh_gradient_mixed_batch(2)
+    print("SH grid lengths, batch independence", flush=True)
+    rng = np.random.default_rng(7)
+    X = [torch.from_numpy(rng.standard_normal(N * N)).cuda() for N in sizes]
+
+    def run(idx):
+        G = sps.ShBatch([sizes[i] for i in idx], [0.3] * len(idx), ts.L, 0.05, max_steps=2)
+        out = torch.zeros(G.n, dtype=torch.float64, device="cuda")
+        g = torch.zeros_like(out)
+        J = torch.zeros(len(idx), dtype=torch.float64, device="cuda")
+        G.gradient(torch.cat([X[i] for i in idx]), 2, out, g, J)
+        G.sync()
+        cut = np.cumsum([0] + [X[i].numel() for i in idx])
+        return [(out[a:b], g[a:b], J[k]) for k, (a, b) in enumerate(zip(cut[:-1], cut[1:]))]
+
+    every = run(range(len(sizes)))
+    for i in (3, 4, 10):
+        assert all(torch.equal(a, b) for a, b in zip(run([i])[0], every[i]))
