@@ -81,33 +81,35 @@ struct BlockPass {
     v[r] = buf[bf_at<r * NR * TC>(base, pb)];
     if constexpr (r + 1 < R) read1<r + 1>(v, buf, base, pb);
   }
+  static __device__ __forceinline__ void read_one(cplx* v, const cplx* buf, int it) {
+    const int base = bfly(it) * TC + seq(it);
+    read1(v, buf, base, bf_pad(base));
+  }
   static __device__ __forceinline__ void read(cplx (&v)[MB][R], const cplx* buf, int tid) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int it = tid + i * NT;
-      if (full || it < NB) {
-        const int base = bfly(it) * TC + seq(it);
-        read1(v[i], buf, base, bf_pad(base));
-      }
+      if (full || it < NB) read_one(v[i], buf, it);
     }
   }
-  // twiddles (tw[t] = exp(-2 pi i t / N)) and the butterflies
+  // twiddles (tw[t] = exp(-2 pi i t / N)) and the butterfly
+  static __device__ __forceinline__ void work_one(cplx* v, const cplx* tw, int sign, int it) {
+    if constexpr (NS > 1) {
+      const int t = (bfly(it) % NS) * (N / (NS * R));
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        cplx w = tw[r * t];
+        if (sign > 0) w = cconj(w);
+        v[r] = cmul(v[r], w);
+      }
+    }
+    bf_dft<R>(v, sign);
+  }
   static __device__ __forceinline__ void work(cplx (&v)[MB][R], const cplx* tw, int sign, int tid) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int it = tid + i * NT;
-      if (full || it < NB) {
-        if constexpr (NS > 1) {
-          const int t = (bfly(it) % NS) * (N / (NS * R));
-#pragma unroll
-          for (int r = 1; r < R; ++r) {
-            cplx w = tw[r * t];
-            if (sign > 0) w = cconj(w);
-            v[i][r] = cmul(v[i][r], w);
-          }
-        }
-        bf_dft<R>(v[i], sign);
-      }
+      if (full || it < NB) work_one(v[i], tw, sign, it);
     }
   }
   static __device__ __forceinline__ int out_base(int it) {   // entry of output 0
@@ -121,14 +123,15 @@ struct BlockPass {
     else buf[bf_at<r * NS * TC>(base, pb)] = v[r];
     if constexpr (r + 1 < R) write1<r + 1>(v, buf, base, pb);
   }
+  static __device__ __forceinline__ void write_one(const cplx* v, cplx* buf, int it) {
+    const int base = out_base(it);
+    write1(v, buf, base, bf_pad(base));
+  }
   static __device__ __forceinline__ void write(const cplx (&v)[MB][R], cplx* buf, int tid) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int it = tid + i * NT;
-      if (full || it < NB) {
-        const int base = out_base(it);
-        write1(v[i], buf, base, bf_pad(base));
-      }
+      if (full || it < NB) write_one(v[i], buf, it);
     }
   }
 };
@@ -155,6 +158,72 @@ struct BlockFft {
     Last::read(v, buf, tid);
     __syncthreads();
     Last::work(v, tw, sign, tid);
+  }
+};
+
+// Three fields of TC sequences each, a thread holding the same butterfly of all three in the first and last
+// pass (so that products of the fields stay in its registers); first radices of 2 to 6 keep those few.
+template <int N> struct Block3Plan { static constexpr bool ok = false; };
+#define SPS_BLOCK3_PLAN(N_, A, B) \
+  template <> struct Block3Plan<N_> { static constexpr bool ok = true; static constexpr int R0 = A, R1 = B; \
+                                      static_assert(A * B * A == N_, "radices"); };
+SPS_BLOCK3_PLAN(24, 2, 6)
+SPS_BLOCK3_PLAN(36, 3, 4)
+SPS_BLOCK3_PLAN(48, 4, 3)
+SPS_BLOCK3_PLAN(72, 3, 8)
+SPS_BLOCK3_PLAN(96, 4, 6)
+SPS_BLOCK3_PLAN(108, 3, 12)
+SPS_BLOCK3_PLAN(144, 6, 4)
+SPS_BLOCK3_PLAN(192, 4, 12)
+#undef SPS_BLOCK3_PLAN
+
+template <int N, int TC, int JF0, int JF2>
+struct Block3 {
+  static constexpr int R0 = Block3Plan<N>::R0, R1 = Block3Plan<N>::R1, NT = N / R0 * TC, NR = N / R0;
+  static constexpr int BS = bf_size(TC * N);   // entries of a field's buffer
+  using First = BlockPass<N, R0, 1, TC, NT, JF0>;
+  using Mid = BlockPass<N, R1, R0, TC, NT, 1>;
+  using Last = BlockPass<N, R0, R0 * R1, TC, NT, JF2>;
+  // v: the inputs at positions First::bfly(tid) + r N / R0 of sequence First::seq(tid), then the outputs at
+  // Last's; every thread must be past its reads of buf, and is again on return.
+  static __device__ __forceinline__ void transform(cplx (&v)[3][R0], cplx* buf, const cplx* tw, int sign, int tid) {
+    asm volatile("" : "+v"(tid));   // index arithmetic is redone for every transform, not kept in registers between them
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+      First::work_one(v[f], tw, sign, tid);
+      First::write_one(v[f], buf + f * BS, tid);
+    }
+    constexpr int NM = 3 * Mid::NB, MM = (NM + NT - 1) / NT;
+    {
+      cplx m[MM][R1];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < MM; ++i) {
+        const int it = tid + i * NT;
+        if (NM % NT == 0 || it < NM) Mid::read_one(m[i], buf + it / Mid::NB * BS, it % Mid::NB);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < MM; ++i) {
+        const int it = tid + i * NT;
+        if (NM % NT == 0 || it < NM) {
+          Mid::work_one(m[i], tw, sign, it % Mid::NB);
+          Mid::write_one(m[i], buf + it / Mid::NB * BS, it % Mid::NB);
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < 3; ++f) Last::read_one(v[f], buf + f * BS, tid);
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < 3; ++f) Last::work_one(v[f], tw, sign, tid);
+  }
+  // the last outputs to buf in natural order, ends synchronized
+  static __device__ __forceinline__ void store(const cplx (&v)[3][R0], cplx* buf, int tid) {
+#pragma unroll
+    for (int f = 0; f < 3; ++f) Last::write_one(v[f], buf + f * BS, tid);
+    __syncthreads();
   }
 };
 

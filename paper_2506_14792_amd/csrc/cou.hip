@@ -26,8 +26,10 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
+#include "block_fft.h"
 #include "cou.h"
 #include "sps_device.h"
 #include "sps_internal.h"
@@ -170,8 +172,7 @@ __device__ __forceinline__ cplx cou_unpack(const cplx* r, int base, int m, int G
 // ---------------------------------------------------------------------------- A: z inverse
 // Grid (x-mode tiles, 3 components, Ngy).  Component g (u, v, w) writes fields g, 3 + g, 6 + g
 // of Z: the component, its y-derivative, i kz times it.  (The x-derivative is a factor per x mode that
-// the row kernels apply: a quarter fewer transforms here and fields through memory, 58 -> 47 us per
-// launch at 128x64x64.)
+// the row kernels apply: a quarter fewer transforms here and fields through memory.)
 template <int NT>
 __global__ void __launch_bounds__(NT) cou_zinv(CouDev d, const cplx* zg, int tc, cplx* Z) {
   extern __shared__ double smem_d[];
@@ -469,6 +470,378 @@ __global__ void __launch_bounds__(NT) cou_zinv_adj(CouDev d, const cplx* Gb, int
   }
 }
 
+// ---------------------------------------------------------------------------- kernels of a known grid length
+// The six kernels on Block3, for the padded lengths it has a plan for (3/2 padding): three fields at a time, the
+// first pass read from memory and the last one used in registers.  A row kernel goes through its 12 or 27
+// transforms in threes, holding only what the products still need: u, v, w in LDS (each of a point's nine
+// products has one of them as a factor) and in registers the three densities, or their cotangents and three
+// sums.  At 128x64x64, us a launch: cou_zinv 46 -> 32 (147 MB moved), cou_xrow 86 -> 60 (113 MB), cou_zfwd 21 -> 13, cou_zfwd_adj
+// 18 -> 12, cou_xrow_adj 141 -> 112 (198 MB; 125 with u, v, w in registers, which spill), cou_zinv_adj 62 -> 30.  The row kernels are
+// held back by their registers, two waves per SIMD.
+template <int G>
+struct CouRows {
+  static constexpr int PAIRS = G >= 144 ? 4 : G >= 72 ? 8 : 16;   // row pairs of a block
+  using B = Block3<G, PAIRS, 4, 4>;
+  static constexpr bool ok = B::R0 <= 4;   // (six values a field do not fit the registers)
+  static constexpr int HELD = 3 * B::R0 * B::NT;   // u, v, w of the block's threads, held in LDS
+  static constexpr size_t lds = sizeof(cplx) * (G + 3 * B::BS + HELD);
+};
+template <int G>
+struct CouCols {
+  static constexpr int TC = G >= 144 ? 4 : 8;   // x modes of a block: 64 or 128 bytes of a row
+  using Inv = Block3<G, TC, 4, 1>;   // modes (z contiguous) to the plane fields (x contiguous)
+  using Fwd = Block3<G, TC, 1, 4>;
+  static constexpr size_t lds = sizeof(cplx) * (G + 3 * Inv::BS);
+};
+template <typename Fn>
+bool cou_with_length(int G, Fn fn) {
+  switch (G) {
+    case 24: fn(std::integral_constant<int, 24>()); return true;
+    case 36: fn(std::integral_constant<int, 36>()); return true;
+    case 48: fn(std::integral_constant<int, 48>()); return true;
+    case 72: fn(std::integral_constant<int, 72>()); return true;
+    case 96: fn(std::integral_constant<int, 96>()); return true;
+    case 108: fn(std::integral_constant<int, 108>()); return true;
+    case 144: fn(std::integral_constant<int, 144>()); return true;
+    case 192: fn(std::integral_constant<int, 192>()); return true;
+    default: return false;
+  }
+}
+
+// Packed spectra (cou_pack) of the row pair at U (second row Kx further) for three consecutive fields, fstr
+// apart, at this thread's points x = j + r G / R0; on: the pair exists.
+template <int G, int R0>
+__device__ __forceinline__ void cou_load3(const cplx* U, long long fstr, int j, bool on, double scale, cplx (&p)[3][R0]) {
+  constexpr int Kx = G / 3, NR = G / R0;
+  asm volatile("" : "+v"(j));   // not loaded before it is wanted
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    asm volatile("" ::: "memory");   // a field at a time: all three at once spill
+    cplx u[R0], w[R0];
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      u[r] = w[r] = czero();
+      if (r * NR >= Kx && (r + 1) * NR - 1 <= G - Kx) continue;
+      const int x = j + r * NR;
+      if (on && (x < Kx || x > G - Kx)) {
+        const cplx* q = U + f * fstr + (x < Kx ? x : G - x);
+        u[r] = q[0];
+        w[r] = q[Kx];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const int x = j + r * NR;
+      if (x == 0) p[f][r] = cmk(u[r].x, w[r].x);
+      else p[f][r] = cscale((x < Kx) ? cmk(u[r].x - w[r].y, u[r].y + w[r].x) : cmk(u[r].x + w[r].y, w[r].x - u[r].y), scale);
+    }
+  }
+}
+// signed x wavenumber of point x of a packed spectrum, 0 outside the modes
+template <int G>
+__device__ __forceinline__ int cou_signed(int x) {
+  return x < G / 3 ? x : (x > G - G / 3 ? x - G : 0);
+}
+__device__ __forceinline__ cplx cmul2(cplx a, cplx b) { return cmk(a.x * b.x, a.y * b.y); }   // the two packed rows' products
+__device__ __forceinline__ cplx csub2(cplx a, cplx b, cplx c) { return cmk(a.x - b.x * c.x, a.y - b.y * c.y); }
+
+// Half spectra of the packed natural-order spectra of three fields in buf to out (field f at f fstr), times
+// (m == 0 ? 1 : wm).
+template <int G, int PAIRS, int NT>
+__device__ __forceinline__ void cou_unpack3(const cplx* buf, int bs, int z0, int Gz, long long fstr, double wm, cplx* out, int tid) {
+  constexpr int Kx = G / 3;
+  for (int e = tid; e < 3 * PAIRS * 2 * Kx; e += NT) {
+    const int m = e % Kx, rr = e / Kx, yy = rr & 1, pr = (rr >> 1) % PAIRS, f = (rr >> 1) / PAIRS;
+    const cplx* h = buf + f * bs;
+    const cplx zm = h[bf_pad(m * PAIRS + pr)], zq = h[bf_pad((m == 0 ? 0 : G - m) * PAIRS + pr)];
+    const cplx v = yy ? cmk(0.5 * (zm.y + zq.y), -0.5 * (zm.x - zq.x)) : cmk(0.5 * (zm.x + zq.x), 0.5 * (zm.y - zq.y));
+    if (z0 + 2 * pr < Gz) out[f * fstr + (long long)(z0 + 2 * pr + yy) * Kx + m] = (m == 0) ? v : cscale(v, wm);
+  }
+}
+
+// cou_xrow.  Grid (row pairs / PAIRS, Ngy).
+template <int G>
+__global__ void __launch_bounds__(CouRows<G>::B::NT, 2) cou_xrow_b(CouDev d, const cplx* __restrict__ Z, cplx* __restrict__ W) {
+  using B = typename CouRows<G>::B;
+  constexpr int PAIRS = CouRows<G>::PAIRS, R0 = B::R0, NR = B::NR, Kx = G / 3;
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  cplx* held = buf + 3 * B::BS + threadIdx.x;   // [f R0 + r][thread]
+  const int tid = threadIdx.x, y = blockIdx.y, z0 = 2 * PAIRS * blockIdx.x, Gz = d.Ngz;
+  const int j = B::First::bfly(tid), zr = z0 + 2 * B::First::seq(tid);
+  const bool on = zr < Gz;
+  const long long fstr = (long long)d.Ngy * Gz * Kx;
+  const cplx* U = Z + ((long long)y * Gz + zr) * Kx;
+  cplx p[3][R0], c[3][R0], n[3][R0];
+  cou_load3<G>(U, fstr, j, on, 1.0, p);
+  for (int e = tid; e < G; e += B::NT) tw[e] = d.twx[e];
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      c[f][r] = p[f][r];
+      p[f][r] = cscale(cmul_i(p[f][r]), 2.0 * M_PI * cou_signed<G>(j + r * NR) / d.lx);
+    }
+  B::transform(c, buf, tw, +1, tid);   // u, v, w
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) held[(f * R0 + r) * B::NT] = c[f][r];
+  B::transform(p, buf, tw, +1, tid);   // their x-derivatives
+  const double Uy = d.unode[y], dU = d.du;
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    const cplx u = held[r * B::NT], a = cmk(-(u.x + Uy), -(u.y + Uy));
+#pragma unroll
+    for (int f = 0; f < 3; ++f) n[f][r] = cmul2(a, p[f][r]);
+    n[0][r] = csub(n[0][r], cscale(held[(R0 + r) * B::NT], dU));
+  }
+#pragma unroll
+  for (int q = 1; q < 3; ++q) {        // the y- and z-derivatives, with v and w
+    cou_load3<G>(U + 3 * q * fstr, fstr, j, on, 1.0, p);
+    B::transform(p, buf, tw, +1, tid);
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) n[f][r] = csub2(n[f][r], held[(q * R0 + r) * B::NT], p[f][r]);
+  }
+  B::transform(n, buf, tw, -1, tid);
+  B::store(n, buf, tid);
+  cou_unpack3<G, PAIRS, B::NT>(buf, B::BS, z0, Gz, fstr, 1.0, W + (long long)y * Gz * Kx, tid);
+}
+
+// cou_xrow_adj.  Grid (row pairs / PAIRS, Ngy).
+template <int G>
+__global__ void __launch_bounds__(CouRows<G>::B::NT, 2)
+cou_xrow_adj_b(CouDev d, const cplx* __restrict__ Zp, const cplx* __restrict__ Wb, cplx* __restrict__ Gb) {
+  using B = typename CouRows<G>::B;
+  constexpr int PAIRS = CouRows<G>::PAIRS, R0 = B::R0, NR = B::NR, Kx = G / 3;
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  cplx* held = buf + 3 * B::BS + threadIdx.x;   // [f R0 + r][thread]
+  const int tid = threadIdx.x, y = blockIdx.y, z0 = 2 * PAIRS * blockIdx.x, Gz = d.Ngz;
+  const int j = B::First::bfly(tid), zr = z0 + 2 * B::First::seq(tid);
+  const bool on = zr < Gz;
+  const long long fstr = (long long)d.Ngy * Gz * Kx, row = ((long long)y * Gz + zr) * Kx;
+  cplx* out = Gb + (long long)y * Gz * Kx;
+  const double kf = 2.0 * M_PI / d.lx, Uy = d.unode[y], dU = d.du;
+  cplx nb[3][R0], c[3][R0], p[3][R0], s[3][R0];
+  for (int e = tid; e < G; e += B::NT) tw[e] = d.twx[e];
+  cou_load3<G>(Wb + row, fstr, j, on, 0.5, nb);
+  B::transform(nb, buf, tw, +1, tid);  // cotangents of the densities
+  cou_load3<G>(Zp + row, fstr, j, on, 1.0, c);
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) p[f][r] = cscale(cmul_i(c[f][r]), kf * cou_signed<G>(j + r * NR));
+  B::transform(c, buf, tw, +1, tid);   // u, v, w
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) held[(f * R0 + r) * B::NT] = c[f][r];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {        // the x-, y- and z-derivatives: the cotangents of u, v, w
+    if (q > 0) cou_load3<G>(Zp + row + 3 * q * fstr, fstr, j, on, 1.0, p);
+    B::transform(p, buf, tw, +1, tid);
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      cplx t = (q == 1) ? cscale(nb[0][r], -dU) : czero();
+#pragma unroll
+      for (int f = 0; f < 3; ++f) t = csub2(t, nb[f][r], p[f][r]);
+      s[q][r] = t;
+    }
+  }
+  // the x-derivatives' cotangents, transposed (conj(i kx)) in their spectra, onto the components'
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const cplx u = held[r * B::NT];
+      p[f][r] = cmul2(nb[f][r], cmk(-(u.x + Uy), -(u.y + Uy)));
+    }
+  B::transform(p, buf, tw, -1, tid);
+  B::transform(s, buf, tw, -1, tid);
+#pragma unroll
+  for (int f = 0; f < 3; ++f)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) s[f][r] = cadd(s[f][r], cscale(cmul_mi(p[f][r]), kf * cou_signed<G>(j + r * NR)));
+  B::store(s, buf, tid);
+  cou_unpack3<G, PAIRS, B::NT>(buf, B::BS, z0, Gz, fstr, 2.0, out, tid);
+#pragma unroll
+  for (int q = 1; q < 3; ++q) {        // the y- and z-derivatives' cotangents
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) p[f][r] = csub2(czero(), nb[f][r], held[(q * R0 + r) * B::NT]);
+    __syncthreads();                   // (the unpacking reads buf)
+    B::transform(p, buf, tw, -1, tid);
+    B::store(p, buf, tid);
+    cou_unpack3<G, PAIRS, B::NT>(buf, B::BS, z0, Gz, fstr, 2.0, out + 3 * q * fstr, tid);
+  }
+}
+
+// z mode of padded position p (p < Nz / 2, or p > G - Nz / 2), Nz = 2 G / 3
+template <int G>
+__device__ __forceinline__ bool cou_zmode(int p, int& n) {
+  constexpr int Nz = 2 * G / 3;
+  n = p < Nz / 2 ? p : p - G + Nz;
+  return p < Nz / 2 || p > G - Nz / 2;
+}
+// compile-time: no position j + r NR, j < NR, holds a mode (STRICT: nor stands for the Nyquist mode Nz / 2)
+template <int G, int NR>
+__device__ constexpr bool cou_nomode(int r, bool strict) {
+  constexpr int Nz = 2 * G / 3;
+  return (strict ? r * NR > Nz / 2 : r * NR >= Nz / 2) && (r + 1) * NR - 1 <= G - Nz / 2;
+}
+
+// cou_zinv (ADJ: cou_zfwd_adj).  Grid (x-mode tiles, 3 components (ADJ: 1), Ngy).
+template <int G, bool ADJ>
+__global__ void __launch_bounds__(CouCols<G>::Inv::NT) cou_zinv_b(CouDev d, const cplx* in, cplx* out) {
+  using B = typename CouCols<G>::Inv;
+  constexpr int R0 = B::R0, NR = B::NR, TC = CouCols<G>::TC, Nz = 2 * G / 3;
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  const int tid = threadIdx.x, g = blockIdx.y, y = blockIdx.z, m0 = TC * blockIdx.x, Kx = d.Kx;
+  const int j = B::First::bfly(tid), m = m0 + B::First::seq(tid);
+  const long long fin = (long long)d.Ngy * d.K;
+  const cplx* X = in + (long long)y * d.K + (long long)m * Nz;
+  const double s = 1.0 / ((double)d.Ngx * G);
+  cplx v[3][R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    v[0][r] = v[1][r] = v[2][r] = czero();
+    int n;
+    if (cou_nomode<G, NR>(r, false) || !cou_zmode<G>(j + r * NR, n) || m >= Kx) continue;
+    if (ADJ) {
+      v[0][r] = X[n];
+      v[1][r] = X[fin + n];
+      v[2][r] = X[2 * fin + n];
+    } else if (g == 1) {
+      v[0][r] = X[fin + n];
+      v[1][r] = X[4 * fin + n];
+    } else {   // u_par, u_perp and their y-derivatives, rotated below (v[2]: the second, spare until then)
+      v[0][r] = X[n];
+      v[2][r] = X[2 * fin + n];
+      v[1][r] = X[3 * fin + n];
+    }
+  }
+  cplx dc[R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    dc[r] = czero();
+    int n;
+    if (ADJ || g == 1 || cou_nomode<G, NR>(r, false) || !cou_zmode<G>(j + r * NR, n) || m >= Kx) continue;
+    dc[r] = X[5 * fin + n];
+  }
+  for (int e = tid; e < G; e += B::NT) tw[e] = d.twz[e];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    int n;
+    if (cou_nomode<G, NR>(r, false) || !cou_zmode<G>(j + r * NR, n) || m >= Kx) continue;
+    const Wave w = cou_wave(d, m, n);
+    const cplx a = v[0][r], b = v[1][r], c = v[2][r];
+    if (ADJ) {
+      v[0][r] = cscale(lin2(w.ex, a, -w.ez, c), s);
+      v[1][r] = cscale(b, s);
+      v[2][r] = cscale(lin2(w.ez, a, w.ex, c), s);
+    } else {
+      if (g == 0) {          // u = ex u_par - ez u_perp
+        v[0][r] = lin2(w.ex, a, -w.ez, c);
+        v[1][r] = lin2(w.ex, b, -w.ez, dc[r]);
+      } else if (g == 2) {   // w = ez u_par + ex u_perp
+        v[0][r] = lin2(w.ez, a, w.ex, c);
+        v[1][r] = lin2(w.ez, b, w.ex, dc[r]);
+      }
+      v[2][r] = cscale(cmul_i(v[0][r]), w.kz);
+    }
+  }
+  B::transform(v, buf, tw, +1, tid);
+  const int zo = B::Last::bfly(tid), mo = m0 + B::Last::seq(tid);
+  if (mo < Kx) {
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+      for (int r = 0; r < R0; ++r)
+        out[(((long long)(ADJ ? f : 3 * f + g) * d.Ngy + y) * G + zo + r * NR) * Kx + mo] = v[f][r];
+  }
+}
+
+// cou_zfwd (ADJ: cou_zinv_adj; group 0 the u and w fields, one after the other, group 1 the v fields).  Grid (x-mode
+// tiles, groups (1; ADJ: 2), Ngy).
+template <int G, bool ADJ>
+__global__ void __launch_bounds__(CouCols<G>::Fwd::NT) cou_zfwd_b(CouDev d, const cplx* in, cplx* out) {
+  using B = typename CouCols<G>::Fwd;
+  constexpr int R0 = B::R0, NR = B::NR, TC = CouCols<G>::TC, Nz = 2 * G / 3;
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  const int tid = threadIdx.x, grp = blockIdx.y, y = blockIdx.z, m0 = TC * blockIdx.x, Kx = d.Kx;
+  const int zi = B::First::bfly(tid), mi = m0 + B::First::seq(tid);
+  auto load = [&](int f0, int fs, cplx (&v)[3][R0]) {   // fields f0, f0 + fs, f0 + 2 fs
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+      for (int r = 0; r < R0; ++r)
+        v[f][r] = mi < Kx ? in[(((long long)(f0 + f * fs) * d.Ngy + y) * G + zi + r * NR) * Kx + mi] : czero();
+  };
+  for (int e = tid; e < G; e += B::NT) tw[e] = d.twz[e];
+  cplx v[3][R0], u[3][R0];   // u: the u fields' spectra (ADJ, group 0)
+  if (!ADJ) {
+    load(0, 1, v);
+    B::transform(v, buf, tw, -1, tid);
+  } else {
+    load(grp, 3, v);
+    B::transform(v, buf, tw, -1, tid);
+    if (grp == 0) {
+#pragma unroll
+      for (int f = 0; f < 3; ++f)
+#pragma unroll
+        for (int r = 0; r < R0; ++r) u[f][r] = v[f][r];
+      load(2, 3, v);
+      B::transform(v, buf, tw, -1, tid);
+    }
+  }
+  const int j = B::Last::bfly(tid), m = m0 + B::Last::seq(tid);
+  if (m >= Kx) return;
+  const double s = 1.0 / ((double)d.Ngx * G);
+  const long long fo = (long long)d.Ngy * d.K;
+  cplx* X = out + (long long)y * d.K + (long long)m * Nz;
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    // position Nz / 2 stands for the unforced Nyquist mode
+    int n = 0;
+    const int p = j + r * NR;
+    if (cou_nomode<G, NR>(r, true)) continue;
+    const bool keep = cou_zmode<G>(p, n);
+    if (!keep && p != Nz / 2) continue;
+    if (!keep) n = Nz / 2;
+    const Wave w = cou_wave(d, m, n);
+    auto put = [&](int f, cplx x) { X[f * fo + n] = keep ? x : czero(); };
+    if (!ADJ) {
+      const cplx a = cscale(v[0][r], s), b = cscale(v[1][r], s), c = cscale(v[2][r], s);
+      put(0, lin2(w.ex, a, w.ez, c));
+      put(1, b);
+      put(2, lin2(-w.ez, a, w.ex, c));
+    } else {
+      // total cotangent of a component: value (with the d/dx part) + conj(i kz) d/dz part
+      const cplx t = cadd(v[0][r], cscale(cmul_mi(v[2][r]), w.kz));
+      if (grp == 1) {
+        put(1, t);
+        put(4, v[1][r]);
+      } else {
+        const cplx ut = cadd(u[0][r], cscale(cmul_mi(u[2][r]), w.kz));
+        put(0, lin2(w.ex, ut, w.ez, t));
+        put(2, lin2(-w.ez, ut, w.ex, t));
+        put(3, lin2(w.ex, u[1][r], w.ez, v[1][r]));
+        put(5, lin2(-w.ez, u[1][r], w.ex, v[1][r]));
+      }
+    }
+  }
+}
+
 // Launch shapes.  A block transforms in place at most 6 NT points (ip_fft); the column kernels
 // take x-mode tiles of tc columns of nf fields.  Blocks of 256 threads with at most kCouLdsBudget
 // bytes of LDS, so that several share a CU; 1024 threads where one column of nf fields needs
@@ -508,6 +881,7 @@ struct CouettePlanes::Impl {
   CouDev d{};
   DevArena arena;
   ColShape A, C, A2;
+  bool rowsb = false, colsb = false;   // Ngx, Ngz have Block3 plans (and 3/2 padding)
   int ntB = 256, ntB2 = 256;
   size_t ldsB = 0, ldsB2 = 0;
   cplx *Zf = nullptr, *Wf = nullptr, *Zv = nullptr, *Wbv = nullptr, *Gv = nullptr;
@@ -548,6 +922,24 @@ CouettePlanes::CouettePlanes(const CouetteGeom& g, hipStream_t s) : p_(new Impl)
         (const void*)cou_xrow<512>, (const void*)cou_xrow<1024>, (const void*)cou_xrow_adj<256>,
         (const void*)cou_xrow_adj<512>, (const void*)cou_xrow_adj<1024>})
     SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCouLdsMax));
+  auto lds_attr = [](const void* k, size_t b) {
+    SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b));
+  };
+  if (g.Ngx == 3 * g.Kx) cou_with_length(g.Ngx, [&](auto n) {
+    constexpr int G = decltype(n)::value;
+    if constexpr (CouRows<G>::ok) {
+      lds_attr((const void*)cou_xrow_b<G>, CouRows<G>::lds);
+      lds_attr((const void*)cou_xrow_adj_b<G>, CouRows<G>::lds);
+      m.rowsb = true;
+    }
+  });
+  m.colsb = 2 * g.Ngz == 3 * g.Nz && cou_with_length(g.Ngz, [&](auto n) {
+    constexpr int G = decltype(n)::value;
+    lds_attr((const void*)cou_zinv_b<G, false>, CouCols<G>::lds);
+    lds_attr((const void*)cou_zinv_b<G, true>, CouCols<G>::lds);
+    lds_attr((const void*)cou_zfwd_b<G, false>, CouCols<G>::lds);
+    lds_attr((const void*)cou_zfwd_b<G, true>, CouCols<G>::lds);
+  });
   const size_t plane = (size_t)g.Ngy * g.Ngz * g.Kx;
   m.Zf = m.arena.alloc<cplx>(9 * plane);
   m.Wf = m.arena.alloc<cplx>(3 * plane);
@@ -563,7 +955,21 @@ namespace {
 dim3 col_grid(const CouDev& d, const ColShape& c, int groups) { return dim3((d.Kx + c.tc - 1) / c.tc, groups, d.Ngy); }
 dim3 col_grid_y(const CouDev& d, const ColShape& c) { return dim3((d.Kx + c.tc - 1) / c.tc, d.Ngy); }
 
-void launch_zinv(const CouDev& d, const ColShape& c, const cplx* zg, cplx* Z, hipStream_t s) {
+// one of the column kernels of a known length; kern(length) gives it
+template <typename Kern>
+void launch_col_b(const CouDev& d, int groups, const cplx* in, cplx* out, hipStream_t s, Kern kern) {
+  cou_with_length(d.Ngz, [&](auto n) {
+    using C = CouCols<decltype(n)::value>;
+    hipLaunchKernelGGL(kern(n), dim3((d.Kx + C::TC - 1) / C::TC, groups, d.Ngy), dim3(C::Inv::NT), C::lds, s, d, in, out);
+  });
+  SPS_CHECK_LAUNCH();
+}
+
+void launch_zinv(const CouDev& d, const ColShape& c, bool block, const cplx* zg, cplx* Z, hipStream_t s) {
+  if (block) {
+    launch_col_b(d, 3, zg, Z, s, [](auto n) { return cou_zinv_b<decltype(n)::value, false>; });
+    return;
+  }
   launch_col(
       c, [&](dim3 g, hipStream_t st) { hipLaunchKernelGGL(cou_zinv<kColSmall>, g, dim3(kColSmall), c.lds, st, d, zg, c.tc, Z); },
       [&](dim3 g, hipStream_t st) { hipLaunchKernelGGL(cou_zinv<kColLarge>, g, dim3(kColLarge), c.lds, st, d, zg, c.tc, Z); },
@@ -575,15 +981,26 @@ void launch_zinv(const CouDev& d, const ColShape& c, const cplx* zg, cplx* Z, hi
 void CouettePlanes::forward(const double2* zg, double2* nl, hipStream_t s) {
   Impl& m = *p_;
   const CouDev& d = m.d;
-  launch_zinv(d, m.A, zg, m.Zf, s);
+  launch_zinv(d, m.A, m.colsb, zg, m.Zf, s);
   const dim3 gb(d.Ngz / 2, d.Ngy);
-  if (m.ntB == 256)
+  if (m.rowsb)
+    cou_with_length(d.Ngx, [&](auto n) {
+      using R = CouRows<decltype(n)::value>;
+      if constexpr (R::ok)
+      hipLaunchKernelGGL(cou_xrow_b<decltype(n)::value>, dim3((d.Ngz / 2 + R::PAIRS - 1) / R::PAIRS, d.Ngy), dim3(R::B::NT), R::lds, s,
+                         d, m.Zf, m.Wf);
+    });
+  else if (m.ntB == 256)
     hipLaunchKernelGGL(cou_xrow<256>, gb, dim3(256), m.ldsB, s, d, m.Zf, m.Wf);
   else if (m.ntB == 512)
     hipLaunchKernelGGL(cou_xrow<512>, gb, dim3(512), m.ldsB, s, d, m.Zf, m.Wf);
   else
     hipLaunchKernelGGL(cou_xrow<1024>, gb, dim3(1024), m.ldsB, s, d, m.Zf, m.Wf);
   SPS_CHECK_LAUNCH();
+  if (m.colsb) {
+    launch_col_b(d, 1, m.Wf, nl, s, [](auto n) { return cou_zfwd_b<decltype(n)::value, false>; });
+    return;
+  }
   const ColShape& c = m.C;
   launch_col(
       c, [&](dim3 g, hipStream_t st) { hipLaunchKernelGGL(cou_zfwd<kColSmall>, g, dim3(kColSmall), c.lds, st, d, m.Wf, c.tc, nl); },
@@ -594,8 +1011,11 @@ void CouettePlanes::forward(const double2* zg, double2* nl, hipStream_t s) {
 void CouettePlanes::vjp(const double2* nlbar, const double2* zg, double2* zbar, hipStream_t s) {
   Impl& m = *p_;
   const CouDev& d = m.d;
-  launch_zinv(d, m.A, zg, m.Zv, s);
+  launch_zinv(d, m.A, m.colsb, zg, m.Zv, s);
   const ColShape& c = m.C;
+  if (m.colsb)
+    launch_col_b(d, 1, nlbar, m.Wbv, s, [](auto n) { return cou_zinv_b<decltype(n)::value, true>; });
+  else
   launch_col(
       c,
       [&](dim3 g, hipStream_t st) {
@@ -606,13 +1026,24 @@ void CouettePlanes::vjp(const double2* nlbar, const double2* zg, double2* zbar, 
       },
       col_grid_y(d, c), s);
   const dim3 gb(d.Ngz / 2, d.Ngy);
-  if (m.ntB2 == 256)
+  if (m.rowsb)
+    cou_with_length(d.Ngx, [&](auto n) {
+      using R = CouRows<decltype(n)::value>;
+      if constexpr (R::ok)
+      hipLaunchKernelGGL(cou_xrow_adj_b<decltype(n)::value>, dim3((d.Ngz / 2 + R::PAIRS - 1) / R::PAIRS, d.Ngy), dim3(R::B::NT), R::lds,
+                         s, d, m.Zv, m.Wbv, m.Gv);
+    });
+  else if (m.ntB2 == 256)
     hipLaunchKernelGGL(cou_xrow_adj<256>, gb, dim3(256), m.ldsB2, s, d, m.Zv, m.Wbv, m.Gv);
   else if (m.ntB2 == 512)
     hipLaunchKernelGGL(cou_xrow_adj<512>, gb, dim3(512), m.ldsB2, s, d, m.Zv, m.Wbv, m.Gv);
   else
     hipLaunchKernelGGL(cou_xrow_adj<1024>, gb, dim3(1024), m.ldsB2, s, d, m.Zv, m.Wbv, m.Gv);
   SPS_CHECK_LAUNCH();
+  if (m.colsb) {
+    launch_col_b(d, 2, m.Gv, zbar, s, [](auto n) { return cou_zfwd_b<decltype(n)::value, true>; });
+    return;
+  }
   const ColShape& a2 = m.A2;
   launch_col(
       a2,

@@ -13,6 +13,7 @@ if not torch.cuda.is_available():
 
 import paper_2506_14792_amd as sps  # noqa: E402
 from test_gpu_closure import test_closure_net_forward_and_vjp as check_closure_net  # noqa: E402
+from test_gpu_couette import test_couette_explicit_term_and_solve as check_couette_F  # noqa: E402
 from test_gpu_ks import test_ks_F_vjp_and_solve as check_ks_F  # noqa: E402
 from test_gpu_ks import test_ks_forward_and_gradient as check_ks_gradient  # noqa: E402
 from test_gpu_ks import test_ks_rk_forward_and_gradient as check_ks_rk_gradient  # noqa: E402
@@ -184,3 +185,10 @@ def test_sh_grid_lengths(monkeypatch):
     every = run(range(len(sizes)))
     for i in (3, 4, 10):
         assert all(torch.equal(a, b) for a, b in zip(run([i])[0], every[i]))
+
+
+# plane Couette flow: the padded x and z lengths with a plan of their own (24 to 192), tiles of modes and of row
+# pairs that are not full (Kx = 12, 36; 6, 12 and 18 row pairs), and lengths with a plan next to one without
+@pytest.mark.parametrize("nx,nz", [(16, 16), (24, 24), (32, 8), (12, 32), (48, 48), (64, 64), (72, 72), (96, 96), (128, 128)])
+def test_couette_grid_lengths(nx, nz):
+    check_couette_F(dict(Nx=nx, Ny=8, Nz=nz, Lx=3.0, Lz=2.5))
