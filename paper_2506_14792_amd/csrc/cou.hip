@@ -493,6 +493,11 @@ struct CouCols {
   using Fwd = Block3<G, TC, 1, 4>;
   static constexpr size_t lds = sizeof(cplx) * (G + 3 * Inv::BS);
 };
+// The row kernels' blocks are larger and their chain of transforms is longer, so they need a block for nearly
+// every CU: 10 steps and their gradient at 240 blocks (72x40x36) 4.58 ms against 4.81 with the general row
+// kernels, at 324 (128x24x48) 6.19 against 6.41; at 180 (48x24x48) 3.33 against 3.11, at 48 (32x16x32) 2.64
+// against 2.11.  The column kernels gain at every size.
+constexpr int kRowBlocks = 240;
 template <typename Fn>
 bool cou_with_length(int G, Fn fn) {
   switch (G) {
@@ -928,9 +933,10 @@ CouettePlanes::CouettePlanes(const CouetteGeom& g, hipStream_t s) : p_(new Impl)
   if (g.Ngx == 3 * g.Kx) cou_with_length(g.Ngx, [&](auto n) {
     constexpr int G = decltype(n)::value;
     if constexpr (CouRows<G>::ok) {
+      const int blocks = (g.Ngz / 2 + CouRows<G>::PAIRS - 1) / CouRows<G>::PAIRS;
       lds_attr((const void*)cou_xrow_b<G>, CouRows<G>::lds);
       lds_attr((const void*)cou_xrow_adj_b<G>, CouRows<G>::lds);
-      m.rowsb = true;
+      m.rowsb = blocks * g.Ngy >= kRowBlocks;
     }
   });
   m.colsb = 2 * g.Ngz == 3 * g.Nz && cou_with_length(g.Ngz, [&](auto n) {
