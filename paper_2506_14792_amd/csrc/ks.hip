@@ -258,34 +258,55 @@ struct KsDirect {
 // are twice as many base points.  Two barriers an evaluation.  Bound by the chain of a step (two LDS
 // round trips and barriers, T1 and T2 products, seven DPP steps): 200 steps at K = 32 and their reverse
 // sweep take 0.12 and 0.14 ms, with the direct sums 0.6 each.
-template <int NT_, int LP, int T1, int T2>
+// Beyond K = 64 (T1 = T2 = 0) the twiddles do not fit and are gathered from a table in LDS, bound by those reads:
+// 50 ARS(4,4,3) steps at K = 128 and their reverse sweep take 3.5 ms, with the direct sums 11.6.
+template <int NT_, int LP, int LPM, int T1, int T2>
 struct KsFold {
-  static constexpr int NT = NT_, LPM = 4;
-  static constexpr int CS = LP * T1 + 2, VS = LPM * T2 + 2;   // strides in LDS (16 B off the banks' period)
+  static constexpr int NT = NT_;
+  static constexpr bool GATHER = T1 == 0;
   using V = double;
-  static int base_points(int Ng) { return (Ng % 2) ? (Ng + 1) / 2 : Ng / 4 + 1; }
+  static __host__ __device__ int base_points(int Ng) { return (Ng % 2) ? (Ng + 1) / 2 : Ng / 4 + 1; }
+  // terms of a lane, to the grid and back, and the strides of the sums' inputs in LDS (16 B off the banks' period)
+  static __host__ __device__ int t1(int K) { return GATHER ? ((K + 1) / 2 + LP - 1) / LP : T1; }
+  static __host__ __device__ int t2(int Ng) { return GATHER ? (base_points(Ng) + LPM - 1) / LPM : T2; }
+  static __host__ __device__ int cstride(int K) { return (LP * t1(K) + 3) / 2 * 2; }
+  static __host__ __device__ int vstride(int Ng) { return (LPM * t2(Ng) + 3) / 2 * 2; }
   // every lane's sums fit
   static bool fits(int K, int Ng) {
     const int nb = base_points(Ng);
-    return nb * 4 * LP <= NT && 2 * K * LPM <= NT && (K + 1) / 2 <= LP * T1 && nb <= LPM * T2;
+    return nb * 4 * LP <= NT && 2 * K * LPM <= NT && (K + 1) / 2 <= LP * t1(K) && nb <= LPM * t2(Ng);
   }
-  static size_t lds(const KsDev&) { return sizeof(double) * 4 * (2 * CS + VS); }
+  static size_t lds(const KsDev& d) {
+    return sizeof(double) * (4 * (2 * cstride(d.K) + vstride(d.Ng)) + (GATHER ? 2 * d.Ng : 0));
+  }
   template <bool ADJ>
   struct Eval {
     double *cs, *ss, *vs;   // LDS: [4][CS] state, [4][CS] cotangent, [4][VS] folded grid values
-    double tw1[T1], tw2[T2];
+    double tw1[T1 + 1], tw2[T2 + 1];
+    const double *tab1, *tab2;    // GATHER: cosines or -sines of this lane's sums
+    int n1, n2, i1, i2, s1, s2, Ng;   // its terms; first index into the table and step
     const double *rc, *rs, *rv;   // this lane's terms
     double *wv, *wc, *wsb;        // where it writes
     double so, sb_, wt, lin, k2, w, scale;
     int comp;
     bool own, put, putv;
     __device__ __forceinline__ Eval(const KsDev& d, double* smem) {
+      const int tid = threadIdx.x, K = d.K;
+      Ng = d.Ng;
+      const int CS = cstride(K), VS = vstride(Ng);
       cs = smem;
       ss = cs + 4 * CS;
       vs = ss + 4 * CS;
-      for (int t = threadIdx.x; t < 4 * (2 * CS + VS); t += NT) smem[t] = 0.0;
-      const int tid = threadIdx.x, Ng = d.Ng, K = d.K;
-      const int nb = (Ng % 2) ? (Ng + 1) / 2 : Ng / 4 + 1;
+      for (int t = tid; t < 4 * (2 * CS + VS); t += NT) smem[t] = 0.0;
+      double* tab = vs + 4 * VS;
+      if (GATHER)
+        for (int t = tid; t < Ng; t += NT) {
+          tab[t] = d.ex[t].x;
+          tab[Ng + t] = -d.ex[t].y;
+        }
+      n1 = t1(K);
+      n2 = t2(Ng);
+      const int nb = base_points(Ng);
       auto trig = [&](int m, int j, int type) {
         const cplx e = d.ex[(m * j) % Ng];
         return type ? -e.y : e.x;
@@ -293,13 +314,19 @@ struct KsFold {
       {
         const int l = tid % LP, s = (tid / LP) & 3, o = s & 1, b = s >> 1, jb = tid / (4 * LP);
         const bool in = jb < nb;
+        if (GATHER) {
+          tab1 = tab + b * Ng;
+          i1 = (2 * l * n1 + o) * min(jb, nb - 1) % Ng;
+          s1 = 2 * min(jb, nb - 1) % Ng;
+        } else {
 #pragma unroll
-        for (int i = 0; i < T1; ++i) {
-          const int m = 2 * (l * T1 + i) + o;
-          tw1[i] = (in && m < K) ? trig(m, jb, b) : 0.0;
+          for (int i = 0; i < T1; ++i) {
+            const int m = 2 * (l * T1 + i) + o;
+            tw1[i] = (in && m < K) ? trig(m, jb, b) : 0.0;
+          }
         }
-        rc = cs + s * CS + l * T1;
-        rs = ss + s * CS + l * T1;
+        rc = cs + s * CS + l * n1;
+        rs = ss + s * CS + l * n1;
         so = o ? -1.0 : 1.0;
         sb_ = b ? -1.0 : 1.0;
         // weight of grid value (p, q) = (o, b): points that coincide in pairs count a half
@@ -312,12 +339,18 @@ struct KsFold {
         const int h = tid % LPM, cq = tid / LPM, b = cq & 1, m = cq >> 1, o = m & 1;
         own = m < K;
         const int mc = min(m, K - 1);
+        if (GATHER) {
+          tab2 = tab + b * Ng;
+          i2 = h * n2 * mc % Ng;
+          s2 = mc;
+        } else {
 #pragma unroll
-        for (int i = 0; i < T2; ++i) {
-          const int jb = h * T2 + i;
-          tw2[i] = (own && jb < nb) ? trig(mc, jb, b) : 0.0;
+          for (int i = 0; i < T2; ++i) {
+            const int jb = h * T2 + i;
+            tw2[i] = (own && jb < nb) ? trig(mc, jb, b) : 0.0;
+          }
         }
-        rv = vs + (2 * b + o) * VS + h * T2;
+        rv = vs + (2 * b + o) * VS + h * n2;
         put = own && h == 0;
         // F: the cosine sums give imaginary parts; VJP: real parts
         comp = 2 * mc + (ADJ ? b : 1 - b);
@@ -354,18 +387,44 @@ struct KsFold {
       return fma(sb_, v, dpp_d<0x1B>(dpp_mirror8(v)));   // reversed in eight, then in four: lane ^ 4
     }
     template <int T>
-    __device__ __forceinline__ static double dot(const double (&t)[T], const double* v) {
+    __device__ __forceinline__ static double dot(const double (&t)[T + 1], const double* v) {
       double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int i = 0; i < T; ++i) s[i & 3] = fma(t[i], v[i], s[i & 3]);
       return (s[0] + s[1]) + (s[2] + s[3]);
     }
-    __device__ __forceinline__ double grid(const double* v) const { return hadamard(group_sum<LP>(dot(tw1, v))); }
+    // n terms by eight (the inputs past n are followed by finite values, which take a zero)
+    __device__ __forceinline__ double dot_table(const double* tab, int i0, int step, const double* v, int n) const {
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+      int idx = i0;
+      for (int k = 0; k < n; k += 8) {
+        double t[8], x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          t[u] = tab[idx];
+          x[u] = v[min(k + u, n - 1)];
+          idx += step;
+          idx -= (idx >= Ng) ? Ng : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s[u & 3] = fma(k + u < n ? t[u] : 0.0, x[u], s[u & 3]);
+      }
+      return (s[0] + s[1]) + (s[2] + s[3]);
+    }
+    __device__ __forceinline__ double grid(const double* v) const {
+      double s;
+      if constexpr (GATHER) s = dot_table(tab1, i1, s1, v, n1);
+      else s = dot<T1>(tw1, v);
+      return hadamard(group_sum<LP>(s));
+    }
     __device__ __forceinline__ V back(double v) {
       v = hadamard(v);
       if (putv) *wv = v;
       __syncthreads();
-      return scale * group_sum<LPM>(dot(tw2, rv));
+      double s;
+      if constexpr (GATHER) s = dot_table(tab2, i2, s2, rv, n2);
+      else s = dot<T2>(tw2, rv);
+      return scale * group_sum<LPM>(s);
     }
     template <class W>
     __device__ __forceinline__ V F(V x, W work) {
@@ -852,14 +911,17 @@ class KsProblem : public ProblemImpl {
 
  private:
   const double* rk_dts() const { return var_n_ ? dts_ : nullptr; }
-  // The folded sums where every lane's twiddles fit its registers (K <= 64), with the fewest threads that
-  // hold them; the direct sums beyond.
+  // The folded sums in the form with the fewest threads that fits: with the twiddles in registers up to K = 64, from
+  // a table beyond; the direct sums where not even 1024 lanes hold them (odd grids from K = 171 on).
   template <class Fn>
   void with_evaluator(Fn fn) {
-    if (KsFold<256, 2, 8, 8>::fits(K_, Ng_)) fn(KsFold<256, 2, 8, 8>());          // K <= 32, Ng even
-    else if (KsFold<256, 1, 16, 16>::fits(K_, Ng_)) fn(KsFold<256, 1, 16, 16>());  // K < 32, Ng odd
-    else if (KsFold<512, 2, 16, 16>::fits(K_, Ng_)) fn(KsFold<512, 2, 16, 16>());  // K <= 64, Ng even
-    else if (KsFold<512, 1, 32, 32>::fits(K_, Ng_)) fn(KsFold<512, 1, 32, 32>());  // K < 64, Ng odd
+    if (KsFold<256, 2, 4, 8, 8>::fits(K_, Ng_)) fn(KsFold<256, 2, 4, 8, 8>());            // K <= 32, Ng even
+    else if (KsFold<256, 1, 4, 16, 16>::fits(K_, Ng_)) fn(KsFold<256, 1, 4, 16, 16>());   // K < 32, Ng odd
+    else if (KsFold<512, 2, 4, 16, 16>::fits(K_, Ng_)) fn(KsFold<512, 2, 4, 16, 16>());   // K <= 64, Ng even
+    else if (KsFold<512, 1, 4, 32, 32>::fits(K_, Ng_)) fn(KsFold<512, 1, 4, 32, 32>());   // K < 64, Ng odd
+    else if (KsFold<1024, 2, 4, 0, 0>::fits(K_, Ng_)) fn(KsFold<1024, 2, 4, 0, 0>());     // K <= 128, Ng even
+    else if (KsFold<1024, 1, 4, 0, 0>::fits(K_, Ng_)) fn(KsFold<1024, 1, 4, 0, 0>());     // K < 128, Ng odd
+    else if (KsFold<1024, 1, 2, 0, 0>::fits(K_, Ng_)) fn(KsFold<1024, 1, 2, 0, 0>());     // K <= 256, Ng even; K < 171
     else fn(KsDirect());
   }
   // one-block sweep launch, bracketed by the timer's events while it records

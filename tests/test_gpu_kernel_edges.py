@@ -115,9 +115,10 @@ def test_poiseuille_inverse_iteration_steps(nz, iters):
 
 
 # folded sums: the smallest grids (6 and 9 points), the last size of every form (K = 32, 31, 64, 63: 96, 93,
-# 192 and 189 points), the first past it (K = 33), a grid of 4 n + 2 points (K = 6), and the direct sums (K =
-# 65, 256).  Sums of at most 768 terms of size one: 768 u = 1e-13, within the checks' 1e-11.
-@pytest.mark.parametrize("nx", [4, 6, 12, 62, 64, 66, 126, 128, 130, 512])
+# 192 and 189 points; with the table of twiddles K = 128, 127, 256, 169), the first past each (K = 33, 66, 65, 129),
+# a grid of 4 n + 2 points (K = 6), and the direct sums (K = 171, 255).  Sums of at most 768 terms of size one:
+# 768 u = 1e-13, within the checks' 1e-11.
+@pytest.mark.parametrize("nx", [4, 6, 12, 62, 64, 66, 126, 128, 130, 132, 254, 256, 258, 338, 342, 510, 512])
 def test_ks_sizes(nx):
     cfg = (nx, 32.0, 0.01)
     check_ks_F(cfg)
