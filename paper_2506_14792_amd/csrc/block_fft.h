@@ -17,12 +17,17 @@ template <int N> struct BlockPlan { static constexpr bool ok = false; };
 #define SPS_BLOCK_PLAN(N_, A, B) \
   template <> struct BlockPlan<N_> { static constexpr bool ok = true; static constexpr int R0 = A, R1 = B; \
                                      static_assert(A * B * A == N_, "radices"); };
+SPS_BLOCK_PLAN(24, 2, 6)
+SPS_BLOCK_PLAN(36, 3, 4)
 SPS_BLOCK_PLAN(48, 4, 3)
 SPS_BLOCK_PLAN(64, 4, 4)
+SPS_BLOCK_PLAN(72, 3, 8)
 SPS_BLOCK_PLAN(96, 4, 6)
+SPS_BLOCK_PLAN(108, 3, 12)
 SPS_BLOCK_PLAN(128, 8, 2)
 SPS_BLOCK_PLAN(144, 6, 4)
 SPS_BLOCK_PLAN(192, 8, 3)
+SPS_BLOCK_PLAN(216, 6, 6)
 SPS_BLOCK_PLAN(256, 8, 4)
 SPS_BLOCK_PLAN(288, 6, 8)
 SPS_BLOCK_PLAN(384, 8, 6)

@@ -44,6 +44,7 @@
 #include "band_lu.h"
 #include "ckpt.h"
 #include "cou.h"
+#include "rows.h"
 #include "sps_device.h"
 #include "sps_internal.h"
 #include "ultra_ops.h"
@@ -3578,17 +3579,23 @@ class RbcProblem : public ProblemImpl {
     }
     launch_xf_rows(zg, nl_, s ? s : stream);
   }
-  // the grid-row forward kernel: one wave per FFT where the row length is 64 R1 (R1 = 3, 6)
+  // the grid-row forward kernel: one wave per FFT where the row length is 64 R1 (R1 = 3, 6: 5.8 and 6.9 us a launch
+  // and its transpose at 256x64, against 6.7 and 10.4 with rows.h), rows.h for the other lengths it has
   void launch_xf_rows(const cplx* zg, cplx* nl, hipStream_t s) {
     XfArgs a{zg, nl};
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const bool t = timed(2, s, &e0, &e1);
     const dim3 g(Ngz_, B_);
+    if (rows_b_) {
+      rows_fwd(rows_args(), zg, nl, s, t ? e0 : nullptr, t ? e1 : nullptr);
+      return;
+    }
     if (wave_r1_ == 6) hipExtLaunchKernelGGL(rbc_xfwd_w<6>, g, dim3(256), xfw_lds(), s, t ? e0 : nullptr, t ? e1 : nullptr, 0, dv_, a);
     else if (wave_r1_ == 3) hipExtLaunchKernelGGL(rbc_xfwd_w<3>, g, dim3(256), xfw_lds(), s, t ? e0 : nullptr, t ? e1 : nullptr, 0, dv_, a);
     else hipExtLaunchKernelGGL(rbc_xfwd, g, dim3(NTX), xf_lds(), s, t ? e0 : nullptr, t ? e1 : nullptr, 0, dv_, a);
     SPS_CHECK_LAUNCH();
   }
+  RowsArgs rows_args() const { return RowsArgs{B_, Ngx_, Ngz_, dv_.kx, dv_.twx}; }
   size_t xfw_lds() const { return sizeof(cplx) * (3 * Ngx_ + 4 * wave_sc()); }
   size_t xaw_lds() const { return sizeof(cplx) * (5 * Ngx_ + 6 * wave_sc()); }
   int wave_sc() const { return wave_r1_ == 6 ? WaveRow<6>::SC : WaveRow<3>::SC; }
@@ -3632,6 +3639,10 @@ class RbcProblem : public ProblemImpl {
     const bool t = timed(3, stream, &e0, &e1);
     if (!t) e0 = e1 = nullptr;
     const dim3 g(Ngz_, B_);
+    if (rows_b_) {
+      rows_adj(rows_args(), nlbar_, zg, zbar_, stream, e0, e1);
+      return;
+    }
     if (wave_r1_ == 6) hipExtLaunchKernelGGL(rbc_xadj_w<6>, g, dim3(384), xaw_lds(), stream, e0, e1, 0, dv_, a);
     else if (wave_r1_ == 3) hipExtLaunchKernelGGL(rbc_xadj_w<3>, g, dim3(384), xaw_lds(), stream, e0, e1, 0, dv_, a);
     else hipExtLaunchKernelGGL(rbc_xadj, g, dim3(NTX), xa_lds(), stream, e0, e1, 0, dv_, a);
@@ -4387,13 +4398,14 @@ class RbcProblem : public ProblemImpl {
         {(const void*)kfwd_fn(), kf_lds()}, {(const void*)kadj_fn(), ka_lds()}, {(const void*)rbc_factor, fac_lds}};
     if (!cou_) {
       wave_r1_ = (Ngx_ == 384) ? 6 : (Ngx_ == 192 ? 3 : 0);
+      rows_b_ = wave_r1_ == 0 && rows_supported(Ngx_, K_);
       if (wave_r1_ == 6) {
         lds.push_back({(const void*)rbc_xfwd_w<6>, xfw_lds()});
         lds.push_back({(const void*)rbc_xadj_w<6>, xaw_lds()});
       } else if (wave_r1_ == 3) {
         lds.push_back({(const void*)rbc_xfwd_w<3>, xfw_lds()});
         lds.push_back({(const void*)rbc_xadj_w<3>, xaw_lds()});
-      } else {
+      } else if (!rows_b_) {
         lds.push_back({(const void*)rbc_xfwd, xf_lds()});
         lds.push_back({(const void*)rbc_xadj, xa_lds()});
       }
@@ -4410,6 +4422,7 @@ class RbcProblem : public ProblemImpl {
   double nu_, ka_, dt_ = 0.0, cp_ = 1.0, bc0_ = 1.0, cost_scale_ = 1.0;
   int Kz_ = 1, ncost_ = 2;
   bool cou_ = false, stream_solve_ = false, share_ = false;
+  bool rows_b_ = false;              // grid rows of a length with kernels of its own (rows.h)
   int wave_r1_ = 0;                  // grid rows of 64*wave_r1_ points use the one-wave-per-FFT kernels (0: off)
   int B_ = 1;                        // instances of a batch
   std::vector<double> rab_;          // a batch's Rayleigh numbers (empty: a single problem)

@@ -14,6 +14,8 @@ if not torch.cuda.is_available():
 import paper_2506_14792_amd as sps  # noqa: E402
 from test_gpu_closure import test_closure_net_forward_and_vjp as check_closure_net  # noqa: E402
 from test_gpu_couette import test_couette_explicit_term_and_solve as check_couette_F  # noqa: E402
+from test_gpu_rbc import test_explicit_term_and_vjp as check_rbc_F  # noqa: E402
+from test_gpu_rbc_batch import test_batch_against_oracle as check_rbc_batch  # noqa: E402
 from test_gpu_ks import test_ks_F_vjp_and_solve as check_ks_F  # noqa: E402
 from test_gpu_ks import test_ks_forward_and_gradient as check_ks_gradient  # noqa: E402
 from test_gpu_ks import test_ks_rk_forward_and_gradient as check_ks_rk_gradient  # noqa: E402
@@ -193,3 +195,14 @@ def test_sh_grid_lengths(monkeypatch):
 @pytest.mark.parametrize("nx,nz", [(16, 16), (24, 24), (32, 8), (12, 32), (48, 48), (64, 64), (72, 72), (96, 96), (128, 128)])
 def test_couette_grid_lengths(nx, nz):
     check_couette_F(dict(Nx=nx, Ny=8, Nz=nz, Lx=3.0, Lz=2.5))
+
+
+# 2D convection: the padded row lengths with kernels of their own (24 to 288 points), an odd number of rows (15:
+# two rows a block up to 72 points), a length without (54); and three instances at once
+@pytest.mark.parametrize("nx", [16, 24, 32, 36, 48, 64, 72, 96, 144, 192])
+def test_rbc_row_lengths(nx):
+    check_rbc_F((nx, 10, 3.0, 1e5, 0.7, 2e-3))
+
+
+def test_rbc_row_lengths_batch():
+    check_rbc_batch(64, 10, 3.0, 0.7, 2e-3, [1e4, 1e5, 3e5], 4, 2, [0, 1, 2])
