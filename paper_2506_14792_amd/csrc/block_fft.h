@@ -18,6 +18,7 @@ template <int N> struct BlockPlan { static constexpr bool ok = false; };
   template <> struct BlockPlan<N_> { static constexpr bool ok = true; static constexpr int R0 = A, R1 = B; \
                                      static_assert(A * B * A == N_, "radices"); };
 SPS_BLOCK_PLAN(24, 2, 6)
+SPS_BLOCK_PLAN(32, 4, 2)
 SPS_BLOCK_PLAN(36, 3, 4)
 SPS_BLOCK_PLAN(48, 4, 3)
 SPS_BLOCK_PLAN(64, 4, 4)
@@ -31,6 +32,7 @@ SPS_BLOCK_PLAN(216, 6, 6)
 SPS_BLOCK_PLAN(256, 8, 4)
 SPS_BLOCK_PLAN(288, 6, 8)
 SPS_BLOCK_PLAN(384, 8, 6)
+SPS_BLOCK_PLAN(512, 8, 8)
 SPS_BLOCK_PLAN(576, 12, 4)
 SPS_BLOCK_PLAN(768, 8, 12)
 #undef SPS_BLOCK_PLAN

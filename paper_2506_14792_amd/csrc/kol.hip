@@ -404,11 +404,14 @@ __global__ void __launch_bounds__(NTK) kol_cols_fwd(KolDev d, KolCol a, int tc, 
 }
 
 // ---------------------------------------------------------------------------- steps of a known grid length
-// The three kernels of a forward step on block_fft.h, for the grid lengths it has a plan for: columns and
-// row pairs are transformed in place with the first pass read from memory and the last one used in
+// The kernels of a step and of a reverse step on block_fft.h, for the padded lengths it has a plan for: columns
+// and row pairs are transformed in place with the first pass read from memory and the last one used in
 // registers.  At N = 512, six instances: columns inverse 61 -> 22 us (113 MB moved), rows 87 -> 42 (94 MB), columns
 // forward 34 -> 20 (113 MB).  Bound by LDS and the vector unit together in the rows (some 17 and 14 us of the 42), by
-// memory in the columns.
+// memory in the columns.  At training sizes (N = 64, 16 instances, closure) a launch costs 4 to 5 us whatever it does, most
+// of it the launch and the first loads, so independent passes share one: a forward and a reverse step took 6 row
+// launches of 6.1 us and one of 5.2, now 4 of 4.1 to 7.4 (42 -> 21 us together), and 6 launches of column inverses of
+// 4.8 us and 2 column passes of 12, now 2 of 5.0 and one each of 5.4 and 6.1 (53 -> 22 us).
 template <int G>
 struct KolFft {
   static constexpr int N = 2 * G / 3, Nh = G / 3, R0 = BlockPlan<G>::R0, R1 = BlockPlan<G>::R1;
@@ -417,7 +420,23 @@ struct KolFft {
   static constexpr int TC = G >= 576 ? 4 : 8, PAIRS = G >= 576 ? 1 : (G == 48 ? 4 : 2);
   static constexpr int NTC = TC * G / R0, NTR = 4 * PAIRS * G / R0;
   static constexpr size_t lds_cols = sizeof(cplx) * (G + bf_size(TC * G)), lds_rows = sizeof(cplx) * (G + bf_size(4 * PAIRS * G));
-  static_assert(Nh % TC == 0 && (G / 2) % PAIRS == 0, "tiles");
+  static constexpr size_t lds_vjp = lds_rows + sizeof(cplx) * bf_size(PAIRS * G);
+  // row pairs of a block on the N-point grid: as many as the padded rows' threads take
+  static constexpr int PN = 4 * PAIRS, NTN = PN * N / BlockPlan<N>::R0;
+  static constexpr size_t lds_n = sizeof(cplx) * (N + bf_size(PN * N));
+  // columns of a block with the four products of a reverse step: up to 512 threads (with the closure's) where that
+  // leaves two columns, as beyond registers spill
+  static constexpr int TA = G >= 288 ? 2 : 4, NTA = 4 * TA * G / R0;
+  // threads of the closure's columns beside those of the padded ones, from a wave's start
+  static constexpr int wave(int n) { return (n + 63) / 64 * 64; }
+  static constexpr int step_threads(bool clo) { return clo ? wave(NTC) + TC * N / BlockPlan<N>::R0 : NTC; }
+  static constexpr int adj_threads(bool clo) { return clo ? wave(NTA) + TA * N / BlockPlan<N>::R0 : NTA; }
+  static constexpr size_t lds_clo(int tc) { return sizeof(cplx) * (N + bf_size(tc * N)); }
+  static constexpr size_t lds_step(bool clo) { return lds_cols + (clo ? lds_clo(TC) : 0); }
+  static constexpr size_t lds_adj(bool clo) { return sizeof(cplx) * (G + bf_size(4 * TA * G)) + (clo ? lds_clo(TA) : 0); }
+  static_assert(Nh % TC == 0 && Nh % TA == 0 && (G / 2) % PAIRS == 0 && (N / 2) % PN == 0, "tiles");
+  static_assert(TC * N / BlockPlan<N>::R0 <= NTC && NTN <= NTR, "the N-point grid's blocks fit the padded grid's");
+  static_assert(adj_threads(true) <= 1024 && lds_adj(true) <= kLdsMax && lds_vjp <= kLdsMax, "one block");
 };
 // Column tile of a block.  Tiles of four columns write half of a 128-byte line: the two halves' blocks are
 // dealt to the same XCD, one after the other.
@@ -426,81 +445,172 @@ __device__ __forceinline__ int kol_tile(int x, int tiles) {
   return (TC == 4 && tiles % 16 == 0) ? ((x & ~15) | ((x & 7) << 1) | ((x >> 3) & 1)) : x;
 }
 
-// kol_cols_inv on the padded grid.  Grid (column tiles, fields, instances).
-template <int G>
-__global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_inv_b(KolDev d, const cplx* X, int set, cplx* Z) {
-  using P = KolFft<G>;
-  constexpr int N = P::N, Nh = P::Nh, R0 = P::R0, TC = P::TC, NR = G / R0;
-  using F = BlockFft<G, TC, P::NTC, 4, 1>;   // the states have a column's modes next to each other, Z a row's
-  static_assert(F::First::MB == 1 && F::First::full, "one butterfly a thread");
-  extern __shared__ double smem_d[];
-  cplx* tw = reinterpret_cast<cplx*>(smem_d);
-  cplx* buf = tw + G;
-  const int b = blockIdx.z, f = blockIdx.y, nf = gridDim.y, c0 = TC * kol_tile<TC>(blockIdx.x, gridDim.x), tid = threadIdx.x;
+// One block's columns c0 .. c0 + TC - 1 of kol_cols_inv on an L-point grid: Xb and Zb are the instance's states and
+// the field's grid, f < 4 one of the derived fields.
+template <int L, int N, int TC, int NT>
+__device__ __forceinline__ void kol_inv_columns(const cplx* Xb, int f, cplx* Zb, const cplx* g, int c0, int tid,
+                                                double* smem) {
+  constexpr int R0 = BlockPlan<L>::R0, NR = L / R0, Nh = N / 2;
+  using F = BlockFft<L, TC, NT, 4, 1>;   // the states have a column's modes next to each other, Z a row's
+  static_assert(F::First::MB == 1 && F::Last::MB == 1, "one butterfly a thread");
+  cplx* tw = reinterpret_cast<cplx*>(smem);
+  cplx* buf = tw + L;
+  const bool act = F::First::full || tid < F::First::NB;
   const int j = F::First::bfly(tid), m = c0 + F::First::seq(tid);
-  const cplx* g = d.tw + d.twoff[d.pNg];
-  const cplx* Xc = X + ((long long)b * Nh + m) * N;
+  const cplx* Xc = Xb + (long long)m * N;
   cplx v[1][R0];
 #pragma unroll
-  for (int r = 0; r < R0; ++r) {   // grid position p holds mode p (p < N / 2) or p - G + N (p > G - N / 2)
+  for (int r = 0; r < R0; ++r) {   // grid position p holds mode p (p < N / 2) or p - L + N (p > L - N / 2)
     const int p = j + r * NR;
     v[0][r] = czero();
-    if (r * NR >= N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
-    if (p < N / 2 || p > G - N / 2) v[0][r] = Xc[p < N / 2 ? p : p - G + N];
+    if (r * NR >= N / 2 && (r + 1) * NR - 1 <= L - N / 2) continue;
+    if (act && (p < N / 2 || p > L - N / 2)) v[0][r] = Xc[p < N / 2 ? p : p - L + N];
   }
-  for (int e = tid; e < G; e += P::NTC) tw[e] = g[e];
-  if (set == FS_PRIMAL4) {
+  for (int e = tid; e < L; e += NT) tw[e] = g[e];
+  if (f < 4) {
 #pragma unroll
     for (int r = 0; r < R0; ++r) {
-      if (r * NR >= N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
+      if (r * NR >= N / 2 && (r + 1) * NR - 1 <= L - N / 2) continue;
       const int p = j + r * NR;
-      v[0][r] = cmul(v[0][r], field_factor(f, m, p < N / 2 ? p : p - G + N, N));
+      v[0][r] = cmul(v[0][r], field_factor(f, m, p < N / 2 ? p : p - L + N, N));
     }
   }
   F::First::work(v, tw, +1, tid);   // (the first pass has no twiddles)
   F::First::write(v, buf, tid);
   F::rest(v, buf, tw, +1, tid);
-  cplx* Zc = Z + (((long long)b * nf + f) * G + F::Last::bfly(tid)) * Nh + c0 + F::Last::seq(tid);
+  if (!act) return;
+  cplx* Zc = Zb + (long long)F::Last::bfly(tid) * Nh + c0 + F::Last::seq(tid);
 #pragma unroll
   for (int r = 0; r < R0; ++r) Zc[(long long)r * NR * Nh] = v[0][r];
 }
 
-// kol_rows in mode R_ADV.  The four fields of a row pair are in one row of 16 lanes, so the products are formed
-// by lane exchanges in the last inverse pass, whose outputs are the inputs of the forward transform's
-// first.  Grid (G / 2 / PAIRS, instances).
+// All column inverses of an evaluation (or of its VJP with the cotangent Fb) in one launch, which at training
+// sizes costs what each of them would: at N = 64, 16 instances, 5.0 us, and 4.6 for the four fields alone.  blockIdx.y: 0 .. 3 the fields of X on the padded grid -> Z4; then with Fb: Fb on the padded grid ->
+// Zg; then with the closure: X on the N-point grid -> Zc, and with Fb: Fb on it -> Zgc.
+// Grid (column tiles, fields, instances).
+struct KolInv {
+  const cplx *X, *Fb;
+  cplx *Z4, *Zg, *Zc, *Zgc;
+};
 template <int G>
-__global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const cplx* Z4, cplx* W) {
+__global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_inv_b(KolDev d, KolInv a) {
   using P = KolFft<G>;
-  constexpr int Nh = P::Nh, R0 = P::R0, PAIRS = P::PAIRS, TC = 4 * PAIRS, NT = P::NTR, NR = G / R0;
-  using FI = BlockFft<G, TC, NT, 4, 4>;
-  using FF = BlockFft<G, PAIRS, NT, 1, 1>;
-  static_assert(FI::First::MB == 1 && FI::First::full && FF::Last::MB == 1, "one butterfly a thread");
+  constexpr int N = P::N, Nh = P::Nh, TC = P::TC;
   extern __shared__ double smem_d[];
-  cplx* tw = reinterpret_cast<cplx*>(smem_d);
-  cplx* buf = tw + G;
-  const int b = blockIdx.y, tid = threadIdx.x, j = FI::First::bfly(tid), f = FI::First::seq(tid) & 3, pr = FI::First::seq(tid) >> 2;
-  const cplx* U = Z4 + (((long long)b * 4 + f) * G + 2 * (blockIdx.x * PAIRS + pr)) * Nh;
-  const cplx* g = d.tw + d.twoff[d.pNg];
-  // two rows' half spectra as one spectrum (kol_pack): x < Nh direct, x > G - Nh mirrored, zero between
-  cplx v[1][R0], u[R0], w[R0];
+  const int b = blockIdx.z, c0 = TC * kol_tile<TC>(blockIdx.x, gridDim.x), tid = threadIdx.x;
+  const int f = blockIdx.y + (blockIdx.y >= 4 && !a.Fb);   // 4 Zg, 5 Zc, 6 Zgc
+  const cplx* Xb = ((f == 4 || f == 6) ? a.Fb : a.X) + (long long)b * Nh * N;
+  if (f <= 4) {
+    cplx* Zb = (f < 4) ? a.Z4 + ((long long)b * 4 + f) * G * Nh : a.Zg + (long long)b * G * Nh;
+    kol_inv_columns<G, N, TC, P::NTC>(Xb, f, Zb, d.tw + d.twoff[d.pNg], c0, tid, smem_d);
+  } else {
+    kol_inv_columns<N, N, TC, P::NTC>(Xb, f, (f == 5 ? a.Zc : a.Zgc) + (long long)b * N * Nh, d.tw + d.twoff[d.pN], c0, tid,
+                                      smem_d);
+  }
+}
+
+// Inputs of the first inverse pass of butterfly j of a row pair (kol_pack): U the first row's half spectrum of Nh
+// modes, the second one's behind it; x < Nh direct, x > L - Nh mirrored, zero between.
+template <int L, int Nh>
+__device__ __forceinline__ void kol_load_pair(cplx (&v)[BlockPlan<L>::R0], const cplx* U, int j) {
+  constexpr int R0 = BlockPlan<L>::R0, NR = L / R0;
+  cplx u[R0], w[R0];
 #pragma unroll
   for (int r = 0; r < R0; ++r) {
     u[r] = w[r] = czero();
-    if (r * NR >= Nh && (r + 1) * NR - 1 <= G - Nh) continue;
+    if (r * NR >= Nh && (r + 1) * NR - 1 <= L - Nh) continue;
     const int x = j + r * NR;
-    if (x < Nh || x > G - Nh) {
-      const int i = x < Nh ? x : G - x;
+    if (x < Nh || x > L - Nh) {
+      const int i = x < Nh ? x : L - x;
       u[r] = U[i];
       w[r] = U[Nh + i];
     }
   }
-  for (int e = tid; e < G; e += NT) tw[e] = g[e];
 #pragma unroll
   for (int r = 0; r < R0; ++r) {
     const int x = j + r * NR;
     if (x == 0) u[r].y = w[r].y = 0.0;
-    v[0][r] = (x < Nh) ? cmk(u[r].x - w[r].y, u[r].y + w[r].x) : cmk(u[r].x + w[r].y, w[r].x - u[r].y);
+    v[r] = (x < Nh) ? cmk(u[r].x - w[r].y, u[r].y + w[r].x) : cmk(u[r].x + w[r].y, w[r].x - u[r].y);
   }
+}
+// Half spectrum entry m of row yy of the pair in sequence q of TC: Y_y = (Z_m + conj Z_-m) / 2, Y_y+1 = (Z_m -
+// conj Z_-m) / 2i.
+template <int L, int TC>
+__device__ __forceinline__ cplx kol_unpack(const cplx* buf, int m, int yy, int q) {
+  const cplx zm = buf[bf_pad(m * TC + q)], zq = buf[bf_pad((m == 0 ? 0 : L - m) * TC + q)];
+  return yy ? cmk(0.5 * (zm.y + zq.y), -0.5 * (zm.x - zq.x)) : cmk(0.5 * (zm.x + zq.x), 0.5 * (zm.y - zq.y));
+}
+
+// kol_rows in mode R_GRID for the PN row pairs from pair0 of one instance: Zb its field, grid its values.
+template <int N, int PN, int NT>
+__device__ __forceinline__ void kol_grid_rows(const cplx* Zb, double* grid, const cplx* g, int pair0, double wscale,
+                                              double gscale, int tid, double* smem) {
+  constexpr int R0 = BlockPlan<N>::R0, NR = N / R0, Nh = N / 2;
+  using F = BlockFft<N, PN, NT, 4, 8>;
+  static_assert(F::First::MB == 1 && F::Last::MB == 1, "one butterfly a thread");
+  cplx* tw = reinterpret_cast<cplx*>(smem);
+  cplx* buf = tw + N;
+  const bool act = F::First::full || tid < F::First::NB;
+  cplx v[1][R0];
+  if (act) {
+    const int j = F::First::bfly(tid);
+    kol_load_pair<N, Nh>(v[0], Zb + (long long)2 * (pair0 + F::First::seq(tid)) * Nh, j);
+#pragma unroll
+    for (int r = 0; r < R0; ++r)
+      if (j + r * NR != 0) v[0][r] = cscale(v[0][r], wscale);
+  }
+  for (int e = tid; e < N; e += NT) tw[e] = g[e];
+  F::First::work(v, tw, +1, tid);
+  F::First::write(v, buf, tid);
+  F::rest(v, buf, tw, +1, tid);
+  if (!act) return;
+  double* r0 = grid + (long long)2 * (pair0 + F::Last::seq(tid)) * N + F::Last::bfly(tid);
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    r0[r * NR] = v[0][r].x * gscale;
+    r0[N + r * NR] = v[0][r].y * gscale;
+  }
+}
+
+// Rows of the closure's grids behind the padded ones in the same launch, blocks from G / 2 / PAIRS on: og = X on the
+// grid, then (VJP) yg = the F cotangent's transpose.
+struct KolGrids {
+  const cplx *Zc, *Zgc;
+  double *og, *yg;
+};
+template <int G>
+__device__ __forceinline__ bool kol_closure_rows(const KolDev& d, const KolGrids& c, double* smem) {
+  using P = KolFft<G>;
+  constexpr int N = P::N, blocks = N / 2 / P::PN;
+  const int x = blockIdx.x - G / 2 / P::PAIRS;
+  if (x < 0) return false;
+  const bool cot = x >= blocks;
+  const long long b = blockIdx.y;
+  kol_grid_rows<N, P::PN, P::NTR>((cot ? c.Zgc : c.Zc) + b * N * P::Nh, (cot ? c.yg : c.og) + b * N * N,
+                                  d.tw + d.twoff[d.pN], (x - (cot ? blocks : 0)) * P::PN, cot ? 0.5 : 1.0,
+                                  cot ? 1.0 / ((double)N * N) : 1.0, threadIdx.x, smem);
+  return true;
+}
+
+// kol_rows in mode R_ADV.  The four fields of a row pair are in one row of 16 lanes, so the products are formed
+// by lane exchanges in the last inverse pass, whose outputs are the inputs of the forward transform's
+// first.  Grid (G / 2 / PAIRS [+ closure rows], instances).
+template <int G>
+__global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const cplx* Z4, cplx* W, KolGrids c) {
+  using P = KolFft<G>;
+  constexpr int Nh = P::Nh, R0 = P::R0, PAIRS = P::PAIRS, TC = 4 * PAIRS, NT = P::NTR;
+  using FI = BlockFft<G, TC, NT, 4, 4>;
+  using FF = BlockFft<G, PAIRS, NT, 1, 1>;
+  static_assert(FI::First::MB == 1 && FI::First::full && FF::Last::MB == 1, "one butterfly a thread");
+  extern __shared__ double smem_d[];
+  if (kol_closure_rows<G>(d, c, smem_d)) return;
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  const int b = blockIdx.y, tid = threadIdx.x, j = FI::First::bfly(tid), f = FI::First::seq(tid) & 3, pr = FI::First::seq(tid) >> 2;
+  const cplx* g = d.tw + d.twoff[d.pNg];
+  cplx v[1][R0];
+  kol_load_pair<G, Nh>(v[0], Z4 + (((long long)b * 4 + f) * G + 2 * (blockIdx.x * PAIRS + pr)) * Nh, j);
+  for (int e = tid; e < G; e += NT) tw[e] = g[e];
   FI::First::work(v, tw, +1, tid);
   FI::First::write(v, buf, tid);
   FI::rest(v, buf, tw, +1, tid);
@@ -520,46 +630,200 @@ __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const
   FF::rest(v, buf, tw, -1, tid);
   if (FF::Last::full || tid < FF::Last::NB) FF::Last::write(v, buf, tid);
   __syncthreads();
-  // unpack the two real rows' half spectra: Y_y = (Z_m + conj Z_-m) / 2, Y_y+1 = (Z_m - conj Z_-m) / 2i
   for (int e = tid; e < PAIRS * 2 * Nh; e += NT) {
     const int rr = e / Nh, m = e - rr * Nh, yy = rr & 1, p = rr >> 1;
-    const cplx zm = buf[bf_pad(m * PAIRS + p)], zq = buf[bf_pad((m == 0 ? 0 : G - m) * PAIRS + p)];
-    const cplx y = yy ? cmk(0.5 * (zm.y + zq.y), -0.5 * (zm.x - zq.x)) : cmk(0.5 * (zm.x + zq.x), 0.5 * (zm.y - zq.y));
-    W[((long long)b * G + 2 * (blockIdx.x * PAIRS + p) + yy) * Nh + m] = y;
+    W[((long long)b * G + 2 * (blockIdx.x * PAIRS + p) + yy) * Nh + m] = kol_unpack<G, PAIRS>(buf, m, yy, p);
   }
 }
 
-// kol_cols_fwd in mode K_STEP without the closure.  Grid (column tiles, instances).
+// kol_rows in mode R_ADV_VJP.  As kol_rows_adv_b, with the cotangent's row pairs transformed beside the fields': a
+// quarter of the threads has its first two passes' butterflies as well, and the last pass of butterfly j is
+// computed in the lanes of all four fields, which then have the cotangent q where they have their field; output f
+// is -q times the field a turn by 8 away.  7.4 us at N = 64, 16 instances, with the closure's rows.
 template <int G>
-__global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_step_b(KolDev d, KolCol a) {
+__global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_vjp_b(KolDev d, const cplx* Z4, const cplx* Zg, cplx* W, KolGrids c) {
   using P = KolFft<G>;
-  constexpr int N = P::N, Nh = P::Nh, R0 = P::R0, TC = P::TC, NR = G / R0;
+  constexpr int Nh = P::Nh, R0 = P::R0, R1 = P::R1, PAIRS = P::PAIRS, TC = 4 * PAIRS, NT = P::NTR;
+  using FI = BlockFft<G, TC, NT, 4, 4>;
+  using FQ = BlockFft<G, PAIRS, NT, 4, 1>;
+  static_assert(FI::First::MB == 1 && FI::First::full, "one butterfly a thread");
+  extern __shared__ double smem_d[];
+  if (kol_closure_rows<G>(d, c, smem_d)) return;
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  cplx* bufq = buf + bf_size(TC * G);
+  const int b = blockIdx.y, tid = threadIdx.x, j = FI::First::bfly(tid), f = FI::First::seq(tid) & 3, pr = FI::First::seq(tid) >> 2;
+  const int y0 = 2 * blockIdx.x * PAIRS;
+  const cplx* g = d.tw + d.twoff[d.pNg];
+  cplx v[1][R0], q[1][R0];
+  kol_load_pair<G, Nh>(v[0], Z4 + (((long long)b * 4 + f) * G + y0 + 2 * pr) * Nh, j);
+  if (tid < FQ::First::NB) {
+    const int jq = FQ::First::bfly(tid);
+    kol_load_pair<G, Nh>(q[0], Zg + ((long long)b * G + y0 + 2 * FQ::First::seq(tid)) * Nh, jq);
+#pragma unroll
+    for (int r = 0; r < R0; ++r)   // F's cotangent has weight-1 modes
+      if (jq + r * (G / R0) != 0) q[0][r] = cscale(q[0][r], 0.5);
+    FQ::First::work_one(q[0], tw, +1, tid);
+    FQ::First::write_one(q[0], bufq, tid);
+  }
+  for (int e = tid; e < G; e += NT) tw[e] = g[e];
+  FI::First::work(v, tw, +1, tid);
+  FI::First::write(v, buf, tid);
+  {
+    cplx m[FI::Mid::MB][R1], mq[FQ::Mid::MB][R1];
+    __syncthreads();
+    FI::Mid::read(m, buf, tid);
+    FQ::Mid::read(mq, bufq, tid);
+    __syncthreads();
+    FI::Mid::work(m, tw, +1, tid);
+    FI::Mid::write(m, buf, tid);
+    FQ::Mid::work(mq, tw, +1, tid);
+    FQ::Mid::write(mq, bufq, tid);
+  }
+  __syncthreads();
+  FI::Last::read(v, buf, tid);
+  FQ::Last::read_one(q[0], bufq, j * PAIRS + pr);
+  __syncthreads();
+  FI::Last::work(v, tw, +1, tid);
+  FQ::Last::work_one(q[0], tw, +1, j * PAIRS + pr);
+  const double inv2 = 1.0 / ((double)G * G);
+#pragma unroll
+  for (int r = 0; r < R0; ++r)   // u bar = qb omega_x, v bar = qb omega_y, omega_x bar = qb u, omega_y bar = qb v
+    v[0][r] = cmk(-q[0][r].x * inv2 * dpp_d<0x128>(v[0][r].x), -q[0][r].y * inv2 * dpp_d<0x128>(v[0][r].y));
+  FI::First::work(v, tw, -1, tid);
+  FI::First::write(v, buf, tid);
+  FI::rest(v, buf, tw, -1, tid);
+  FI::Last::write(v, buf, tid);
+  __syncthreads();
+  for (int e = tid; e < TC * 2 * Nh; e += NT) {
+    const int rr = e / Nh, m = e - rr * Nh, yy = rr & 1, s = rr >> 1;
+    W[(((long long)b * 4 + (s & 3)) * G + y0 + 2 * (s >> 2) + yy) * Nh + m] = kol_unpack<G, TC>(buf, m, yy, s);
+  }
+}
+
+// kol_rows in mode R_FWD_GRID.  Grid (N / 2 / PN, instances).
+template <int G>
+__global__ void __launch_bounds__(KolFft<G>::NTN) kol_rows_fwd_b(KolDev d, const double* gin, cplx* W) {
+  using P = KolFft<G>;
+  constexpr int N = P::N, Nh = P::Nh, PN = P::PN, NT = P::NTN, R0 = BlockPlan<N>::R0, NR = N / R0;
+  using F = BlockFft<N, PN, NT, 8, 1>;
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + N;
+  const int b = blockIdx.y, tid = threadIdx.x, y0 = 2 * blockIdx.x * PN;
+  const cplx* g = d.tw + d.twoff[d.pN];
+  const double* r0 = gin + ((long long)b * N + y0 + 2 * F::First::seq(tid)) * N + F::First::bfly(tid);
+  cplx v[1][R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) v[0][r] = cmk(r0[r * NR], r0[N + r * NR]);
+  for (int e = tid; e < N; e += NT) tw[e] = g[e];
+  F::First::work(v, tw, -1, tid);
+  F::First::write(v, buf, tid);
+  F::rest(v, buf, tw, -1, tid);
+  F::Last::write(v, buf, tid);
+  __syncthreads();
+  for (int e = tid; e < PN * 2 * Nh; e += NT) {
+    const int rr = e / Nh, m = e - rr * Nh;
+    W[((long long)b * N + y0 + rr) * Nh + m] = kol_unpack<N, PN>(buf, m, rr & 1, rr >> 1);
+  }
+}
+
+// Forward y-transforms of a block's columns: A the padded grid's (threads from 0), C the closure's on the N-point grid
+// (threads from tc0 on, beside them between the same barriers).  v: the first pass's inputs, then A's outputs;
+// C's outputs are left in bufc in natural order, synchronized.
+template <typename A, typename C, bool CLO, int NTA, int NTC>
+__device__ __forceinline__ void kol_fwd_columns(cplx (&v)[1][A::R0], cplx (&vc)[1][C::R0], cplx* buf, cplx* bufc,
+                                                const cplx* tw, const cplx* twc, int tid, int tc0) {
+  static_assert(A::First::MB == 1 && A::First::full && C::First::MB == 1 && C::First::full, "one butterfly a thread");
+  const int itc = tid - tc0;
+  const bool aa = !CLO || tid < NTA, ac = CLO && itc >= 0;
+  constexpr int MA = A::Mid::MB * A::R1, MC = C::Mid::MB * C::R1;
+  cplx x[MA > MC ? MA : MC];
+  auto& m = reinterpret_cast<cplx(&)[A::Mid::MB][A::R1]>(x);
+  auto& mc = reinterpret_cast<cplx(&)[C::Mid::MB][C::R1]>(x);
+  __syncthreads();
+  if (aa) A::Mid::read(m, buf, tid);
+  if (ac) C::Mid::read(mc, bufc, itc);
+  __syncthreads();
+  if (aa) {
+    A::Mid::work(m, tw, -1, tid);
+    A::Mid::write(m, buf, tid);
+  }
+  if (ac) {
+    C::Mid::work(mc, twc, -1, itc);
+    C::Mid::write(mc, bufc, itc);
+  }
+  __syncthreads();
+  if (aa) {
+    A::Last::read(v, buf, tid);
+    A::Last::work(v, tw, -1, tid);
+  }
+  if (ac) C::Last::read(vc, bufc, itc);
+  if (!CLO) return;
+  __syncthreads();
+  if (ac) {
+    C::Last::work(vc, twc, -1, itc);
+    C::Last::write(vc, bufc, itc);
+  }
+  __syncthreads();
+}
+
+// kol_cols_fwd in mode K_STEP.  Grid (column tiles, instances).
+template <int G, bool CLO>
+__global__ void __launch_bounds__(KolFft<G>::step_threads(CLO)) kol_cols_step_b(KolDev d, KolCol a) {
+  using P = KolFft<G>;
+  constexpr int N = P::N, Nh = P::Nh, R0 = P::R0, TC = P::TC, NR = G / R0, RN = BlockPlan<N>::R0, NTN = TC * N / RN;
+  constexpr int NT = P::step_threads(CLO), TC0 = P::wave(P::NTC);
   using F = BlockFft<G, TC, P::NTC, 1, 4>;   // as kol_cols_inv_b, the other way
+  using C = BlockFft<N, TC, NTN, 1, 1>;
   extern __shared__ double smem_d[];
   cplx* tw = reinterpret_cast<cplx*>(smem_d);
   cplx* buf = tw + G;
+  cplx* twc = buf + bf_size(TC * G);
+  cplx* bufc = twc + N;
   const int b = blockIdx.y, tid = threadIdx.x, c0 = TC * kol_tile<TC>(blockIdx.x, gridDim.x);
   const int j = F::Last::bfly(tid), m = c0 + F::Last::seq(tid);
   const cplx* g = d.tw + d.twoff[d.pNg];
-  const cplx* Wc = a.W + ((long long)b * G + F::First::bfly(tid)) * Nh + c0 + F::First::seq(tid);
-  cplx v[1][R0];
+  cplx x[R0 > RN ? R0 : RN];   // a thread has one of the two transforms: the same registers
+  auto& v = reinterpret_cast<cplx(&)[1][R0]>(x);
+  auto& vc = reinterpret_cast<cplx(&)[1][RN]>(x);
+  const bool act = !CLO || tid < P::NTC;
+  if (act) {
+    const cplx* Wc = a.W + ((long long)b * G + F::First::bfly(tid)) * Nh + c0 + F::First::seq(tid);
 #pragma unroll
-  for (int r = 0; r < R0; ++r) v[0][r] = Wc[(long long)r * NR * Nh];
-  for (int e = tid; e < G; e += P::NTC) tw[e] = g[e];
-  F::First::work(v, tw, -1, tid);
-  F::First::write(v, buf, tid);
+    for (int r = 0; r < R0; ++r) v[0][r] = Wc[(long long)r * NR * Nh];
+  }
+  if (CLO && tid >= TC0) {
+    const int it = tid - TC0;
+    const cplx* Wc = a.Wc + ((long long)b * N + C::First::bfly(it)) * Nh + c0 + C::First::seq(it);
+#pragma unroll
+    for (int r = 0; r < RN; ++r) vc[0][r] = Wc[(long long)r * (N / RN) * Nh];
+  }
+  for (int e = tid; e < G; e += NT) tw[e] = g[e];
+  if (CLO)
+    for (int e = tid; e < N; e += NT) twc[e] = d.tw[d.twoff[d.pN] + e];
+  if (act) {
+    F::First::work(v, tw, -1, tid);
+    F::First::write(v, buf, tid);
+  }
+  if (CLO && tid >= TC0) {
+    C::First::work(vc, twc, -1, tid - TC0);
+    C::First::write(vc, bufc, tid - TC0);
+  }
   // the previous states and F of this thread's modes: grid position p holds mode p (p < N / 2) or p - G + N
   // (p > G - N / 2); p = N / 2 stands for the Nyquist row, which is kept zero
   const long long st = (long long)d.B * Nh * N, io = ((long long)b * Nh + m) * N;
+  constexpr bool early = NT <= 512;   // (beyond, there are no registers to keep them)
   StepIn in[R0];
 #pragma unroll
   for (int r = 0; r < R0; ++r) {
     const int p = j + r * NR;
     if (r * NR > N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
-    if (p <= N / 2 || p > G - N / 2) in[r] = kol_step_load(a, st, io + (p <= N / 2 ? p : p - G + N));
+    if (early && act && (p <= N / 2 || p > G - N / 2)) in[r] = kol_step_load(a, st, io + (p <= N / 2 ? p : p - G + N));
   }
-  F::rest(v, buf, tw, -1, tid);
-  const double ng2 = 1.0 / ((double)G * G);
+  kol_fwd_columns<F, C, CLO, P::NTC, NTN>(v, vc, buf, bufc, tw, twc, tid, TC0);
+  if (!act) return;
+  const double ng2 = 1.0 / ((double)G * G), n2 = 1.0 / ((double)N * N);
 #pragma unroll
   for (int r = 0; r < R0; ++r) {
     const int p = j + r * NR;
@@ -571,10 +835,129 @@ __global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_step_b(KolDev d, KolC
       if (keep) {
         f = cscale(v[0][r], ng2);
         if (m == 0 && N > 8 && (iy == 4 || iy == N - 4)) f = cadd(f, cmk(-2.0, 0.0));   // -4 cos 4y
+        if (CLO) f = cadd(f, cscale(bufc[bf_pad(iy * TC + (m - c0))], n2));
       }
       const double ky = kol_ky(iy, N), lin = d.nu * ((double)m * m + ky * ky) + d.drag;
-      kol_step_entry(d, a, b, m, iy, keep, f, in[r], lin, st, io + iy);
+      kol_step_entry(d, a, b, m, iy, keep, f, early ? in[r] : kol_step_load(a, st, io + iy), lin, st, io + iy);
     }
+  }
+}
+
+// kol_cols_fwd in mode K_ADJ: the products of a column's four fields on lanes 4 f + (0 .. 3) of a row of 16, so their
+// sum is two lane exchanges, after which the lanes of field f finish the positions j + r G / R0 with r = f
+// (mod 4).  12.0 -> 6.1 us at N = 64, 16 instances, with the closure.  Grid (column tiles, instances).
+template <int G, bool CLO>
+__global__ void __launch_bounds__(KolFft<G>::adj_threads(CLO)) kol_cols_adj_b(KolDev d, KolCol a) {
+  using P = KolFft<G>;
+  constexpr int N = P::N, Nh = P::Nh, R0 = P::R0, TA = P::TA, TC = 4 * TA, NR = G / R0, RN = BlockPlan<N>::R0, NTN = TA * N / RN;
+  constexpr int NT = P::adj_threads(CLO), TC0 = P::wave(P::NTA), RQ = (R0 + 3) / 4;
+  using F = BlockFft<G, TC, P::NTA, 1, 4>;
+  using C = BlockFft<N, TA, NTN, 1, 1>;
+  extern __shared__ double smem_d[];
+  cplx* tw = reinterpret_cast<cplx*>(smem_d);
+  cplx* buf = tw + G;
+  cplx* twc = buf + bf_size(TC * G);
+  cplx* bufc = twc + N;
+  const int b = blockIdx.y, tid = threadIdx.x, c0 = TA * blockIdx.x;
+  const cplx* g = d.tw + d.twoff[d.pNg];
+  cplx x[R0 > RN ? R0 : RN];   // a thread has one of the two transforms: the same registers
+  auto& v = reinterpret_cast<cplx(&)[1][R0]>(x);
+  auto& vc = reinterpret_cast<cplx(&)[1][RN]>(x);
+  const bool act = !CLO || tid < P::NTA;
+  if (act) {   // sequence 4 column + field
+    const int s = F::First::seq(tid);
+    const cplx* Wc = a.W + (((long long)b * 4 + (s & 3)) * G + F::First::bfly(tid)) * Nh + c0 + (s >> 2);
+#pragma unroll
+    for (int r = 0; r < R0; ++r) v[0][r] = Wc[(long long)r * NR * Nh];
+  }
+  if (CLO && tid >= TC0) {
+    const int it = tid - TC0;
+    const cplx* Wc = a.Wc + ((long long)b * N + C::First::bfly(it)) * Nh + c0 + C::First::seq(it);
+#pragma unroll
+    for (int r = 0; r < RN; ++r) vc[0][r] = Wc[(long long)r * (N / RN) * Nh];
+  }
+  for (int e = tid; e < G; e += NT) tw[e] = g[e];
+  if (CLO)
+    for (int e = tid; e < N; e += NT) twc[e] = d.tw[d.twoff[d.pN] + e];
+  if (act) {
+    F::First::work(v, tw, -1, tid);
+    F::First::write(v, buf, tid);
+  }
+  if (CLO && tid >= TC0) {
+    C::First::work(vc, twc, -1, tid - TC0);
+    C::First::write(vc, bufc, tid - TC0);
+  }
+  // what this thread's modes need from memory, positions as in kol_cols_step_b
+  const int j = F::Last::bfly(tid), f = F::Last::seq(tid) & 3, m = c0 + (F::Last::seq(tid) >> 2), k = a.n - 1;
+  const long long st = (long long)d.B * Nh * N, io = ((long long)b * Nh + m) * N;
+  const cplx* H = a.H + hidx(a, k, st);
+  const cplx* T = (a.targ && k >= 1) ? a.targ + (long long)(k - 1) * st : nullptr;
+  cplx ln[RQ], yn[RQ], dh[RQ], dm[RQ];
+#pragma unroll
+  for (int i = 0; i < RQ; ++i) {
+    ln[i] = yn[i] = dh[i] = dm[i] = czero();
+    const int r = f + 4 * i, p = j + r * NR;
+    if (!act || r >= R0 || !(p <= N / 2 || p > G - N / 2)) continue;
+    const int iy = p <= N / 2 ? p : p - G + N;
+    ln[i] = a.Ln[io + iy];
+    yn[i] = a.Yn[io + iy];
+    if (T) {
+      dh[i] = csub(H[io + iy], T[io + iy]);
+      if (m == 0) dm[i] = csub(H[io + (N - iy) % N], T[io + (N - iy) % N]);
+    }
+  }
+  kol_fwd_columns<F, C, CLO, P::NTA, NTN>(v, vc, buf, bufc, tw, twc, tid, TC0);
+  if (!act) return;
+  // the fields' conjugate factors (u: -i ky/|k|^2, v: i kx/|k|^2, omega_x: -i kx, omega_y: -i ky) and their sum
+  const double kx = m, wm = (m == 0) ? 1.0 : 2.0;
+#pragma unroll
+  for (int r = 0; r < R0; ++r) {
+    if (r * NR > N / 2 && (r + 1) * NR - 1 <= G - N / 2) continue;
+    const int p = j + r * NR;
+    const double ky = (p < N / 2) ? p : p - G, k2 = kx * kx + ky * ky;
+    const double ik2 = (k2 > 0.0) ? 1.0 / k2 : 0.0;
+    const double q = wm * (f == 0 ? ky * ik2 : f == 1 ? -kx * ik2 : f == 2 ? kx : ky);
+    double sx = q * v[0][r].y, sy = -q * v[0][r].x;
+    sx += dpp_d<0x128>(sx);
+    sy += dpp_d<0x128>(sy);
+    v[0][r] = cmk(sx + dpp_d<0x124>(sx), sy + dpp_d<0x124>(sy));
+  }
+  const SbdfC q = sbdf_c(max(k, 1), d.dt), qn = sbdf_c(k + 1, d.dt);
+#pragma unroll
+  for (int i = 0; i < RQ; ++i) {
+    const int r = f + 4 * i, p = j + r * NR;
+    cplx xb = czero();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (4 * i + e < R0) {
+        xb.x = (f == e) ? v[0][4 * i + e].x : xb.x;
+        xb.y = (f == e) ? v[0][4 * i + e].y : xb.y;
+      }
+    if (r >= R0 || !(p <= N / 2 || p > G - N / 2)) continue;
+    const int iy = p <= N / 2 ? p : p - G + N;
+    const bool keep = p != N / 2;
+    if (!keep) xb = czero();
+    if (CLO && keep) xb = cadd(xb, cscale(bufc[bf_pad(iy * TA + (m - c0))], wm));
+    xb = csub(xb, ln[i]);
+    if (T && keep) {
+      // d/dX_k of (1/nsteps) mean over the N x N grid of (omega_k - target_k)^2
+      const cplx e1 = (m == 0) ? cmk(0.5 * (dh[i].x + dm[i].x), 0.5 * (dh[i].y - dm[i].y)) : dh[i];
+      xb = cadd(xb, cscale(e1, 2.0 * wm / a.nsteps));
+    }
+    if (k == 0) {
+      a.out[io + iy] = xb;
+      continue;
+    }
+    cplx y = czero(), gk = czero(), l = czero();
+    if (keep) {   // (k + 1 <= nsteps: Yn holds the next step's)
+      const double ky = kol_ky(iy, N), lin = d.nu * (kx * kx + ky * ky) + d.drag;
+      y = cscale(xb, 1.0 / (q.a0 + lin));
+      gk = cadd(cscale(y, q.c1), cscale(yn[i], qn.c2));
+      l = cadd(cscale(y, q.a1), cscale(yn[i], qn.a2));
+    }
+    a.Yn[io + iy] = y;
+    a.Ln[io + iy] = l;
+    a.Gk[io + iy] = gk;
   }
 }
 
@@ -711,9 +1094,16 @@ class KolProblem : public ProblemImpl {
       SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
     block_ = with_block_fft([&](auto g) {
       constexpr int G = decltype(g)::value;
-      SPS_HIP(hipFuncSetAttribute((const void*)kol_cols_inv_b<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)KolFft<G>::lds_cols));
-      SPS_HIP(hipFuncSetAttribute((const void*)kol_rows_adv_b<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)KolFft<G>::lds_rows));
-      SPS_HIP(hipFuncSetAttribute((const void*)kol_cols_step_b<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)KolFft<G>::lds_cols));
+      using P = KolFft<G>;
+      const auto lds = [](const void* k, size_t n) { SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)n)); };
+      lds((const void*)kol_cols_inv_b<G>, P::lds_cols);
+      lds((const void*)kol_rows_adv_b<G>, P::lds_rows);
+      lds((const void*)kol_rows_vjp_b<G>, P::lds_vjp);
+      lds((const void*)kol_rows_fwd_b<G>, P::lds_n);
+      lds((const void*)kol_cols_step_b<G, false>, P::lds_step(false));
+      lds((const void*)kol_cols_step_b<G, true>, P::lds_step(true));
+      lds((const void*)kol_cols_adj_b<G, false>, P::lds_adj(false));
+      lds((const void*)kol_cols_adj_b<G, true>, P::lds_adj(true));
     });
     SPS_HIP(hipStreamSynchronize(stream));
   }
@@ -913,11 +1303,22 @@ class KolProblem : public ProblemImpl {
       default: return false;
     }
   }
+  template <int G, bool CLO>
+  void launch_cols_b(const KolCol& a) {
+    using P = KolFft<G>;
+    if (a.mode == K_STEP)
+      hipLaunchKernelGGL((kol_cols_step_b<G, CLO>), dim3(P::Nh / P::TC, B_), dim3(P::step_threads(CLO)), P::lds_step(CLO), stream,
+                         d_, a);
+    else
+      hipLaunchKernelGGL((kol_cols_adj_b<G, CLO>), dim3(P::Nh / P::TA, B_), dim3(P::adj_threads(CLO)), P::lds_adj(CLO), stream, d_,
+                         a);
+  }
   void launch_cols(const KolCol& a) {
-    if (block_ && a.mode == K_STEP && !a.closure) {
+    if (block_ && (a.mode == K_STEP || a.mode == K_ADJ)) {
       with_block_fft([&](auto g) {
-        using P = KolFft<decltype(g)::value>;
-        hipLaunchKernelGGL(kol_cols_step_b<decltype(g)::value>, dim3(P::Nh / P::TC, B_), dim3(P::NTC), P::lds_cols, stream, d_, a);
+        constexpr int G = decltype(g)::value;
+        if (a.closure) launch_cols_b<G, true>(a);
+        else launch_cols_b<G, false>(a);
       });
       SPS_CHECK_LAUNCH();
       return;
@@ -929,30 +1330,12 @@ class KolProblem : public ProblemImpl {
   void cols_inv(const cplx* X, int set, int G, int plan, cplx* Z) {
     const int tc = (G == Ng_) ? tc_ig_ : tc_in_;
     const int nf = (set == FS_PRIMAL4) ? 4 : 1;
-    if (block_ && G == Ng_) {
-      with_block_fft([&](auto g) {
-        using P = KolFft<decltype(g)::value>;
-        hipLaunchKernelGGL(kol_cols_inv_b<decltype(g)::value>, dim3(P::Nh / P::TC, nf, B_), dim3(P::NTC), P::lds_cols, stream, d_,
-                           X, set, Z);
-      });
-      SPS_CHECK_LAUNCH();
-      return;
-    }
     hipLaunchKernelGGL(kol_cols_inv, dim3((Nh_ + tc - 1) / tc, nf, B_), dim3(NTK), inv_lds(G, tc), stream, d_, X,
                        set, G, plan, tc, Z);
     SPS_CHECK_LAUNCH();
   }
   void rows(int mode, int G, int plan, const cplx* Z4, const cplx* Zg, double* grid, const double* gin, cplx* W,
             double wscale, double gscale) {
-    if (mode == R_ADV && block_) {
-      with_block_fft([&](auto g) {
-        using P = KolFft<decltype(g)::value>;
-        hipLaunchKernelGGL(kol_rows_adv_b<decltype(g)::value>, dim3(decltype(g)::value / 2 / P::PAIRS, B_), dim3(P::NTR), P::lds_rows,
-                           stream, d_, Z4, W);
-      });
-      SPS_CHECK_LAUNCH();
-      return;
-    }
     if (mode == R_ADV && G >= 384) {
       const size_t l2 = sizeof(cplx) * (G + 2 * (size_t)fpad_size(2 * G) + fpad_size(G));
       hipLaunchKernelGGL(kol_rows_adv2<512>, dim3(G / 2, B_), dim3(512), l2, stream, d_, G, plan, Z4, W);
@@ -970,15 +1353,50 @@ class KolProblem : public ProblemImpl {
                          gin, W, wscale, gscale);
     SPS_CHECK_LAUNCH();
   }
+  // The column inverses and row passes of F at X, or of its VJP with the cotangent Fb, up to the closure's network,
+  // in two launches (padded lengths with a plan).
+  void block_products(const cplx* X, const cplx* Fb) {
+    with_block_fft([&](auto g) {
+      constexpr int G = decltype(g)::value;
+      using P = KolFft<G>;
+      const int extra = (Fb ? 1 : 0) + (closure_ ? (Fb ? 2 : 1) : 0), grids = closure_ ? (Fb ? 2 : 1) : 0;
+      hipLaunchKernelGGL(kol_cols_inv_b<G>, dim3(P::Nh / P::TC, 4 + extra, B_), dim3(P::NTC), P::lds_cols, stream, d_,
+                         KolInv{X, Fb, Z4_, Zg_, Zc_, Zgc_});
+      SPS_CHECK_LAUNCH();
+      const dim3 rows(G / 2 / P::PAIRS + grids * (P::N / 2 / P::PN), B_);
+      const KolGrids cg{Zc_, Zgc_, og_, yg_};
+      if (Fb) hipLaunchKernelGGL(kol_rows_vjp_b<G>, rows, dim3(P::NTR), P::lds_vjp, stream, d_, Z4_, Zg_, W_, cg);
+      else hipLaunchKernelGGL(kol_rows_adv_b<G>, rows, dim3(P::NTR), P::lds_rows, stream, d_, Z4_, W_, cg);
+      SPS_CHECK_LAUNCH();
+    });
+  }
+  // x-spectra of the network's output on the grid (Wc)
+  void closure_spectra(const double* grid) {
+    const bool done = with_block_fft([&](auto g) {
+      using P = KolFft<decltype(g)::value>;
+      hipLaunchKernelGGL(kol_rows_fwd_b<decltype(g)::value>, dim3(P::N / 2 / P::PN, B_), dim3(P::NTN), P::lds_n, stream, d_, grid, Wc_);
+      SPS_CHECK_LAUNCH();
+    });
+    if (!done) rows(R_FWD_GRID, N_, d_.pN, nullptr, nullptr, nullptr, grid, Wc_, 1.0, 1.0);
+  }
   // x-spectra of the products of F at X (W) and of the closure output (Wc)
   void eval_products(const cplx* X) {
+    if (block_) {
+      block_products(X, nullptr);
+    } else {
+      general_products(X);
+    }
+    if (closure_) {
+      net_->forward(og_, yg_, 1.0, false);
+      closure_spectra(yg_);
+    }
+  }
+  void general_products(const cplx* X) {
     cols_inv(X, FS_PRIMAL4, Ng_, d_.pNg, Z4_);
     rows(R_ADV, Ng_, d_.pNg, Z4_, nullptr, nullptr, nullptr, W_, 1.0, 1.0);
     if (closure_) {
       cols_inv(X, FS_ONE, N_, d_.pN, Zc_);
       rows(R_GRID, N_, d_.pN, Zc_, nullptr, og_, nullptr, nullptr, 1.0, 1.0);
-      net_->forward(og_, yg_, 1.0, false);
-      rows(R_FWD_GRID, N_, d_.pN, nullptr, nullptr, nullptr, yg_, Wc_, 1.0, 1.0);
     }
   }
   // x-spectra of the VJP of F at X with cotangent G (W: 4 fields; Wc).  The closure's parameter
@@ -987,6 +1405,20 @@ class KolProblem : public ProblemImpl {
   enum ThetaMode { NO_THETA, ADD_THETA, ACC_THETA };
   void eval_vjp(const cplx* X, const cplx* G, ThetaMode tm, double* th_bar) {
     SPS_REQUIRE(nwmax_ == 4, "VJPs need a problem built with keep_history");
+    if (block_) {
+      block_products(X, G);
+    } else {
+      general_vjp_products(X, G);
+    }
+    if (closure_) {
+      if (tm == ACC_THETA)
+        net_->vjp_accumulate(og_, yg_, xg_, 1.0, false);
+      else
+        net_->vjp(og_, yg_, xg_, 1.0, false, tm == ADD_THETA ? th_bar : nullptr);
+      closure_spectra(xg_);
+    }
+  }
+  void general_vjp_products(const cplx* X, const cplx* G) {
     cols_inv(X, FS_PRIMAL4, Ng_, d_.pNg, Z4_);
     cols_inv(G, FS_ONE, Ng_, d_.pNg, Zg_);
     rows(R_ADV_VJP, Ng_, d_.pNg, Z4_, Zg_, nullptr, nullptr, W_, 1.0, 1.0);
@@ -995,11 +1427,6 @@ class KolProblem : public ProblemImpl {
       rows(R_GRID, N_, d_.pN, Zc_, nullptr, og_, nullptr, nullptr, 1.0, 1.0);
       cols_inv(G, FS_ONE, N_, d_.pN, Zgc_);
       rows(R_GRID, N_, d_.pN, Zgc_, nullptr, yg_, nullptr, nullptr, 0.5, 1.0 / ((double)N_ * N_));
-      if (tm == ACC_THETA)
-        net_->vjp_accumulate(og_, yg_, xg_, 1.0, false);
-      else
-        net_->vjp(og_, yg_, xg_, 1.0, false, tm == ADD_THETA ? th_bar : nullptr);
-      rows(R_FWD_GRID, N_, d_.pN, nullptr, nullptr, nullptr, xg_, Wc_, 1.0, 1.0);
     }
   }
 

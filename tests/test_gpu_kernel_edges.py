@@ -162,6 +162,47 @@ def test_kolmo_grid_lengths(N):
             assert rel(s[k, b].T, ref) <= 1e-11
 
 
+# The reverse steps at the same lengths, with and without the closure (whose grids N = 32 to 96 are in
+# test_gpu_kolmo.py): gradient of a rollout of two steps, so one with and one without a target's term.  Bounds of
+# test_gpu_kolmo.py: 1e-11 without the closure; with it (activations rounded to bfloat16) 2^-7 of the largest at
+# most and 2^-13 in the median.
+@pytest.mark.parametrize("N,closure", [(N, False) for N in (32, 64, 96, 128, 192, 256, 384, 512)]
+                         + [(N, True) for N in (128, 192, 256, 384, 512)])
+def test_kolmo_gradient_grid_lengths(N, closure):
+    from oracle import closure as cl
+    from oracle.kolmo import Kolmogorov, rollout_loss_and_gradients
+    from test_gpu_kolmo import from_dev, params, rel, to_dev
+    print(f"Kolmogorov gradient, N = {N}, closure {closure}", flush=True)
+    B, dt, n = (2 if N <= 128 else 1), 1e-3 * 64 / N, 2
+    p = params(11) if closure else None
+    c0 = wl.kolmo_vorticity(seed=2, N=N, batch=B)
+    tg = [wl.kolmo_vorticity(seed=20 + k, N=N, batch=B) for k in range(n)]
+    P = Kolmogorov(N, Re=1000.0, params=p, bf=True, drag=0.1)
+    G = sps.Kolmogorov(B, N, Re=1000.0, dt=dt, max_steps=n, closure=closure, keep_history=True, drag=0.1)
+    X0, gth = to_dev(list(c0)), None
+    if closure:
+        theta = torch.from_numpy(cl.flatten(p)).cuda()
+        G.set_params(theta)
+        gth = torch.zeros_like(theta)
+    J, g0 = torch.zeros(B, dtype=torch.float64, device="cuda"), torch.zeros_like(X0)
+    G.rollout(X0, torch.cat([to_dev(list(t)) for t in tg]), n, J=J, dJdX0=g0, dJdtheta=gth)
+    G.sync()
+    g0, J, tr = from_dev(g0, B, N), J.cpu().numpy(), 0.0
+    for b in range(B):
+        Jo, go, gp, _ = rollout_loss_and_gradients(P, c0[b].reshape(-1, 1), [t[b].reshape(-1, 1) for t in tg], dt, n)
+        e = np.abs(g0[b] - go.reshape(N, N // 2)) / np.max(np.abs(go))
+        if not closure:
+            assert e.max() <= 1e-11 and abs(J[b] - Jo) <= 1e-11 * abs(Jo)
+            continue
+        assert e.max() <= 2.0 ** -7 and np.median(e) <= 2.0 ** -13
+        tr = tr + gp
+    if closure:
+        tp, to = cl.unflatten(gth.cpu().numpy()), cl.unflatten(tr)
+        for k in cl.PARAM_ORDER:
+            e = np.abs(tp[k] - to[k]) / np.max(np.abs(to[k]))
+            assert e.max() <= 2.0 ** -7 and np.median(e) <= 2.0 ** -13, k
+
+
 # Swift-Hohenberg grid lengths with a plan of their own (48 to 384 points, so N = 24 to 192), one of them with a
 # partial column tile (N = 72), together with lengths that have none; sizes above the largest plan.  Same checks as
 # test_gpu_sh.py; and an instance alone gives the same bits as in the mixed batch.
