@@ -65,6 +65,15 @@ __device__ __forceinline__ float gelu_df(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
+// Block i of n as a block of pixels: the blocks of one XCD (i mod 8) take one contiguous part of them, in every
+// kernel the same, so that the rows that neighbouring blocks, the nine taps and the next kernel read again are in
+// that XCD's L2 (dealt out one by one, each L2 read every image).  At 65536 pixels: layer 2 11.4 -> 10.4 us, layer 3
+// 6.0 -> 5.1, its backward 8.4 -> 8.0, layer 2's input cotangent 24.5 -> 20.3 (with its pre-activations loaded early).
+__device__ __forceinline__ int slab(int i, int n) {
+  const int xcd = i & 7, q = n >> 3, r = n & 7;
+  return xcd * q + min(xcd, r) + (i >> 3);
+}
+
 // parameters (FP64) -> stored tables
 __global__ void cnn_prepare(const double* th, float* w1, float* b1, __bf16* w2r, float* w2f, float* b2, float* w3,
                             float* b3) {
@@ -97,7 +106,7 @@ __global__ void __launch_bounds__(NTC) cnn_l1(CnnDev d, const double* x) {
   if (threadIdx.x < CH) bs[threadIdx.x] = d.b1[threadIdx.x];
   __syncthreads();
   const int HW = d.H * d.W;
-  const int g = blockIdx.x * L1_PIX + (threadIdx.x >> 2), c0 = (threadIdx.x & 3) * 8;
+  const int g = slab(blockIdx.x, gridDim.x) * L1_PIX + (threadIdx.x >> 2), c0 = (threadIdx.x & 3) * 8;
   if (g >= d.B * HW) return;
   const int b = g / HW, p = g - b * HW;
   float v[9];
@@ -128,7 +137,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2(CnnDev d) {
     reinterpret_cast<bf16x8*>(w)[e] = reinterpret_cast<const bf16x8*>(d.w2r)[e];
   __syncthreads();
   const int HW = d.H * d.W, lane = threadIdx.x & 63;
-  const int tile = blockIdx.x * (NTC / 64) + (threadIdx.x >> 6);   // 32-pixel tiles
+  const int tile = slab(blockIdx.x, gridDim.x) * (NTC / 64) + (threadIdx.x >> 6);   // 32-pixel tiles
   const int tiles_per_img = HW / 32;
   if (tile >= d.B * tiles_per_img) return;
   const int b = tile / tiles_per_img, p0 = (tile - b * tiles_per_img) * 32;
@@ -157,7 +166,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2(CnnDev d) {
 // layer 3 (32 -> 1): one thread per pixel; y (FP64) = scale * output (+= when accumulate)
 __global__ void __launch_bounds__(NTC) cnn_l3(CnnDev d, double* y, double scale, int accumulate) {
   const int HW = d.H * d.W;
-  const int g = blockIdx.x * NTC + threadIdx.x;
+  const int g = slab(blockIdx.x, gridDim.x) * NTC + threadIdx.x;
   if (g >= d.B * HW) return;
   const int b = g / HW, p = g - b * HW;
   float s = d.b3[0];
@@ -184,7 +193,7 @@ __global__ void __launch_bounds__(NTC) cnn_l3_back(CnnDev d, const double* yb) {
   for (int e = threadIdx.x; e < NP3; e += NTC) w[(e % 9) * CH + e / 9] = d.w3[e];
   __syncthreads();
   const int HW = d.H * d.W;
-  const int g = blockIdx.x * L3B_PIX + (threadIdx.x >> 3), c0 = (threadIdx.x & 7) * 4;
+  const int g = slab(blockIdx.x, gridDim.x) * L3B_PIX + (threadIdx.x >> 3), c0 = (threadIdx.x & 7) * 4;
   if (g >= d.B * HW) return;
   const int b = g / HW, p = g - b * HW;
   const float4 z = *reinterpret_cast<const float4*>(d.z2 + (long long)g * CH + c0);
@@ -211,7 +220,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
     reinterpret_cast<float4*>(w)[e] = reinterpret_cast<const float4*>(d.w2f)[e];
   __syncthreads();
   const int HW = d.H * d.W, lane = threadIdx.x & 63;
-  const int tile = blockIdx.x * (NTC / 64) + (threadIdx.x >> 6);
+  const int tile = slab(blockIdx.x, gridDim.x) * (NTC / 64) + (threadIdx.x >> 6);
   const int tiles_per_img = HW / 32;
   if (tile >= d.B * tiles_per_img) return;
   const int b = tile / tiles_per_img, p0 = (tile - b * tiles_per_img) * 32;
@@ -220,7 +229,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
   f32x16 acc = {};
   // 16-byte loads: lane (pixel row, half) holds channels 8j + 4 half .. 8j + 4 half + 3, and
   // each of the four MFMAs pairs channel 8j + m (half 0) with 8j + 4 + m (half 1); a tap's loads are
-  // issued before the MFMAs of the tap before it (31 -> 26 us at 65536 pixels)
+  // issued before the MFMAs of the tap before it (31 -> 25 us at 65536 pixels)
   float4 nq[CH / 8];
   auto load = [&](int t) {
     const float4* Gt = reinterpret_cast<const float4*>(G + (long long)nb_t(p0 + row, t, d.H, d.W) * CH);
@@ -228,6 +237,9 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
     for (int j = 0; j < CH / 8; ++j) nq[j] = Gt[2 * j + half];
   };
   load(0);
+  float z[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = d.z1[((long long)b * HW + p0 + 8 * (r >> 2) + 4 * half + (r & 3)) * CH + row];
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
     float4 cq[CH / 8];
@@ -249,7 +261,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
   for (int r = 0; r < 16; ++r) {
     const int pi = p0 + 8 * (r >> 2) + 4 * half + (r & 3);
     const long long o = ((long long)b * HW + pi) * CH + row;
-    d.g1[o] = acc[r] * gelu_df(d.z1[o]);
+    d.g1[o] = acc[r] * gelu_df(z[r]);
   }
 }
 
@@ -258,34 +270,43 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
 // summed in a fixed order; the chunk's partial is written to (add == 0) or added to the FP64
 // accumulator acc2[chunk][t][co][ci] (each slot has one owner: deterministic).
 constexpr int W2_CHUNK = 512;
-__global__ void __launch_bounds__(256) cnn_l2_back_weight(CnnDev d, double* acc2, int add) {
-  __shared__ float red[3][16][64];
-  const int HW = d.H * d.W, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int t = blockIdx.x % 9, chunk = blockIdx.x / 9;
+__device__ __forceinline__ void l2_back_weight(const CnnDev& d, int t, int chunk, double* acc2, int add,
+                                               float (&red)[3][16][64]) {
+  const int HW = d.H * d.W, lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q0 = chunk * W2_CHUNK + wv * (W2_CHUNK / 4);
   const int total = d.B * HW;
   const int row = lane & 31, half = lane >> 5;
   f32x16 acc = {};
   const int dy = t / 3 - 1, dx = t % 3 - 1;
-  // a segment of 32 pixels lies within one image row (W is a multiple of 32), so its loads need no
-  // division or branch and are all issued before its MFMAs (45 -> 25 us at 65536 pixels)
+  // acc[r]: co = 8 (r / 4) + 4 half + r % 4, ci = row
+  double* o = acc2 + ((long long)chunk * 9 + t) * CH * CH + 4 * half * CH + row;
+  double old[16];
+  if (wv == 0 && add) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) old[r] = o[(8 * (r >> 2) + (r & 3)) * CH];
+  }
+  // a segment of 32 pixels lies within one image row (W is a multiple of 32), so its loads need no division or
+  // branch, are all issued before its MFMAs and, but for the first and the last pixel,
+  // which may be on the row's other end, have constant offsets (with an address a load, and the accumulator read at
+  // the end, 27.5 us by itself at 65536 pixels, so 20.2; the MFMAs alone take 7.7)
   for (int s0 = 0; s0 < W2_CHUNK / 4; s0 += 32) {
     const int qs = q0 + s0;
     if (qs >= total) break;   // the total is a multiple of 32
     const int b = qs / HW, ps = qs - b * HW, y = ps / d.W, x0 = ps - y * d.W;
     const int yy = (y + dy < 0) ? d.H - 1 : (y + dy >= d.H ? 0 : y + dy);
-    const float* gp = d.g2 + (long long)qs * CH + row;
-    const __bf16* ap = d.a1 + ((long long)b * HW + (long long)yy * d.W) * CH + row;
-    float av[16], bv[16];
+    const float* gp = d.g2 + (long long)qs * CH + half * CH + row;
+    const __bf16* ap = d.a1 + ((long long)b * HW + (long long)yy * d.W + x0 + dx) * CH + half * CH + row;
+    const __bf16* a_first = (x0 + dx + half < 0) ? ap + d.W * CH : ap;
+    const __bf16* a_last = ((x0 + 30 + dx + half >= d.W) ? ap - d.W * CH : ap) + 30 * CH;
+    float av[16];
+    __bf16 bv[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-      int xx = x0 + 2 * k + half + dx;
-      xx += (xx < 0) ? d.W : (xx >= d.W ? -d.W : 0);
-      av[k] = gp[(2 * k + half) * CH];
-      bv[k] = (float)ap[xx * CH];
+      av[k] = gp[2 * k * CH];
+      bv[k] = *(k == 0 ? a_first : k == 15 ? a_last : ap + 2 * k * CH);
     }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[k], bv[k], acc, 0, 0, 0);
+    for (int k = 0; k < 16; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[k], (float)bv[k], acc, 0, 0, 0);
   }
   if (wv > 0) {
 #pragma unroll
@@ -293,20 +314,17 @@ __global__ void __launch_bounds__(256) cnn_l2_back_weight(CnnDev d, double* acc2
   }
   __syncthreads();
   if (wv != 0) return;
-  // acc[r]: co = 8 (r / 4) + 4 half + r % 4, ci = row
-  double* o = acc2 + ((long long)chunk * 9 + t) * CH * CH;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const float v = ((acc[r] + red[0][r][lane]) + red[1][r][lane]) + red[2][r][lane];
-    double* slot = o + (8 * (r >> 2) + 4 * half + (r & 3)) * CH + row;
-    *slot = add ? *slot + (double)v : (double)v;
+    const double v = (double)(((acc[r] + red[0][r][lane]) + red[1][r][lane]) + red[2][r][lane]);
+    o[(8 * (r >> 2) + (r & 3)) * CH] = add ? old[r] + v : v;
   }
 }
 
 // layer 1 input cotangent, one thread per pixel: xb = xscale sum_{t, c} w1[c][t] g1[p - d_t][c]
-__global__ void __launch_bounds__(NTC) cnn_l1_back_input(CnnDev d, double* xb, double xscale, int accumulate) {
+__device__ __forceinline__ void l1_back_input(const CnnDev& d, int block, double* xb, double xscale, int accumulate) {
   const int HW = d.H * d.W;
-  const int g = blockIdx.x * NTC + threadIdx.x;
+  const int g = block * NTC + threadIdx.x;
   if (g >= d.B * HW) return;
   const int b = g / HW, p = g - b * HW;
   float s = 0.f;
@@ -325,91 +343,122 @@ __global__ void __launch_bounds__(NTC) cnn_l1_back_input(CnnDev d, double* xb, d
   xb[g] = accumulate ? xb[g] + v : v;
 }
 
-// the small parameter gradients (dw1, db1, dw3, db3, db2) of one chunk of SW_CHUNK pixels: a
-// thread per (4 channels, tap) or per 4 channels (biases) sums over the chunk's pixels in order
-// with 16-byte loads of the channel vectors; written to (add == 0) or added to the FP64
+// the small parameter gradients (dw1, db1, dw3, db3, db2) of one chunk of SW_CHUNK pixels, one wave: a lane per pair of
+// channels and row of three taps, which share the loads of a0 and a2 as a window along the image row (a thread per
+// tap read every vector nine times over, at 16 bytes a lane and pixel the L1's limit), the last 16 lanes for
+// the bias of layer 2.  Sums are over the pixels in order; written to (add == 0) or added to the FP64
 // accumulator acc1[chunk][SMALL] (one owner per slot).  SMALL layout: dw1 [c][t], db1 [c],
 // dw3 [c][t], db3, db2 [c].
 constexpr int SMALL = NP1 + CH + NP3 + 1 + CH;
 constexpr int SW_CHUNK = 64;
-constexpr int SW_THREADS = 128;   // 72 weight threads, 8 bias threads
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void acc_store(double* slot, float v, int add) { *slot = add ? *slot + (double)v : (double)v; }
-__global__ void __launch_bounds__(SW_THREADS) cnn_small_weight(CnnDev d, const double* yb, double* acc1, int add) {
-  const int HW = d.H * d.W, total = d.B * HW, tid = threadIdx.x;
-  const int q0 = blockIdx.x * SW_CHUNK;
-  double* o = acc1 + (long long)blockIdx.x * SMALL;
-  if (tid < 72) {
-    const int c4 = tid & 7, t = tid >> 3, dy = t / 3 - 1, dx = t % 3 - 1;
-    float s1[4] = {0.f, 0.f, 0.f, 0.f}, s3[4] = {0.f, 0.f, 0.f, 0.f};
-    // segments of 32 pixels lie within one image row (W is a multiple of 32): eight pixels' loads
-    // are issued at once, the sums keep the pixels' order (52 -> 23 us at 65536 pixels)
-    for (int qs = q0; qs < q0 + SW_CHUNK && qs < total; qs += 32) {
-      const int b = qs / HW, ps = qs - b * HW, y = ps / d.W, x0 = ps - y * d.W;
-      const int yy = (y + dy < 0) ? d.H - 1 : (y + dy >= d.H ? 0 : y + dy);
-      const long long nrow = (long long)b * HW + (long long)yy * d.W;
-      for (int i0 = 0; i0 < 32; i0 += 8) {
-        float4 g[8];
-        bf16x4 a2[8];
-        float a0[8], yv[8];
+constexpr int SW_LOADS = 8;       // pixels whose loads are issued at once
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void small_weight(const CnnDev& d, int chunk, const double* yb, double* acc1, int add) {
+  const int HW = d.H * d.W, total = d.B * HW, lane = threadIdx.x & 63;
+  const int c2 = lane & 15, part = lane >> 4, dy = (part == 3) ? 0 : part - 1;
+  const int q0 = chunk * SW_CHUNK;
+  double* o = acc1 + (long long)chunk * SMALL;
+  double* o1 = o + 2 * c2 * 9 + 3 * part;
+  double* o3 = o1 + NP1 + CH;
+  double* ob = o + 2 * c2 + (part == 3 ? NP1 + CH + NP3 + 1 : NP1);
+  double* oy = o + NP1 + CH + NP3;
+  const bool taps = part < 3, bias = part == 0 || part == 3;
+  double old1[2][3], old3[2][3], oldb[2], oldy = 0.0;
+  if (add) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          int xx = x0 + i0 + i + dx;
-          xx += (xx < 0) ? d.W : (xx >= d.W ? -d.W : 0);
-          g[i] = *reinterpret_cast<const float4*>(d.g1 + (long long)(qs + i0 + i) * CH + 4 * c4);
-          a2[i] = *reinterpret_cast<const bf16x4*>(d.a2 + (nrow + xx) * CH + 4 * c4);
-          a0[i] = (float)d.a0[nrow + xx];
-          yv[i] = (float)yb[qs + i0 + i];
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (taps) {
+          old1[j][k] = o1[9 * j + k];
+          old3[j][k] = o3[9 * j + k];
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          s1[0] = fmaf(g[i].x, a0[i], s1[0]);
-          s1[1] = fmaf(g[i].y, a0[i], s1[1]);
-          s1[2] = fmaf(g[i].z, a0[i], s1[2]);
-          s1[3] = fmaf(g[i].w, a0[i], s1[3]);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) s3[j] = fmaf(yv[i], (float)a2[i][j], s3[j]);
-        }
-      }
+      if (bias) oldb[j] = ob[j];
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = 4 * c4 + j;
-      acc_store(o + c * 9 + t, s1[j], add);
-      acc_store(o + NP1 + CH + c * 9 + t, s3[j], add);
-    }
-  } else if (tid < 80) {
-    const int c4 = tid - 72;
-    float sb1[4] = {0.f, 0.f, 0.f, 0.f}, sb2[4] = {0.f, 0.f, 0.f, 0.f}, sb3 = 0.f;
-    for (int qs = q0; qs < q0 + SW_CHUNK && qs < total; qs += 8) {   // the total is a multiple of 32
-      float4 g1[8], g2[8];
-      float yv[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        g1[i] = *reinterpret_cast<const float4*>(d.g1 + (long long)(qs + i) * CH + 4 * c4);
-        g2[i] = *reinterpret_cast<const float4*>(d.g2 + (long long)(qs + i) * CH + 4 * c4);
-        yv[i] = (float)yb[qs + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        sb1[0] += g1[i].x;
-        sb1[1] += g1[i].y;
-        sb1[2] += g1[i].z;
-        sb1[3] += g1[i].w;
-        sb2[0] += g2[i].x;
-        sb2[1] += g2[i].y;
-        sb2[2] += g2[i].z;
-        sb2[3] += g2[i].w;
-        sb3 += yv[i];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      acc_store(o + NP1 + 4 * c4 + j, sb1[j], add);
-      acc_store(o + NP1 + CH + NP3 + 1 + 4 * c4 + j, sb2[j], add);
-    }
-    if (c4 == 0) acc_store(o + NP1 + CH + NP3, sb3, add);
+    if (lane == 0) oldy = *oy;
   }
+  float s1[2][3] = {}, s3[2][3] = {}, sb[2] = {}, sy = 0.f;
+  // segments of 32 pixels lie within one image row (W is a multiple of 32): constant offsets but for the first and the
+  // last pixel of the window, as in l2_back_weight
+  for (int qs = q0; qs < q0 + SW_CHUNK && qs < total; qs += 32) {
+    const int b = qs / HW, ps = qs - b * HW, y = ps / d.W, x0 = ps - y * d.W;
+    const int yy = (y + dy < 0) ? d.H - 1 : (y + dy >= d.H ? 0 : y + dy);
+    const long long n0 = (long long)b * HW + (long long)yy * d.W + x0 - 1;   // the window's first pixel
+    const long long nf = n0 + (x0 == 0 ? d.W : 0), nl = n0 + 33 - (x0 + 32 >= d.W ? d.W : 0);
+    const float* gp = (part == 3 ? d.g2 : d.g1) + (long long)qs * CH + 2 * c2;
+    const __bf16* a2p = d.a2 + 2 * c2;
+#pragma unroll
+    for (int i0 = 0; i0 < 32; i0 += SW_LOADS) {
+      float2 g[SW_LOADS];
+      bf16x2 a2[SW_LOADS + 2];
+      __bf16 a0[SW_LOADS + 2];
+      double yv[SW_LOADS];
+#pragma unroll
+      for (int i = 0; i < SW_LOADS + 2; ++i) {
+        const int e = i0 + i;
+        a2[i] = *reinterpret_cast<const bf16x2*>(e == 0 ? a2p + nf * CH : e == 33 ? a2p + nl * CH : a2p + n0 * CH + e * CH);
+        a0[i] = *(e == 0 ? d.a0 + nf : e == 33 ? d.a0 + nl : d.a0 + n0 + e);
+      }
+#pragma unroll
+      for (int i = 0; i < SW_LOADS; ++i) {
+        g[i] = *reinterpret_cast<const float2*>(gp + (i0 + i) * CH);
+        yv[i] = yb[qs + i0 + i];
+      }
+#pragma unroll
+      for (int i = 0; i < SW_LOADS; ++i) {
+        const float yf = (float)yv[i];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const float a0v = (float)a0[i + k];
+          s1[0][k] = fmaf(g[i].x, a0v, s1[0][k]);
+          s1[1][k] = fmaf(g[i].y, a0v, s1[1][k]);
+          s3[0][k] = fmaf(yf, (float)a2[i + k][0], s3[0][k]);
+          s3[1][k] = fmaf(yf, (float)a2[i + k][1], s3[1][k]);
+        }
+        sb[0] += g[i].x;
+        sb[1] += g[i].y;
+        sy += yf;
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (taps) {
+        o1[9 * j + k] = add ? old1[j][k] + (double)s1[j][k] : (double)s1[j][k];
+        o3[9 * j + k] = add ? old3[j][k] + (double)s3[j][k] : (double)s3[j][k];
+      }
+    if (bias) ob[j] = add ? oldb[j] + (double)sb[j] : (double)sb[j];
+  }
+  if (lane == 0) *oy = add ? oldy + (double)sy : (double)sy;
+}
+
+// Everything that follows g1 and g2, in one launch: the weight gradients of layer 2 (matrix instructions, nw blocks), the
+// small gradients (chains of loads, four chunks a block) and the input cotangent of layer 1, none of which depends on
+// another or fills the chip's units by itself: 28.1 + 26.0 + 10.1 us at 65536 pixels as three launches, now 34.5 (20.2,
+// 10.3 and 9.7 by themselves).  At most 128 registers, so four blocks share a CU (178 and two blocks: 40.2 us).  The parts start at multiples of eight blocks, for slab().
+__host__ __device__ constexpr int up8(int n) { return (n + 7) & ~7; }
+__global__ void __launch_bounds__(NTC, 4) cnn_back_tail(CnnDev d, const double* yb, double* acc1, int n1, double* acc2, int n2,
+                                                     int add, double* xb, double xscale, int accumulate) {
+  __shared__ float red[3][16][64];
+  const int nw = 9 * n2, ns = (n1 + 3) / 4;
+  int i = blockIdx.x;
+  if (i < up8(nw)) {
+    if (i >= nw) return;
+    i = slab(i, nw);
+    l2_back_weight(d, i % 9, i / 9, acc2, add, red);
+    return;
+  }
+  i -= up8(nw);
+  if (i < up8(ns)) {
+    if (i >= ns) return;
+    const int chunk = 4 * slab(i, ns) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (chunk < n1) small_weight(d, chunk, yb, acc1, add);
+    return;
+  }
+  i -= up8(ns);
+  l1_back_input(d, slab(i, gridDim.x - up8(nw) - up8(ns)), xb, xscale, accumulate);
 }
 
 // Sums the FP64 partials over chunks in a fixed order and adds them to the parameter gradient.  A
@@ -541,13 +590,9 @@ void Cnn::backward(const double* x, const double* yb, double* xb, double xscale,
   SPS_CHECK_LAUNCH();
   hipLaunchKernelGGL(cnn_l2_back_input, dim3(g2), dim3(NTC), 0, m.s, m.d);
   SPS_CHECK_LAUNCH();
-  if (params) {
-    hipLaunchKernelGGL(cnn_l2_back_weight, dim3(9 * m.n2), dim3(256), 0, m.s, m.d, m.acc2, (int)add);
-    SPS_CHECK_LAUNCH();
-    hipLaunchKernelGGL(cnn_small_weight, dim3(m.n1), dim3(SW_THREADS), 0, m.s, m.d, yb, m.acc1, (int)add);
-    SPS_CHECK_LAUNCH();
-  }
-  hipLaunchKernelGGL(cnn_l1_back_input, dim3(g1), dim3(NTC), 0, m.s, m.d, xb, xscale, (int)accumulate);
+  const int n1 = params ? m.n1 : 0, n2 = params ? m.n2 : 0;
+  hipLaunchKernelGGL(cnn_back_tail, dim3(up8(9 * n2) + up8((n1 + 3) / 4) + g1), dim3(NTC), 0, m.s, m.d, yb, m.acc1, n1, m.acc2,
+                     n2, (int)add, xb, xscale, (int)accumulate);
   SPS_CHECK_LAUNCH();
 }
 

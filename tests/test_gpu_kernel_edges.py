@@ -30,6 +30,13 @@ def test_closure_net_ragged_chunks(shape):
     check_closure_net(shape)
 
 
+# numbers of blocks that are no multiple of the eight parts an image is dealt out in (9 and 17 blocks of tiles, 27 and
+# 45 of weights), chunks that leave one and two waves of a block without work
+@pytest.mark.parametrize("shape", [(5, 7, 32), (1, 33, 64)], ids=["7x32x5", "33x64"])
+def test_closure_net_block_parts(shape):
+    check_closure_net(shape)
+
+
 # one step, one more step than the summing block has threads
 @pytest.mark.parametrize("nsteps", [1, 257])
 def test_rollout_loss_steps(nsteps):
