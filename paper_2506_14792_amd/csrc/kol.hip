@@ -492,7 +492,7 @@ struct KolInv {
   const cplx *X, *Fb;
   cplx *Z4, *Zg, *Zc, *Zgc;
 };
-template <int G>
+template <int G, bool CLO>
 __global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_inv_b(KolDev d, KolInv a) {
   using P = KolFft<G>;
   constexpr int N = P::N, Nh = P::Nh, TC = P::TC;
@@ -500,7 +500,7 @@ __global__ void __launch_bounds__(KolFft<G>::NTC) kol_cols_inv_b(KolDev d, KolIn
   const int b = blockIdx.z, c0 = TC * kol_tile<TC>(blockIdx.x, gridDim.x), tid = threadIdx.x;
   const int f = blockIdx.y + (blockIdx.y >= 4 && !a.Fb);   // 4 Zg, 5 Zc, 6 Zgc
   const cplx* Xb = ((f == 4 || f == 6) ? a.Fb : a.X) + (long long)b * Nh * N;
-  if (f <= 4) {
+  if (!CLO || f <= 4) {   // (without the closure the kernel keeps to the registers of the padded columns)
     cplx* Zb = (f < 4) ? a.Z4 + ((long long)b * 4 + f) * G * Nh : a.Zg + (long long)b * G * Nh;
     kol_inv_columns<G, N, TC, P::NTC>(Xb, f, Zb, d.tw + d.twoff[d.pNg], c0, tid, smem_d);
   } else {
@@ -595,7 +595,7 @@ __device__ __forceinline__ bool kol_closure_rows(const KolDev& d, const KolGrids
 // kol_rows in mode R_ADV.  The four fields of a row pair are in one row of 16 lanes, so the products are formed
 // by lane exchanges in the last inverse pass, whose outputs are the inputs of the forward transform's
 // first.  Grid (G / 2 / PAIRS [+ closure rows], instances).
-template <int G>
+template <int G, bool CLO>
 __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const cplx* Z4, cplx* W, KolGrids c) {
   using P = KolFft<G>;
   constexpr int Nh = P::Nh, R0 = P::R0, PAIRS = P::PAIRS, TC = 4 * PAIRS, NT = P::NTR;
@@ -603,7 +603,7 @@ __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const
   using FF = BlockFft<G, PAIRS, NT, 1, 1>;
   static_assert(FI::First::MB == 1 && FI::First::full && FF::Last::MB == 1, "one butterfly a thread");
   extern __shared__ double smem_d[];
-  if (kol_closure_rows<G>(d, c, smem_d)) return;
+  if (CLO && kol_closure_rows<G>(d, c, smem_d)) return;
   cplx* tw = reinterpret_cast<cplx*>(smem_d);
   cplx* buf = tw + G;
   const int b = blockIdx.y, tid = threadIdx.x, j = FI::First::bfly(tid), f = FI::First::seq(tid) & 3, pr = FI::First::seq(tid) >> 2;
@@ -640,7 +640,7 @@ __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_adv_b(KolDev d, const
 // quarter of the threads has its first two passes' butterflies as well, and the last pass of butterfly j is
 // computed in the lanes of all four fields, which then have the cotangent q where they have their field; output f
 // is -q times the field a turn by 8 away.  7.4 us at N = 64, 16 instances, with the closure's rows.
-template <int G>
+template <int G, bool CLO>
 __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_vjp_b(KolDev d, const cplx* Z4, const cplx* Zg, cplx* W, KolGrids c) {
   using P = KolFft<G>;
   constexpr int Nh = P::Nh, R0 = P::R0, R1 = P::R1, PAIRS = P::PAIRS, TC = 4 * PAIRS, NT = P::NTR;
@@ -648,7 +648,7 @@ __global__ void __launch_bounds__(KolFft<G>::NTR) kol_rows_vjp_b(KolDev d, const
   using FQ = BlockFft<G, PAIRS, NT, 4, 1>;
   static_assert(FI::First::MB == 1 && FI::First::full, "one butterfly a thread");
   extern __shared__ double smem_d[];
-  if (kol_closure_rows<G>(d, c, smem_d)) return;
+  if (CLO && kol_closure_rows<G>(d, c, smem_d)) return;
   cplx* tw = reinterpret_cast<cplx*>(smem_d);
   cplx* buf = tw + G;
   cplx* bufq = buf + bf_size(TC * G);
@@ -1096,9 +1096,12 @@ class KolProblem : public ProblemImpl {
       constexpr int G = decltype(g)::value;
       using P = KolFft<G>;
       const auto lds = [](const void* k, size_t n) { SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)n)); };
-      lds((const void*)kol_cols_inv_b<G>, P::lds_cols);
-      lds((const void*)kol_rows_adv_b<G>, P::lds_rows);
-      lds((const void*)kol_rows_vjp_b<G>, P::lds_vjp);
+      lds((const void*)kol_cols_inv_b<G, false>, P::lds_cols);
+      lds((const void*)kol_cols_inv_b<G, true>, P::lds_cols);
+      lds((const void*)kol_rows_adv_b<G, false>, P::lds_rows);
+      lds((const void*)kol_rows_adv_b<G, true>, P::lds_rows);
+      lds((const void*)kol_rows_vjp_b<G, false>, P::lds_vjp);
+      lds((const void*)kol_rows_vjp_b<G, true>, P::lds_vjp);
       lds((const void*)kol_rows_fwd_b<G>, P::lds_n);
       lds((const void*)kol_cols_step_b<G, false>, P::lds_step(false));
       lds((const void*)kol_cols_step_b<G, true>, P::lds_step(true));
@@ -1357,18 +1360,24 @@ class KolProblem : public ProblemImpl {
   // in two launches (padded lengths with a plan).
   void block_products(const cplx* X, const cplx* Fb) {
     with_block_fft([&](auto g) {
-      constexpr int G = decltype(g)::value;
-      using P = KolFft<G>;
-      const int extra = (Fb ? 1 : 0) + (closure_ ? (Fb ? 2 : 1) : 0), grids = closure_ ? (Fb ? 2 : 1) : 0;
-      hipLaunchKernelGGL(kol_cols_inv_b<G>, dim3(P::Nh / P::TC, 4 + extra, B_), dim3(P::NTC), P::lds_cols, stream, d_,
-                         KolInv{X, Fb, Z4_, Zg_, Zc_, Zgc_});
-      SPS_CHECK_LAUNCH();
-      const dim3 rows(G / 2 / P::PAIRS + grids * (P::N / 2 / P::PN), B_);
-      const KolGrids cg{Zc_, Zgc_, og_, yg_};
-      if (Fb) hipLaunchKernelGGL(kol_rows_vjp_b<G>, rows, dim3(P::NTR), P::lds_vjp, stream, d_, Z4_, Zg_, W_, cg);
-      else hipLaunchKernelGGL(kol_rows_adv_b<G>, rows, dim3(P::NTR), P::lds_rows, stream, d_, Z4_, W_, cg);
-      SPS_CHECK_LAUNCH();
+      if (closure_) block_products_g<decltype(g)::value, true>(X, Fb);
+      else block_products_g<decltype(g)::value, false>(X, Fb);
     });
+  }
+  template <int G, bool CLO>
+  void block_products_g(const cplx* X, const cplx* Fb) {
+    using P = KolFft<G>;
+    const int grids = CLO ? (Fb ? 2 : 1) : 0, fields = 4 + (Fb ? 1 : 0) + grids;
+    hipLaunchKernelGGL((kol_cols_inv_b<G, CLO>), dim3(P::Nh / P::TC, fields, B_), dim3(P::NTC), P::lds_cols, stream, d_,
+                       KolInv{X, Fb, Z4_, Zg_, Zc_, Zgc_});
+    SPS_CHECK_LAUNCH();
+    const dim3 rows(G / 2 / P::PAIRS + grids * (P::N / 2 / P::PN), B_);
+    const KolGrids cg{Zc_, Zgc_, og_, yg_};
+    if (Fb)
+      hipLaunchKernelGGL((kol_rows_vjp_b<G, CLO>), rows, dim3(P::NTR), P::lds_vjp, stream, d_, Z4_, Zg_, W_, cg);
+    else
+      hipLaunchKernelGGL((kol_rows_adv_b<G, CLO>), rows, dim3(P::NTR), P::lds_rows, stream, d_, Z4_, W_, cg);
+    SPS_CHECK_LAUNCH();
   }
   // x-spectra of the network's output on the grid (Wc)
   void closure_spectra(const double* grid) {
