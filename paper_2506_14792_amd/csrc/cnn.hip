@@ -39,7 +39,7 @@ struct CnnDev {
   const float* w3;     // [32][9]   bf16-rounded
   const float* b3;     // [1]
   __bf16 *a0, *a1, *a2;   // a0: [B][HW]; a1, a2: [B][HW][32]
-  float *z1, *z2;         // pre-activations [B][HW][32]
+  float *dz1, *dz2;       // gelu' of the pre-activations z1, z2 [B][HW][32] (backward passes)
   float *g1, *g2;         // cotangents of z1, z2
 };
 
@@ -60,9 +60,15 @@ __device__ __forceinline__ int nb_yx(int y, int x, int dy, int dx, int H, int W)
   xx += (xx < 0) ? W : (xx >= W ? -W : 0);
   return yy * W + xx;
 }
-__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_df(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+// GELU z Phi(z) and its derivative, with e = erff(z / sqrt 2): the forward kernels of a backward pass, which have e for
+// the activation, store the derivative in place of z (evaluated again from z, erff and expf were more than half the
+// vector instructions of layer 3's backward), those of a forward pass neither.  At 65536 pixels: layers 1 and 2 8.1 and
+// 10.4 us -> 6.9 and 8.2 in a forward pass, 9.2 and 12.5 in a backward pass, whose layer 3 takes 6.0 us, so 8.0, and
+// layer 2's input cotangent 17.8, so 20.2.
+__device__ __forceinline__ float gelu_e(float z) { return erff(z * 0.70710678118654752f); }
+__device__ __forceinline__ float gelu_f(float z, float e) { return 0.5f * z * (1.0f + e); }
+__device__ __forceinline__ float gelu_df(float z, float e) {
+  return 0.5f * (1.0f + e) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
 // Block i of n as a block of pixels: the blocks of one XCD (i mod 8) take one contiguous part of them, in every
@@ -97,8 +103,9 @@ __global__ void cnn_prepare(const double* th, float* w1, float* b1, __bf16* w2r,
 // ---------------------------------------------------------------------------- forward
 // layer 1 (1 -> 32) and GELU: four lanes per pixel, eight channels each, so that a wave's 16-byte
 // stores fill whole lines (one lane per pixel wrote 64 lines per store instruction).  Bound by the
-// 192 bytes a pixel writes: 15.3 -> 9.5 us at 65536 pixels.
+// 192 bytes a pixel writes in a backward pass, 64 in a forward one: 15.3 -> 9.2 and 6.9 us at 65536 pixels.
 constexpr int L1_PIX = NTC / 4;   // pixels per block
+template <bool GRAD>
 __global__ void __launch_bounds__(NTC) cnn_l1(CnnDev d, const double* x) {
   __shared__ float w[9 * CH];   // [t][c]
   __shared__ float bs[CH];
@@ -122,15 +129,22 @@ __global__ void __launch_bounds__(NTC) cnn_l1(CnnDev d, const double* x) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) z[j] = fmaf(w[t * CH + c0 + j], v[t], z[j]);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) a[j] = (__bf16)gelu_f(z[j]);
-  float4* zo = reinterpret_cast<float4*>(d.z1 + (long long)g * CH + c0);
-  zo[0] = make_float4(z[0], z[1], z[2], z[3]);
-  zo[1] = make_float4(z[4], z[5], z[6], z[7]);
+  for (int j = 0; j < 8; ++j) {
+    const float e = gelu_e(z[j]);
+    a[j] = (__bf16)gelu_f(z[j], e);
+    if (GRAD) z[j] = gelu_df(z[j], e);
+  }
+  if (GRAD) {
+    float4* zo = reinterpret_cast<float4*>(d.dz1 + (long long)g * CH + c0);
+    zo[0] = make_float4(z[0], z[1], z[2], z[3]);
+    zo[1] = make_float4(z[4], z[5], z[6], z[7]);
+  }
   *reinterpret_cast<bf16x8*>(d.a1 + (long long)g * CH + c0) = a;
 }
 
 // layer 2 (32 -> 32) and GELU on MFMA: each wave computes 32 pixels (a row segment) x 32
 // output channels; K = 9 taps x 32 input channels in 18 steps of 16.  LDS: w2r.
+template <bool GRAD>
 __global__ void __launch_bounds__(NTC) cnn_l2(CnnDev d) {
   __shared__ __bf16 w[9 * CH * CH];
   for (int e = threadIdx.x; e < 9 * CH * CH / 8; e += NTC)
@@ -158,8 +172,9 @@ __global__ void __launch_bounds__(NTC) cnn_l2(CnnDev d) {
     const int pi = p0 + 8 * (r >> 2) + 4 * half + (r & 3);
     const float z = acc[r] + d.b2[row];
     const long long o = ((long long)b * HW + pi) * CH + row;
-    d.z2[o] = z;
-    d.a2[o] = (__bf16)gelu_f(z);
+    const float e = gelu_e(z);
+    d.a2[o] = (__bf16)gelu_f(z, e);
+    if (GRAD) d.dz2[o] = gelu_df(z, e);
   }
 }
 
@@ -186,7 +201,7 @@ __global__ void __launch_bounds__(NTC) cnn_l3(CnnDev d, double* y, double scale,
 // ---------------------------------------------------------------------------- backward
 // layer 3: g2 = (w3 conv^T ybar) * gelu'(z2); eight lanes per pixel, four channels each, so that
 // the 16-byte loads and stores of a wave are contiguous.  Bound by the 256 bytes a pixel moves:
-// 12.4 -> 9.0 us at 65536 pixels.
+// 12.4 -> 6.0 us at 65536 pixels.
 constexpr int L3B_PIX = NTC / 8;   // pixels per block
 __global__ void __launch_bounds__(NTC) cnn_l3_back(CnnDev d, const double* yb) {
   __shared__ float w[9 * CH];   // [t][c]
@@ -196,7 +211,7 @@ __global__ void __launch_bounds__(NTC) cnn_l3_back(CnnDev d, const double* yb) {
   const int g = slab(blockIdx.x, gridDim.x) * L3B_PIX + (threadIdx.x >> 3), c0 = (threadIdx.x & 7) * 4;
   if (g >= d.B * HW) return;
   const int b = g / HW, p = g - b * HW;
-  const float4 z = *reinterpret_cast<const float4*>(d.z2 + (long long)g * CH + c0);
+  const float4 z = *reinterpret_cast<const float4*>(d.dz2 + (long long)g * CH + c0);
   float ys[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) ys[t] = (float)yb[(long long)b * HW + nb_t(p, t, d.H, d.W)];
@@ -207,7 +222,7 @@ __global__ void __launch_bounds__(NTC) cnn_l3_back(CnnDev d, const double* yb) {
     float s = 0.f;
 #pragma unroll
     for (int t = 0; t < 9; ++t) s = fmaf(w[t * CH + c0 + j], ys[t], s);
-    r[j] = s * gelu_df(zz[j]);
+    r[j] = s * zz[j];
   }
   *reinterpret_cast<float4*>(d.g2 + (long long)g * CH + c0) = make_float4(r[0], r[1], r[2], r[3]);
 }
@@ -239,7 +254,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
   load(0);
   float z[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = d.z1[((long long)b * HW + p0 + 8 * (r >> 2) + 4 * half + (r & 3)) * CH + row];
+  for (int r = 0; r < 16; ++r) z[r] = d.dz1[((long long)b * HW + p0 + 8 * (r >> 2) + 4 * half + (r & 3)) * CH + row];
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
     float4 cq[CH / 8];
@@ -261,7 +276,7 @@ __global__ void __launch_bounds__(NTC) cnn_l2_back_input(CnnDev d) {
   for (int r = 0; r < 16; ++r) {
     const int pi = p0 + 8 * (r >> 2) + 4 * half + (r & 3);
     const long long o = ((long long)b * HW + pi) * CH + row;
-    d.g1[o] = acc[r] * gelu_df(z[r]);
+    d.g1[o] = acc[r] * z[r];
   }
 }
 
@@ -549,8 +564,8 @@ Cnn::Cnn(int batch, int H, int W, hipStream_t s) : p_(new Impl) {
   d.a0 = m.arena.alloc<__bf16>(n);
   d.a1 = m.arena.alloc<__bf16>(n * CH);
   d.a2 = m.arena.alloc<__bf16>(n * CH);
-  d.z1 = m.arena.alloc<float>(n * CH);
-  d.z2 = m.arena.alloc<float>(n * CH);
+  d.dz1 = m.arena.alloc<float>(n * CH);
+  d.dz2 = m.arena.alloc<float>(n * CH);
   d.g1 = m.arena.alloc<float>(n * CH);
   d.g2 = m.arena.alloc<float>(n * CH);
 }
@@ -569,9 +584,9 @@ void Cnn::forward(const double* x, double* y, double scale, bool accumulate) {
   Impl& m = *p_;
   const long long n = (long long)m.B * m.H * m.W;
   const int g1 = (int)((n + NTC - 1) / NTC), g2 = (int)((n / 32 + 3) / 4);
-  hipLaunchKernelGGL(cnn_l1, dim3((unsigned)((n + L1_PIX - 1) / L1_PIX)), dim3(NTC), 0, m.s, m.d, x);
+  hipLaunchKernelGGL(cnn_l1<false>, dim3((unsigned)((n + L1_PIX - 1) / L1_PIX)), dim3(NTC), 0, m.s, m.d, x);
   SPS_CHECK_LAUNCH();
-  hipLaunchKernelGGL(cnn_l2, dim3(g2), dim3(NTC), 0, m.s, m.d);
+  hipLaunchKernelGGL(cnn_l2<false>, dim3(g2), dim3(NTC), 0, m.s, m.d);
   SPS_CHECK_LAUNCH();
   hipLaunchKernelGGL(cnn_l3, dim3(g1), dim3(NTC), 0, m.s, m.d, y, scale, (int)accumulate);
   SPS_CHECK_LAUNCH();
@@ -582,9 +597,9 @@ void Cnn::backward(const double* x, const double* yb, double* xb, double xscale,
   const long long n = (long long)m.B * m.H * m.W;
   const int g1 = (int)((n + NTC - 1) / NTC), g2 = (int)((n / 32 + 3) / 4);
   // the forward activations of this input (recomputed: the adjoint sweep revisits states)
-  hipLaunchKernelGGL(cnn_l1, dim3((unsigned)((n + L1_PIX - 1) / L1_PIX)), dim3(NTC), 0, m.s, m.d, x);
+  hipLaunchKernelGGL(cnn_l1<true>, dim3((unsigned)((n + L1_PIX - 1) / L1_PIX)), dim3(NTC), 0, m.s, m.d, x);
   SPS_CHECK_LAUNCH();
-  hipLaunchKernelGGL(cnn_l2, dim3(g2), dim3(NTC), 0, m.s, m.d);
+  hipLaunchKernelGGL(cnn_l2<true>, dim3(g2), dim3(NTC), 0, m.s, m.d);
   SPS_CHECK_LAUNCH();
   hipLaunchKernelGGL(cnn_l3_back, dim3((unsigned)((n + L3B_PIX - 1) / L3B_PIX)), dim3(NTC), 0, m.s, m.d, yb);
   SPS_CHECK_LAUNCH();
