@@ -308,6 +308,7 @@ __device__ inline void band_condense(const double* ab, const int* spiv, int n, i
 #pragma unroll
     for (int r = 0; r < SPS_TW; ++r) v[r] = (r == c) ? 1.0 : 0.0;
     int pos = c;
+#pragma unroll 1   // (unrolled, rbc_factor spills a register)
     for (int q = 0; q < SPS_BLK; ++q) {
       const int j = tb + q;
       if (j >= n) break;

@@ -1926,7 +1926,7 @@ __device__ __forceinline__ void block_sums(double (&v)[C], double (*red)[NT]) {
 // All inverse iterations of one wavenumber in one block, the right (blockIdx.y = 0) and the left
 // (1) eigenvector side by side: mu = <x, y> (x has unit norm), x <- y / |y|, lam = sigma - 1/mu.  The
 // block operators are read once and stay in LDS, so an iteration is bound by the two sweeps' dependent
-// chain (256x64, 30 iterations: 1.63 ms as three launches per iteration and side, 0.53 ms here).
+// chain (256x64, 30 iterations: 1.63 ms as three launches per iteration and side, this one 431 us).
 // LDS: vA (S + SPS_PAD), vB, x (S complex each), the T and G blocks.
 __global__ void __launch_bounds__(NTK) rbc_evp_iterate(RbcDev d, const cplx* start, cplx* X, cplx* Y, double sigma,
                                                        int iters, cplx* lam) {

@@ -128,7 +128,7 @@ __device__ __forceinline__ void stockham_pass(const cplx* __restrict__ src, cplx
     cplx v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = src[fpad(base + j + r * nR)];
-    // the first pass has none: a third of its LDS reads and its products (the batched Swift-Hohenberg sweep: 47.7
+    // the first pass has none: a third of its LDS reads and its products (the batched Swift-Hohenberg sweep, then on it: 47.7
     // -> 45.5 ms)
     if (Ns > 1) {
 #pragma unroll
