@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <functional>
 #include <vector>
 
 #include "cnn.h"
@@ -605,10 +606,15 @@ void Cnn::backward(const double* x, const double* yb, double* xb, double xscale,
   SPS_CHECK_LAUNCH();
   hipLaunchKernelGGL(cnn_l2_back_input, dim3(g2), dim3(NTC), 0, m.s, m.d);
   SPS_CHECK_LAUNCH();
-  const int n1 = params ? m.n1 : 0, n2 = params ? m.n2 : 0;
-  hipLaunchKernelGGL(cnn_back_tail, dim3(up8(9 * n2) + up8((n1 + 3) / 4) + g1), dim3(NTC), 0, m.s, m.d, yb, m.acc1, n1, m.acc2,
-                     n2, (int)add, xb, xscale, (int)accumulate);
-  SPS_CHECK_LAUNCH();
+  const auto tail = [&](int n1, int n2, int blocks) {
+    hipLaunchKernelGGL(cnn_back_tail, dim3(up8(9 * n2) + up8((n1 + 3) / 4) + blocks), dim3(NTC), 0, m.s, m.d, yb, m.acc1, n1,
+                       m.acc2, n2, (int)add, xb, xscale, (int)accumulate);
+    SPS_CHECK_LAUNCH();
+  };
+  // a caller may have xb on yb, which the small gradients read
+  const bool apart = std::less<const double*>()(xb, yb + n) && std::less<const double*>()(yb, xb + n);
+  if (params && apart) tail(m.n1, m.n2, 0);
+  tail(params && !apart ? m.n1 : 0, params && !apart ? m.n2 : 0, g1);
 }
 
 void Cnn::vjp(const double* x, const double* yb, double* xb, double xscale, bool accumulate, double* th_bar) {

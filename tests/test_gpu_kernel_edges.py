@@ -37,6 +37,28 @@ def test_closure_net_block_parts(shape):
     check_closure_net(shape)
 
 
+# the input cotangent written over the output's, and half over it: the same bits as in a buffer of its own
+@pytest.mark.parametrize("shift", [0, 1])
+def test_closure_net_cotangent_in_place(shift):
+    from oracle import closure as cl
+    from test_gpu_closure import params
+    print(f"closure net, cotangent in place, {shift}", flush=True)
+    B, H, W = 4, 64, 64
+    net, n = sps.ClosureNet(B, H, W), B * H * W
+    theta = torch.from_numpy(cl.flatten(params(7))).cuda()
+    net.set_params(theta)
+    rng = np.random.default_rng(9)
+    x, yb = (torch.from_numpy(rng.standard_normal(n)).cuda() for _ in range(2))
+    xb, tb, tb2 = torch.zeros_like(x), torch.zeros_like(theta), torch.zeros_like(theta)
+    net.vjp(x, yb, xb, tb)
+    buf = torch.zeros(n + shift * n // 2, dtype=torch.float64, device="cuda")
+    buf[:n] = yb
+    out = buf[shift * n // 2:]
+    net.vjp(x, buf[:n], out, tb2)
+    torch.cuda.synchronize()
+    assert torch.equal(out, xb) and torch.equal(tb, tb2)
+
+
 # one step, one more step than the summing block has threads
 @pytest.mark.parametrize("nsteps", [1, 257])
 def test_rollout_loss_steps(nsteps):
