@@ -646,35 +646,41 @@ __device__ __forceinline__ void row_item_b(const ShDev& d, const ShInst& I, int 
 
 // ---------------------------------------------------------------------------- cost phase
 // J = 1/2 mean over the N x N grid of u^2 = 1/2 sum w |c~|^2 with c~ the coefficients of
-// the real field (the k_x = 0 column made Hermitian in k_y), dJ/dX = w c~.
+// the real field (the k_x = 0 column made Hermitian in k_y), dJ/dX = w c~.  J is COST_SUMS sums over every
+// COST_SUMS-th mode, added in one tree, whatever the number of threads: that number is the build-time tuner's choice
+// for batches of general lengths, 256 beside a length with a plan, and J may depend on neither (with a sum a
+// thread, J of the same state differed in its last bit between two builds).
+constexpr int COST_SUMS = 256;
 template <int NT>
 __device__ void cost_item(const ShDev& d, const ShRun& a, int inst, double* smem) {
   const ShInst I = d.inst[inst];
   const int N = I.N, Nh = I.Nh, tid = threadIdx.x;
   const cplx* X = d.work + I.xo + (long long)a.nsteps * Nh * N;
-  double* red = smem;
-  double part = 0.0;
-  for (int e = tid; e < Nh * N; e += NT) {
-    const int m = e / N, iy = e - m * N;
-    cplx c = czero();
-    if (iy != N / 2) {
-      c = X[e];
-      if (m == 0) {
-        const int jm = (N - iy) % N;        // row of -k_y
-        const cplx cm = X[jm];
-        c = cmk(0.5 * (c.x + cm.x), 0.5 * (c.y - cm.y));
+  double* red = smem;   // [COST_SUMS]
+  for (int v = tid; v < COST_SUMS; v += NT) {
+    double part = 0.0;
+    for (int e = v; e < Nh * N; e += COST_SUMS) {
+      const int m = e / N, iy = e - m * N;
+      cplx c = czero();
+      if (iy != N / 2) {
+        c = X[e];
+        if (m == 0) {
+          const int jm = (N - iy) % N;        // row of -k_y
+          const cplx cm = X[jm];
+          c = cmk(0.5 * (c.x + cm.x), 0.5 * (c.y - cm.y));
+        }
       }
+      const double w = (m == 0) ? 1.0 : 2.0;
+      const cplx g = cscale(c, w);
+      d.work[I.bo + e] = g;
+      if (a.dJ) a.dJ[I.so + e] = g;
+      part = fma(0.5 * w, fma(c.x, c.x, c.y * c.y), part);   // (spelled out: the same contraction in every kernel)
     }
-    const double w = (m == 0) ? 1.0 : 2.0;
-    const cplx g = cscale(c, w);
-    d.work[I.bo + e] = g;
-    if (a.dJ) a.dJ[I.so + e] = g;
-    part += 0.5 * w * (c.x * c.x + c.y * c.y);
+    red[v] = part;
   }
-  red[tid] = part;
   __syncthreads();
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
+  for (int s = COST_SUMS / 2; s > 0; s >>= 1) {
+    for (int v = tid; v < s; v += NT) red[v] += red[v + s];
     __syncthreads();
   }
   if (tid == 0 && a.J) a.J[inst] = red[0];
@@ -735,7 +741,8 @@ __global__ void __launch_bounds__(NT) sh_persistent(ShDev d, ShRun a) {
 
 // The same launch for batches with a grid length that has a plan: one loop over the phases of the run, so that
 // the items' code, a copy for each length, is there once.  An instance's length alone decides how it is
-// transformed, so that its results do not depend on the batch it is in.  MIXED: some lengths have none (a
+// transformed, and its cost is summed in one order (cost_item), so that its results do not depend on the batch it is
+// in, bit for bit, in this kernel as in the general one.  MIXED: some lengths have none (a
 // kernel of its own: the general items' registers spill 448 bytes a thread, 15 % of the time).
 template <bool MIXED>
 __global__ void __launch_bounds__(SH_BT, 2) sh_persistent_b(ShDev d, ShRun a) {
@@ -1144,16 +1151,16 @@ class ShProblem : public ProblemImpl {
       if (block_) {   // the tiles of the length's plan, or of some 1024 points
         if (sh_with_length(I.Ng, [&](auto g) {
               I.tc = I.trp = ShTile<decltype(g)::value>::TC;
-              lds_ = std::max({lds_, ShTile<decltype(g)::value>::lds, sizeof(double) * nt});
+              lds_ = std::max({lds_, ShTile<decltype(g)::value>::lds, sizeof(double) * COST_SUMS});
             }))
           continue;
         I.tc = I.trp = I.Ng <= 128 ? 8 : I.Ng <= 256 ? 4 : I.Ng <= 512 ? 2 : 1;
-        lds_ = std::max({lds_, col_lds(I, I.tc), row_lds(I, I.trp), sizeof(double) * nt});
+        lds_ = std::max({lds_, col_lds(I, I.tc), row_lds(I, I.trp), sizeof(double) * COST_SUMS});
         continue;
       }
       I.tc = tcs[size_class(I.N)];
       I.trp = trps[size_class(I.N)];
-      lds_ = std::max({lds_, col_lds(I, I.tc), row_lds(I, I.trp), sizeof(double) * nt});
+      lds_ = std::max({lds_, col_lds(I, I.tc), row_lds(I, I.trp), sizeof(double) * COST_SUMS});
     }
     struct It {
       double cost;

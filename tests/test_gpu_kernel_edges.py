@@ -260,6 +260,42 @@ def test_sh_grid_lengths(monkeypatch):
         assert all(torch.equal(a, b) for a, b in zip(run([i])[0], every[i]))
 
 
+# Lengths without a plan, alone (in blocks of as many threads as the build's tuner found fastest: 128 or 256 for
+# N = 36 and 54, which varies from build to build) and next to a planned length (in blocks of 256): state, gradient,
+# cost and its derivative, each the same bits.  Several builds and states, as the order in which a cost is summed
+# shows in the last bit of some states only.
+def test_sh_general_lengths_alone():
+    import test_gpu_sh as ts
+    sizes = [8, 18, 36, 54, 162, 24]
+    rng = np.random.default_rng(17)
+    X = [[torch.from_numpy(rng.standard_normal(N * N)).cuda() for N in sizes] for _ in range(16)]
+
+    def run(idx):
+        G = sps.ShBatch([sizes[i] for i in idx], [0.3] * len(idx), ts.L, 0.05, max_steps=2)
+        cut = np.cumsum([0] + [sizes[i] ** 2 for i in idx])
+        res = []
+        for Xs in X:
+            x = torch.cat([Xs[i] for i in idx])
+            out, g, dJ = (torch.zeros_like(x) for _ in range(3))
+            J, J0 = (torch.zeros(len(idx), dtype=torch.float64, device="cuda") for _ in range(2))
+            G.gradient(x, 2, out, g, J)
+            G.cost(x, J0, dJ)
+            G.sync()
+            res.append([dict(state=out[a:b], gradient=g[a:b], J=J[k], cost=J0[k], dJ=dJ[a:b])
+                        for k, (a, b) in enumerate(zip(cut[:-1], cut[1:]))])
+        return G.tuning()["threads"], res
+
+    every = run(range(len(sizes)))[1]
+    bad = []
+    for i, N in enumerate(sizes):
+        for build in range(6):
+            threads, alone = run([i])
+            print(f"SH alone, N = {N}, build {build}, {threads} threads", flush=True)
+            bad += [(N, threads, s, what) for s in range(len(X)) for what, v in alone[s][0].items()
+                    if not torch.equal(v, every[s][i][what])]
+    assert not bad, f"(N, threads alone, which input, array): {bad}"
+
+
 # plane Couette flow: the padded x and z lengths with a plan of their own (24 to 192), tiles of modes and of row
 # pairs that are not full (Kx = 12, 36; 6, 12 and 18 row pairs), and lengths with a plan next to one without
 @pytest.mark.parametrize("nx,nz", [(16, 16), (24, 24), (32, 8), (12, 32), (48, 48), (64, 64), (72, 72), (96, 96), (128, 128)])
