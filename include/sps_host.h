@@ -1,5 +1,5 @@
 /*
- * sps_host.h — host-only introspection of the library's operator assembly.
+ * sps_host.h — host-only introspection of the library's operator assembly and kernel choice.
  *
  * Needs no GPU.  It exposes the real banded systems the library factors for the 2D
  * Rayleigh-Benard problem, so the assembly of M and L (paper, Supplementary: Initial
@@ -39,6 +39,11 @@ int sps_rbc_host_bands(const sps_desc *desc, int *kl, int *ku, double *BM, doubl
  * learn S, kl and ku.  8 <= nz <= 256.  Returns SPS_OK or an error. */
 int sps_poiseuille_host_band(int nz, double alpha, double re, double sig_re, double sig_im, int *S, int *kl,
                              int *ku, double *band, int *rowmap, int *colmap, double *rho);
+
+/* Which plane kernels a plane Couette problem of this size runs (sps_build_couette): rows, cols = 1
+ * where the x rows and the z columns have kernels of their own for the padded length, 0 where the
+ * kernels of any length run.  nx, ny, nz even and positive.  Returns SPS_OK or an error. */
+int sps_couette_plane_kernels(int nx, int ny, int nz, int *rows, int *cols);
 
 #ifdef __cplusplus
 }

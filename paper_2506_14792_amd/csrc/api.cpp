@@ -8,6 +8,7 @@
 
 #include "ckpt.h"
 #include "cnn.h"
+#include "cou.h"
 #include "fft_plan.h"
 #include "sps_internal.h"
 #include "../../include/sps_host.h"
@@ -380,6 +381,16 @@ int sps_poiseuille_host_band(int nz, double alpha, double re, double sig_re, dou
   } catch (const sps::Error& e) {
     return fail(e.code, e.what());
   }
+}
+
+int sps_couette_plane_kernels(int nx, int ny, int nz, int* rows, int* cols) {
+  if (!rows || !cols) return fail(SPS_E_ARG, "null argument");
+  if (nx < 2 || ny < 2 || nz < 2 || nx > 65536 || ny > 65536 || nz > 65536 || nx % 2 || ny % 2 || nz % 2)
+    return fail(SPS_E_ARG, "sizes must be even and positive");
+  const sps::CouetteKernels k = sps::couette_kernels({nx / 2, nz, 3 * nx / 2, 3 * nz / 2, 3 * ny / 2, 0.0, 0.0, nullptr, 0.0});
+  *rows = k.rows;
+  *cols = k.cols;
+  return SPS_OK;
 }
 
 int sps_build_kolmo(int batch, int n, double re, double drag, double dt, int max_steps, int closure,

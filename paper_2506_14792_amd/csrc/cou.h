@@ -16,6 +16,13 @@ struct CouetteGeom {
   double dunode;
 };
 
+// Which of a geometry's plane kernels are those of a known length (cou.hip): the x rows', the z columns'.  Reads no
+// node values and needs no device.
+struct CouetteKernels {
+  bool rows = false, cols = false;
+};
+CouetteKernels couette_kernels(const CouetteGeom& g);
+
 class CouettePlanes {
  public:
   CouettePlanes(const CouetteGeom& g, hipStream_t s);

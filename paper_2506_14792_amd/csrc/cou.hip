@@ -882,11 +882,22 @@ void launch_col(const ColShape& c, F1 small, F2 large, dim3 grid, hipStream_t s)
 
 }  // namespace
 
+CouetteKernels couette_kernels(const CouetteGeom& g) {
+  CouetteKernels k;
+  if (g.Ngx == 3 * g.Kx)
+    cou_with_length(g.Ngx, [&](auto n) {
+      using R = CouRows<decltype(n)::value>;
+      k.rows = R::ok && (g.Ngz / 2 + R::PAIRS - 1) / R::PAIRS * g.Ngy >= kRowBlocks;
+    });
+  k.cols = 2 * g.Ngz == 3 * g.Nz && cou_with_length(g.Ngz, [](auto) {});
+  return k;
+}
+
 struct CouettePlanes::Impl {
   CouDev d{};
   DevArena arena;
   ColShape A, C, A2;
-  bool rowsb = false, colsb = false;   // Ngx, Ngz have Block3 plans (and 3/2 padding)
+  bool rowsb = false, colsb = false;   // the kernels of a known length (couette_kernels)
   int ntB = 256, ntB2 = 256;
   size_t ldsB = 0, ldsB2 = 0;
   cplx *Zf = nullptr, *Wf = nullptr, *Zv = nullptr, *Wbv = nullptr, *Gv = nullptr;
@@ -930,22 +941,25 @@ CouettePlanes::CouettePlanes(const CouetteGeom& g, hipStream_t s) : p_(new Impl)
   auto lds_attr = [](const void* k, size_t b) {
     SPS_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b));
   };
-  if (g.Ngx == 3 * g.Kx) cou_with_length(g.Ngx, [&](auto n) {
-    constexpr int G = decltype(n)::value;
-    if constexpr (CouRows<G>::ok) {
-      const int blocks = (g.Ngz / 2 + CouRows<G>::PAIRS - 1) / CouRows<G>::PAIRS;
-      lds_attr((const void*)cou_xrow_b<G>, CouRows<G>::lds);
-      lds_attr((const void*)cou_xrow_adj_b<G>, CouRows<G>::lds);
-      m.rowsb = blocks * g.Ngy >= kRowBlocks;
-    }
-  });
-  m.colsb = 2 * g.Ngz == 3 * g.Nz && cou_with_length(g.Ngz, [&](auto n) {
-    constexpr int G = decltype(n)::value;
-    lds_attr((const void*)cou_zinv_b<G, false>, CouCols<G>::lds);
-    lds_attr((const void*)cou_zinv_b<G, true>, CouCols<G>::lds);
-    lds_attr((const void*)cou_zfwd_b<G, false>, CouCols<G>::lds);
-    lds_attr((const void*)cou_zfwd_b<G, true>, CouCols<G>::lds);
-  });
+  const CouetteKernels known = couette_kernels(g);
+  m.rowsb = known.rows;
+  m.colsb = known.cols;
+  if (m.rowsb)
+    cou_with_length(g.Ngx, [&](auto n) {
+      constexpr int G = decltype(n)::value;
+      if constexpr (CouRows<G>::ok) {
+        lds_attr((const void*)cou_xrow_b<G>, CouRows<G>::lds);
+        lds_attr((const void*)cou_xrow_adj_b<G>, CouRows<G>::lds);
+      }
+    });
+  if (m.colsb)
+    cou_with_length(g.Ngz, [&](auto n) {
+      constexpr int G = decltype(n)::value;
+      lds_attr((const void*)cou_zinv_b<G, false>, CouCols<G>::lds);
+      lds_attr((const void*)cou_zinv_b<G, true>, CouCols<G>::lds);
+      lds_attr((const void*)cou_zfwd_b<G, false>, CouCols<G>::lds);
+      lds_attr((const void*)cou_zfwd_b<G, true>, CouCols<G>::lds);
+    });
   const size_t plane = (size_t)g.Ngy * g.Ngz * g.Kx;
   m.Zf = m.arena.alloc<cplx>(9 * plane);
   m.Wf = m.arena.alloc<cplx>(3 * plane);
@@ -993,8 +1007,8 @@ void CouettePlanes::forward(const double2* zg, double2* nl, hipStream_t s) {
     cou_with_length(d.Ngx, [&](auto n) {
       using R = CouRows<decltype(n)::value>;
       if constexpr (R::ok)
-      hipLaunchKernelGGL(cou_xrow_b<decltype(n)::value>, dim3((d.Ngz / 2 + R::PAIRS - 1) / R::PAIRS, d.Ngy), dim3(R::B::NT), R::lds, s,
-                         d, m.Zf, m.Wf);
+        hipLaunchKernelGGL(cou_xrow_b<decltype(n)::value>, dim3((d.Ngz / 2 + R::PAIRS - 1) / R::PAIRS, d.Ngy), dim3(R::B::NT),
+                           R::lds, s, d, m.Zf, m.Wf);
     });
   else if (m.ntB == 256)
     hipLaunchKernelGGL(cou_xrow<256>, gb, dim3(256), m.ldsB, s, d, m.Zf, m.Wf);
@@ -1022,22 +1036,22 @@ void CouettePlanes::vjp(const double2* nlbar, const double2* zg, double2* zbar, 
   if (m.colsb)
     launch_col_b(d, 1, nlbar, m.Wbv, s, [](auto n) { return cou_zinv_b<decltype(n)::value, true>; });
   else
-  launch_col(
-      c,
-      [&](dim3 g, hipStream_t st) {
-        hipLaunchKernelGGL(cou_zfwd_adj<kColSmall>, g, dim3(kColSmall), c.lds, st, d, nlbar, c.tc, m.Wbv);
-      },
-      [&](dim3 g, hipStream_t st) {
-        hipLaunchKernelGGL(cou_zfwd_adj<kColLarge>, g, dim3(kColLarge), c.lds, st, d, nlbar, c.tc, m.Wbv);
-      },
-      col_grid_y(d, c), s);
+    launch_col(
+        c,
+        [&](dim3 g, hipStream_t st) {
+          hipLaunchKernelGGL(cou_zfwd_adj<kColSmall>, g, dim3(kColSmall), c.lds, st, d, nlbar, c.tc, m.Wbv);
+        },
+        [&](dim3 g, hipStream_t st) {
+          hipLaunchKernelGGL(cou_zfwd_adj<kColLarge>, g, dim3(kColLarge), c.lds, st, d, nlbar, c.tc, m.Wbv);
+        },
+        col_grid_y(d, c), s);
   const dim3 gb(d.Ngz / 2, d.Ngy);
   if (m.rowsb)
     cou_with_length(d.Ngx, [&](auto n) {
       using R = CouRows<decltype(n)::value>;
       if constexpr (R::ok)
-      hipLaunchKernelGGL(cou_xrow_adj_b<decltype(n)::value>, dim3((d.Ngz / 2 + R::PAIRS - 1) / R::PAIRS, d.Ngy), dim3(R::B::NT), R::lds,
-                         s, d, m.Zv, m.Wbv, m.Gv);
+        hipLaunchKernelGGL(cou_xrow_adj_b<decltype(n)::value>, dim3((d.Ngz / 2 + R::PAIRS - 1) / R::PAIRS, d.Ngy),
+                           dim3(R::B::NT), R::lds, s, d, m.Zv, m.Wbv, m.Gv);
     });
   else if (m.ntB2 == 256)
     hipLaunchKernelGGL(cou_xrow_adj<256>, gb, dim3(256), m.ldsB2, s, d, m.Zv, m.Wbv, m.Gv);

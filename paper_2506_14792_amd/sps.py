@@ -119,6 +119,8 @@ def lib():
                                                     ctypes.c_double, ctypes.POINTER(ctypes.c_int),
                                                     ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int),
                                                     _P, _P, _P, _P]),
+        "sps_couette_plane_kernels": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                                     ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     }
     for name, (res, args) in sig.items():
         f = getattr(L, name)
@@ -642,6 +644,14 @@ def poiseuille_host_band(nz, alpha, Re, sigma):
     _check(lib().sps_poiseuille_host_band(int(nz), float(alpha), float(Re), sg.real, sg.imag, ctypes.byref(S),
                                           ctypes.byref(kl), ctypes.byref(ku), p(band), p(rowmap), p(colmap), p(rho)))
     return dict(S=n, kl=kl.value, ku=ku.value, band=band, rowmap=rowmap, colmap=colmap, rho=rho)
+
+
+def couette_plane_kernels(nx, ny, nz):
+    """(rows, cols): whether a plane Couette problem of this size runs the kernels of a known length on
+    its x rows and z columns (no GPU)."""
+    rows, cols = ctypes.c_int(), ctypes.c_int()
+    _check(lib().sps_couette_plane_kernels(int(nx), int(ny), int(nz), ctypes.byref(rows), ctypes.byref(cols)))
+    return bool(rows.value), bool(cols.value)
 
 
 def rbc_host_bands(nx, nz, lx, Ra, Pr, dt=1e-3):

@@ -12,6 +12,7 @@ if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
 import paper_2506_14792_amd as sps  # noqa: E402
+from test_couette_host import ROW_SIZES  # noqa: E402
 from test_gpu_closure import test_closure_net_forward_and_vjp as check_closure_net  # noqa: E402
 from test_gpu_couette import test_couette_explicit_term_and_solve as check_couette_F  # noqa: E402
 from test_gpu_rbc import test_explicit_term_and_vjp as check_rbc_F  # noqa: E402
@@ -296,11 +297,26 @@ def test_sh_general_lengths_alone():
     assert not bad, f"(N, threads alone, which input, array): {bad}"
 
 
-# plane Couette flow: the padded x and z lengths with a plan of their own (24 to 192), tiles of modes and of row
-# pairs that are not full (Kx = 12, 36; 6, 12 and 18 row pairs), and lengths with a plan next to one without
+# plane Couette flow: the padded z lengths with a plan of their own (24 to 192), tiles of modes that are not full (Kx =
+# 12, 36), and lengths with a plan next to one without; of the x lengths only 192 has blocks enough for its row kernels
 @pytest.mark.parametrize("nx,nz", [(16, 16), (24, 24), (32, 8), (12, 32), (48, 48), (64, 64), (72, 72), (96, 96), (128, 128)])
 def test_couette_grid_lengths(nx, nz):
     check_couette_F(dict(Nx=nx, Ny=8, Nz=nz, Lx=3.0, Lz=2.5))
+
+
+# The row kernels of every x length that has them, their last tiles not full: F and its VJP against the oracle (whose
+# transforms need none of its dense matrices)
+@pytest.mark.parametrize("nx,ny,nz", ROW_SIZES)
+def test_couette_row_kernels(nx, ny, nz, monkeypatch):
+    import test_gpu_couette as tc
+
+    class Planes(tc.Couette):
+        def _build_matrices(self):
+            return None, None
+
+    assert sps.couette_plane_kernels(nx, ny, nz)[0]
+    monkeypatch.setattr(tc, "Couette", Planes)
+    check_couette_F(dict(Nx=nx, Ny=ny, Nz=nz, Lx=3.0, Lz=2.5))
 
 
 # 2D convection: the padded row lengths with kernels of their own (24 to 288 points), an odd number of rows (15:
