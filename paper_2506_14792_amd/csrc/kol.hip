@@ -965,32 +965,37 @@ __global__ void __launch_bounds__(KolFft<G>::adj_threads(CLO)) kol_cols_adj_b(Ko
 // N x N grid of the squared difference).  One block per step and instance writes that step's sum
 // (the states and targets are read once, at the memory's rate); kol_loss_sum adds the steps in a
 // fixed order.  One block per instance for the whole run: 884 us, now 33 + 5 us (16 runs of
-// 64 x 64, 200 steps; 420 MB read).
-__global__ void __launch_bounds__(NTK) kol_loss(KolDev d, const cplx* H, const cplx* T, double* part) {
+// 64 x 64, 200 steps; 420 MB read).  Beyond kLossBlocks steps a block takes several: a launch of one block per
+// step is refused from 2^24 steps on (2^32 threads), which small grids have the memory for.
+constexpr int kLossBlocks = 4096;
+__global__ void __launch_bounds__(NTK) kol_loss(KolDev d, const cplx* H, const cplx* T, int nsteps, double* part) {
   __shared__ double red[NTK];
-  const int b = blockIdx.y, k = blockIdx.x + 1, N = d.N, Nh = d.Nh, tid = threadIdx.x;
+  const int b = blockIdx.y, N = d.N, Nh = d.Nh, tid = threadIdx.x;
   const long long st = (long long)d.B * Nh * N, io = (long long)b * Nh * N;
-  const cplx* Hk = H + (long long)k * st + io;
-  const cplx* Tk = T + (long long)(k - 1) * st + io;
-  double s = 0.0;
-  for (int e = tid; e < Nh * N; e += NTK) {
-    const int m = e / N, iy = e - m * N;
-    if (iy == N / 2) continue;
-    cplx c = csub(Hk[e], Tk[e]);
-    if (m == 0) {
-      const int sm = (N - iy) % N;
-      const cplx c2 = csub(Hk[sm], Tk[sm]);
-      c = cmk(0.5 * (c.x + c2.x), 0.5 * (c.y - c2.y));
+  for (int k = blockIdx.x; k < nsteps; k += gridDim.x) {   // (nsteps + gridDim.x: below 2^31 for every history that fits)
+    const cplx* Hk = H + (k + 1LL) * st + io;
+    const cplx* Tk = T + (long long)k * st + io;
+    double s = 0.0;
+    for (int e = tid; e < Nh * N; e += NTK) {
+      const int m = e / N, iy = e - m * N;
+      if (iy == N / 2) continue;
+      cplx c = csub(Hk[e], Tk[e]);
+      if (m == 0) {
+        const int sm = (N - iy) % N;
+        const cplx c2 = csub(Hk[sm], Tk[sm]);
+        c = cmk(0.5 * (c.x + c2.x), 0.5 * (c.y - c2.y));
+      }
+      s += ((m == 0) ? 1.0 : 2.0) * (c.x * c.x + c.y * c.y);
     }
-    s += ((m == 0) ? 1.0 : 2.0) * (c.x * c.x + c.y * c.y);
-  }
-  red[tid] = s;
-  __syncthreads();
-  for (int w = NTK / 2; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
+    red[tid] = s;
+    __syncthreads();
+    for (int w = NTK / 2; w > 0; w >>= 1) {
+      if (tid < w) red[tid] += red[tid + w];
+      __syncthreads();
+    }
+    if (tid == 0) part[(long long)b * nsteps + k] = red[0];
     __syncthreads();
   }
-  if (tid == 0) part[(long long)b * gridDim.x + blockIdx.x] = red[0];
 }
 // J[b] = (1/nsteps) sum of the steps' sums, one block per instance
 __global__ void __launch_bounds__(NTK) kol_loss_sum(const double* part, int nsteps, double* J) {
@@ -1190,7 +1195,8 @@ class KolProblem : public ProblemImpl {
 
   void loss(const cplx* targets, int nsteps, double* J) {
     SPS_REQUIRE(hring_ == 0 && tape_ == nsteps, "loss: needs the full history of the last forward run");
-    hipLaunchKernelGGL(kol_loss, dim3(nsteps, B_), dim3(NTK), 0, stream, d_, H_, targets, lpart_);
+    hipLaunchKernelGGL(kol_loss, dim3(std::min(nsteps, kLossBlocks), B_), dim3(NTK), 0, stream, d_, H_, targets, nsteps,
+                       lpart_);
     SPS_CHECK_LAUNCH();
     hipLaunchKernelGGL(kol_loss_sum, dim3(B_), dim3(NTK), 0, stream, lpart_, nsteps, J);
     SPS_CHECK_LAUNCH();

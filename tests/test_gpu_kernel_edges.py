@@ -80,6 +80,30 @@ def test_rollout_loss_steps(nsteps):
         assert abs(J[i].item() - Jo) < 1e-11 * Jo
 
 
+# more steps than the loss's launch has blocks (4096): from the run's own states, the squared differences summed in
+# numpy.  At most 4096 terms a lane and tree, all positive: 1e-12 and less
+def test_rollout_loss_many_steps():
+    from oracle.kolmo import Kolmogorov
+    N, B, dt, n = 8, 2, 1e-4, 4099
+    print(f"rollout loss, {n} steps", flush=True)
+    P = Kolmogorov(N, Re=1000.0, drag=0.1)
+    G = sps.Kolmogorov(B, N, Re=1000.0, dt=dt, max_steps=n, drag=0.1)
+    X0 = torch.cat([dev(wl.kolmo_vorticity(seed=s, N=N)[0].T) for s in range(B)])
+    rng = np.random.default_rng(3)
+    T = torch.from_numpy(rng.standard_normal((n, X0.numel()))).cuda()
+    J = torch.zeros(B, dtype=torch.float64, device="cuda")
+    snap = torch.zeros(n * B * N * N, dtype=torch.float64, device="cuda")
+    G.rollout(X0, T.reshape(-1), n, J=J)
+    G.forward(X0, n, snap=snap, every=1, nc=N)
+    G.sync()
+    view = lambda t: t.cpu().numpy().view(np.complex128).reshape(n, B, N // 2, N).transpose(0, 1, 3, 2)
+    e = view(snap) - view(T)
+    e[:, :, N // 2] = 0.0
+    for b in range(B):
+        ref = np.mean([np.mean(P.T.to_grid(c, N) ** 2) for c in e[:, b]])
+        assert abs(J[b].item() - ref) <= 1e-11 * ref
+
+
 # inverse iteration from the library's fixed start vector, iteration by iteration, on the smallest
 # Chebyshev size, a size whose last block of eight rows is partial, and the largest; the solves' relative
 # error is about eps times the condition number of sigma M + L_s (1e5 to 1e6 here)
