@@ -476,8 +476,10 @@ __global__ void __launch_bounds__(NT) cou_zinv_adj(CouDev d, const cplx* Gb, int
 // transforms in threes, holding only what the products still need: u, v, w in LDS (each of a point's nine
 // products has one of them as a factor) and in registers the three densities, or their cotangents and three
 // sums.  At 128x64x64, us a launch: cou_zinv 46 -> 32 (147 MB moved), cou_xrow 86 -> 60 (113 MB), cou_zfwd 21 -> 13, cou_zfwd_adj
-// 18 -> 12, cou_xrow_adj 141 -> 112 (198 MB; 125 with u, v, w in registers, which spill), cou_zinv_adj 62 -> 30.  The row kernels are
-// held back by their registers, two waves per SIMD.
+// 18 -> 12, cou_xrow_adj 141 -> 112 (198 MB; 125 with u, v, w in registers), cou_zinv_adj 62 -> 30.  The row kernels are
+// held back by their registers: 256 a lane for two waves per SIMD, and some spill beyond those, in cou_xrow_b 88 (96
+// and 192 points) and 104 bytes a lane (48), in cou_xrow_adj_b 76 (72), 156 (96) and 172 (48 and 192)
+// (tests/test_kernel_resources.py holds them to that).
 template <int G>
 struct CouRows {
   static constexpr int PAIRS = G >= 144 ? 4 : G >= 72 ? 8 : 16;   // row pairs of a block
@@ -521,7 +523,7 @@ __device__ __forceinline__ void cou_load3(const cplx* U, long long fstr, int j, 
   asm volatile("" : "+v"(j));   // not loaded before it is wanted
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
-    asm volatile("" ::: "memory");   // a field at a time: all three at once spill
+    asm volatile("" ::: "memory");   // a field at a time: fewer values held (the transpose at 192 points 113 -> 111 us)
     cplx u[R0], w[R0];
 #pragma unroll
     for (int r = 0; r < R0; ++r) {

@@ -425,7 +425,8 @@ struct KolFft {
   static constexpr int PN = 4 * PAIRS, NTN = PN * N / BlockPlan<N>::R0;
   static constexpr size_t lds_n = sizeof(cplx) * (N + bf_size(PN * N));
   // columns of a block with the four products of a reverse step: up to 512 threads (with the closure's) where that
-  // leaves two columns, as beyond registers spill
+  // leaves two columns, as beyond registers spill.  At 768 points two columns take 768 threads and the closure's 128: 128
+  // registers a lane, of which that instantiation (kol_cols_adj_b<768, true>) spills 76 bytes.
   static constexpr int TA = G >= 288 ? 2 : 4, NTA = 4 * TA * G / R0;
   // threads of the closure's columns beside those of the padded ones, from a wave's start
   static constexpr int wave(int n) { return (n + 63) / 64 * 64; }
