@@ -823,12 +823,12 @@ def rbc_batch_timing(reps=2):
 
 def poiseuille_timing():
     """Plane Poiseuille stability (the neutral-curve example), nz = 128 (S = 389): (a) the onset at
-    alpha = 1.02056 by Newton in Re from Re = 5000 in one launch (factorization, 20 inverse
+    alpha = 1.02056 by Newton in Re from Re = 5000 in one call (factorization, 20 inverse
     iterations for each of the right and left eigenvectors and the sensitivities per Newton step),
     against the oracle's dense eigensolves with left vectors for the same Newton steps; (b) a batch
-    of 128 neutral points in one launch: Newton in Re from Re = 5000 at 128 wavenumbers from 0.9
+    of 128 neutral points in one call: Newton in Re from Re = 5000 at 128 wavenumbers from 0.9
     to 1.09 (both branches near the onset); (c) 20 continuation steps along the curve from the
-    onset, one launch each."""
+    onset, one call each."""
     import torch
     import paper_2506_14792_amd as sps
     from oracle.poiseuille import Poiseuille

@@ -54,13 +54,7 @@ __device__ __forceinline__ int nb(int p, int t, int H, int W) {
   return yy * W + xx;
 }
 __device__ __forceinline__ int nb_t(int p, int t, int H, int W) { return nb(p, 8 - t, H, W); }   // (y - dy, x - dx)
-// neighbour (y + dy, x + dx) of the pixel at row y, column x (periodic)
-__device__ __forceinline__ int nb_yx(int y, int x, int dy, int dx, int H, int W) {
-  int yy = y + dy, xx = x + dx;
-  yy += (yy < 0) ? H : (yy >= H ? -H : 0);
-  xx += (xx < 0) ? W : (xx >= W ? -W : 0);
-  return yy * W + xx;
-}
+
 // GELU z Phi(z) and its derivative, with e = erff(z / sqrt 2): the forward kernels of a backward pass, which have e for
 // the activation, store the derivative in place of z (evaluated again from z, erff and expf were more than half the
 // vector instructions of layer 3's backward), those of a forward pass neither.  At 65536 pixels: layers 1 and 2 8.1 and

@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(NT) cou_zinv_adj(CouDev d, const cplx* Gb, int
 
 // ---------------------------------------------------------------------------- kernels of a known grid length
 // The six kernels on Block3, for the padded lengths it has a plan for (3/2 padding): three fields at a time, the
-// first pass read from memory and the last one used in registers.  A row kernel goes through its 12 or 27
+// first pass read from memory and the last one used in registers.  A row kernel goes through its 15 or 27
 // transforms in threes, holding only what the products still need: u, v, w in LDS (each of a point's nine
 // products has one of them as a factor) and in registers the three densities, or their cotangents and three
 // sums.  At 128x64x64, us a launch: cou_zinv 46 -> 32 (147 MB moved), cou_xrow 86 -> 60 (113 MB), cou_zfwd 21 -> 13, cou_zfwd_adj
