@@ -1298,7 +1298,8 @@ class KolProblem : public ProblemImpl {
     a.err = err_;
     return a;
   }
-  // fn(the padded length as a type) if block_fft.h has a plan for it
+  // fn(the padded length as a type) if the kernels of a known length are built for it.  The others take about twice as
+  // long: 16 forward steps of one instance 554 us at N = 144, 270 at 128 and 291 at 192; 332 at N = 48, 191 at 64.
   template <typename Fn>
   bool with_block_fft(Fn fn) const {
     switch (Ng_) {
